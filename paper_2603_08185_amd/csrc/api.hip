@@ -207,7 +207,10 @@ static int linear_common(LinearArgs& a, int64_t M, int64_t N, int64_t K, int fla
   if (path != SERQ_PATH_AUTO && path != SERQ_PATH_SKINNY && path != SERQ_PATH_MFMA) return SERQ_EUNSUPPORTED;
   if (path == SERQ_PATH_SKINNY && M > 32) return SERQ_ESHAPE;
   const bool skinny = path == SERQ_PATH_SKINNY || (path == SERQ_PATH_AUTO && M <= 32);
-  return skinny ? launch_skinny(a, (hipStream_t)stream) : launch_mfma(a, (hipStream_t)stream);
+  if (skinny) return launch_skinny(a, (hipStream_t)stream);
+  if (path == SERQ_PATH_AUTO && a.splitk == 0 && a.groupm == 0 && a.coltiles == 0 && mid_wanted(a))
+    return launch_mid(a, (hipStream_t)stream);
+  return launch_mfma(a, (hipStream_t)stream);
 }
 
 int serq_linear(const void* Xq, const float* scale, int abits,

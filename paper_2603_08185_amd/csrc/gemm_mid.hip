@@ -1,0 +1,342 @@
+// SERQ linear layer for batches between decode and prefill: the integer layer of gemm_mfma.hip in tiles of
+// 64 tokens x 64 channels, the 8 waves of a workgroup sharing K (mid_tile.h says why).
+//   Y[m,n] = scale[m] * ( wscale[n] * sum_k Xq[m,k] Wq[n,k] + sum_j Xq[m,S_j] R[j,n] )
+//
+// The waves' INT32 partial tiles meet in LDS once: wave w sums half of MFMA tile w/2 (8 registers per lane) over the 8
+// waves -- integer addition, the same bits as the tiled kernel -- scales it and adds the rank-r term with the matrix
+// unit on top, exactly as the tiled kernel does.  The two waves of a tile compute the rank-r term of the whole tile
+// twice (8 MFMAs at r = 128): cheaper than another meeting.
+//
+// What bounds it: the L2 -> LDS stream.  A step (64 channels of 8-bit tokens) is 6 KiB for 8 MFMAs; with all compute
+// units busy the direct loads bring 70-90 B/ns to each (64 B/clk is the address unit's limit, reached with up to half
+// of the chip).  Fixed costs are about 4.7 us (K = 1024), of which 1.3 us lie between dependent launches.
+// Measured (M = 256, 4096 x 11008, W4A8, r = 128): 20 us, the tiled kernel with 4 K slices and a second launch 30 us;
+// M = 100, 6144 x 4096: 9.6 against 24.4 us.  The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.
+#include "mid_tile.h"
+
+namespace serq {
+namespace {
+
+struct MidParams {
+  const uint8_t* Xq; const float* scale;
+  const u4* Wq; const float* wscale;
+  const u4* Rp; int s_begin; int r;
+  const float* rscale;
+  int M, N, K;
+  void* Y; int y_dtype; int64_t ldy;
+  int32_t* acc_out; int64_t ldacc;
+  int tiles_m, tiles_n;
+};
+
+template <int ABITS>
+struct Mid {
+  static constexpr int FR = ABITS == 8 ? 1 : 2;
+  static constexpr int STAGE = kMidX + 2 * FR * 1024;   // 6 KiB / 8 KiB
+  static constexpr int NS = ABITS == 8 ? 3 : 2;
+  static constexpr int NL = 4 + 2 * FR;
+  static constexpr int REGION = NS * STAGE;          // LDS of one wave: 18 KiB / 16 KiB
+  static constexpr int SH = ABITS == 8 ? 4 : 8;
+  // The rank-r term in chunks of 128 ranks: the R fragments that wave w brings lie behind its own partial tile (8-bit:
+  // the ring leaves 2 KiB there) or behind the rings (4-bit), the token codes behind that
+  static constexpr int LRR_STEP = ABITS == 8 ? REGION : 2048;
+  static constexpr int LRR_OFF = ABITS == 8 ? kMidPart : kMidWaves * REGION;
+  static __device__ __forceinline__ int lr_frag(bool per_wave_1, int f) {
+    return LRR_OFF + (per_wave_1 ? f * LRR_STEP : (f >> 1) * LRR_STEP + (f & 1) * 1024);
+  }
+  static constexpr int LRX_OFF = kMidWaves * REGION + (ABITS == 8 ? 0 : 16 * 1024);
+  static constexpr int LDS = LRX_OFF + 64 * 256;
+  static_assert(REGION >= kMidPart, "a partial tile fits the ring it replaces");
+  static_assert(ABITS == 4 || REGION - kMidPart >= 2048, "two R fragments fit behind it");
+  static_assert(LDS <= 160 * 1024, "LDS budget");
+};
+
+template <int FR>
+struct MidOp { u4 w[2][FR], x[2][2]; };              // x: [token block][8-bit: K half, 4-bit: fragment]
+
+template <int ABITS, int LRT>
+__global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void serq_mid_kernel(const MidParams p) {
+  using T = Mid<ABITS>;
+  constexpr int FR = T::FR, NS = T::NS;
+  __shared__ __align__(16) uint8_t lds[T::LDS];
+  const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tile_m, tile_n;
+  map_block(blockIdx.x, p.tiles_m, p.tiles_n, p.tiles_m, tile_m, tile_n);
+  const int m0 = tile_m * 64, nb0 = tile_n * 2;
+  const int NB = p.N >> 5;
+  const int nbt = NB - nb0 < 2 ? 1 : 2;
+  const int mrows = p.M - m0 < 64 ? p.M - m0 : 64;
+  const uint32_t rowbytes = (uint32_t)p.K * ABITS / 8;
+
+  MidLoads<FR> ld;
+  ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
+  const int steps = (ld.KB + FR - 1) / FR;
+  const int nst = steps > w ? (steps - w + kMidWaves - 1) / kMidWaves : 0;   // steps w, w + 8, ... are this wave's
+  uint8_t* my = lds + w * T::REGION;
+  const uint32_t my_lds = __builtin_amdgcn_readfirstlane(lds_addr(my));
+
+  v16i acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
+
+  const int xsw = mid_swz(lm);                       // the same for row lm and row 32 + lm
+  auto slot = [&](int t) { return (t % NS) * T::STAGE; };
+  auto read = [&](int t, MidOp<FR>& o) {
+    const uint8_t* s = my + slot(t);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int f = 0; f < FR; ++f) o.w[i][f] = *(const u4*)(s + kMidX + (i * FR + f) * 1024 + l * 16);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = ABITS == 8 ? 2 * g + h : 2 * h + g;
+        o.x[j][h] = *(const u4*)(s + (32 * j + lm) * 64 + 16 * (c ^ xsw));
+      }
+    if (FR == 2 && ld.KB - (w + kMidWaves * t) * FR < FR) {   // no second fragment: zero weights
+#pragma unroll
+      for (int i = 0; i < 2; ++i) o.w[i][FR - 1] = u4{0u, 0u, 0u, 0u};
+    }
+  };
+  // group k: token block k % 2, channel block k / 2 % 2 of fragment k / 4
+  auto product = [&](const MidOp<FR>& o, int k) {
+    const int j = k & 1, i = (k >> 1) & 1, f = k >> 2;
+    v4i a0, a1, b0, b1;
+    unpack_frag(o.w[i][f], a0, a1);
+    if constexpr (ABITS == 8) {
+      b0 = as_v4i(o.x[j][0]);
+      b1 = as_v4i(o.x[j][1]);
+    } else {
+      unpack_frag(o.x[j][f], b0, b1);
+    }
+    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[i][j], 0, 0, 0);
+    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
+  };
+  mid_loop<NS, T::NL, 4 * FR, MidOp<FR>>(
+      nst, [&](int t) { ld.issue(w + kMidWaves * t, my_lds + slot(t)); },
+      [&](int t, int k) { ld.issue_one(w + kMidWaves * t, my_lds + slot(t), k); }, read, product);
+
+  // ---- what the end of the tile needs from memory, requested before the waves meet ------------------------------
+  // wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j
+  const int ti = w >> 2, tj = (w >> 1) & 1, hq = 2 * (w & 1);
+  const int blk = nb0 + (ti < nbt ? ti : 0);          // (a block past the layer repeats the first and is not stored)
+  const int mloc = 32 * tj + lm;
+  const int m = m0 + (mloc < mrows ? mloc : mrows - 1);
+  constexpr float kInv = 1.0f / (float)(1 << T::SH);
+  constexpr bool lr_int = LRT == SERQ_I4;
+  constexpr bool bf = LRT != SERQ_F16;
+  const int JB = p.acc_out ? 0 : (lr_int ? (p.r + 63) >> 6 : p.r >> 4);   // fragments of R per channel block
+  constexpr int NJ = lr_int ? 2 : 8;                  // of which a chunk holds so many
+  // A chunk of the rank-r term: every wave brings 2 (4-bit R: waves 0..3, one) of its R fragments and 16 codes of 8 token
+  // rows per lane; 16-bit R takes the codes as exact 16-bit floats, converted once here instead of by every wave
+  // that multiplies them.
+  u4 lrr[2], lrx;
+  const int lrow = 8 * w + (l >> 3);
+  auto lr_fetch = [&](int jb0) {
+#pragma unroll
+    for (int q = 0; q < (lr_int ? 1 : 2); ++q) {
+      const int f = lr_int ? (w & 3) : 2 * w + q;
+      const int b = f / NJ, jb = jb0 + f % NJ;
+      lrr[q] = p.Rp[((size_t)(nb0 + (b < nbt ? b : 0)) * JB + (jb < JB ? jb : JB - 1)) * 64 + l];
+    }
+    const int c0 = p.s_begin + (lr_int ? 64 : 16) * jb0;   // first channel of the chunk
+    const int have = (JB - jb0) * (lr_int ? 64 : 16);  // channels it has
+    const int c = 16 * (l & 7) < have ? 16 * (l & 7) : 0;
+    const uint8_t* src = p.Xq + (size_t)(m0 + (lrow < mrows ? lrow : mrows - 1)) * rowbytes + (size_t)(c0 + c) * ABITS / 8;
+    if constexpr (ABITS == 8) {
+      lrx = *(const u4*)src;
+    } else {
+      const u2 v = *(const u2*)src;
+      lrx = u4{v.x, v.y, 0u, 0u};
+    }
+  };
+  auto lr_park = [&]() {
+#pragma unroll
+    for (int q = 0; q < (lr_int ? 1 : 2); ++q) {
+      const int f = lr_int ? (w & 3) : 2 * w + q;
+      if (!lr_int || w < 4) *(u4*)(lds + T::lr_frag(lr_int, f) + l * 16) = lrr[q];
+    }
+    uint8_t* row = lds + T::LRX_OFF + lrow * 256;
+    const int c = l & 7;                              // 16 channels
+    if constexpr (lr_int) {
+      if constexpr (ABITS == 8) *(u4*)(row + 16 * (c ^ (lrow & 15))) = lrx;
+      else *(u2*)(row + 16 * ((c >> 1) ^ (lrow & 15)) + 8 * (c & 1)) = u2{lrx.x, lrx.y};
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        int k[8];
+        if constexpr (ABITS == 8) codes_from_a8(h ? lrx.z : lrx.x, h ? lrx.w : lrx.y, k);
+        else codes_from_a4(h ? lrx.y : lrx.x, k);
+        *(u4*)(row + 16 * ((2 * c + h) ^ (lrow & 15))) = codes8_to_16bit(k, bf);
+      }
+    }
+  };
+  if (JB > 0) lr_fetch(0);
+  float wsc[8], rsc[8], sm = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) wsc[e] = rsc[e] = 0.0f;
+  if (!p.acc_out) {
+    sm = p.scale[m];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int n = 32 * blk + 8 * (hq + q) + 4 * g;
+      const float4 v = *(const float4*)(p.wscale + n);
+      wsc[4 * q] = v.x * kInv; wsc[4 * q + 1] = v.y * kInv; wsc[4 * q + 2] = v.z * kInv; wsc[4 * q + 3] = v.w * kInv;
+      if (lr_int && JB > 0) {
+        const float4 u = *(const float4*)(p.rscale + n);
+        rsc[4 * q] = u.x * kInv; rsc[4 * q + 1] = u.y * kInv; rsc[4 * q + 2] = u.z * kInv; rsc[4 * q + 3] = u.w * kInv;
+      }
+    }
+  }
+
+  // ---- the waves meet -------------------------------------------------------------------------------------------
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *(v4i*)(my + ((2 * i + j) * 4 + q) * 1024 + l * 16) =
+            v4i{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+  // (8-bit: the R fragments land in stages of this and of no other wave, which has read them all)
+  if (JB > 0) lr_park();
+  __syncthreads();
+  int tot[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) tot[e] = 0;
+#pragma unroll
+  for (int ww = 0; ww < kMidWaves; ++ww)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const v4i v = *(const v4i*)(lds + ww * T::REGION + ((w >> 1) * 4 + hq + q) * 1024 + l * 16);
+      tot[4 * q] += v.x; tot[4 * q + 1] += v.y; tot[4 * q + 2] += v.z; tot[4 * q + 3] += v.w;
+    }
+
+  const bool live = mloc < mrows && ti < nbt;
+  const int n = 32 * blk + 8 * hq + 4 * g;             // registers 4*q + e: channel n + 8*q + e
+  if (p.acc_out) {
+    if (live) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        *(v4i*)(p.acc_out + (size_t)m * p.ldacc + n + 8 * q) =
+            v4i{tot[4 * q] >> T::SH, tot[4 * q + 1] >> T::SH, tot[4 * q + 2] >> T::SH, tot[4 * q + 3] >> T::SH};
+    }
+    return;
+  }
+  float y[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) y[e] = wsc[e] * (float)tot[e];
+  v16f af;                                            // 16-bit R: the tile the matrix unit adds to
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    af[e] = hq ? 0.0f : y[e];
+    af[8 + e] = hq ? y[e] : 0.0f;
+  }
+  for (int jb0 = 0; jb0 < JB; jb0 += NJ) {
+    if (jb0 > 0) {                                     // (the loads of this chunk were requested a chunk ago)
+      __syncthreads();
+      lr_park();
+      __syncthreads();
+    }
+    if (jb0 + NJ < JB) lr_fetch(jb0 + NJ);
+    const uint8_t* row = lds + T::LRX_OFF + mloc * 256;
+    auto piece = [&](int c) { return *(const u4*)(row + 16 * (c ^ (mloc & 15))); };
+#pragma unroll
+    for (int q = 0; q < NJ; ++q) {
+      if (jb0 + q < JB) {                              // uniform
+        const int f = ti * NJ + q;
+        const u4 rr = *(const u4*)(lds + T::lr_frag(lr_int, f) + l * 16);
+        if constexpr (lr_int) {
+          v4i a0, a1, b0, b1;
+          unpack_frag(rr, a0, a1);
+          if constexpr (ABITS == 8) {
+            b0 = as_v4i(piece(4 * q + 2 * g));
+            b1 = as_v4i(piece(4 * q + 2 * g + 1));
+          } else {
+            unpack_frag(piece(2 * q + g), b0, b1);
+          }
+          v16i tq;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) tq[e] = 0;
+          tq = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, tq, 0, 0, 0);
+          tq = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, tq, 0, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) y[e] = __builtin_fmaf(rsc[e], (float)(hq ? tq[8 + e] : tq[e]), y[e]);
+        } else {
+          const u4 xf = piece(2 * q + g);
+          if constexpr (bf)
+            af = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, rr), __builtin_bit_cast(v8bf, xf), af, 0, 0, 0);
+          else
+            af = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, rr), __builtin_bit_cast(v8h, xf), af, 0, 0, 0);
+        }
+      }
+    }
+  }
+  if constexpr (!lr_int) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = hq ? af[8 + e] : af[e];
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) y[e] *= sm;
+
+  if (p.y_dtype == SERQ_F32) {
+    if (live) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        *(float4*)((float*)p.Y + (size_t)m * p.ldy + n + 8 * q) = make_float4(y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]);
+    }
+    return;
+  }
+  __syncthreads();                                     // every wave has read the partial tiles: the rows take their place
+#pragma unroll
+  for (int q = 0; q < 2; ++q) mid_park16(lds, mloc, 4 * ti + hq + q, g, y + 4 * q, p.y_dtype == SERQ_BF16);
+  __syncthreads();
+  mid_store16(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
+}
+
+}  // namespace
+
+// Up to two tiles per compute unit.  Measured (us, tiled kernel / this one, r = 128, bf16 R, W4A8; W4A4 the same or better):
+//   1 round:  4096 x 4096 M = 256 24.7 / 9.8;  6144 x 4096 M = 100 23.7 / 9.5;  4096 x 11008 M = 256 29.3 / 19.4;
+//             1024 x 1024 M = 1024 11.8 / 5.8;  11008 x 4096 M = 40 27.8 / 9.6
+//   2 rounds: 4096 x 4096 M = 512 24.9 / 18.1;  6144 x 4096 M = 256 24.7 / 17.8;  4096 x 11008 M = 512 41.1 / 39.6;
+//             28672 x 4096 M = 64 33.7 / 25.4
+//   3 rounds: 6144 x 4096 M = 400 25.4 / 24.6;  4096 x 11008 M = 640 53.3 / 56.8;  28672 x 4096 M = 100 (4) 33.3 / 39.8
+// (N x K; "tiled" slices K where its own plan does).  From three rounds on the larger tiles of that kernel, which move
+// half the bytes per product, are as fast or faster.
+bool mid_wanted(const LinearArgs& a) { return mid_rounds(a.M, a.N, device_cu_count()) <= 2; }
+
+int launch_mid(const LinearArgs& a, hipStream_t st) {
+  MidParams p;
+  p.Xq = a.Xq; p.scale = a.scale; p.Wq = a.Wq; p.wscale = a.wscale;
+  p.Rp = a.Rp; p.s_begin = a.s_begin; p.r = a.Rp ? a.r : 0;
+  p.rscale = a.rscale;
+  p.M = a.M; p.N = a.N; p.K = a.K;
+  p.Y = a.Y; p.y_dtype = a.y_dtype; p.ldy = a.ldy;
+  p.acc_out = a.acc_out; p.ldacc = a.ldacc;
+  p.tiles_m = (a.M + 63) / 64;
+  p.tiles_n = (a.N + 63) / 64;
+  const dim3 grid((unsigned)(p.tiles_m * p.tiles_n)), block(kMidThreads);
+  const bool has_lr = p.r > 0 && p.acc_out == nullptr;
+  const int lrt = !has_lr ? SERQ_BF16 : a.r_dtype;
+#define SERQ_MID_LAUNCH(AB, LRT) hipLaunchKernelGGL((serq_mid_kernel<AB, LRT>), grid, block, 0, st, p)
+  if (a.abits == 8) {
+    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(8, SERQ_I4);
+    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(8, SERQ_F16);
+    else SERQ_MID_LAUNCH(8, SERQ_BF16);
+  } else {
+    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(4, SERQ_I4);
+    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(4, SERQ_F16);
+    else SERQ_MID_LAUNCH(4, SERQ_BF16);
+  }
+#undef SERQ_MID_LAUNCH
+  return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;
+}
+
+}  // namespace serq

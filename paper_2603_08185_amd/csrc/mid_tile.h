@@ -1,0 +1,163 @@
+// Pieces shared by the kernels for batches between decode and prefill (gemm_mid.hip, gemm_mid_mx.hip, grouped_mid.hip):
+// 64 tokens x 64 output channels per workgroup, K dealt out to its 8 waves.
+//
+// Why this shape.  With a few hundred tokens the layer is bound by the bytes that go from L2 to the compute
+// units, and by having a workgroup for each of them.  Tiles of 256 tokens leave most of the chip idle (one token
+// tile x N/64) unless K is cut across workgroups, whose partial tiles then have to meet in memory in a second
+// launch.  Here the partial tiles meet in LDS: every wave owns the whole 64 x 64 tile for its share of K
+// (64 accumulator registers), so nothing is shared between waves and the main loop has no barrier -- a wave
+// waits for its own loads only, and the other wave of its SIMD works meanwhile.
+//
+// A wave's loads run through a ring of stages in its own LDS region, filled by direct global -> LDS loads counted
+// by hand.  A stage holds 64 token rows of 64 bytes and the weight fragments of two channel blocks for the same
+// channels; steps are dealt round-robin, so that the 8 waves read neighbouring pieces of the same rows.
+#ifndef SERQ_MID_TILE_H_
+#define SERQ_MID_TILE_H_
+#include <type_traits>
+
+#include "gemm_tile.h"
+
+namespace serq {
+namespace {
+
+constexpr int kMidWaves = 8;
+constexpr int kMidThreads = 64 * kMidWaves;
+constexpr int kMidX = 64 * 64;                       // token bytes of a stage
+constexpr int kMidPart = 4 * 4 * 64 * 16;            // a wave's partial tile: [tile 2*i + j][register quad][lane][16 B]
+
+// A 64-byte row is a quarter of the 256 bytes that the 64 banks serve at once: rows r .. r+3 take the quarters in
+// turn, and the pieces of rows 4 apart are spread by the xor.
+__device__ __forceinline__ int mid_swz(int row) { return (row >> 2) & 3; }
+
+// how many tiles the busiest compute unit gets
+inline long long mid_rounds(int M, int N, int ncu) {
+  const long long tiles = ((long long)M + 63) / 64 * (((long long)N + 63) / 64);
+  return (tiles + ncu - 1) / ncu;
+}
+
+// The workgroup's tile and a wave's share of its loads.
+// FR: fragments of 64 channels per stage (1: 8-bit tokens, 2: 4-bit tokens).
+template <int FR>
+struct MidLoads {
+  const uint8_t* xbase; const uint8_t* wbase;        // first token row / first weight fragment of the tile
+  uint32_t xv[4];                                    // this lane's four token pieces: row offset + piece
+  uint32_t back;                                     // what a piece of the second fragment steps back when there is none
+  uint32_t wl;
+  size_t wstep1;                                     // from the fragments of block 0 to those of block 1 (0: there is none)
+  int KB;                                            // fragments per channel block
+
+  __device__ __forceinline__ void init(const uint8_t* Xq, const u4* Wq, int K, uint32_t rowbytes, int m0, int mrows, int nb0,
+                                       int nbt, int l) {
+    KB = K >> 6;
+    xbase = Xq + (size_t)m0 * rowbytes;
+    wbase = (const uint8_t*)Wq + (size_t)nb0 * KB * 1024;
+    wstep1 = nbt > 1 ? (size_t)KB * 1024 : 0;
+    wl = (uint32_t)l * 16u;
+    const int c = (l & 3) ^ ((l >> 4) & 3);          // piece 64*i + l is slot l%4 of row 16*i + l/4
+    back = c >= 2 ? 32u : 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int row = 16 * i + (l >> 2);
+      row = row < mrows ? row : mrows - 1;           // rows past M: duplicates, never stored
+      xv[i] = (uint32_t)row * rowbytes + 16u * c;
+    }
+  }
+  // direct load k (of 4 + 2*FR) of step s into the stage at LDS address `st`
+  __device__ __forceinline__ void issue_one(int s, uint32_t st, int k) const {
+    const bool half = FR == 2 && KB - s * FR < FR;   // the last step of an odd number of fragments
+    if (k < 4) {
+      dma16(xbase + (size_t)s * 64, FR == 2 && half ? xv[k] - back : xv[k], st + 1024u * k);
+    } else {
+      const int i = (k - 4) / FR, f = (k - 4) % FR;
+      dma16(wbase + (size_t)s * FR * 1024 + i * wstep1 + (half ? 0 : f) * 1024, wl, st + 1024u * k);
+    }
+  }
+  __device__ __forceinline__ void issue(int s, uint32_t st) const {
+#pragma unroll
+    for (int k = 0; k < 4 + 2 * FR; ++k) issue_one(s, st, k);
+  }
+};
+
+// wait until all but the youngest `n * NL` vector-memory operations of this wave have completed (n = 0 .. 2)
+template <int NL>
+__device__ __forceinline__ void mid_wait(int n) {
+  if (n >= 2) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * NL) : "memory");
+  else if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NL) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+// this wave's LDS reads have returned: the stage they came from may be refilled
+__device__ __forceinline__ void mid_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// The main loop of a wave: its stages 0 .. nst-1 in order.  The operands of a stage are copied to registers one stage
+// ahead, which frees its slot: the slot is refilled, NS stages further, between the products of the stage before.
+// (A direct load blocks the wave while the address unit is busy with the other waves' loads; between two products
+// that costs nothing.)
+//   start(t)              the first loads of stage t (prologue)
+//   fill(t, k)            direct load k of stage t into its slot
+//   read(t, op)           the operands of stage t, from LDS
+//   product(op, k)        the k-th of NP groups of products on the operands `op`
+template <int NS, int NL, int NP, class Op, class Start, class Fill, class Read, class Product>
+__device__ __forceinline__ void mid_loop(int nst, const Start& start, const Fill& fill, const Read& read,
+                                         const Product& product) {
+  if (nst == 0) return;
+#pragma unroll
+  for (int t = 0; t < NS; ++t)
+    if (t < nst) start(t);
+  Op A, B;
+  mid_wait<NL>(nst - 1 < NS - 1 ? nst - 1 : NS - 1);
+  read(0, A);
+  mid_reads_done();
+  if (NS < nst) start(NS);
+  int t = 0;
+  auto half = [&](auto steady_c, const Op& cur, Op& nxt) {
+    constexpr bool STEADY = decltype(steady_c)::value;
+    const bool refill = STEADY || t + 1 + NS < nst;
+    if (STEADY) {
+      mid_wait<NL>(NS - 1);
+      read(t + 1, nxt);
+    } else if (t + 1 < nst) {
+      const int behind = nst - 2 - t;
+      mid_wait<NL>(behind < NS - 1 ? behind : NS - 1);
+      read(t + 1, nxt);
+    }
+    fence();
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      product(cur, k);
+      if (k == 0) mid_reads_done();
+#pragma unroll
+      for (int d = 0; d < NL; ++d)
+        if (d * (NP - 1) / NL == k && refill) fill(t + 1 + NS, d);
+      fence();
+    }
+    ++t;
+  };
+  while (t + 2 + NS < nst) {
+    half(std::true_type{}, A, B);
+    half(std::true_type{}, B, A);
+  }
+  while (t < nst) {
+    half(std::false_type{}, A, B);
+    if (t < nst) half(std::false_type{}, B, A);
+  }
+}
+
+// Rows of 64 16-bit results in LDS (128 bytes), 16-byte piece pc of row r at piece pc ^ (r & 7): four consecutive channels
+// of one token per lane in, whole row segments out.
+constexpr int kMidOut = 64 * 128;
+__device__ __forceinline__ void mid_park16(uint8_t* out, int r, int pc, int g, const float y[4], bool bf) {
+  u2 o;
+  if (bf) o = u2{f32x2_to_bf16x2(y[0], y[1]), f32x2_to_bf16x2(y[2], y[3])};
+  else o = u2{f32x2_to_f16x2(y[0], y[1]), f32x2_to_f16x2(y[2], y[3])};
+  *(u2*)(out + r * 128 + 16 * (pc ^ (r & 7)) + 8 * g) = o;
+}
+__device__ __forceinline__ void mid_store16(const uint8_t* out, int tid, uint16_t* Y, int64_t ldy, int m0, int mrows, int n0,
+                                            int nbt) {
+  const int r = tid >> 3, pc = tid & 7;
+  if (r < mrows && pc < 4 * nbt)
+    *(u4*)(Y + (size_t)(m0 + r) * ldy + n0 + 8 * pc) = *(const u4*)(out + r * 128 + 16 * (pc ^ (r & 7)));
+}
+
+}  // namespace
+}  // namespace serq
+#endif  // SERQ_MID_TILE_H_

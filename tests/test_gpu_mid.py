@@ -1,0 +1,45 @@
+"""The kernels for batches between decode and prefill (64 x 64 tiles, K shared by the waves of a workgroup), which AUTO takes
+for these sizes: against the oracle, and against the tiled kernels."""
+import pytest
+import torch
+
+from paper_2603_08185_amd import binding as serq
+from tests import test_gpu_parity as parity
+
+pytestmark = pytest.mark.gpu
+
+# one token past the decode range, ragged last token tile, one / two / an odd number of channel blocks; K from a single
+# fragment (seven waves idle) over odd fragment counts to rings that wrap
+SHAPES = [
+    (33, 64, 32, 16),
+    (64, 192, 64, 0),
+    (65, 576, 96, 48),
+    (100, 1088, 288, 128),
+    (200, 4160, 160, 144),       # two chunks of the rank-r term, the second ragged
+    (129, 2560, 1056, 320),
+    (333, 6144, 64, 64),
+]
+
+
+@pytest.mark.parametrize("abits", [4, 8])
+@pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
+@pytest.mark.parametrize("M,K,N,r", SHAPES)
+def test_integer_layer(abits, in_dtype, out_dtype, M, K, N, r):
+    spec = parity._small_spec(abits, M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype)
+    mode = "random" if r else "none"
+    Y, _, _ = parity._run_layer(spec, R_mode=mode)          # (also the exact integer sums of gemm_i32)
+    Yt, _, _ = parity._run_layer(spec, R_mode=mode, path=serq.PATH_MFMA, check_pack=False)
+    # the same integer sums, the same order of the rank-r products: the same bits as the tiled kernel
+    assert torch.equal(Y, Yt)
+
+
+@pytest.mark.parametrize("abits", [4, 8])
+@pytest.mark.parametrize("out_dtype", ["fp16", "fp32"])
+@pytest.mark.parametrize("M,K,N,r", [s for s in SHAPES if s[3]])
+def test_integer_layer_q4r(abits, out_dtype, M, K, N, r):
+    parity._run_layer_q4r(parity._small_spec(abits, M, K, N, r, in_dtype="fp16", out_dtype=out_dtype))
+
+
+def test_salient_block_offset():
+    for abits in (4, 8):
+        parity._run_layer_q4r(parity._small_spec(abits, 70, 768, 96, 160), s_begin=416)
