@@ -334,8 +334,8 @@ int serq_g128_pack_weights(const void* W, int w_dtype, const float* s, const int
 int serq_g128_unpack_scales(const void* gscale, int64_t N, int64_t K, float* out, void* stream);
 /* The layer.  zero may be NULL (symmetric codes of serq_quantize_act: the same layer without zero points).
  * Rp / r_dtype: the packed 16-bit compensation matrix as for serq_linear (r = 0 or NULL: none); s_begin a
- * multiple of 32.  Y [M,N] in y_dtype, row stride ldy (multiple of 8).  flags: SERQ_PATH_* only (M <= 32 takes
- * a weight-streaming kernel, larger M an LDS-tiled one).  fp32 sums are added in a fixed order: results do
+ * multiple of 32.  Y [M,N] in y_dtype, row stride ldy (multiple of 8).  flags: SERQ_PATH_* only (AUTO: M <= 32
+ * takes a weight-streaming kernel, larger M small or large LDS tiles by size).  fp32 sums are added in a fixed order: results do
  * not vary from run to run.  No workspace. */
 int serq_g128_linear(const void* Xq, const float* scale, const int32_t* zero, int abits,
                      const void* Wq, const void* gscale, const float* wsum,

@@ -86,7 +86,7 @@ void serq_mid_kernel(const MidParams p) {
 
   const int xsw = mid_swz(lm);                       // the same for row lm and row 32 + lm
   auto slot = [&](int t) { return (t % NS) * T::STAGE; };
-  auto read = [&](int t, MidOp<FR>& o) {
+  auto read = [&](auto, int t, MidOp<FR>& o) {
     const uint8_t* s = my + slot(t);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -105,7 +105,7 @@ void serq_mid_kernel(const MidParams p) {
     }
   };
   // group k: token block k % 2, channel block k / 2 % 2 of fragment k / 4
-  auto product = [&](const MidOp<FR>& o, int k) {
+  auto product = [&](auto, const MidOp<FR>& o, int k) {
     const int j = k & 1, i = (k >> 1) & 1, f = k >> 2;
     v4i a0, a1, b0, b1;
     unpack_frag(o.w[i][f], a0, a1);
@@ -118,7 +118,7 @@ void serq_mid_kernel(const MidParams p) {
     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[i][j], 0, 0, 0);
     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
   };
-  mid_loop<NS, T::NL, 4 * FR, MidOp<FR>>(
+  mid_loop<NS, T::NL, T::NL, 4 * FR, MidOp<FR>>(
       nst, [&](int t) { ld.issue(w + kMidWaves * t, my_lds + slot(t)); },
       [&](int t, int k) { ld.issue_one(w + kMidWaves * t, my_lds + slot(t), k); }, read, product);
 

@@ -293,13 +293,7 @@ inline unsigned blocks_for(size_t n) { return (unsigned)((n + kT - 1) / kT); }
 // ---------------------------------------------------------------------------------------------------
 // the layer
 // ---------------------------------------------------------------------------------------------------
-struct GParams {
-  const uint8_t* Xq; const float* scale; const int32_t* zero;
-  const u4* Wq; const uint16_t* gsc; const float* wsum;
-  const u4* Rp; int r_dtype; int s_begin; int r;
-  int M, N, K;
-  void* Y; int y_dtype; int64_t ldy;
-};
+using GParams = G128Args;
 
 __device__ __forceinline__ void store_y(const GParams& p, int m, int n, const float y[4]) {
   const size_t o = (size_t)m * p.ldy + n;
@@ -924,6 +918,7 @@ int serq_g128_linear(const void* Xq, const float* scale, const int32_t* zero, in
   p.Y = Y; p.y_dtype = y_dtype; p.ldy = ldy;
   hipStream_t st = (hipStream_t)stream;
   const bool skinny = path == SERQ_PATH_SKINNY || (path == SERQ_PATH_AUTO && M <= 32);
+  if (path == SERQ_PATH_AUTO && !skinny && flags == 0 && g128_mid_wanted(p)) return launch_g128_mid(p, abits, st);
   if (skinny) {
     dim3 grid((unsigned)(N / 32));
     // specialised on ceil(M / 8): the number of accumulator register quads that hold tokens

@@ -94,51 +94,59 @@ __device__ __forceinline__ void mid_reads_done() { asm volatile("s_waitcnt lgkmc
 // that costs nothing.)
 //   start(t)              the first loads of stage t (prologue)
 //   fill(t, k)            direct load k of stage t into its slot
-//   read(t, op)           the operands of stage t, from LDS
-//   product(op, k)        the k-th of NP groups of products on the operands `op`
-template <int NS, int NL, int NP, class Op, class Start, class Fill, class Read, class Product>
+//   read(par, t, op)      the operands of stage t, from LDS
+//   product(par, op, k)   the k-th of NP groups of products on the operands `op`
+// par: t % 2 as a compile-time constant.  Even stages take NL0 direct loads, odd ones NL1 (which may differ for NS = 2).
+// Loads requested before the loop are older than its own, so they do not disturb its counting.
+template <int NS, int NL0, int NL1, int NP, class Op, class Start, class Fill, class Read, class Product>
 __device__ __forceinline__ void mid_loop(int nst, const Start& start, const Fill& fill, const Read& read,
                                          const Product& product) {
+  static_assert(NL0 == NL1 || NS == 2, "the youngest NS - 1 stages are one stage of known parity, or all alike");
+  using Even = std::integral_constant<int, 0>;
+  using Odd = std::integral_constant<int, 1>;
   if (nst == 0) return;
 #pragma unroll
   for (int t = 0; t < NS; ++t)
     if (t < nst) start(t);
   Op A, B;
-  mid_wait<NL>(nst - 1 < NS - 1 ? nst - 1 : NS - 1);
-  read(0, A);
+  mid_wait<NL1>(nst - 1 < NS - 1 ? nst - 1 : NS - 1);
+  read(Even{}, 0, A);
   mid_reads_done();
   if (NS < nst) start(NS);
   int t = 0;
-  auto half = [&](auto steady_c, const Op& cur, Op& nxt) {
+  auto half = [&](auto steady_c, auto par_c, const Op& cur, Op& nxt) {
     constexpr bool STEADY = decltype(steady_c)::value;
+    constexpr int PAR = decltype(par_c)::value;
+    constexpr int NLB = PAR ? NL1 : NL0;              // of stage t + 2, which stays in flight (NS = 2)
+    constexpr int NLR = (PAR + 1 + NS) % 2 ? NL1 : NL0;   // of stage t + 1 + NS, which is requested here
     const bool refill = STEADY || t + 1 + NS < nst;
     if (STEADY) {
-      mid_wait<NL>(NS - 1);
-      read(t + 1, nxt);
+      mid_wait<NLB>(NS - 1);
+      read(std::integral_constant<int, 1 - PAR>{}, t + 1, nxt);
     } else if (t + 1 < nst) {
       const int behind = nst - 2 - t;
-      mid_wait<NL>(behind < NS - 1 ? behind : NS - 1);
-      read(t + 1, nxt);
+      mid_wait<NLB>(behind < NS - 1 ? behind : NS - 1);
+      read(std::integral_constant<int, 1 - PAR>{}, t + 1, nxt);
     }
     fence();
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-      product(cur, k);
+      product(par_c, cur, k);
       if (k == 0) mid_reads_done();
 #pragma unroll
-      for (int d = 0; d < NL; ++d)
-        if (d * (NP - 1) / NL == k && refill) fill(t + 1 + NS, d);
+      for (int d = 0; d < NLR; ++d)
+        if (d * (NP - 1) / NLR == k && refill) fill(t + 1 + NS, d);
       fence();
     }
     ++t;
   };
   while (t + 2 + NS < nst) {
-    half(std::true_type{}, A, B);
-    half(std::true_type{}, B, A);
+    half(std::true_type{}, Even{}, A, B);
+    half(std::true_type{}, Odd{}, B, A);
   }
   while (t < nst) {
-    half(std::false_type{}, A, B);
-    if (t < nst) half(std::false_type{}, B, A);
+    half(std::false_type{}, Even{}, A, B);
+    if (t < nst) half(std::false_type{}, Odd{}, B, A);
   }
 }
 

@@ -233,6 +233,16 @@ int launch_mfma_fp4_peak(const void* operands, int iters, int workgroups, int sc
                          hipStream_t st);
 int launch_read_peak(const void* src, size_t bytes, int workgroups, void* sink, hipStream_t st);
 
+// the layer with group-128 weight scales (grouped.hip, grouped_mid.hip)
+struct G128Args {
+  const uint8_t* Xq; const float* scale; const int32_t* zero;
+  const u4* Wq; const uint16_t* gsc; const float* wsum;
+  const u4* Rp; int r_dtype; int s_begin; int r;
+  int M, N, K;
+  void* Y; int y_dtype; int64_t ldy;
+};
+bool g128_mid_wanted(const G128Args& a);
+int launch_g128_mid(const G128Args& a, int abits, hipStream_t st);
 // MXFP4 path (mx.hip, gemm_mx.hip)
 struct MxLinearArgs {
   const uint8_t* Xq; const uint8_t* xsc;

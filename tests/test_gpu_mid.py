@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2603_08185_amd import binding as serq
+from tests import test_gpu_grouped as grouped
 from tests import test_gpu_parity as parity
 
 pytestmark = pytest.mark.gpu
@@ -43,3 +44,22 @@ def test_integer_layer_q4r(abits, out_dtype, M, K, N, r):
 def test_salient_block_offset():
     for abits in (4, 8):
         parity._run_layer_q4r(parity._small_spec(abits, 70, 768, 96, 160), s_begin=416)
+
+
+# K: one group (seven waves idle), 9 groups, 33 groups (a ragged last round of the ring)
+@pytest.mark.parametrize("abits", [4, 8])
+@pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
+@pytest.mark.parametrize("M,K,N,r", [(33, 128, 32, 16), (65, 1152, 96, 0), (100, 4224, 288, 128), (200, 2560, 160, 144),
+                                     (129, 384, 1056, 320), (333, 6144, 64, 64)])
+def test_g128_layer(abits, in_dtype, out_dtype, M, K, N, r):
+    spec = grouped._spec(abits, M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype)
+    Y, _, _ = grouped._run(spec, R_mode="residual" if r else "none")
+    Yb, _, _ = grouped._run(spec, R_mode="residual" if r else "none")
+    assert torch.equal(Y, Yb)                               # fixed summation order
+
+
+def test_g128_layer_variants():
+    for abits in (4, 8):
+        spec = grouped._spec(abits, 70, 768, 96, 160, out_dtype="fp32")
+        grouped._run(spec, asym=False)                      # symmetric codes, no zero points
+        grouped._run(spec, R_mode="random", s_begin=416)    # salient block elsewhere, not on a group boundary
