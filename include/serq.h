@@ -243,7 +243,7 @@ int serq_gemm_i32(const void* Xq, int abits, const void* Wq,
  * Weights, activations and the compensation matrix (along its rank index) all take this form (Eq. 7,
  * second line, with Q = MXFP4), so the layer is
  *   Y[m,n] = sum_k X^[m,k] W^[n,k] + sum_{j<r} X^[m,s_begin+j] R^[n,j]
- * with no further scales.  It runs on the block-scaled FP4 matrix instructions, in a tiled kernel for
+ * with no further scales.  It runs on the block-scaled FP4 matrix instructions, in tiled kernels for
  * M > 32 and a weight-streaming kernel for M <= 32 (SERQ_PATH_* as for serq_linear).
  *
  * Buffers (device memory, 16-byte aligned; opaque except through the unpack calls):

@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libserq.so")
-SOURCES = ["api.hip", "quantize_act.hip", "pack.hip", "skinny.hip", "gemm_mfma.hip", "gemm_mid.hip", "gemm_mx.hip", "skinny_mx.hip",
+SOURCES = ["api.hip", "quantize_act.hip", "pack.hip", "skinny.hip", "gemm_mfma.hip", "gemm_mid.hip", "gemm_mx.hip", "gemm_mid_mx.hip", "skinny_mx.hip",
            "mx.hip", "peaks.hip", "noalloc.hip", "grouped.hip", "grouped_mid.hip", "fp6.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -364,7 +364,9 @@ int serq_mx_linear(const void* Xq, const uint8_t* xscale, const void* Wq, const 
   if (path != SERQ_PATH_AUTO && path != SERQ_PATH_SKINNY && path != SERQ_PATH_MFMA) return SERQ_EUNSUPPORTED;
   if (path == SERQ_PATH_SKINNY && M > 32) return SERQ_ESHAPE;
   const bool skinny = path == SERQ_PATH_SKINNY || (path == SERQ_PATH_AUTO && M <= 32);
-  return skinny ? launch_skinny_mx(a, (hipStream_t)stream) : launch_mx_linear(a, (hipStream_t)stream);
+  if (skinny) return launch_skinny_mx(a, (hipStream_t)stream);
+  if (path == SERQ_PATH_AUTO && a.splitk == 0 && a.coltiles == 0 && mx_mid_wanted(a)) return launch_mx_mid(a, (hipStream_t)stream);
+  return launch_mx_linear(a, (hipStream_t)stream);
 }
 
 int serq_bench_mfma_peak(const void* operands, int iters, int workgroups, void* sink, void* stream) {

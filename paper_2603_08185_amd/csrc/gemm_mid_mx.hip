@@ -1,0 +1,243 @@
+// The MXFP4 layer for batches between decode and prefill: tiles of 64 tokens x 64 channels, the 8 waves of a workgroup
+// sharing K (mid_tile.h says why).
+//   Y[m,n] = sum_k X^[m,k] W^[n,k] + sum_{j<r} X^[m,s_begin+j] R^[n,j]
+//
+// A wave takes whole 256-channel scale tiles: two stages of 128 channels (two fragments of two channel blocks), the
+// scales of the tile with the first.  A 16-byte piece from LDS is an operand of the block-scaled MFMA as it is.  The
+// compensation fragments (64 ranks each) are dealt to the waves one by one after the main loop; their operands are
+// requested before it.  The waves' fp32 tiles are added through LDS in wave order: the same result from run to run.
+//
+// What bounds it: the L2 -> LDS stream (8.5 KiB per 128 channels and wave beside 8 MFMAs), as in gemm_mid.hip.  Measured
+// (M = 200, 4096 x 14336, r = 128): 17 us, the tiled kernel with 4 K slices and a second launch 29 us; the rank-r term
+// costs nothing that shows.
+#include "mid_tile.h"
+
+namespace serq {
+namespace {
+
+struct MxMidParams {
+  const uint8_t* Xq; const uint8_t* xsc;
+  const u4* Wq; const uint8_t* wsc;
+  const u4* Rq; const uint8_t* rsc; int s_begin; int r;
+  int M, N, K;
+  void* Y; int y_dtype; int64_t ldy;
+  int tiles_m, tiles_n;
+};
+
+constexpr int FR = 2;
+constexpr int STAGE = kMidX + 2 * FR * 1024;         // 8 KiB
+constexpr int NS = 2;
+constexpr int WS_OFF = NS * STAGE;                   // weight scales of a tile: 2 blocks x 64 dwords
+constexpr int XS_OFF = WS_OFF + 512;                 // token scales of a tile: 64 rows x 8 bytes
+constexpr int REGION = XS_OFF + 512;
+constexpr int LDS = kMidWaves * REGION;              // 136 KiB
+static_assert(REGION >= kMidPart, "a partial tile fits the ring it replaces");
+
+struct MxMidOp { u4 w[2][FR], x[2][FR]; };
+
+__global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void serq_mx_mid_kernel(const MxMidParams p) {
+  __shared__ __align__(16) uint8_t lds[LDS];
+  const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tile_m, tile_n;
+  map_block(blockIdx.x, p.tiles_m, p.tiles_n, p.tiles_m, tile_m, tile_n);
+  const int m0 = tile_m * 64, nb0 = tile_n * 2;
+  const int NB = p.N >> 5;
+  const int nbt = NB - nb0 < 2 ? 1 : 2;
+  const int mrows = p.M - m0 < 64 ? p.M - m0 : 64;
+  const uint32_t rowbytes = (uint32_t)p.K >> 1;
+  const size_t Mp = (size_t)((p.M + 1) & ~1);          // rows of a tile of the token-scale array
+
+  MidLoads<FR> ld;
+  ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
+  const int KB = ld.KB, T = (KB + 3) >> 2;             // fragments, scale tiles
+  const int nt = T > w ? (T - w + kMidWaves - 1) / kMidWaves : 0;   // tiles w, w + 8, ... are this wave's
+  // stages: two per tile, but for a last tile of one or two fragments
+  const bool short_last = nt > 0 && KB - 4 * (w + kMidWaves * (nt - 1)) <= 2;
+  const int nst = 2 * nt - (short_last ? 1 : 0);
+  uint8_t* my = lds + w * REGION;
+  const uint32_t my_lds = __builtin_amdgcn_readfirstlane(lds_addr(my));
+  const uint32_t xsel = g ? 0x07050301u : 0x06040200u;   // bytes g, 2+g, 4+g, 6+g of a token's 8 scales
+
+  // ---- the first compensation fragment of this wave, requested before everything else (oldest loads) ----------------
+  const int LF = (p.r + 63) >> 6, LT = (LF + 3) >> 2;   // fragments and scale tiles of the compensation matrix per block
+  u4 rq[2], rx[2];
+  uint32_t rs[2], rxs[2];
+  auto lr_fetch = [&](int jf) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const size_t b = nb0 + (i < nbt ? i : 0);
+      rq[i] = p.Rq[(b * LF + jf) * 64 + l];
+      rs[i] = ((const uint32_t*)p.rsc)[(b * LT + (jf >> 2)) * 64 + l] >> (8 * (jf & 3));
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int r0 = 32 * j + lm, m = m0 + (r0 < mrows ? r0 : mrows - 1);
+      rx[j] = *(const u4*)(p.Xq + (size_t)m * rowbytes + ((p.s_begin + 64 * jf) >> 1) + 16 * g);
+      const u2 e = *(const u2*)(p.xsc + ((size_t)((p.s_begin >> 8) + (jf >> 2)) * Mp + m) * 8);
+      rxs[j] = __builtin_amdgcn_perm(e.y, e.x, xsel) >> (8 * (jf & 3));
+    }
+  };
+  if (w < LF) lr_fetch(w);
+
+  // ---- main loop ------------------------------------------------------------------------------------------------
+  v16f acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+  const int xsw = mid_swz(lm);
+  // scales of a tile: lanes 0..15 / 16..31 bring those of weight block 0 / 1, lanes 0..31 those of two token rows each
+  const uint32_t wsv = (uint32_t)(((l >> 4) & 1) && nbt > 1 ? T * 256 : 0) + (l & 15) * 16;
+  const int rp = 2 * (l & 31) < mrows ? l & 31 : (mrows - 1) >> 1;
+  auto tile = [&](int t) { return w + kMidWaves * (t >> 1); };
+  auto fill = [&](int t, int k) {
+    const int u = tile(t);
+    if (k < 8) ld.issue_one(2 * u + (t & 1), my_lds + (t & 1) * STAGE, k);
+    else if (l < 32) {
+      if (k == 8) dma16(p.wsc + ((size_t)nb0 * T + u) * 256, wsv, my_lds + WS_OFF);
+      else dma16(p.xsc + ((size_t)u * Mp + m0) * 8, (uint32_t)rp * 16u, my_lds + XS_OFF);
+    }
+  };
+  uint32_t ws[2], xs[2], wsn[2], xsn[2];               // scales of the tile being multiplied / read ahead
+  auto read = [&](auto par, int t, MxMidOp& o) {
+    const uint8_t* s = my + decltype(par)::value * STAGE;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int f = 0; f < FR; ++f) o.w[i][f] = *(const u4*)(s + kMidX + (i * FR + f) * 1024 + l * 16);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int f = 0; f < FR; ++f) o.x[j][f] = *(const u4*)(s + (32 * j + lm) * 64 + 16 * ((2 * f + g) ^ xsw));
+    if constexpr (decltype(par)::value == 0) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) wsn[i] = *(const uint32_t*)(my + WS_OFF + 256 * i + 4 * l);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const u2 e = *(const u2*)(my + XS_OFF + (32 * j + lm) * 8);
+        xsn[j] = __builtin_amdgcn_perm(e.y, e.x, xsel);
+      }
+      // a last tile without all its fragments: scales that are not there become 1 (their codes are zero)
+      const int nf = KB - 4 * tile(t);
+      if (nf < 4) {
+        const uint32_t keep = (1u << (8 * nf)) - 1u, one = 0x7f7f7f7fu & ~keep;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          wsn[i] = (wsn[i] & keep) | one;
+          xsn[i] = (xsn[i] & keep) | one;
+        }
+      }
+    }
+    if (KB - 4 * tile(t) - 2 * decltype(par)::value < 2) {   // no second fragment in this stage
+#pragma unroll
+      for (int i = 0; i < 2; ++i) o.w[i][1] = u4{0u, 0u, 0u, 0u};
+    }
+  };
+  auto product = [&](auto par, const MxMidOp& o, int k) {
+    constexpr int PAR = decltype(par)::value;
+    if (PAR == 0 && k == 0) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        ws[i] = wsn[i];
+        xs[i] = xsn[i];
+      }
+    }
+    const int j = k & 1, i = (k >> 1) & 1;
+    if (k < 4)
+      acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(o.w[i][0]), fp4_operand(o.x[j][0]), acc[i][j], 4, 4,
+                                                                  2 * PAR, (int)ws[i], 2 * PAR, (int)xs[j]);
+    else
+      acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(o.w[i][1]), fp4_operand(o.x[j][1]), acc[i][j], 4, 4,
+                                                                  2 * PAR + 1, (int)ws[i], 2 * PAR + 1, (int)xs[j]);
+  };
+  mid_loop<NS, 10, 8, 8, MxMidOp>(
+      nst,
+      [&](int t) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) fill(t, k);
+        if ((t & 1) == 0) {
+          fill(t, 8);
+          fill(t, 9);
+        }
+      },
+      fill, read, product);
+
+  // ---- compensation fragments w, w + 8, ... ---------------------------------------------------------------------------
+  for (int jf = w; jf < LF; jf += kMidWaves) {
+    if (jf != w) lr_fetch(jf);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(rq[i]), fp4_operand(rx[j]), acc[i][j], 4, 4, 0,
+                                                                    (int)rs[i], 0, (int)rxs[j]);
+  }
+
+  // ---- the waves meet; wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j ------------------
+  const int ti = w >> 2, tj = (w >> 1) & 1, hq = 2 * (w & 1);
+  const int blk = nb0 + (ti < nbt ? ti : 0);
+  const int mloc = 32 * tj + lm;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *(v4f*)(my + ((2 * i + j) * 4 + q) * 1024 + l * 16) =
+            v4f{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+  __syncthreads();
+  float y[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) y[e] = 0.0f;
+#pragma unroll
+  for (int ww = 0; ww < kMidWaves; ++ww)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const v4f v = *(const v4f*)(lds + ww * REGION + ((w >> 1) * 4 + hq + q) * 1024 + l * 16);
+      y[4 * q] += v.x; y[4 * q + 1] += v.y; y[4 * q + 2] += v.z; y[4 * q + 3] += v.w;
+    }
+  if (p.y_dtype == SERQ_F32) {
+    if (mloc < mrows && ti < nbt) {
+      const int n = 32 * blk + 8 * hq + 4 * g;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        *(float4*)((float*)p.Y + (size_t)(m0 + mloc) * p.ldy + n + 8 * q) =
+            make_float4(y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]);
+    }
+    return;
+  }
+  __syncthreads();                                     // every wave has read the partial tiles: the rows take their place
+#pragma unroll
+  for (int q = 0; q < 2; ++q) mid_park16(lds, mloc, 4 * ti + hq + q, g, y + 4 * q, p.y_dtype == SERQ_BF16);
+  __syncthreads();
+  mid_store16(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
+}
+
+}  // namespace
+
+// Up to two tiles per compute unit.  Measured (us, tiled kernel / this one, r = 128):
+//   1 round:  4096 x 14336 M = 200 29.4 / 17.3;  4096 x 11008 M = 256 28.9 / 15.4;  6144 x 4096 M = 100 20.9 / 8.2;
+//             1024 x 1024 M = 1024 10.1 / 5.1
+//   2 rounds: 4096 x 11008 M = 512 36.2 / 27.7;  6144 x 4096 M = 256 21.1 / 15.1;  28672 x 4096 M = 64 28.0 / 21.8
+//   3 rounds: 6144 x 4096 M = 512 21.6 / 21.6;  4096 x 4096 M = 768 21.5 / 21.3;  4096 x 11008 M = 768 47.5 / 41.9;
+//             28672 x 4096 M = 100 (4) 28.1 / 33.6
+// (N x K; "tiled" slices K where its own plan does.)
+bool mx_mid_wanted(const MxLinearArgs& a) { return mid_rounds(a.M, a.N, device_cu_count()) <= 2; }
+
+int launch_mx_mid(const MxLinearArgs& a, hipStream_t st) {
+  MxMidParams p;
+  p.Xq = a.Xq; p.xsc = a.xsc; p.Wq = a.Wq; p.wsc = a.wsc;
+  p.Rq = a.Rq; p.rsc = a.rsc; p.s_begin = a.s_begin; p.r = a.Rq ? a.r : 0;
+  p.M = a.M; p.N = a.N; p.K = a.K;
+  p.Y = a.Y; p.y_dtype = a.y_dtype; p.ldy = a.ldy;
+  p.tiles_m = (a.M + 63) / 64;
+  p.tiles_n = (a.N + 63) / 64;
+  hipLaunchKernelGGL(serq_mx_mid_kernel, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(kMidThreads), 0, st, p);
+  return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;
+}
+
+}  // namespace serq

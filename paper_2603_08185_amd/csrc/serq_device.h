@@ -263,6 +263,8 @@ int mx_unpack_weights_impl(const void* Wq, const uint8_t* wsc, int N, int K, uin
 int mx_unpack_act_impl(const void* Xq, const uint8_t* xsc, int64_t M, int K, uint8_t* codes, uint8_t* E, hipStream_t st);
 int launch_mx_linear(const MxLinearArgs& a, hipStream_t st);
 int launch_skinny_mx(const MxLinearArgs& a, hipStream_t st);
+bool mx_mid_wanted(const MxLinearArgs& a);
+int launch_mx_mid(const MxLinearArgs& a, hipStream_t st);
 size_t skinny_mx_workspace_bytes(int N);
 
 int pack_weights_impl(const void* W, int w_dtype, const float* s, const int32_t* perm_in, int N, int K, int r,

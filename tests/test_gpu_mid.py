@@ -5,6 +5,7 @@ import torch
 
 from paper_2603_08185_amd import binding as serq
 from tests import test_gpu_grouped as grouped
+from tests import test_gpu_mx as mx
 from tests import test_gpu_parity as parity
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +64,19 @@ def test_g128_layer_variants():
         spec = grouped._spec(abits, 70, 768, 96, 160, out_dtype="fp32")
         grouped._run(spec, asym=False)                      # symmetric codes, no zero points
         grouped._run(spec, R_mode="random", s_begin=416)    # salient block elsewhere, not on a group boundary
+
+
+# K: one fragment; a last scale tile of 1, 2 and 3 fragments, alone in its wave and behind others; several compensation fragments
+@pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
+@pytest.mark.parametrize("M,K,N,r", [(33, 64, 32, 32), (65, 128, 96, 0), (100, 448, 64, 96), (200, 4416, 288, 128),
+                                     (129, 2688, 1056, 640), (333, 6144, 64, 64), (64, 4160, 160, 256)])
+def test_mx_layer(in_dtype, out_dtype, M, K, N, r):
+    spec = mx._spec(M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype)
+    Y, Y64, _ = mx._run_mx(spec)
+    Yb, _, _ = mx._run_mx(spec)
+    assert torch.equal(Y, Yb)                               # fixed summation order
+    mx._run_mx(spec, path=serq.PATH_MFMA)
+
+
+def test_mx_salient_block_offset():
+    mx._run_mx(mx._spec(70, 1344, 96, 160, out_dtype="fp32"), s_begin=768)
