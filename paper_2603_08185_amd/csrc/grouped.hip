@@ -32,8 +32,7 @@ __device__ __forceinline__ float f16bits_to_f32(uint16_t u) { return (float)__bu
 // z = rne(-lo / scale), code = clip(rne(v / scale) + z, 0, 2^n - 1); stored re-centred by 2^(n-1).
 // Every decision is IEEE fp32, as in the oracle.  One workgroup per token, the row kept in registers.
 // ---------------------------------------------------------------------------------------------------
-constexpr int kQT = 256;
-
+template <int KT>
 __device__ __forceinline__ void block_minmax(float& lo, float& hi, float* red) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -45,7 +44,7 @@ __device__ __forceinline__ void block_minmax(float& lo, float& hi, float* red) {
   __syncthreads();
   lo = red[0]; hi = red[1];
 #pragma unroll
-  for (int i = 1; i < kQT / 64; ++i) { lo = fminf(lo, red[2 * i]); hi = fmaxf(hi, red[2 * i + 1]); }
+  for (int i = 1; i < KT / 64; ++i) { lo = fminf(lo, red[2 * i]); hi = fmaxf(hi, red[2 * i + 1]); }
 }
 
 // codes of 8 values: rne(v / sc) + z, clamped to [0, top], re-centred.  t = v * rcp(sc) decides unless it
@@ -93,12 +92,12 @@ __device__ __forceinline__ void flat8(const float* s_inv, int chunk, float v[8])
   }
 }
 
-// NC = 16-byte pieces a thread keeps in registers (0: any K, the row is read twice)
-template <int XDT, int ABITS, int NC>
-__global__ __launch_bounds__(kQT) void quantize_act_asym_kernel(const void* __restrict__ X, const float* __restrict__ s_inv,
+// KT = threads per row, NC = 16-byte pieces a thread keeps in registers (0: any K, the row is read twice)
+template <int XDT, int ABITS, int KT, int NC>
+__global__ __launch_bounds__(KT) void quantize_act_asym_kernel(const void* __restrict__ X, const float* __restrict__ s_inv,
                                                                  int K, int64_t ldx, void* __restrict__ Xq,
                                                                  float* __restrict__ scale, int32_t* __restrict__ zero) {
-  __shared__ float red[2 * kQT / 64];
+  __shared__ float red[2 * KT / 64];
   const int64_t m = blockIdx.x;
   const int nchunk = K >> 3;
   constexpr size_t esz = (XDT == SERQ_F32) ? 4 : 2;
@@ -110,7 +109,7 @@ __global__ __launch_bounds__(kQT) void quantize_act_asym_kernel(const void* __re
   if constexpr (NC > 0) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const int chunk = threadIdx.x + c * kQT;
+      const int chunk = threadIdx.x + c * KT;
       if (chunk < nchunk) {
         load8<XDT>(row, chunk, v[c]);
         flat8(s_inv, chunk, v[c]);
@@ -119,14 +118,14 @@ __global__ __launch_bounds__(kQT) void quantize_act_asym_kernel(const void* __re
       }
     }
   } else {
-    for (int chunk = threadIdx.x; chunk < nchunk; chunk += kQT) {
+    for (int chunk = threadIdx.x; chunk < nchunk; chunk += KT) {
       load8<XDT>(row, chunk, v[0]);
       flat8(s_inv, chunk, v[0]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) { lo = fminf(lo, v[0][i]); hi = fmaxf(hi, v[0][i]); }
     }
   }
-  block_minmax(lo, hi, red);
+  block_minmax<KT>(lo, hi, red);
   const float span = hi - lo;
   const float sc = span > 0.0f ? span / top : 1.0f;
   const float z = rintf(-lo / sc);
@@ -139,14 +138,14 @@ __global__ __launch_bounds__(kQT) void quantize_act_asym_kernel(const void* __re
   if constexpr (NC > 0) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const int chunk = threadIdx.x + c * kQT;
+      const int chunk = threadIdx.x + c * KT;
       if (chunk < nchunk) {
         asym_codes8<ABITS>(v[c], sc, rsc, z, c8);
         store_codes8<ABITS>(c8, xq_row, chunk);
       }
     }
   } else {
-    for (int chunk = threadIdx.x; chunk < nchunk; chunk += kQT) {
+    for (int chunk = threadIdx.x; chunk < nchunk; chunk += KT) {
       load8<XDT>(row, chunk, v[0]);
       flat8(s_inv, chunk, v[0]);
       asym_codes8<ABITS>(v[0], sc, rsc, z, c8);
@@ -158,14 +157,21 @@ __global__ __launch_bounds__(kQT) void quantize_act_asym_kernel(const void* __re
 template <int XDT, int ABITS>
 int launch_asym_t(const void* X, const float* s_inv, int64_t M, int K, int64_t ldx, void* Xq, float* scale,
                   int32_t* zero, hipStream_t st) {
-  const int per = ((K >> 3) + kQT - 1) / kQT;
-  dim3 grid((unsigned)M), block(kQT);
-#define SERQ_QAA(NC) hipLaunchKernelGGL((quantize_act_asym_kernel<XDT, ABITS, NC>), grid, block, 0, st, X, s_inv, K, ldx, Xq, scale, zero)
-  if (per <= 1) SERQ_QAA(1);
-  else if (per <= 2) SERQ_QAA(2);
-  else if (per <= 4) SERQ_QAA(4);
-  else if (per <= 8) SERQ_QAA(8);
-  else SERQ_QAA(0);
+  // as for the symmetric quantiser, but long rows of large batches are better off with 512 threads of 3 or 4 pieces (us,
+  // 256 x 8 / 512 / 1024 threads: K = 11008 M = 100 6.0 / 4.3 / 4.1, M = 4096 37.6 / 32.1 / 37.8)
+  const int nchunk = K >> 3;
+  const int threads = nchunk > 1024 && nchunk <= 2048 ? (M <= 512 ? 1024 : 512) : 256;
+  const int per = (nchunk + threads - 1) / threads;
+  dim3 grid((unsigned)M), block((unsigned)threads);
+#define SERQ_QAA(KT, NC) \
+  hipLaunchKernelGGL((quantize_act_asym_kernel<XDT, ABITS, KT, NC>), grid, block, 0, st, X, s_inv, K, ldx, Xq, scale, zero)
+  if (threads == 1024) SERQ_QAA(1024, 2);
+  else if (threads == 512 && per <= 3) SERQ_QAA(512, 3);
+  else if (threads == 512) SERQ_QAA(512, 4);
+  else if (per <= 1) SERQ_QAA(256, 1);
+  else if (per <= 2) SERQ_QAA(256, 2);
+  else if (per <= 4) SERQ_QAA(256, 4);
+  else SERQ_QAA(256, 0);
 #undef SERQ_QAA
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;
 }

@@ -83,8 +83,8 @@ __device__ __forceinline__ uint32_t pack8(const uint32_t c[8]) {
 // tile gathered by shuffles into one 8-byte store, measured 10 % slower.)
 // GLU: the row is the gated product silu(X) * U formed in fp32 (the input of the down projection,
 // quantised where it is made; Sec. 3.2, the decoder-layer flow of Fig. 2(b)).
-template <int XDT, bool GLU>
-__global__ __launch_bounds__(kT) void mx_quantize_act_kernel(const void* __restrict__ X, const void* __restrict__ U,
+template <int XDT, int KT, bool GLU>
+__global__ __launch_bounds__(KT) void mx_quantize_act_kernel(const void* __restrict__ X, const void* __restrict__ U,
                                                              const float* __restrict__ s_inv, int K, int64_t ldx,
                                                              int64_t ldu, int64_t M, uint32_t* __restrict__ Xq,
                                                              uint8_t* __restrict__ xsc) {
@@ -94,9 +94,9 @@ __global__ __launch_bounds__(kT) void mx_quantize_act_kernel(const void* __restr
   const char* urow = GLU ? (const char*)U + (size_t)m * (size_t)ldu * esz : nullptr;
   const int nchunk = K >> 3;
   const size_t Mp = (size_t)((M + 1) & ~(int64_t)1);
-  const int nround = (nchunk + kT - 1) / kT;                          // kT is a multiple of 4: blocks never straddle rounds
+  const int nround = (nchunk + KT - 1) / KT;                          // KT is a multiple of 4: blocks never straddle rounds
   for (int rd = 0; rd < nround; ++rd) {
-    const int chunk = rd * kT + threadIdx.x;
+    const int chunk = rd * KT + threadIdx.x;
     const bool live = chunk < nchunk;
     float v[8];
 #pragma unroll
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kT) void mx_quantize_act_kernel(const void* __restr
   }
   // the padding row of an odd M
   if (m == M - 1 && (size_t)M < Mp)
-    for (int blk = threadIdx.x; blk < nblk8; blk += kT) xsc[((size_t)(blk >> 3) * Mp + (size_t)M) * 8 + (blk & 7)] = 127;
+    for (int blk = threadIdx.x; blk < nblk8; blk += KT) xsc[((size_t)(blk >> 3) * Mp + (size_t)M) * 8 + (blk & 7)] = 127;
 }
 
 // ---- weights and compensation matrix ------------------------------------------------------------------
@@ -279,18 +279,31 @@ __global__ __launch_bounds__(kT) void mx_unpack_act_kernel(const uint32_t* __res
 
 int launch_mx_quantize_act(const void* X, const void* U, int x_dtype, const float* s_inv, int64_t M, int K, int64_t ldx,
                            int64_t ldu, void* Xq, uint8_t* xsc, hipStream_t st) {
-  dim3 grid((unsigned)M), block(kT);
-#define SERQ_MXQ_LAUNCH(XDT)                                                                                          \
+  // A row is walked in rounds of one piece per thread: while the rows do not fill the chip, one round each (two for the
+  // longest), above that the most even of a few.  Measured (us, 256 / 512 / 1024 threads): K = 4096 M = 24 2.8 / 2.5 / -,
+  // K = 11008 M = 24 4.4 / 3.2 / 2.9, M = 256 5.8 / 4.2 / 3.8, M = 4096 27.3 / 27.4 / 29.5 (gated product 46.2 / 42.7 /
+  // 43.0); K = 8192 M = 4096 18.8 / - / 22.2.
+  const int nchunk = K >> 3;
+  const int threads = nchunk <= 256 ? 256 : M <= 512 ? (nchunk <= 512 ? 512 : 1024) : nchunk > 1024 ? 512 : 256;
+  dim3 grid((unsigned)M), block((unsigned)threads);
+#define SERQ_MXQ_LAUNCH_T(XDT, KT)                                                                                    \
   do {                                                                                                                \
-    if (U) hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, true>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, M,   \
-                              (uint32_t*)Xq, xsc);                                                                    \
-    else hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, false>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, M,    \
-                            (uint32_t*)Xq, xsc);                                                                      \
+    if (U) hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, KT, true>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu,  \
+                              M, (uint32_t*)Xq, xsc);                                                                 \
+    else hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, KT, false>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu,   \
+                            M, (uint32_t*)Xq, xsc);                                                                   \
+  } while (0)
+#define SERQ_MXQ_LAUNCH(XDT)                              \
+  do {                                                    \
+    if (threads == 1024) SERQ_MXQ_LAUNCH_T(XDT, 1024);    \
+    else if (threads == 512) SERQ_MXQ_LAUNCH_T(XDT, 512); \
+    else SERQ_MXQ_LAUNCH_T(XDT, 256);                     \
   } while (0)
   if (x_dtype == SERQ_F32) SERQ_MXQ_LAUNCH(SERQ_F32);
   else if (x_dtype == SERQ_F16) SERQ_MXQ_LAUNCH(SERQ_F16);
   else SERQ_MXQ_LAUNCH(SERQ_BF16);
 #undef SERQ_MXQ_LAUNCH
+#undef SERQ_MXQ_LAUNCH_T
   return ok();
 }
 

@@ -2,7 +2,7 @@
 //
 // Sec. 3.2 Eq. 4 (X~ = X diag(1/s)) followed by Sec. 2.1 Eq. 1 per token:
 //   scale[m] = max_k |x~| / qmax,  code = clip(rne(x~ / scale), -qmax, qmax).
-// One 256-thread workgroup per token; the row is read from HBM once, in
+// One workgroup per token; the row is read from HBM once, in
 // 16-byte pieces, and kept in registers between the absmax pass and the
 // quantise pass.  (Variants that walk several tokens per workgroup or per wave,
 // with the next row prefetched and the flattening factors kept in registers,
@@ -21,8 +21,6 @@
 
 namespace serq {
 namespace {
-
-constexpr int kThreads = 256;
 
 // v <- silu(v) * u, elementwise
 template <int XDT>
@@ -104,6 +102,7 @@ __device__ __forceinline__ void quant_store8(const float v[8], float sc, void* x
   }
 }
 
+template <int KT>
 __device__ __forceinline__ float block_max(float m, float* red) {
   m = wave_max(m);
   const int w = threadIdx.x >> 6;
@@ -111,17 +110,17 @@ __device__ __forceinline__ float block_max(float m, float* red) {
   __syncthreads();
   float r = red[0];
 #pragma unroll
-  for (int i = 1; i < kThreads / 64; ++i) r = fmaxf(r, red[i]);
+  for (int i = 1; i < KT / 64; ++i) r = fmaxf(r, red[i]);
   return r;
 }
 
-// NC = 16-byte pieces (8 channels each) a thread keeps in registers; NC = 0 is
+// KT = threads per row; NC = 16-byte pieces (8 channels each) a thread keeps in registers; NC = 0 is
 // the any-K variant that reads the row a second time (from L2).
-template <int XDT, int ABITS, int NC, bool GLU>
-__global__ __launch_bounds__(kThreads) void quantize_act_kernel(
+template <int XDT, int ABITS, int KT, int NC, bool GLU>
+__global__ __launch_bounds__(KT) void quantize_act_kernel(
     const void* __restrict__ X, const void* __restrict__ U, const float* __restrict__ s_inv, int K, int64_t ldx,
     int64_t ldu, void* __restrict__ Xq, float* __restrict__ scale) {
-  __shared__ float red[kThreads / 64];
+  __shared__ float red[KT / 64];
   const int64_t m = blockIdx.x;
   const int nchunk = K >> 3;
   constexpr size_t esz = (XDT == SERQ_F32) ? 4 : 2;
@@ -135,7 +134,7 @@ __global__ __launch_bounds__(kThreads) void quantize_act_kernel(
     float amax = 0.0f;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const int chunk = threadIdx.x + c * kThreads;
+      const int chunk = threadIdx.x + c * KT;
       if (chunk < nchunk) {
         load8<XDT>(row, chunk, v[c]);
         if constexpr (GLU) glu8<XDT>(urow, chunk, v[c]);
@@ -143,27 +142,27 @@ __global__ __launch_bounds__(kThreads) void quantize_act_kernel(
         amax = absmax8(v[c], amax);
       }
     }
-    amax = block_max(amax, red);
+    amax = block_max<KT>(amax, red);
     const float sc = amax > 0.0f ? amax / q : 1.0f;
     if (threadIdx.x == 0) scale[m] = sc;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const int chunk = threadIdx.x + c * kThreads;
+      const int chunk = threadIdx.x + c * KT;
       if (chunk < nchunk) quant_store8<ABITS>(v[c], sc, xq_row, chunk);
     }
   } else {
     float amax = 0.0f;
-    for (int chunk = threadIdx.x; chunk < nchunk; chunk += kThreads) {
+    for (int chunk = threadIdx.x; chunk < nchunk; chunk += KT) {
       float v[8];
       load8<XDT>(row, chunk, v);
       if constexpr (GLU) glu8<XDT>(urow, chunk, v);
       flatten8(s_inv, chunk, v);
       amax = absmax8(v, amax);
     }
-    amax = block_max(amax, red);
+    amax = block_max<KT>(amax, red);
     const float sc = amax > 0.0f ? amax / q : 1.0f;
     if (threadIdx.x == 0) scale[m] = sc;
-    for (int chunk = threadIdx.x; chunk < nchunk; chunk += kThreads) {
+    for (int chunk = threadIdx.x; chunk < nchunk; chunk += KT) {
       float v[8];
       load8<XDT>(row, chunk, v);
       if constexpr (GLU) glu8<XDT>(urow, chunk, v);
@@ -177,15 +176,20 @@ template <int XDT, int ABITS, bool GLU>
 int launch_t(const void* X, const void* U, const float* s_inv, int64_t M, int K, int64_t ldx, int64_t ldu, void* Xq,
              float* scale, hipStream_t st) {
   const int nchunk = K >> 3;
-  const int per = (nchunk + kThreads - 1) / kThreads;
-  dim3 grid((unsigned)M), block(kThreads);
-#define SERQ_QA_LAUNCH(NC) \
-  hipLaunchKernelGGL((quantize_act_kernel<XDT, ABITS, NC, GLU>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, Xq, scale)
-  if (per <= 1) SERQ_QA_LAUNCH(1);
-  else if (per <= 2) SERQ_QA_LAUNCH(2);
-  else if (per <= 4) SERQ_QA_LAUNCH(4);
-  else if (per <= 8) SERQ_QA_LAUNCH(8);
-  else SERQ_QA_LAUNCH(0);
+  // 256 threads with 1, 2 or 4 pieces each; rows of 1025 .. 2048 pieces would take 8 (most of them past the row) and go to
+  // 1024 threads with 2 instead.  Measured (us, 256 x 8 / 1024 x 2, 8-bit codes; the gated product behind the semicolon):
+  // K = 11008 M = 1 4.4 / 3.1, M = 256 6.3 / 4.6; 7.7 / 5.3, M = 4096 36.6 / 35.3; 51.3 / 45.0; K = 14336 M = 256
+  // 6.9 / 4.9.  Shorter rows gain nothing from more threads (K = 8192 M = 256 4.9 / 4.8, M = 4096 25.0 / 34.6).
+  const int threads = nchunk > 1024 && nchunk <= 2048 ? 1024 : 256;
+  const int per = (nchunk + threads - 1) / threads;
+  dim3 grid((unsigned)M), block((unsigned)threads);
+#define SERQ_QA_LAUNCH(KT, NC)                                                                                            \
+  hipLaunchKernelGGL((quantize_act_kernel<XDT, ABITS, KT, NC, GLU>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, Xq, scale)
+  if (threads == 1024) SERQ_QA_LAUNCH(1024, 2);
+  else if (per <= 1) SERQ_QA_LAUNCH(256, 1);
+  else if (per <= 2) SERQ_QA_LAUNCH(256, 2);
+  else if (per <= 4) SERQ_QA_LAUNCH(256, 4);
+  else SERQ_QA_LAUNCH(256, 0);
 #undef SERQ_QA_LAUNCH
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;
 }
