@@ -98,11 +98,13 @@ def lib() -> C.CDLL:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()          # (ctypes makes the void* from the number)
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # torch.cuda.current_stream().cuda_stream without the Stream object built on the way: 0.2 instead of 2.7 us, a
+    # third of what a call costs the host
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(fn: str, rc: int):
