@@ -301,23 +301,6 @@ inline unsigned blocks_for(size_t n) { return (unsigned)((n + kT - 1) / kT); }
 // ---------------------------------------------------------------------------------------------------
 using GParams = G128Args;
 
-__device__ __forceinline__ void store_y(const GParams& p, int m, int n, const float y[4]) {
-  const size_t o = (size_t)m * p.ldy + n;
-  if (p.y_dtype == SERQ_F32) *(float4*)((float*)p.Y + o) = make_float4(y[0], y[1], y[2], y[3]);
-  else if (p.y_dtype == SERQ_BF16) *(u2*)((uint16_t*)p.Y + o) = u2{f32x2_to_bf16x2(y[0], y[1]), f32x2_to_bf16x2(y[2], y[3])};
-  else *(u2*)((uint16_t*)p.Y + o) = u2{f32x2_to_f16x2(y[0], y[1]), f32x2_to_f16x2(y[2], y[3])};
-}
-
-// the 16 group scales a lane needs for one 32-channel block: channels 8i + 4g + 0..3, i = 0..3, as stored
-// (fp16: the fold below widens them inside a mixed-precision fused multiply-add)
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-struct GS16 { h4 v[4]; };
-// accf += gscale * acc for one 32 x 32 tile (register e: channel 8*(e/4) + 4g + e%4)
-__device__ __forceinline__ void fold_tile(const GS16& gs, const v16i& acc, v16f& accf) {
-#pragma unroll
-  for (int e = 0; e < 16; ++e) accf[e] = __builtin_fmaf((float)gs.v[e >> 2][e & 3], (float)acc[e], accf[e]);
-}
-
 // 8 re-centred codes (code - zero) of one lane as exact 16-bit floats; all zero for a lane without a token
 // (in two steps, so that a loop can have the loads of several fragments in flight before it converts the first)
 template <int ABITS>
@@ -505,17 +488,19 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void serq_g128_skinny_kernel(con
   }
 }
 
-// ---- M > 32: LDS-tiled kernel, 128 tokens x 128 channels per workgroup of 4 waves (2 x 2) ----------------
+// ---- larger M: LDS-tiled kernel, 128 tokens x 128 channels per workgroup of 4 waves (2 x 2) ---------------
 // One stage = one group of 128 input channels: 4 blocks x 2 weight fragments (8 KiB), 128 token rows
 // (16 KiB at 8 bits, 8 KiB at 4 bits; 16-byte pieces xor-swizzled per row so that the operand reads are
 // free of bank conflicts) and the group's 128 scales (256 B).  The stages form a ring (3 deep at 8 bits,
 // 4 at 4 bits) filled by direct global -> LDS loads (no staging registers) that run two or three groups
 // ahead of the arithmetic and are counted by hand with vmcnt; one barrier per group.  Two workgroups
 // share a compute unit, so the barrier of one is covered by the other.
-// Each wave owns 2 x 2 MFMA tiles: 64 INT32 accumulators, folded into 64 fp32 accumulators after every
-// group.  The four MFMAs of a group run tile by tile, and the convert-and-FMA pairs that fold the tile
-// finished before are issued between them, so that the vector unit works in the shadow of the matrix
-// unit (a group costs as many cycles on the one as on the other).
+// Each wave owns 2 x 2 MFMA tiles of fp32 accumulators.  Tokens are the MFMA's row operand and weights its column
+// operand: a lane holds one channel of each block, so a group's scales are one register per block.  The operands of
+// the next group are copied from LDS to registers while this group is multiplied (the registers for that come from
+// the scales and from keeping two INT32 tiles, not four): the products never wait for an LDS read.  The four MFMAs
+// of a group run tile by tile, and the convert-and-FMA pairs that fold the tile before are issued between them, so
+// that the vector unit works in the shadow of the matrix unit.
 template <int ABITS>
 struct GTile {
   static constexpr int XROW = 128 * ABITS / 8;       // bytes of a token's 128 codes
@@ -527,9 +512,14 @@ struct GTile {
   static constexpr int NS = ABITS == 8 ? 3 : 4;      // ring depth
   static constexpr int NLX = 128 * P / 256;          // token loads per thread and group: 4 or 2
   static constexpr int NL = 2 + NLX + 1;             // direct loads per wave and group
+  static constexpr int TS_OFF = NS * STAGE;          // for the epilogue: 128 token scales, zero points and wsum of the tile
+  static constexpr int LDS = TS_OFF + 3 * 128 * 4;
   static __device__ __forceinline__ int swz(int row) { return ABITS == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
-  static_assert(2 * NS * STAGE <= 160 * 1024, "two workgroups per compute unit");
+  static_assert(2 * LDS <= 160 * 1024, "two workgroups per compute unit");
 };
+
+template <int ABITS>
+struct GOp { u4 w[2][2], x[2][ABITS == 8 ? 4 : 2]; float gs[2]; };   // raw operands and scales of one group
 
 template <int ABITS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void serq_g128_tiled_kernel(const GParams p) {
@@ -537,7 +527,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int SH = ABITS == 8 ? 4 : 8;
   constexpr float kInv = 1.0f / (float)(1 << SH);
   constexpr int NS = T::NS;
-  __shared__ __align__(16) uint8_t lds[NS * T::STAGE];
+  __shared__ __align__(16) uint8_t lds[T::LDS];
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lm = l & 31, g = l >> 5;
   const int wn = w & 1, wm = w >> 1;
   const int NB = p.N >> 5, KB = p.K >> 6, G = p.K >> 7;
@@ -557,23 +547,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // pieces, and (4 lanes) the 64 bytes of scales of block w.
   const int wu = __builtin_amdgcn_readfirstlane(w);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(lds));
-  uint32_t wv[2], xv[T::NLX];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int pc = tid + 256 * i;                     // [block][fragment][lane]
-    int b = pc >> 7;
-    b = b < nbt ? b : nbt - 1;                        // blocks past the tile: duplicates, never stored
-    wv[i] = (uint32_t)((b * KB + ((pc >> 6) & 1)) * 1024 + (pc & 63) * 16);
-  }
-#pragma unroll
-  for (int i = 0; i < T::NLX; ++i) {
-    const int q = tid + 256 * i;                      // LDS piece: row q / P, slot q % P
-    const int row = q / T::P;
-    const int c = (q % T::P) ^ T::swz(row);           // the global piece that lives in that slot
-    const int rr = row < mrows ? row : mrows - 1;     // rows past M: duplicates, never stored
-    xv[i] = (uint32_t)((size_t)rr * rowbytes) + 16u * c;
-  }
-  const uint32_t sv = (uint32_t)((wu < nbt ? wu : nbt - 1) * G * 64 + (l & 3) * 16);
+  // (few registers, every one is taken in the main loop: the weight and scale offsets are wave-uniform but for the lane, and
+  // the token rows of the NLX loads lie 1024 / XROW * 4 rows apart, with the same swizzle)
+  constexpr int XSTEP = 256 / T::P;                   // rows from one token load of a thread to its next
+  static_assert((XSTEP & 15) == 0, "the same swizzle");
+  const int xrow0 = tid / T::P;
+  const int xc = (tid % T::P) ^ T::swz(xrow0);        // the global piece that lives in this lane's slot
+  const uint32_t xv0 = (uint32_t)xrow0 * (uint32_t)rowbytes + 16u * xc;
+  const uint32_t xlast = (uint32_t)(mrows - 1) * (uint32_t)rowbytes + 16u * xc;   // rows past M: duplicates of the last, never stored
   const uint8_t* wbase = (const uint8_t*)p.Wq + (size_t)nb0 * KB * 1024;
   const uint8_t* xbase = p.Xq + (size_t)m0 * rowbytes;
   const uint8_t* sbase = (const uint8_t*)p.gsc + (size_t)nb0 * G * 64;
@@ -588,154 +569,219 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int gi = q < G ? q : lg0 + (q - G);
     const uint32_t sb = lds0 + (uint32_t)st * T::STAGE;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) dma16(wbase + (size_t)gi * 2048, wv[i], sb + 1024 * wu + 4096 * i);
+    for (int i = 0; i < 2; ++i) {
+      int b = 2 * i + (wu >> 1);                      // blocks past the tile: duplicates, never stored
+      b = b < nbt ? b : nbt - 1;
+      dma16(wbase + (size_t)gi * 2048 + (size_t)(b * KB + (wu & 1)) * 1024, (uint32_t)l * 16u, sb + 1024 * wu + 4096 * i);
+    }
 #pragma unroll
-    for (int i = 0; i < T::NLX; ++i) dma16(xbase + (size_t)gi * T::XROW, xv[i], sb + T::WB + 1024 * wu + 4096 * i);
-    if (l < 4) dma16(sbase + (size_t)gi * 64, sv, sb + T::SC_OFF + 64 * wu);
+    for (int i = 0; i < T::NLX; ++i) {
+      const uint32_t xv = xv0 + (uint32_t)(i * XSTEP) * (uint32_t)rowbytes;
+      dma16(xbase + (size_t)gi * T::XROW, xv < xlast ? xv : xlast, sb + T::WB + 1024 * wu + 4096 * i);
+    }
+    if (l < 4)
+      dma16(sbase + (size_t)gi * 64 + (size_t)(wu < nbt ? wu : nbt - 1) * G * 64, (uint32_t)l * 16u, sb + T::SC_OFF + 64 * wu);
   };
 
-  // this wave's blocks 2*wn + i and token rows 32*(2*wm + j) + lm
-  int xoff[2], xsw[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = 32 * (2 * wm + j) + lm;
-    xoff[j] = T::WB + row * T::XROW;
-    xsw[j] = T::swz(row);
+  // what the epilogue needs of the tile's tokens and channels, requested before the ring (older loads do not disturb its
+  // counting) and straight into LDS: waves 0, 1 bring scales and zero points, waves 2, 3 wsum
+  {
+    const int i = 64 * (wu & 1) + l;
+    const uint32_t ts = lds0 + T::TS_OFF + 256 * (wu & 1);
+    if (wu < 2) {
+      const uint32_t row = 4u * (uint32_t)(i < mrows ? i : mrows - 1);
+      dma4(p.scale + m0, row, ts);
+      if (p.zero) dma4(p.zero + m0, row, ts + 512);
+    } else {
+      dma4(p.wsum + 32 * nb0, 4u * (uint32_t)(i < 32 * nbt ? i : 0), ts + 1024);
+    }
   }
+
+  // this wave's blocks 2*wn + i and token rows 32*(2*wm + j) + lm
+  const int xrow = 64 * wm + lm;                      // (row 32 further: the same swizzle)
+  const int xoff = T::WB + xrow * T::XROW, xsw = T::swz(xrow);
+  // piece c ^ xsw of that row for c = (piece of this half-wave) ^ k: one address and an xor of 16 * k, because the row and
+  // stage offsets leave those bits free
+  const int xbase_off = xoff + 16 * ((ABITS == 8 ? 2 * g : g) ^ xsw);
+  static_assert(T::STAGE % 128 == 0 && T::WB % 128 == 0, "stage offsets keep the low address bits free for the xor");
   int bi[2];                                          // block index in the layer, clamped for the loads of the epilogue
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int b = 2 * wn + i;
     bi[i] = nb0 + (b < nbt ? b : nbt - 1);
   }
-
-  v16i acc[2][2];
-  v16f accf[2][2];
-  const v16i kZero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { acc[i][j][e] = 0; accf[i][j][e] = 0.0f; }
-  GS16 gprev;                                         // scales of the tiles whose fold is still owed: block 1 of the group before
-#pragma unroll
-  for (int q4 = 0; q4 < 4; ++q4) gprev.v[q4] = h4{0, 0, 0, 0};
-
-  // the four MFMAs of tile (i,j) of a group, each followed by a quarter of the fold of tile `fa` into `ff`
-  auto tile = [&](const v4i (&a)[4], const v4i (&b)[4], v16i& t_acc, const GS16& fg, const v16i& fa, v16f& ff) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      // the first product of a group starts from zero (a constant operand, no registers to clear)
-      if (t == 0) t_acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[t], b[t], kZero16, 0, 0, 0);
-      else t_acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[t], b[t], t_acc, 0, 0, 0);
-#pragma unroll
-      for (int e = 4 * t; e < 4 * t + 4; ++e) ff[e] = __builtin_fmaf((float)fg.v[e >> 2][e & 3], (float)fa[e], ff[e]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-#pragma unroll
-  for (int s = 0; s < NS - 1; ++s)
-    if (s < GT) issue(s, s);
-  int st = 0, sti = NS - 1;
-#pragma unroll 1
-  for (int gi = 0; gi < G; ++gi) {
-    // group gi has landed (this wave's loads: all but those of the NS-2 groups behind it), every wave has
-    // got here, so everybody's loads have landed and the stage read last round may be refilled
-    const int last = gi + NS - 2 < GT - 1 ? gi + NS - 2 : GT - 1;
-    if (last - gi == NS - 2) wait_dma_barrier<(NS - 2) * T::NL>();
-    else wait_dma_barrier<0>();
-    if (gi + NS - 1 < GT) issue(gi + NS - 1, sti);
-    sti = sti + 1 == NS ? 0 : sti + 1;
+  auto read_w = [&](int st, GOp<ABITS>& o) {
     const uint8_t* s = lds + st * T::STAGE;
-    st = st + 1 == NS ? 0 : st + 1;
-    v4i a[2][4], b[2][4];                             // operands of the group's four 32-channel steps
-    GS16 gs[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
 #pragma unroll
-      for (int f = 0; f < 2; ++f)
-        unpack_frag(*(const u4*)(s + (((2 * wn + i) * 2 + f) * 64 + l) * 16), a[i][2 * f], a[i][2 * f + 1]);
-      const int j = i;
-#pragma unroll
-      for (int f = 0; f < 2; ++f) {
-        if constexpr (ABITS == 8) {
-          const int c = 4 * f + 2 * g;
-          b[j][2 * f] = *(const v4i*)(s + xoff[j] + 16 * (c ^ xsw[j]));
-          b[j][2 * f + 1] = *(const v4i*)(s + xoff[j] + 16 * ((c + 1) ^ xsw[j]));
-        } else {
-          unpack_frag(*(const u4*)(s + xoff[j] + 16 * ((2 * f + g) ^ xsw[j])), b[j][2 * f], b[j][2 * f + 1]);
-        }
-      }
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) gs[i].v[q4] = *(const h4*)(s + T::SC_OFF + 64 * (2 * wn + i) + 2 * (8 * q4 + 4 * g));
+      for (int f = 0; f < 2; ++f) o.w[i][f] = *(const u4*)(s + (((2 * wn + i) * 2 + f) * 64 + l) * 16);
+      o.gs[i] = (float)*(const _Float16*)(s + T::SC_OFF + 64 * (2 * wn + i) + 2 * lm);
     }
-    // each tile's MFMAs shadow the fold of the tile finished two tiles earlier (its results have long arrived);
-    // the two tiles of block 1 are folded during the first half of the next group
-    tile(a[0], b[0], acc[0][0], gprev, acc[1][0], accf[1][0]);
-    tile(a[0], b[1], acc[0][1], gprev, acc[1][1], accf[1][1]);
-    tile(a[1], b[0], acc[1][0], gs[0], acc[0][0], accf[0][0]);
-    tile(a[1], b[1], acc[1][1], gs[0], acc[0][1], accf[0][1]);
-    gprev = gs[1];
-  }
-  fold_tile(gprev, acc[1][0], accf[1][0]);
-  fold_tile(gprev, acc[1][1], accf[1][1]);
-
-  // ---- epilogue: zero point, rank-r term on the re-centred codes, token scale, one store ----------------
-  const bool bf = p.r_dtype == SERQ_BF16;
-  int mrow[2], zm[2];
-  float sm[2];
-  bool rv[2];
+  };
+  auto read_x = [&](int st, GOp<ABITS>& o) {
+    const int xa = st * T::STAGE + xbase_off;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int m = m0 + 32 * (2 * wm + j) + lm;
-    rv[j] = m < p.M;
-    mrow[j] = rv[j] ? m : p.M - 1;
-    zm[j] = p.zero ? p.zero[mrow[j]] : 0;
-    sm[j] = p.scale[mrow[j]];
-  }
+    for (int h = 0; h < (ABITS == 8 ? 4 : 2); ++h) {
+      const int k = ABITS == 8 ? 4 * (h >> 1) + (h & 1) : 2 * h;   // 8-bit: fragment h/2, K half h%2; 4-bit: fragment h
+#pragma unroll
+      for (int j = 0; j < 2; ++j) o.x[j][h] = *(const u4*)(lds + (xa ^ (16 * k)) + 32 * j * T::XROW);
+    }
+  };
+
+  v16i acc[2];                                        // INT32 tiles: the one being multiplied, the one being folded
+  v16f accf[2][2];
+  const v16i kZero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    float ws[16];
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const float4 t = *(const float4*)(p.wsum + (size_t)bi[i] * 32 + 8 * q4 + 4 * g);
-      ws[4 * q4] = t.x; ws[4 * q4 + 1] = t.y; ws[4 * q4 + 2] = t.z; ws[4 * q4 + 3] = t.w;
-    }
+    acc[i] = kZero16;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) accf[i][j][e] = __builtin_fmaf(accf[i][j][e], kInv, -(float)zm[j] * ws[e]);   // 2^-SH: exact
+      for (int e = 0; e < 16; ++e) accf[i][j][e] = 0.0f;
   }
+  float gprev = 0.0f;                                 // scale of the tile whose fold is still owed: tile (1,1) of the group before
+
+  // the four tiles of a group; the MFMAs of tile u = 2*i + j shadow the fold of the tile before.  The next group's weights
+  // are read once the registers of this group's first block are free.
+  auto multiply = [&](const GOp<ABITS>& o, int nst, GOp<ABITS>& nxt) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u == 2) {
+        read_w(nst, nxt);
+        fence();
+      }
+      const int i = u >> 1, j = u & 1;
+      const int pu = (u + 3) & 3, pi = pu >> 1, pj = pu & 1;
+      const float gs = u == 0 ? gprev : o.gs[pi];
+      v4i a[4], b[4];
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        unpack_frag(o.w[i][f], a[2 * f], a[2 * f + 1]);
+        if constexpr (ABITS == 8) {
+          b[2 * f] = as_v4i(o.x[j][2 * f]);
+          b[2 * f + 1] = as_v4i(o.x[j][2 * f + 1]);
+        } else {
+          unpack_frag(o.x[j][f], b[2 * f], b[2 * f + 1]);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        // the first product of a group starts from zero (a constant operand, no registers to clear)
+        if (t == 0) acc[u & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b[t], a[t], kZero16, 0, 0, 0);
+        else acc[u & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b[t], a[t], acc[u & 1], 0, 0, 0);
+        // (nothing behind the first: the last product of the tile before has not come out yet)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (t > 0 && e * 3 / 16 == t - 1)
+            accf[pi][pj][e] = __builtin_fmaf(gs, (float)acc[(u & 1) ^ 1][e], accf[pi][pj][e]);
+        fence();
+      }
+    }
+    gprev = o.gs[1];
+  };
+
+  // the first `younger` stages behind the one waited for may still be in flight
+  auto wait_stage = [&](int younger) {
+    if (younger >= NS - 1) wait_dma_barrier<(NS - 1) * T::NL>();
+    else if (younger == NS - 2) wait_dma_barrier<(NS - 2) * T::NL>();
+    else wait_dma_barrier<0>();
+  };
+  auto behind = [&](int q) { return (q + NS - 1 < GT - 1 ? q + NS - 1 : GT - 1) - q; };
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    if (s < GT) issue(s, s);
+  GOp<ABITS> A, B;
+  wait_stage(behind(0));
+  read_w(0, A);
+  read_x(0, A);
+  int st = 0;                                         // slot of the current group
+  auto group = [&](int gi, const GOp<ABITS>& cur, GOp<ABITS>& nxt) {
+    // the next group has landed (its loads but not those of the NS-2 groups behind it), and every wave has read this
+    // one, whose slot may be refilled
+    const int next = st + 1 == NS ? 0 : st + 1;
+    const int last = gi + NS - 1 < GT - 1 ? gi + NS - 1 : GT - 1;
+    if (last - gi == NS - 1) wait_dma_barrier<(NS - 2) * T::NL>();
+    else wait_dma_barrier<0>();
+    if (gi + NS < GT) issue(gi + NS, st);
+    st = next;
+    read_x(st, nxt);                                  // (behind the last stage: stale bytes, never used)
+    fence();
+    multiply(cur, st, nxt);
+  };
+  int gi = 0;
+#pragma unroll 1
+  for (; gi + 1 < G; gi += 2) {
+    group(gi, A, B);
+    group(gi + 1, B, A);
+  }
+  if (gi < G) group(gi, A, B);
+
+  // ---- epilogue: zero point, rank-r term on the re-centred codes, token scale, one store ----------------
+  // register e of lane (lm, g) in tile (i, j): token 32*(2*wm + j) + 8*(e/4) + 4*g + e%4, channel 32*bi[i] + lm
+  // The R fragments come straight from L2, four 16-rank fragments at a time and a batch ahead of their use, the first
+  // batch requested here.
+  const int JB = p.r >> 4;
+  constexpr int NJ = 4;
+  u4 rr[NJ][2], rn[NJ][2];
+  auto load_r = [&](int jb0) {
+#pragma unroll
+    for (int q4 = 0; q4 < NJ; ++q4) {
+      const int jb = jb0 + q4 < JB ? jb0 + q4 : JB - 1;   // past the end: a duplicate, never used
+#pragma unroll
+      for (int i = 0; i < 2; ++i) rn[q4][i] = p.Rp[((size_t)bi[i] * JB + jb) * 64 + l];
+    }
+  };
+  if (has_lr) load_r(0);
+  fence();
+#pragma unroll
+  for (int e = 0; e < 16; ++e) accf[1][1][e] = __builtin_fmaf(gprev, (float)acc[1][e], accf[1][1][e]);
+  const float* tsc = reinterpret_cast<const float*>(lds + T::TS_OFF);       // (in LDS since the first stage was waited for)
+  const int* tzr = reinterpret_cast<const int*>(lds + T::TS_OFF + 512);
+  const float* tws = reinterpret_cast<const float*>(lds + T::TS_OFF + 1024);
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      v4i z = {0, 0, 0, 0};
+      if (p.zero) z = *(const v4i*)(tzr + 32 * (2 * wm + j) + 8 * q4 + 4 * g);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const float ws = tws[32 * (2 * wn + i) + lm];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          accf[i][j][4 * q4 + e] = __builtin_fmaf(accf[i][j][4 * q4 + e], kInv, -(float)z[e] * ws);   // 2^-SH: exact
+      }
+    }
   if (has_lr) {
     // The token codes of the salient block come back through the ring (they ran ahead of the last main groups,
-    // like any stage); the R fragments come straight from L2, four 16-rank fragments requested before the first
-    // is used.
-    const int JB = p.r >> 4;
-    constexpr int NJ = 4;
+    // like any stage).
+    const bool bf = p.r_dtype == SERQ_BF16;
+    int zm[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) zm[j] = p.zero ? tzr[32 * (2 * wm + j) + lm] : 0;
 #pragma unroll 1
     for (int lg = 0; lg < LG; ++lg) {
       const int q = G + lg;
-      const int last = q + NS - 2 < GT - 1 ? q + NS - 2 : GT - 1;
-      if (last - q == NS - 2) wait_dma_barrier<(NS - 2) * T::NL>();
-      else wait_dma_barrier<0>();
-      if (q + NS - 1 < GT) issue(q + NS - 1, sti);
-      sti = sti + 1 == NS ? 0 : sti + 1;
+      // stage q has landed, and every wave has read the one before, whose slot is refilled (the R fragments in flight are
+      // younger than some of its loads: the wait is then stricter than needed, never looser)
+      wait_stage(lg == 0 ? behind(q) : (q + NS - 2 < GT - 1 ? q + NS - 2 : GT - 1) - q);
+      if (lg > 0) {
+        if (q - 1 + NS < GT) issue(q - 1 + NS, st);
+        st = st + 1 == NS ? 0 : st + 1;
+      }
       const uint8_t* s = lds + st * T::STAGE;
-      st = st + 1 == NS ? 0 : st + 1;
       const int c0 = 128 * (lg0 + lg);                    // first channel of this group of token codes
       const int jb_lo = c0 > p.s_begin ? (c0 - p.s_begin) >> 4 : 0;
       const int jb_end = (c0 + 128 - p.s_begin) >> 4;
       const int jb_hi = jb_end < JB ? jb_end : JB;
 #pragma unroll 1
       for (int jb0 = jb_lo; jb0 < jb_hi; jb0 += NJ) {
-        u4 rr[NJ][2];
 #pragma unroll
-        for (int q4 = 0; q4 < NJ; ++q4) {
-          const int jb = jb0 + q4 < jb_hi ? jb0 + q4 : jb_hi - 1;   // past the end: a duplicate, never used
+        for (int q4 = 0; q4 < NJ; ++q4)
 #pragma unroll
-          for (int i = 0; i < 2; ++i) rr[q4][i] = p.Rp[((size_t)bi[i] * JB + jb) * 64 + l];
-        }
+          for (int i = 0; i < 2; ++i) rr[q4][i] = rn[q4][i];
+        load_r(jb0 + NJ < jb_hi ? jb0 + NJ : jb_hi);
 #pragma unroll
         for (int q4 = 0; q4 < NJ; ++q4) {
           if (jb0 + q4 < jb_hi) {                         // uniform
@@ -745,69 +791,70 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int j = 0; j < 2; ++j) {
               u2 xr;
               if constexpr (ABITS == 8) {
-                xr = *(const u2*)(s + xoff[j] + 16 * ((col >> 4) ^ xsw[j]) + (col & 15));
+                xr = *(const u2*)(s + xoff + 32 * j * T::XROW + 16 * ((col >> 4) ^ xsw) + (col & 15));
               } else {
                 const int byte = col >> 1;
-                xr = u2{*(const uint32_t*)(s + xoff[j] + 16 * ((byte >> 4) ^ xsw[j]) + (byte & 15)), 0u};
+                xr = u2{*(const uint32_t*)(s + xoff + 32 * j * T::XROW + 16 * ((byte >> 4) ^ xsw) + (byte & 15)), 0u};
               }
               xf[j] = lr_convert_packed<ABITS>(xr, zm[j], bf);   // rows past M: duplicates, never stored
             }
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-              for (int j = 0; j < 2; ++j) accf[i][j] = mfma_lr16(rr[q4][i], xf[j], accf[i][j], bf);
+              for (int j = 0; j < 2; ++j) accf[i][j] = mfma_lr16(xf[j], rr[q4][i], accf[i][j], bf);
           }
         }
       }
     }
   }
-  if (p.y_dtype != SERQ_F32) {
-    // 16-bit output: cast, transpose through LDS (the ring is free now; rows of 256 B, the 16-byte piece pc of
-    // row r at piece pc ^ (r & 15)), then stores of whole row segments: 16 lanes write 256 contiguous bytes
-    __syncthreads();                                    // every wave is done with the ring
-    const bool ybf = p.y_dtype == SERQ_BF16;
+  if (p.y_dtype == SERQ_F32) {
+    // fp32 output: 32 lanes write 128 contiguous bytes straight from the accumulators
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int r = 32 * (2 * wm + j) + lm;
+      for (int e = 0; e < 16; ++e) {
+        const int r = 32 * (2 * wm + j) + 8 * (e >> 2) + 4 * g + (e & 3);
+        const float sm = tsc[r];
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int pc = 4 * (2 * wn + i) + q4;
-          const float y0 = sm[j] * accf[i][j][4 * q4], y1 = sm[j] * accf[i][j][4 * q4 + 1];
-          const float y2 = sm[j] * accf[i][j][4 * q4 + 2], y3 = sm[j] * accf[i][j][4 * q4 + 3];
-          u2 o;
-          if (ybf) o = u2{f32x2_to_bf16x2(y0, y1), f32x2_to_bf16x2(y2, y3)};
-          else o = u2{f32x2_to_f16x2(y0, y1), f32x2_to_f16x2(y2, y3)};
-          *(u2*)(lds + r * 256 + 16 * (pc ^ (r & 15)) + 8 * g) = o;
-        }
+        for (int i = 0; i < 2; ++i)
+          if (r < mrows && 2 * wn + i < nbt) ((float*)p.Y)[(size_t)(m0 + r) * p.ldy + 32 * bi[i] + lm] = sm * accf[i][j][e];
       }
-    __syncthreads();
-    const int npc = 4 * nbt;                            // 16-byte pieces of a row that belong to the layer
-#pragma unroll 2
-    for (int rr = 0; rr < 128 / 16; ++rr) {
-      const int r = rr * 16 + (tid >> 4);
-      const int pc = tid & 15;
-      if (r < mrows && pc < npc) {
-        const u4 v = *(const u4*)(lds + r * 256 + 16 * (pc ^ (r & 15)));
-        *(u4*)((uint16_t*)p.Y + (size_t)(m0 + r) * p.ldy + nb0 * 32 + 8 * pc) = v;
-      }
-    }
     return;
   }
-  // fp32 output: 16-byte stores straight from the accumulators
+  // 16-bit output: cast, transpose through LDS (the ring is free now; rows of 256 B, the 16-byte piece pc of
+  // row r at piece pc ^ (r & 15)), then stores of whole row segments: 16 lanes write 256 contiguous bytes.  Two
+  // neighbouring lanes hold two channels of the same tokens: they exchange halves, so that the even lane writes both
+  // channels of one token and the odd lane those of the next.
+  __syncthreads();                                      // every wave is done with the ring
+  const bool ybf = p.y_dtype == SERQ_BF16;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    if (2 * wn + i >= nbt) continue;
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (!rv[j]) continue;
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const int r0 = 32 * (2 * wm + j) + 8 * q4 + 4 * g;
+      const v4f sm = *(const v4f*)(tsc + r0);
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const float y[4] = {sm[j] * accf[i][j][4 * q4], sm[j] * accf[i][j][4 * q4 + 1], sm[j] * accf[i][j][4 * q4 + 2],
-                            sm[j] * accf[i][j][4 * q4 + 3]};
-        store_y(p, mrow[j], bi[i] * 32 + 8 * q4 + 4 * g, y);
-      }
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float y0 = sm[2 * h] * accf[i][j][4 * q4 + 2 * h], y1 = sm[2 * h + 1] * accf[i][j][4 * q4 + 2 * h + 1];
+          const uint32_t own = ybf ? f32x2_to_bf16x2(y0, y1) : f32x2_to_f16x2(y0, y1);
+          const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+          const uint32_t v = (l & 1) ? __builtin_amdgcn_perm(own, nb, 0x07060302u) : __builtin_amdgcn_perm(nb, own, 0x05040100u);
+          const int r = r0 + 2 * h + (l & 1);
+          const int c = 32 * (2 * wn + i) + (lm & ~1);
+          *(uint32_t*)(lds + r * 256 + 16 * ((c >> 3) ^ (r & 15)) + 2 * (c & 7)) = v;
+        }
+    }
+  __syncthreads();
+  const int npc = 4 * nbt;                              // 16-byte pieces of a row that belong to the layer
+#pragma unroll 2
+  for (int rr = 0; rr < 128 / 16; ++rr) {
+    const int r = rr * 16 + (tid >> 4);
+    const int pc = tid & 15;
+    if (r < mrows && pc < npc) {
+      const u4 v = *(const u4*)(lds + r * 256 + 16 * (pc ^ (r & 15)));
+      *(u4*)((uint16_t*)p.Y + (size_t)(m0 + r) * p.ldy + nb0 * 32 + 8 * pc) = v;
     }
   }
 }
