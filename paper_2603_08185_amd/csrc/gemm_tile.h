@@ -11,12 +11,11 @@ namespace {
 // them, each with its own L2), so ids are first regrouped into one contiguous
 // range per XCD; inside a range, tiles are ordered in bands of `groupm` token
 // tiles so that the tiles in flight on one XCD share weight and token panels.
-__device__ __forceinline__ void map_block(int bid, int tm, int tn, int gm, int& tile_m, int& tile_n) {
-  const int T = tm * tn;
-  const int per = (T + 7) >> 3;
-  const int tall = (T & 7) == 0 ? 8 : (T & 7);
-  const int xcd = bid & 7, loc = bid >> 3;
-  const int logical = xcd < tall ? xcd * per + loc : tall * per + (xcd - tall) * (per - 1) + loc;
+__device__ __forceinline__ int xcd_first(int xcd, int T) {          // first of the tiles of an XCD, of T in all
+  const int per = (T + 7) >> 3, tall = (T & 7) == 0 ? 8 : (T & 7);
+  return xcd < tall ? xcd * per : tall * per + (xcd - tall) * (per - 1);
+}
+__device__ __forceinline__ void band_tile(int logical, int tm, int tn, int gm, int& tile_m, int& tile_n) {
   const int gsize = gm * tn;
   const int grp = logical / gsize;
   const int first_m = grp * gm;
@@ -24,6 +23,9 @@ __device__ __forceinline__ void map_block(int bid, int tm, int tn, int gm, int& 
   const int within = logical - grp * gsize;
   tile_m = first_m + within % gsz;
   tile_n = within / gsz;
+}
+__device__ __forceinline__ void map_block(int bid, int tm, int tn, int gm, int& tile_m, int& tile_n) {
+  band_tile(xcd_first(bid & 7, tm * tn) + (bid >> 3), tm, tn, gm, tile_m, tile_n);
 }
 
 // ---- the hand-counted waits of the direct-to-LDS loads (dma16, serq_device.h) ----------------

@@ -17,6 +17,8 @@
 // weight-streaming kernel for M <= 32 and an LDS-tiled kernel above, and their C entry points.
 // Weight codes use the fragment layout of the per-channel path (serq_unpack_weights reads them back);
 // group scales: [N/32][K/128][32 channels] fp16.
+#include <type_traits>
+
 #include "gemm_tile.h"
 #include "serq_device.h"
 
@@ -511,18 +513,18 @@ struct GTile {
   static constexpr int STAGE = SC_OFF + 256;
   static constexpr int NS = ABITS == 8 ? 3 : 4;      // ring depth
   static constexpr int NLX = 128 * P / 256;          // token loads per thread and group: 4 or 2
-  static constexpr int NL = 2 + NLX + 1;             // direct loads per wave and group
+  static constexpr int nl(int ni) { return ni + NLX + 1; }   // direct loads per wave and group
   static constexpr int TS_OFF = NS * STAGE;          // for the epilogue: 128 token scales, zero points and wsum of the tile
   static constexpr int LDS = TS_OFF + 3 * 128 * 4;
   static __device__ __forceinline__ int swz(int row) { return ABITS == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
   static_assert(2 * LDS <= 160 * 1024, "two workgroups per compute unit");
 };
 
-template <int ABITS>
-struct GOp { u4 w[2][2], x[2][ABITS == 8 ? 4 : 2]; float gs[2]; };   // raw operands and scales of one group
+template <int ABITS, int NI>
+struct GOp { u4 w[NI][2], x[2][ABITS == 8 ? 4 : 2]; float gs[NI]; };   // raw operands and scales of one group
 
-template <int ABITS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void serq_g128_tiled_kernel(const GParams p) {
+template <int ABITS, bool HALVES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void serq_g128_tiled_kernel(const GParams p, int full) {
   using T = GTile<ABITS>;
   constexpr int SH = ABITS == 8 ? 4 : 8;
   constexpr float kInv = 1.0f / (float)(1 << SH);
@@ -532,11 +534,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int wn = w & 1, wm = w >> 1;
   const int NB = p.N >> 5, KB = p.K >> 6, G = p.K >> 7;
   // workgroup id -> tile: one contiguous range of tiles per XCD, in bands of 8 token tiles, so that the
-  // tiles in flight on one XCD share their weight and token panels in its L2
+  // tiles in flight on one XCD share their weight and token panels in its L2.  HALVES: workgroups from `full` on
+  // (a multiple of 8) take half a tile each, the 64-channel halves of the tiles that are left on their XCD.
+  const int tm = (p.M + 127) >> 7, tn = (NB + 3) >> 2;
+  const bool halved = HALVES && (int)blockIdx.x >= full;
+  const int bid = halved ? blockIdx.x - full : blockIdx.x;
+  const int logical = xcd_first(bid & 7, tm * tn) + (halved ? (full >> 3) + (bid >> 4) : bid >> 3);
+  if (halved && logical >= xcd_first((bid & 7) + 1, tm * tn)) return;   // (an XCD with a tile less than others)
   int tile_m, tile_n;
-  map_block(blockIdx.x, (p.M + 127) >> 7, (NB + 3) >> 2, 8, tile_m, tile_n);
-  const int nb0 = tile_n * 4;
-  const int nbt = NB - nb0 < 4 ? NB - nb0 : 4;
+  band_tile(logical, tm, tn, 8, tile_m, tile_n);
+  const int nb0 = tile_n * 4 + (halved ? 2 * ((bid >> 3) & 1) : 0);
+  if (nb0 >= NB) return;                              // the second half of a last, narrow tile
+  const int nbt = NB - nb0 < (halved ? 2 : 4) ? NB - nb0 : (halved ? 2 : 4);
   const int m0 = tile_m * 128;
   const int mrows = p.M - m0 < 128 ? p.M - m0 : 128;
   const size_t rowbytes = (size_t)p.K * ABITS / 8;
@@ -565,11 +574,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int lg0 = p.s_begin >> 7;
   const int LG = has_lr ? ((p.s_begin + p.r + 127) >> 7) - lg0 : 0;
   const int GT = G + LG;
+  // Everything from here on is specialised on the channel blocks per wave: 2, or 1 in half a tile.
+  auto body = [&](auto ni_c) {
+  constexpr int NI = decltype(ni_c)::value;
+  using Op = GOp<ABITS, NI>;
   auto issue = [&](int q, int st) {
     const int gi = q < G ? q : lg0 + (q - G);
     const uint32_t sb = lds0 + (uint32_t)st * T::STAGE;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NI; ++i) {
       int b = 2 * i + (wu >> 1);                      // blocks past the tile: duplicates, never stored
       b = b < nbt ? b : nbt - 1;
       dma16(wbase + (size_t)gi * 2048 + (size_t)(b * KB + (wu & 1)) * 1024, (uint32_t)l * 16u, sb + 1024 * wu + 4096 * i);
@@ -597,29 +610,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   }
 
-  // this wave's blocks 2*wn + i and token rows 32*(2*wm + j) + lm
+  // this wave's blocks NI*wn + i and token rows 32*(2*wm + j) + lm
   const int xrow = 64 * wm + lm;                      // (row 32 further: the same swizzle)
   const int xoff = T::WB + xrow * T::XROW, xsw = T::swz(xrow);
   // piece c ^ xsw of that row for c = (piece of this half-wave) ^ k: one address and an xor of 16 * k, because the row and
   // stage offsets leave those bits free
   const int xbase_off = xoff + 16 * ((ABITS == 8 ? 2 * g : g) ^ xsw);
   static_assert(T::STAGE % 128 == 0 && T::WB % 128 == 0, "stage offsets keep the low address bits free for the xor");
-  int bi[2];                                          // block index in the layer, clamped for the loads of the epilogue
+  int bi[NI];                                         // block index in the layer, clamped for the loads of the epilogue
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int b = 2 * wn + i;
+  for (int i = 0; i < NI; ++i) {
+    const int b = NI * wn + i;
     bi[i] = nb0 + (b < nbt ? b : nbt - 1);
   }
-  auto read_w = [&](int st, GOp<ABITS>& o) {
+  auto read_w = [&](int st, Op& o) {
     const uint8_t* s = lds + st * T::STAGE;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NI; ++i) {
 #pragma unroll
-      for (int f = 0; f < 2; ++f) o.w[i][f] = *(const u4*)(s + (((2 * wn + i) * 2 + f) * 64 + l) * 16);
-      o.gs[i] = (float)*(const _Float16*)(s + T::SC_OFF + 64 * (2 * wn + i) + 2 * lm);
+      for (int f = 0; f < 2; ++f) o.w[i][f] = *(const u4*)(s + (((NI * wn + i) * 2 + f) * 64 + l) * 16);
+      o.gs[i] = (float)*(const _Float16*)(s + T::SC_OFF + 64 * (NI * wn + i) + 2 * lm);
     }
   };
-  auto read_x = [&](int st, GOp<ABITS>& o) {
+  auto read_x = [&](int st, Op& o) {
     const int xa = st * T::STAGE + xbase_off;
 #pragma unroll
     for (int h = 0; h < (ABITS == 8 ? 4 : 2); ++h) {
@@ -630,29 +643,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
 
   v16i acc[2];                                        // INT32 tiles: the one being multiplied, the one being folded
-  v16f accf[2][2];
+  v16f accf[NI][2];
   const v16i kZero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    acc[i] = kZero16;
+  for (int j = 0; j < 2; ++j) {
+    acc[j] = kZero16;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int e = 0; e < 16; ++e) accf[i][j][e] = 0.0f;
   }
-  float gprev = 0.0f;                                 // scale of the tile whose fold is still owed: tile (1,1) of the group before
+  float gprev = 0.0f;                                 // scale of the tile whose fold is still owed: the last one of the group before
 
-  // the four tiles of a group; the MFMAs of tile u = 2*i + j shadow the fold of the tile before.  The next group's weights
+  // the tiles of a group; the MFMAs of tile u = 2*i + j shadow the fold of the tile before.  The next group's weights
   // are read once the registers of this group's first block are free.
-  auto multiply = [&](const GOp<ABITS>& o, int nst, GOp<ABITS>& nxt) {
+  auto multiply = [&](const Op& o, int nst, Op& nxt) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (u == 2) {
+    for (int u = 0; u < 2 * NI; ++u) {
+      if (u == NI) {
         read_w(nst, nxt);
         fence();
       }
       const int i = u >> 1, j = u & 1;
-      const int pu = (u + 3) & 3, pi = pu >> 1, pj = pu & 1;
+      const int pu = (u + 2 * NI - 1) % (2 * NI), pi = pu >> 1, pj = pu & 1;
       const float gs = u == 0 ? gprev : o.gs[pi];
       v4i a[4], b[4];
 #pragma unroll
@@ -678,30 +691,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         fence();
       }
     }
-    gprev = o.gs[1];
+    gprev = o.gs[NI - 1];
   };
 
   // the first `younger` stages behind the one waited for may still be in flight
   auto wait_stage = [&](int younger) {
-    if (younger >= NS - 1) wait_dma_barrier<(NS - 1) * T::NL>();
-    else if (younger == NS - 2) wait_dma_barrier<(NS - 2) * T::NL>();
+    if (younger >= NS - 1) wait_dma_barrier<(NS - 1) * T::nl(NI)>();
+    else if (younger == NS - 2) wait_dma_barrier<(NS - 2) * T::nl(NI)>();
     else wait_dma_barrier<0>();
   };
   auto behind = [&](int q) { return (q + NS - 1 < GT - 1 ? q + NS - 1 : GT - 1) - q; };
 #pragma unroll
   for (int s = 0; s < NS; ++s)
     if (s < GT) issue(s, s);
-  GOp<ABITS> A, B;
+  Op A, B;
   wait_stage(behind(0));
   read_w(0, A);
   read_x(0, A);
   int st = 0;                                         // slot of the current group
-  auto group = [&](int gi, const GOp<ABITS>& cur, GOp<ABITS>& nxt) {
+  auto group = [&](int gi, const Op& cur, Op& nxt) {
     // the next group has landed (its loads but not those of the NS-2 groups behind it), and every wave has read this
     // one, whose slot may be refilled
     const int next = st + 1 == NS ? 0 : st + 1;
     const int last = gi + NS - 1 < GT - 1 ? gi + NS - 1 : GT - 1;
-    if (last - gi == NS - 1) wait_dma_barrier<(NS - 2) * T::NL>();
+    if (last - gi == NS - 1) wait_dma_barrier<(NS - 2) * T::nl(NI)>();
     else wait_dma_barrier<0>();
     if (gi + NS < GT) issue(gi + NS, st);
     st = next;
@@ -723,19 +736,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // batch requested here.
   const int JB = p.r >> 4;
   constexpr int NJ = 4;
-  u4 rr[NJ][2], rn[NJ][2];
+  u4 rr[NJ][NI], rn[NJ][NI];
   auto load_r = [&](int jb0) {
 #pragma unroll
     for (int q4 = 0; q4 < NJ; ++q4) {
       const int jb = jb0 + q4 < JB ? jb0 + q4 : JB - 1;   // past the end: a duplicate, never used
 #pragma unroll
-      for (int i = 0; i < 2; ++i) rn[q4][i] = p.Rp[((size_t)bi[i] * JB + jb) * 64 + l];
+      for (int i = 0; i < NI; ++i) rn[q4][i] = p.Rp[((size_t)bi[i] * JB + jb) * 64 + l];
     }
   };
   if (has_lr) load_r(0);
   fence();
 #pragma unroll
-  for (int e = 0; e < 16; ++e) accf[1][1][e] = __builtin_fmaf(gprev, (float)acc[1][e], accf[1][1][e]);
+  for (int e = 0; e < 16; ++e) accf[NI - 1][1][e] = __builtin_fmaf(gprev, (float)acc[1][e], accf[NI - 1][1][e]);
   const float* tsc = reinterpret_cast<const float*>(lds + T::TS_OFF);       // (in LDS since the first stage was waited for)
   const int* tzr = reinterpret_cast<const int*>(lds + T::TS_OFF + 512);
   const float* tws = reinterpret_cast<const float*>(lds + T::TS_OFF + 1024);
@@ -746,8 +759,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       v4i z = {0, 0, 0, 0};
       if (p.zero) z = *(const v4i*)(tzr + 32 * (2 * wm + j) + 8 * q4 + 4 * g);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const float ws = tws[32 * (2 * wn + i) + lm];
+      for (int i = 0; i < NI; ++i) {
+        const float ws = tws[32 * (NI * wn + i) + lm];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           accf[i][j][4 * q4 + e] = __builtin_fmaf(accf[i][j][4 * q4 + e], kInv, -(float)z[e] * ws);   // 2^-SH: exact
@@ -780,7 +793,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int q4 = 0; q4 < NJ; ++q4)
 #pragma unroll
-          for (int i = 0; i < 2; ++i) rr[q4][i] = rn[q4][i];
+          for (int i = 0; i < NI; ++i) rr[q4][i] = rn[q4][i];
         load_r(jb0 + NJ < jb_hi ? jb0 + NJ : jb_hi);
 #pragma unroll
         for (int q4 = 0; q4 < NJ; ++q4) {
@@ -799,7 +812,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
               xf[j] = lr_convert_packed<ABITS>(xr, zm[j], bf);   // rows past M: duplicates, never stored
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
               for (int j = 0; j < 2; ++j) accf[i][j] = mfma_lr16(xf[j], rr[q4][i], accf[i][j], bf);
           }
@@ -816,8 +829,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int r = 32 * (2 * wm + j) + 8 * (e >> 2) + 4 * g + (e & 3);
         const float sm = tsc[r];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-          if (r < mrows && 2 * wn + i < nbt) ((float*)p.Y)[(size_t)(m0 + r) * p.ldy + 32 * bi[i] + lm] = sm * accf[i][j][e];
+        for (int i = 0; i < NI; ++i)
+          if (r < mrows && NI * wn + i < nbt) ((float*)p.Y)[(size_t)(m0 + r) * p.ldy + 32 * bi[i] + lm] = sm * accf[i][j][e];
       }
     return;
   }
@@ -834,7 +847,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       const int r0 = 32 * (2 * wm + j) + 8 * q4 + 4 * g;
       const v4f sm = *(const v4f*)(tsc + r0);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const float y0 = sm[2 * h] * accf[i][j][4 * q4 + 2 * h], y1 = sm[2 * h + 1] * accf[i][j][4 * q4 + 2 * h + 1];
@@ -842,7 +855,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
           const uint32_t v = (l & 1) ? __builtin_amdgcn_perm(own, nb, 0x07060302u) : __builtin_amdgcn_perm(nb, own, 0x05040100u);
           const int r = r0 + 2 * h + (l & 1);
-          const int c = 32 * (2 * wn + i) + (lm & ~1);
+          const int c = 32 * (NI * wn + i) + (lm & ~1);
           *(uint32_t*)(lds + r * 256 + 16 * ((c >> 3) ^ (r & 15)) + 2 * (c & 7)) = v;
         }
     }
@@ -857,6 +870,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       *(u4*)((uint16_t*)p.Y + (size_t)(m0 + r) * p.ldy + nb0 * 32 + 8 * pc) = v;
     }
   }
+  };
+  if constexpr (HALVES) {
+    if (halved) {
+      body(std::integral_constant<int, 1>{});
+      return;
+    }
+  }
+  body(std::integral_constant<int, 2>{});
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -993,9 +1014,21 @@ int serq_g128_linear(const void* Xq, const float* scale, const int32_t* zero, in
   } else {
     const long long tiles = (long long)((N / 32 + 3) / 4) * ((M + 127) / 128);
     if (tiles > 0x7fffffffLL) return SERQ_ESHAPE;
-    dim3 grid((unsigned)tiles);
-    if (abits == 8) hipLaunchKernelGGL(serq_g128_tiled_kernel<8>, grid, dim3(256), 0, st, p);
-    else hipLaunchKernelGGL(serq_g128_tiled_kernel<4>, grid, dim3(256), 0, st, p);
+    // Two workgroups share a compute unit.  What is left after whole rounds is dealt out in halves when that still gives
+    // every compute unit at most one workgroup: alone there, a whole tile takes half a round.  Measured (us, whole / halves,
+    // W4A8 r = 128, N x K): 64 tiles left 6144 x 4096 M = 1500 74.1 / 66.3; 128 left M = 3000 133 / 126; 160 left
+    // 14336 x 4096 M = 700 (W4A4) 71.5 / 75.6; 192 left 11008 x 4096 M = 4096 260 / 264.
+    const long long ncu = device_cu_count();
+    const long long full = tiles / (2 * ncu) * (2 * ncu), left = tiles - full;
+    if (left > 0 && 2 * left <= ncu && full % 8 == 0) {
+      const dim3 grid((unsigned)(full + 16 * ((left + 7) / 8)));
+      if (abits == 8) hipLaunchKernelGGL((serq_g128_tiled_kernel<8, true>), grid, dim3(256), 0, st, p, (int)full);
+      else hipLaunchKernelGGL((serq_g128_tiled_kernel<4, true>), grid, dim3(256), 0, st, p, (int)full);
+    } else {
+      const dim3 grid((unsigned)tiles);
+      if (abits == 8) hipLaunchKernelGGL((serq_g128_tiled_kernel<8, false>), grid, dim3(256), 0, st, p, 0);
+      else hipLaunchKernelGGL((serq_g128_tiled_kernel<4, false>), grid, dim3(256), 0, st, p, 0);
+    }
   }
   return hip_ok();
 }

@@ -228,3 +228,14 @@ def test_g128_error_codes():
     assert serq.lib().serq_g128_scale_bytes(64, 256) == 64 * 2 * 2
     assert serq.lib().serq_g128_scale_bytes(64, 192) == 0
     assert serq.g128_linear(x, f, z, 8, x, x, f, 0, 64, 128).shape == (0, 64)
+
+
+# the last tiles of a launch in 64-channel halves: fewer tiles than a quarter of the slots (with a last tile of 1, 2, 3 and 4
+# channel blocks), and more than one round of whole tiles before them
+@pytest.mark.parametrize("abits", [4, 8])
+@pytest.mark.parametrize("M,K,N,r", [(130, 256, 32, 16), (257, 384, 192, 32), (140, 384, 224, 48), (300, 256, 128, 0),
+                                     (2200, 128, 4000, 16)])
+def test_g128_tiles_in_halves(abits, M, K, N, r):
+    spec = _spec(abits, M, K, N, r, out_dtype="bf16")
+    _run(spec, path=serq.PATH_MFMA, R_mode="residual" if r else "none")
+    _run(_spec(abits, M, K, N, r, out_dtype="fp32"), path=serq.PATH_MFMA, R_mode="residual" if r else "none")
