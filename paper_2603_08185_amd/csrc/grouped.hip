@@ -355,72 +355,109 @@ __device__ __forceinline__ u4 lr_convert_packed(const u2& x, int zm, bool bf) {
   }
   return o;
 }
-template <int ABITS>
-__device__ __forceinline__ u4 lr_operand(const uint8_t* xrow, int col, int zm, bool valid, bool bf) {
-  return lr_convert<ABITS>(lr_load<ABITS>(xrow, col), zm, valid, bf);
-}
-
 __device__ __forceinline__ v16f mfma_lr16(const u4& r, const u4& x, v16f acc, bool bf) {
   if (bf) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, r), __builtin_bit_cast(v8bf, x), acc, 0, 0, 0);
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, r), __builtin_bit_cast(v8h, x), acc, 0, 0, 0);
 }
 
 // ---- M <= 32: one workgroup of 8 waves per block of 32 output channels, weights streamed once ----------
-// Wave w takes the groups w, w+8, ... NG at a time (2, or 4 for K >= 8192, where a wave still has two rounds
-// of them: measured better from there on, worse below): the 1-KiB weight fragments, the groups' scales and
+// Wave w takes the groups w, w+8, ... NG at a time: the 1-KiB weight fragments, the groups' scales and
 // the token codes are all requested before the first is used.  The tokens are the MFMA's row operand
 // and the weights its column operand, so a lane holds ONE output channel (one group scale per lane) and
 // its registers are tokens: register e of lane (c, g) is token 8*(e/4) + 4g + e%4 of channel c.  With M <= 8
 // tokens only registers 0..3 carry anything, with M <= 16 registers 0..7, ...: the fold of a group's INT32
-// tile into the fp32 tile touches 4*MQ registers (MQ = ceil(M/8)), not 16.  The wave adds its share of the
-// rank-r term, and the eight waves are added through LDS in a fixed order (run-to-run identical).
+// tile into the fp32 tile touches 4*MQ registers (MQ = ceil(M/8)), not 16.
+// The token codes come as whole lines, straight into the wave's own LDS region (16-byte pieces xor-swizzled per row), and
+// are read back as operands: per lane from L2 they touch 32 lines an instruction.  They are requested before
+// the weights, because loads retire in order, and one hand-counted wait on "all but the weights" covers them.
+// What the end needs -- a fragment of the rank-r term per wave, scales, zero points, wsum -- is requested before the loop.
+// The eight waves are added through LDS in a fixed order (run-to-run identical).
+//
+// Bound by the weight stream and, with many tokens, by staging the token rows in every workgroup.  Measured (us, token
+// codes per lane from L2 and end operands requested late / this form, r = 128, W4A8, N x K, weights out of cache): 11008 x
+// 4096 M = 1 8.8 / 7.2, M = 16 11.0 / 8.4, M = 32 14.9 / 10.4; 28672 x 8192 M = 1 29.5 / 22.4, M = 32 47.6 / 33.4.
 constexpr int kPitch = 33;
 constexpr int kSkinnyWaves = 8;
 template <int ABITS, int MQ, int NG>
+struct GSkinny {
+  static constexpr int XROW = 128 * ABITS / 8;              // bytes of a token's codes of one group: 128 or 64
+  static constexpr int RPI = 1024 / XROW;                   // token rows one direct load covers: 8 or 16
+  static constexpr int NX = (8 * MQ + RPI - 1) / RPI;       // direct loads per group
+  static constexpr int XG = NX * 1024;
+  static constexpr int RED = 8 * MQ * kPitch * 4;           // a wave's partial sums, later in the same place
+  static constexpr int REGION = NG * XG > RED ? NG * XG : (RED + 15) / 16 * 16;
+  static __device__ __forceinline__ int swz(int row) { return ABITS == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
+};
+template <int ABITS, int MQ, int NG>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void serq_g128_skinny_kernel(const GParams p) {
+  using T = GSkinny<ABITS, MQ, NG>;
   constexpr int SH = ABITS == 8 ? 4 : 8;
   constexpr float kInv = 1.0f / (float)(1 << SH);
   constexpr int NE = 4 * MQ;                                // live accumulator registers
-  __shared__ float red[kSkinnyWaves][8 * MQ * kPitch];
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, m = l & 31, g = l >> 5;
+  __shared__ __align__(16) uint8_t lds[kSkinnyWaves * T::REGION];
+  const int tid = threadIdx.x, l = tid & 63, m = l & 31, g = l >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nb = blockIdx.x;
   const int KB = p.K >> 6, G = p.K >> 7;
-  const size_t rowbytes = (size_t)p.K * ABITS / 8;
+  const uint32_t rowbytes = (uint32_t)p.K * ABITS / 8;
   const bool mv = m < p.M;
   const uint8_t* xrow = p.Xq + (size_t)(mv ? m : 0) * rowbytes;
   const u4* wfr = p.Wq + (size_t)nb * KB * 64 + l;
   const uint16_t* gsl = p.gsc + (size_t)nb * G * 32 + m;    // this lane's channel (lane & 31)
-  const int zm = (p.zero && mv) ? p.zero[m] : 0;
+  uint8_t* my = lds + w * T::REGION;
+  const uint32_t my_lds = __builtin_amdgcn_readfirstlane(lds_addr(my));
   const v16i kZero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+
+  // ---- what the end needs, requested first -----------------------------------------------------------
+  const bool has_lr = p.r > 0 && p.Rp != nullptr;
+  const bool bf = p.r_dtype == SERQ_BF16;
+  const int JB = has_lr ? p.r >> 4 : 0;
+  const u4* rfr = p.Rp + (size_t)nb * JB * 64 + l;
+  const int zm = (p.zero && mv) ? p.zero[m] : 0;
+  u4 rf = {0u, 0u, 0u, 0u};
+  u2 xr = {0u, 0u};
+  if (w < JB) {
+    rf = rfr[(size_t)w * 64];
+    xr = lr_load<ABITS>(xrow, p.s_begin + 16 * w + 8 * g);
+  }
+  constexpr int NQ = (256 * MQ + 64 * kSkinnyWaves - 1) / (64 * kSkinnyWaves);
+  float sc_m[NQ];
+  int z_m[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int mt = (tid >> 5) + q * 2 * kSkinnyWaves;
+    sc_m[q] = mt < p.M ? p.scale[mt] : 0.0f;
+    z_m[q] = (p.zero && mt < p.M) ? p.zero[mt] : 0;
+  }
+  const float wsum = p.wsum[nb * 32 + (tid & 31)];
 
   float accf[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) accf[e] = 0.0f;
-  // the token operands of fragment fr: two int8x16 pieces (8-bit) or one packed piece (4-bit); zero without a token
-  auto load_x = [&](int fr, u4& x0, u4& x1) {
-    x0 = u4{0u, 0u, 0u, 0u};
-    x1 = x0;
-    if (mv) {
-      if constexpr (ABITS == 8) {
-        const uint8_t* xp = xrow + (size_t)fr * 64 + 32 * g;
-        x0 = *(const u4*)xp;
-        x1 = *(const u4*)(xp + 16);
-      } else {
-        x0 = *(const u4*)(xrow + (size_t)fr * 32 + 16 * g);
-      }
-    }
-  };
-  auto group_mfma = [&](const u4& wa, const u4& wb, const u4 (&x)[4], _Float16 gs) {
+  // this lane's piece of a direct load: row l / pieces-per-row of it, slot l % pieces-per-row
+  constexpr int P = T::XROW / 16;
+  const int xr0 = l / P;
+  uint32_t xv[T::NX];
+#pragma unroll
+  for (int i = 0; i < T::NX; ++i) {
+    const int row = xr0 + T::RPI * i;
+    xv[i] = (uint32_t)(row < p.M ? row : p.M - 1) * rowbytes + 16u * ((l % P) ^ T::swz(row));   // rows past M: duplicates
+  }
+  // operand rows of this lane (rows that are not staged: any, their results are not used)
+  const int mr = m < T::NX * T::RPI ? m : T::NX * T::RPI - 1;
+  const uint8_t* xop = my + mr * T::XROW;
+  const int xsw = T::swz(mr);
+  auto group_mfma = [&](const u4& wa, const u4& wb, const uint8_t* xs, float gs) {
     v16i acc;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       v4i a0, a1, b0, b1;
       unpack_frag(u ? wb : wa, a0, a1);
       if constexpr (ABITS == 8) {
-        b0 = as_v4i(x[2 * u]);
-        b1 = as_v4i(x[2 * u + 1]);
+        b0 = *(const v4i*)(xs + 16 * ((4 * u + 2 * g) ^ xsw));
+        b1 = *(const v4i*)(xs + 16 * ((4 * u + 2 * g + 1) ^ xsw));
       } else {
-        unpack_frag(x[2 * u], b0, b1);
+        unpack_frag(*(const u4*)(xs + 16 * ((2 * u + g) ^ xsw)), b0, b1);
       }
       // tokens first: rows of the result are tokens, columns (lanes) are channels; the group starts from zero
       if (u == 0) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0, a0, kZero16, 0, 0, 0);
@@ -428,39 +465,44 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void serq_g128_skinny_kernel(con
       acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(b1, a1, acc, 0, 0, 0);
     }
 #pragma unroll
-    for (int e = 0; e < NE; ++e) accf[e] = __builtin_fmaf((float)gs, (float)acc[e], accf[e]);
+    for (int e = 0; e < NE; ++e) accf[e] = __builtin_fmaf(gs, (float)acc[e], accf[e]);
   };
 #pragma unroll 1
   for (int grp = w; grp < G; grp += NG * kSkinnyWaves) {
-    u4 wv[NG][2], xv[NG][4];
-    _Float16 gsv[NG];
+    u4 wv[NG][2];
+    uint16_t gsv[NG];                                       // (converted where they are used: nothing waits for them here)
+    int gq[NG];                                             // a wave without a q-th group repeats the first (unused)
 #pragma unroll
     for (int q = 0; q < NG; ++q) {
-      const int gq = grp + q * kSkinnyWaves;
-      const int gb = gq < G ? gq : grp;                   // a wave without a q-th group repeats the first (unused)
-      wv[q][0] = __builtin_nontemporal_load(&wfr[(size_t)(2 * gb) * 64]);
-      wv[q][1] = __builtin_nontemporal_load(&wfr[(size_t)(2 * gb + 1) * 64]);
-      load_x(2 * gb, xv[q][0], xv[q][1]);
-      load_x(2 * gb + 1, xv[q][2], xv[q][3]);
-      gsv[q] = __builtin_bit_cast(_Float16, gsl[(size_t)gb * 32]);
+      gq[q] = grp + q * kSkinnyWaves < G ? grp + q * kSkinnyWaves : grp;
+      gsv[q] = gsl[(size_t)gq[q] * 32];
     }
 #pragma unroll
     for (int q = 0; q < NG; ++q)
-      if (grp + q * kSkinnyWaves < G) group_mfma(wv[q][0], wv[q][1], xv[q], gsv[q]);   // uniform over the wave
+#pragma unroll
+      for (int i = 0; i < T::NX; ++i) dma16(p.Xq + (size_t)gq[q] * T::XROW, xv[i], my_lds + (uint32_t)(q * T::XG + 1024 * i));
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) wv[q][f] = __builtin_nontemporal_load(&wfr[(size_t)(2 * gq[q] + f) * 64]);
+    // the weight loads are the only vector-memory operations younger than the token rows
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * NG) : "memory");
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+      if (grp + q * kSkinnyWaves < G) group_mfma(wv[q][0], wv[q][1], xop + q * T::XG, f16bits_to_f32(gsv[q]));   // uniform over the wave
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the operands have been read: the region may be refilled
   }
   // rank-r term on the re-centred codes, added to the wave's tile
-  const bool has_lr = p.r > 0 && p.Rp != nullptr;
-  const bool bf = p.r_dtype == SERQ_BF16;
   if (has_lr) {
     v16f accl;
 #pragma unroll
     for (int e = 0; e < 16; ++e) accl[e] = 0.0f;
-    const int JB = p.r >> 4;
-    const u4* rfr = p.Rp + (size_t)nb * JB * 64 + l;
     for (int jb = w; jb < JB; jb += kSkinnyWaves) {
-      const u4 rr = rfr[(size_t)jb * 64];
-      const u4 xf = lr_operand<ABITS>(xrow, p.s_begin + 16 * jb + 8 * g, zm, mv, bf);
-      accl = mfma_lr16(xf, rr, accl, bf);
+      if (jb != w) {                                        // ranks beyond the first block of each wave
+        rf = rfr[(size_t)jb * 64];
+        xr = lr_load<ABITS>(xrow, p.s_begin + 16 * jb + 8 * g);
+      }
+      accl = mfma_lr16(lr_convert<ABITS>(xr, zm, mv, bf), rf, accl, bf);
     }
 #pragma unroll
     for (int e = 0; e < NE; ++e) accf[e] = __builtin_fmaf(accf[e], kInv, accl[e]);   // 2^-SH: exact
@@ -469,20 +511,19 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void serq_g128_skinny_kernel(con
     for (int e = 0; e < NE; ++e) accf[e] *= kInv;
   }
   // combine: register 4i+e of lane (c,g) is token 8i + 4g + e of channel c
+  float* red = reinterpret_cast<float*>(my);
 #pragma unroll
-  for (int e = 0; e < NE; ++e) red[w][(8 * (e >> 2) + 4 * g + (e & 3)) * kPitch + m] = accf[e];
+  for (int e = 0; e < NE; ++e) red[(8 * (e >> 2) + 4 * g + (e & 3)) * kPitch + m] = accf[e];
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 256 * MQ / (64 * kSkinnyWaves) + (256 * MQ % (64 * kSkinnyWaves) ? 1 : 0); ++q) {
-    const int id = tid + q * 64 * kSkinnyWaves;
-    const int nl = id & 31, mt = id >> 5;
+  for (int q = 0; q < NQ; ++q) {
+    const int nl = tid & 31, mt = (tid >> 5) + q * 2 * kSkinnyWaves;
     if (mt >= p.M) continue;
     float tot = 0.0f;
 #pragma unroll
-    for (int ww = 0; ww < kSkinnyWaves; ++ww) tot += red[ww][mt * kPitch + nl];
+    for (int ww = 0; ww < kSkinnyWaves; ++ww) tot += *reinterpret_cast<const float*>(lds + ww * T::REGION + 4 * (mt * kPitch + nl));
     const int n = nb * 32 + nl;
-    const float zf = p.zero ? (float)p.zero[mt] : 0.0f;
-    const float y = p.scale[mt] * (tot - zf * p.wsum[n]);
+    const float y = sc_m[q] * (tot - (float)z_m[q] * wsum);
     const size_t o = (size_t)mt * p.ldy + n;
     if (p.y_dtype == SERQ_F32) ((float*)p.Y)[o] = y;
     else if (p.y_dtype == SERQ_BF16) ((uint16_t*)p.Y)[o] = f32_to_bf16_rne(y);
@@ -995,20 +1036,25 @@ int serq_g128_linear(const void* Xq, const float* scale, const int32_t* zero, in
   if (path == SERQ_PATH_AUTO && !skinny && flags == 0 && g128_mid_wanted(p)) return launch_g128_mid(p, abits, st);
   if (skinny) {
     dim3 grid((unsigned)(N / 32));
-    // specialised on ceil(M / 8): the number of accumulator register quads that hold tokens
-#define SERQ_G128_SKINNY(AB, MQ)                                                                                   \
-  do {                                                                                                             \
-    if (deep) hipLaunchKernelGGL((serq_g128_skinny_kernel<AB, MQ, 4>), grid, dim3(64 * kSkinnyWaves), 0, st, p);   \
-    else hipLaunchKernelGGL((serq_g128_skinny_kernel<AB, MQ, 2>), grid, dim3(64 * kSkinnyWaves), 0, st, p);        \
-  } while (0)
+    // specialised on ceil(M / 8): the number of accumulator register quads that hold tokens.  Four groups in flight per
+    // wave pay once it has two rounds of them and few tokens to stage (us, 2 / 4 in flight, r = 128, W4A8, N x K):
+    // 4096 x 11008 M = 1 9.2 / 8.3, M = 8 8.5 / 8.5, M = 16 9.9 / 10.2; 11008 x 4096 M = 1 7.2 / 7.1, M = 16 8.4 / 8.5.
+#define SERQ_G128_SKINNY(AB, MQ, NG) \
+  hipLaunchKernelGGL((serq_g128_skinny_kernel<AB, MQ, NG>), grid, dim3(64 * kSkinnyWaves), 0, st, p)
     const int mq = (int)((M + 7) / 8);
-    const bool deep = K / kGroup >= 64;                   // four groups in flight per wave pay once a wave has two rounds of them
+    const bool deep = mq == 1 && K / kGroup >= 64;
     if (abits == 8) {
-      if (mq == 1) SERQ_G128_SKINNY(8, 1); else if (mq == 2) SERQ_G128_SKINNY(8, 2);
-      else if (mq == 3) SERQ_G128_SKINNY(8, 3); else SERQ_G128_SKINNY(8, 4);
+      if (deep) SERQ_G128_SKINNY(8, 1, 4);
+      else if (mq == 1) SERQ_G128_SKINNY(8, 1, 2);
+      else if (mq == 2) SERQ_G128_SKINNY(8, 2, 2);
+      else if (mq == 3) SERQ_G128_SKINNY(8, 3, 2);
+      else SERQ_G128_SKINNY(8, 4, 2);
     } else {
-      if (mq == 1) SERQ_G128_SKINNY(4, 1); else if (mq == 2) SERQ_G128_SKINNY(4, 2);
-      else if (mq == 3) SERQ_G128_SKINNY(4, 3); else SERQ_G128_SKINNY(4, 4);
+      if (deep) SERQ_G128_SKINNY(4, 1, 4);
+      else if (mq == 1) SERQ_G128_SKINNY(4, 1, 2);
+      else if (mq == 2) SERQ_G128_SKINNY(4, 2, 2);
+      else if (mq == 3) SERQ_G128_SKINNY(4, 3, 2);
+      else SERQ_G128_SKINNY(4, 4, 2);
     }
 #undef SERQ_G128_SKINNY
   } else {
