@@ -311,12 +311,17 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu((kG
 #pragma unroll
     for (int ww = 0; ww < kWaves; ++ww) tot_i[q] += *reinterpret_cast<const int*>(lds + (size_t)ww * hregion + 4 * src);
     if (lr_here) {
-      int li = 0;
+      // (all waves' words requested before the first is added; a loop over nwl waits for each in turn)
+      int word[kWaves], li = 0;
       float lf = 0.0f;
-      for (int ww = 0; ww < nwl; ++ww) {
-        const int word = *reinterpret_cast<const int*>(lds + (size_t)ww * hregion + 4 * (hM * kRedPitch + src));
-        if (lr_int) li += word;
-        else lf += __int_as_float(word);
+#pragma unroll
+      for (int ww = 0; ww < kWaves; ++ww)
+        word[ww] = *reinterpret_cast<const int*>(lds + (size_t)ww * hregion + 4 * (hM * kRedPitch + src));
+#pragma unroll
+      for (int ww = 0; ww < kWaves; ++ww) {
+        const int v = ww < nwl ? word[ww] : 0;
+        li += v;
+        lf += __int_as_float(v);
       }
       tot_l[q] = lr_int ? li : __float_as_int(lf);
     }
