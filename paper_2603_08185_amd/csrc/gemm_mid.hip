@@ -1,17 +1,16 @@
 // SERQ linear layer for batches between decode and prefill: the integer layer of gemm_mfma.hip in tiles of
-// 64 tokens x 64 channels, the 8 waves of a workgroup sharing K (mid_tile.h says why).
+// 64 tokens x 64 channels, the 4 or 8 waves of a workgroup sharing K (mid_tile.h says why).
 //   Y[m,n] = scale[m] * ( wscale[n] * sum_k Xq[m,k] Wq[n,k] + sum_j Xq[m,S_j] R[j,n] )
 //
-// The waves' INT32 partial tiles meet in LDS once: wave w sums half of MFMA tile w/2 (8 registers per lane) over the 8
-// waves -- integer addition, the same bits as the tiled kernel -- scales it and adds the rank-r term with the matrix
-// unit on top, exactly as the tiled kernel does.  The two waves of a tile compute the rank-r term of the whole tile
-// twice (8 MFMAs at r = 128): cheaper than another meeting.
+// The waves' INT32 partial tiles meet in LDS once: each wave sums one MFMA tile (4 waves) or half of one (8) over the
+// waves -- integer addition, the same bits as the tiled kernel -- scales it and adds the rank-r term with the matrix unit on
+// top, exactly as the tiled kernel does.
 //
 // What bounds it: the L2 -> LDS stream.  A step (64 channels of 8-bit tokens) is 6 KiB for 8 MFMAs; with all compute
 // units busy the direct loads bring 70-90 B/ns to each (64 B/clk is the address unit's limit, reached with up to half
 // of the chip).  Fixed costs are about 4.7 us (K = 1024), of which 1.3 us lie between dependent launches.
 // Measured (M = 256, 4096 x 11008, W4A8, r = 128): 20 us, the tiled kernel with 4 K slices and a second launch 30 us;
-// M = 100, 6144 x 4096: 9.6 against 24.4 us.  The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.
+// M = 100, 6144 x 4096: 8.7 against 24.0 us.  The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.
 #include "mid_tile.h"
 
 namespace serq {
@@ -28,7 +27,7 @@ struct MidParams {
   int tiles_m, tiles_n;
 };
 
-template <int ABITS>
+template <int ABITS, int NW>
 struct Mid {
   static constexpr int FR = ABITS == 8 ? 1 : 2;
   static constexpr int STAGE = kMidX + 2 * FR * 1024;   // 6 KiB / 8 KiB
@@ -36,27 +35,30 @@ struct Mid {
   static constexpr int NL = 4 + 2 * FR;
   static constexpr int REGION = NS * STAGE;          // LDS of one wave: 18 KiB / 16 KiB
   static constexpr int SH = ABITS == 8 ? 4 : 8;
-  // The rank-r term in chunks of 128 ranks: the R fragments that wave w brings lie behind its own partial tile (8-bit:
-  // the ring leaves 2 KiB there) or behind the rings (4-bit), the token codes behind that
-  static constexpr int LRR_STEP = ABITS == 8 ? REGION : 2048;
-  static constexpr int LRR_OFF = ABITS == 8 ? kMidPart : kMidWaves * REGION;
+  // The rank-r term in chunks of 128 ranks.  8 waves: the R fragments that wave w brings lie behind its own partial tile
+  // (the ring leaves 2 KiB there), the token codes behind the rings.  4 waves: both take the place of the partial tiles once
+  // those have been added.
+  static constexpr bool LATE = NW == 4;
+  static constexpr int LRR_STEP = LATE ? 2048 : REGION;
+  static constexpr int LRR_OFF = LATE ? 0 : kMidPart;
   static __device__ __forceinline__ int lr_frag(bool per_wave_1, int f) {
     return LRR_OFF + (per_wave_1 ? f * LRR_STEP : (f >> 1) * LRR_STEP + (f & 1) * 1024);
   }
-  static constexpr int LRX_OFF = kMidWaves * REGION + (ABITS == 8 ? 0 : 16 * 1024);
-  static constexpr int LDS = LRX_OFF + 64 * 256;
+  static constexpr int LRX_OFF = LATE ? 16 * 1024 : NW * REGION;
+  static constexpr int LDS = LATE ? NW * REGION : LRX_OFF + 64 * 256;
   static_assert(REGION >= kMidPart, "a partial tile fits the ring it replaces");
-  static_assert(ABITS == 4 || REGION - kMidPart >= 2048, "two R fragments fit behind it");
-  static_assert(LDS <= 160 * 1024, "LDS budget");
+  static_assert(LATE || REGION - kMidPart >= 2048, "two R fragments fit behind it");
+  static_assert(!LATE || LDS >= LRX_OFF + 64 * 256, "the rank-r operands fit the rings");
+  static_assert(LDS * (8 / NW) <= 160 * 1024, "LDS budget");
 };
 
 template <int FR>
 struct MidOp { u4 w[2][FR], x[2][2]; };              // x: [token block][8-bit: K half, 4-bit: fragment]
 
-template <int ABITS, int LRT>
-__global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int ABITS, int LRT, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void serq_mid_kernel(const MidParams p) {
-  using T = Mid<ABITS>;
+  using T = Mid<ABITS, NW>;
   constexpr int FR = T::FR, NS = T::NS;
   __shared__ __align__(16) uint8_t lds[T::LDS];
   const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
@@ -72,7 +74,7 @@ void serq_mid_kernel(const MidParams p) {
   MidLoads<FR> ld;
   ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
   const int steps = (ld.KB + FR - 1) / FR;
-  const int nst = steps > w ? (steps - w + kMidWaves - 1) / kMidWaves : 0;   // steps w, w + 8, ... are this wave's
+  const int nst = steps > w ? (steps - w + NW - 1) / NW : 0;   // steps w, w + NW, ... are this wave's
   uint8_t* my = lds + w * T::REGION;
   const uint32_t my_lds = __builtin_amdgcn_readfirstlane(lds_addr(my));
 
@@ -99,7 +101,7 @@ void serq_mid_kernel(const MidParams p) {
         const int c = ABITS == 8 ? 2 * g + h : 2 * h + g;
         o.x[j][h] = *(const u4*)(s + (32 * j + lm) * 64 + 16 * (c ^ xsw));
       }
-    if (FR == 2 && ld.KB - (w + kMidWaves * t) * FR < FR) {   // no second fragment: zero weights
+    if (FR == 2 && ld.KB - (w + NW * t) * FR < FR) {   // no second fragment: zero weights
 #pragma unroll
       for (int i = 0; i < 2; ++i) o.w[i][FR - 1] = u4{0u, 0u, 0u, 0u};
     }
@@ -119,12 +121,15 @@ void serq_mid_kernel(const MidParams p) {
     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
   };
   mid_loop<NS, T::NL, T::NL, 4 * FR, MidOp<FR>>(
-      nst, [&](int t) { ld.issue(w + kMidWaves * t, my_lds + slot(t)); },
-      [&](int t, int k) { ld.issue_one(w + kMidWaves * t, my_lds + slot(t), k); }, read, product);
+      nst, [&](int t) { ld.issue(w + NW * t, my_lds + slot(t)); },
+      [&](int t, int k) { ld.issue_one(w + NW * t, my_lds + slot(t), k); }, read, product);
 
   // ---- what the end of the tile needs from memory, requested before the waves meet ------------------------------
-  // wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j
-  const int ti = w >> 2, tj = (w >> 1) & 1, hq = 2 * (w & 1);
+  // 8 waves: wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j; 4 waves: all of tile w = 2*i + j
+  constexpr int QN = 16 / NW;                         // register quads
+  constexpr int NE = 4 * QN;
+  const int tt = NW == 8 ? w >> 1 : w;
+  const int ti = tt >> 1, tj = tt & 1, hq = NW == 8 ? 2 * (w & 1) : 0;
   const int blk = nb0 + (ti < nbt ? ti : 0);          // (a block past the layer repeats the first and is not stored)
   const int mloc = 32 * tj + lm;
   const int m = m0 + (mloc < mrows ? mloc : mrows - 1);
@@ -136,55 +141,63 @@ void serq_mid_kernel(const MidParams p) {
   // A chunk of the rank-r term: every wave brings 2 (4-bit R: waves 0..3, one) of its R fragments and 16 codes of 8 token
   // rows per lane; 16-bit R takes the codes as exact 16-bit floats, converted once here instead of by every wave
   // that multiplies them.
-  u4 lrr[2], lrx;
-  const int lrow = 8 * w + (l >> 3);
+  constexpr int VH = 8 / NW;                          // (a wave of 4 brings the shares of two of 8)
+  u4 lrr[VH][2], lrx[VH];
   auto lr_fetch = [&](int jb0) {
 #pragma unroll
+    for (int v = 0; v < VH; ++v) {
+    const int vw = VH * w + v, lrow = 8 * vw + (l >> 3);
+#pragma unroll
     for (int q = 0; q < (lr_int ? 1 : 2); ++q) {
-      const int f = lr_int ? (w & 3) : 2 * w + q;
+      const int f = lr_int ? (vw & 3) : 2 * vw + q;
       const int b = f / NJ, jb = jb0 + f % NJ;
-      lrr[q] = p.Rp[((size_t)(nb0 + (b < nbt ? b : 0)) * JB + (jb < JB ? jb : JB - 1)) * 64 + l];
+      lrr[v][q] = p.Rp[((size_t)(nb0 + (b < nbt ? b : 0)) * JB + (jb < JB ? jb : JB - 1)) * 64 + l];
     }
     const int c0 = p.s_begin + (lr_int ? 64 : 16) * jb0;   // first channel of the chunk
     const int have = (JB - jb0) * (lr_int ? 64 : 16);  // channels it has
     const int c = 16 * (l & 7) < have ? 16 * (l & 7) : 0;
     const uint8_t* src = p.Xq + (size_t)(m0 + (lrow < mrows ? lrow : mrows - 1)) * rowbytes + (size_t)(c0 + c) * ABITS / 8;
     if constexpr (ABITS == 8) {
-      lrx = *(const u4*)src;
+      lrx[v] = *(const u4*)src;
     } else {
-      const u2 v = *(const u2*)src;
-      lrx = u4{v.x, v.y, 0u, 0u};
+      const u2 x = *(const u2*)src;
+      lrx[v] = u4{x.x, x.y, 0u, 0u};
+    }
     }
   };
   auto lr_park = [&]() {
 #pragma unroll
+    for (int v = 0; v < VH; ++v) {
+    const int vw = VH * w + v, lrow = 8 * vw + (l >> 3);
+#pragma unroll
     for (int q = 0; q < (lr_int ? 1 : 2); ++q) {
-      const int f = lr_int ? (w & 3) : 2 * w + q;
-      if (!lr_int || w < 4) *(u4*)(lds + T::lr_frag(lr_int, f) + l * 16) = lrr[q];
+      const int f = lr_int ? (vw & 3) : 2 * vw + q;
+      if (!lr_int || vw < 4) *(u4*)(lds + T::lr_frag(lr_int, f) + l * 16) = lrr[v][q];
     }
     uint8_t* row = lds + T::LRX_OFF + lrow * 256;
     const int c = l & 7;                              // 16 channels
     if constexpr (lr_int) {
-      if constexpr (ABITS == 8) *(u4*)(row + 16 * (c ^ (lrow & 15))) = lrx;
-      else *(u2*)(row + 16 * ((c >> 1) ^ (lrow & 15)) + 8 * (c & 1)) = u2{lrx.x, lrx.y};
+      if constexpr (ABITS == 8) *(u4*)(row + 16 * (c ^ (lrow & 15))) = lrx[v];
+      else *(u2*)(row + 16 * ((c >> 1) ^ (lrow & 15)) + 8 * (c & 1)) = u2{lrx[v].x, lrx[v].y};
     } else {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         int k[8];
-        if constexpr (ABITS == 8) codes_from_a8(h ? lrx.z : lrx.x, h ? lrx.w : lrx.y, k);
-        else codes_from_a4(h ? lrx.y : lrx.x, k);
+        if constexpr (ABITS == 8) codes_from_a8(h ? lrx[v].z : lrx[v].x, h ? lrx[v].w : lrx[v].y, k);
+        else codes_from_a4(h ? lrx[v].y : lrx[v].x, k);
         *(u4*)(row + 16 * ((2 * c + h) ^ (lrow & 15))) = codes8_to_16bit(k, bf);
       }
     }
+    }
   };
   if (JB > 0) lr_fetch(0);
-  float wsc[8], rsc[8], sm = 0.0f;
+  float wsc[NE], rsc[NE], sm = 0.0f;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) wsc[e] = rsc[e] = 0.0f;
+  for (int e = 0; e < NE; ++e) wsc[e] = rsc[e] = 0.0f;
   if (!p.acc_out) {
     sm = p.scale[m];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+    for (int q = 0; q < QN; ++q) {
       const int n = 32 * blk + 8 * (hq + q) + 4 * g;
       const float4 v = *(const float4*)(p.wscale + n);
       wsc[4 * q] = v.x * kInv; wsc[4 * q + 1] = v.y * kInv; wsc[4 * q + 2] = v.z * kInv; wsc[4 * q + 3] = v.w * kInv;
@@ -205,16 +218,16 @@ void serq_mid_kernel(const MidParams p) {
         *(v4i*)(my + ((2 * i + j) * 4 + q) * 1024 + l * 16) =
             v4i{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
   // (8-bit: the R fragments land in stages of this and of no other wave, which has read them all)
-  if (JB > 0) lr_park();
+  if (JB > 0 && !T::LATE) lr_park();
   __syncthreads();
-  int tot[8];
+  int tot[NE];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) tot[e] = 0;
+  for (int e = 0; e < NE; ++e) tot[e] = 0;
 #pragma unroll
-  for (int ww = 0; ww < kMidWaves; ++ww)
+  for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const v4i v = *(const v4i*)(lds + ww * T::REGION + ((w >> 1) * 4 + hq + q) * 1024 + l * 16);
+    for (int q = 0; q < QN; ++q) {
+      const v4i v = *(const v4i*)(lds + ww * T::REGION + (tt * 4 + hq + q) * 1024 + l * 16);
       tot[4 * q] += v.x; tot[4 * q + 1] += v.y; tot[4 * q + 2] += v.z; tot[4 * q + 3] += v.w;
     }
 
@@ -223,23 +236,20 @@ void serq_mid_kernel(const MidParams p) {
   if (p.acc_out) {
     if (live) {
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
+      for (int q = 0; q < QN; ++q)
         *(v4i*)(p.acc_out + (size_t)m * p.ldacc + n + 8 * q) =
             v4i{tot[4 * q] >> T::SH, tot[4 * q + 1] >> T::SH, tot[4 * q + 2] >> T::SH, tot[4 * q + 3] >> T::SH};
     }
     return;
   }
-  float y[8];
+  float y[NE];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) y[e] = wsc[e] * (float)tot[e];
+  for (int e = 0; e < NE; ++e) y[e] = wsc[e] * (float)tot[e];
   v16f af;                                            // 16-bit R: the tile the matrix unit adds to
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    af[e] = hq ? 0.0f : y[e];
-    af[8 + e] = hq ? y[e] : 0.0f;
-  }
+  for (int e = 0; e < 16; ++e) af[e] = NW == 4 ? y[e % NE] : (e >> 3) == (hq >> 1) ? y[e & 7] : 0.0f;
   for (int jb0 = 0; jb0 < JB; jb0 += NJ) {
-    if (jb0 > 0) {                                     // (the loads of this chunk were requested a chunk ago)
+    if (jb0 > 0 || T::LATE) {                          // (the loads of this chunk were requested a chunk ago)
       __syncthreads();
       lr_park();
       __syncthreads();
@@ -267,7 +277,7 @@ void serq_mid_kernel(const MidParams p) {
           tq = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, tq, 0, 0, 0);
           tq = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, tq, 0, 0, 0);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) y[e] = __builtin_fmaf(rsc[e], (float)(hq ? tq[8 + e] : tq[e]), y[e]);
+          for (int e = 0; e < NE; ++e) y[e] = __builtin_fmaf(rsc[e], (float)(NW == 4 ? tq[e] : hq ? tq[(8 + e) & 15] : tq[e]), y[e]);
         } else {
           const u4 xf = piece(2 * q + g);
           if constexpr (bf)
@@ -280,37 +290,37 @@ void serq_mid_kernel(const MidParams p) {
   }
   if constexpr (!lr_int) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = hq ? af[8 + e] : af[e];
+    for (int e = 0; e < NE; ++e) y[e] = NW == 4 ? af[e] : hq ? af[(8 + e) & 15] : af[e];
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) y[e] *= sm;
+  for (int e = 0; e < NE; ++e) y[e] *= sm;
 
   if (p.y_dtype == SERQ_F32) {
     if (live) {
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
+      for (int q = 0; q < QN; ++q)
         *(float4*)((float*)p.Y + (size_t)m * p.ldy + n + 8 * q) = make_float4(y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]);
     }
     return;
   }
   __syncthreads();                                     // every wave has read the partial tiles: the rows take their place
 #pragma unroll
-  for (int q = 0; q < 2; ++q) mid_park16(lds, mloc, 4 * ti + hq + q, g, y + 4 * q, p.y_dtype == SERQ_BF16);
+  for (int q = 0; q < QN; ++q) mid_park16(lds, mloc, 4 * ti + hq + q, g, y + 4 * q, p.y_dtype == SERQ_BF16);
   __syncthreads();
-  mid_store16(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
+  mid_store16<64 * NW>(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
 }
 
 }  // namespace
 
-// Up to two tiles per compute unit.  Measured (us, tiled kernel / this one, r = 128, bf16 R, W4A8; W4A4 the same or better):
-//   1 round:  4096 x 4096 M = 256 24.7 / 9.8;  6144 x 4096 M = 100 23.7 / 9.5;  4096 x 11008 M = 256 29.3 / 19.4;
-//             1024 x 1024 M = 1024 11.8 / 5.8;  11008 x 4096 M = 40 27.8 / 9.6
-//   2 rounds: 4096 x 4096 M = 512 24.9 / 18.1;  6144 x 4096 M = 256 24.7 / 17.8;  4096 x 11008 M = 512 41.1 / 39.6;
-//             28672 x 4096 M = 64 33.7 / 25.4
-//   3 rounds: 6144 x 4096 M = 400 25.4 / 24.6;  4096 x 11008 M = 640 53.3 / 56.8;  28672 x 4096 M = 100 (4) 33.3 / 39.8
-// (N x K; "tiled" slices K where its own plan does).  From three rounds on the larger tiles of that kernel, which move
-// half the bytes per product, are as fast or faster.
-bool mid_wanted(const LinearArgs& a) { return mid_rounds(a.M, a.N, device_cu_count()) <= 2; }
+// Up to three tiles per compute unit, four with 4-bit tokens.  Measured (us, tiled kernel / this one, r = 128, N x K):
+//   W4A8  4096 x 4096 M = 256 24.9 / 9.5, M = 512 (2) 25.1 / 15.9, M = 768 (3) 25.9 / 21.5, M = 1024 (4) 28.0 / 29.1;
+//         11008 x 4096 M = 256 (3) 25.6 / 21.2, M = 333 (5) 30.1 / 30.2;  4096 x 11008 M = 256 29.6 / 19.9, M = 768 (3)
+//         55.1 / 54.2, M = 1024 (4) 62.7 / 76.3;  28672 x 4096 M = 100 (4) 35.5 / 31.7
+//   W4A4  4096 x 4096 M = 1024 (4) 25.8 / 23.7;  4096 x 11008 M = 1024 (4) 53.9 / 50.9;  6144 x 4096 M = 768 (5) 29.1 / 28.5;
+//         28672 x 4096 M = 256 (7) 38.9 / 45.9
+// (in brackets: tiles of the busiest compute unit, where more than one; "tiled" slices K where its own plan does).  The
+// larger tiles of that kernel move half the bytes per product.
+bool mid_wanted(const LinearArgs& a) { return mid_rounds(a.M, a.N, device_cu_count()) <= (a.abits == 8 ? 3 : 4); }
 
 int launch_mid(const LinearArgs& a, hipStream_t st) {
   MidParams p;
@@ -322,18 +332,30 @@ int launch_mid(const LinearArgs& a, hipStream_t st) {
   p.acc_out = a.acc_out; p.ldacc = a.ldacc;
   p.tiles_m = (a.M + 63) / 64;
   p.tiles_n = (a.N + 63) / 64;
-  const dim3 grid((unsigned)(p.tiles_m * p.tiles_n)), block(kMidThreads);
+  const dim3 grid((unsigned)(p.tiles_m * p.tiles_n));
   const bool has_lr = p.r > 0 && p.acc_out == nullptr;
   const int lrt = !has_lr ? SERQ_BF16 : a.r_dtype;
-#define SERQ_MID_LAUNCH(AB, LRT) hipLaunchKernelGGL((serq_mid_kernel<AB, LRT>), grid, block, 0, st, p)
-  if (a.abits == 8) {
-    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(8, SERQ_I4);
-    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(8, SERQ_F16);
-    else SERQ_MID_LAUNCH(8, SERQ_BF16);
+  // Workgroups of 4 waves, two of which share a compute unit: one's start and end run beside the other's main loop, and
+  // fewer partial tiles meet.  Only where there is at most one tile per compute unit (and one for most), K is long
+  // and the stages are the small ones of 8-bit tokens, 8 waves keep more loads in flight.  Measured (us, 8 / 4 waves, W4A8
+  // r = 128, N x K): 4096 x 4096 M = 100 9.4 / 8.6, M = 333 17.0 / 14.0; 4096 x 8192 M = 100 12.8 / 11.6, M = 256
+  // 14.8 / 14.8; 4096 x 11008 M = 40 15.9 / 14.8, M = 100 16.7 / 17.7, M = 256 19.9 / 21.1, M = 333 36.1 / 30.1; W4A4
+  // 4096 x 11008 M = 100 13.8 / 14.0, M = 256 16.2 / 15.3, M = 333 27.7 / 23.2.
+  const int ncu = device_cu_count();
+  const bool eight = a.abits == 8 && a.K > 8192 && (int)grid.x <= ncu && 2 * (int)grid.x >= ncu;
+#define SERQ_MID_LAUNCH(AB, LRT, NW) hipLaunchKernelGGL((serq_mid_kernel<AB, LRT, NW>), grid, dim3(64 * NW), 0, st, p)
+  if (eight) {
+    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(8, SERQ_I4, 8);
+    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(8, SERQ_F16, 8);
+    else SERQ_MID_LAUNCH(8, SERQ_BF16, 8);
+  } else if (a.abits == 8) {
+    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(8, SERQ_I4, 4);
+    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(8, SERQ_F16, 4);
+    else SERQ_MID_LAUNCH(8, SERQ_BF16, 4);
   } else {
-    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(4, SERQ_I4);
-    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(4, SERQ_F16);
-    else SERQ_MID_LAUNCH(4, SERQ_BF16);
+    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(4, SERQ_I4, 4);
+    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(4, SERQ_F16, 4);
+    else SERQ_MID_LAUNCH(4, SERQ_BF16, 4);
   }
 #undef SERQ_MID_LAUNCH
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;

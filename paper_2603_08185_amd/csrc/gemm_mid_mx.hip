@@ -214,7 +214,7 @@ void serq_mx_mid_kernel(const MxMidParams p) {
 #pragma unroll
   for (int q = 0; q < 2; ++q) mid_park16(lds, mloc, 4 * ti + hq + q, g, y + 4 * q, p.y_dtype == SERQ_BF16);
   __syncthreads();
-  mid_store16(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
+  mid_store16<kMidThreads>(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
 }
 
 }  // namespace

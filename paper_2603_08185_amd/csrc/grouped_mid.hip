@@ -266,7 +266,7 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
         p.y_dtype == SERQ_BF16 ? f32_to_bf16_rne(y[e]) : f32_to_f16_rne(y[e]);
   }
   __syncthreads();
-  mid_store16(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
+  mid_store16<kMidThreads>(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
 }
 
 }  // namespace

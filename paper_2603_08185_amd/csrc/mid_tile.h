@@ -1,5 +1,5 @@
 // Pieces shared by the kernels for batches between decode and prefill (gemm_mid.hip, gemm_mid_mx.hip, grouped_mid.hip):
-// 64 tokens x 64 output channels per workgroup, K dealt out to its 8 waves.
+// 64 tokens x 64 output channels per workgroup, K dealt out to its 4 or 8 waves.
 //
 // Why this shape.  With a few hundred tokens the layer is bound by the bytes that go from L2 to the compute
 // units, and by having a workgroup for each of them.  Tiles of 256 tokens leave most of the chip idle (one token
@@ -10,7 +10,7 @@
 //
 // A wave's loads run through a ring of stages in its own LDS region, filled by direct global -> LDS loads counted
 // by hand.  A stage holds 64 token rows of 64 bytes and the weight fragments of two channel blocks for the same
-// channels; steps are dealt round-robin, so that the 8 waves read neighbouring pieces of the same rows.
+// channels; steps are dealt round-robin, so that the waves read neighbouring pieces of the same rows.
 #ifndef SERQ_MID_TILE_H_
 #define SERQ_MID_TILE_H_
 #include <type_traits>
@@ -159,11 +159,16 @@ __device__ __forceinline__ void mid_park16(uint8_t* out, int r, int pc, int g, c
   else o = u2{f32x2_to_f16x2(y[0], y[1]), f32x2_to_f16x2(y[2], y[3])};
   *(u2*)(out + r * 128 + 16 * (pc ^ (r & 7)) + 8 * g) = o;
 }
+template <int THREADS>
 __device__ __forceinline__ void mid_store16(const uint8_t* out, int tid, uint16_t* Y, int64_t ldy, int m0, int mrows, int n0,
                                             int nbt) {
-  const int r = tid >> 3, pc = tid & 7;
-  if (r < mrows && pc < 4 * nbt)
-    *(u4*)(Y + (size_t)(m0 + r) * ldy + n0 + 8 * pc) = *(const u4*)(out + r * 128 + 16 * (pc ^ (r & 7)));
+  const int pc = tid & 7;
+#pragma unroll
+  for (int r0 = 0; r0 < 64; r0 += THREADS / 8) {
+    const int r = r0 + (tid >> 3);
+    if (r < mrows && pc < 4 * nbt)
+      *(u4*)(Y + (size_t)(m0 + r) * ldy + n0 + 8 * pc) = *(const u4*)(out + r * 128 + 16 * (pc ^ (r & 7)));
+  }
 }
 
 }  // namespace
