@@ -1,4 +1,4 @@
-// The MXFP4 layer for batches between decode and prefill: tiles of 64 tokens x 64 channels, the 8 waves of a workgroup
+// The MXFP4 layer for batches between decode and prefill: tiles of 64 tokens x 64 channels, the 4 waves of a workgroup
 // sharing K (mid_tile.h says why).
 //   Y[m,n] = sum_k X^[m,k] W^[n,k] + sum_{j<r} X^[m,s_begin+j] R^[n,j]
 //
@@ -8,7 +8,7 @@
 // requested before it.  The waves' fp32 tiles are added through LDS in wave order: the same result from run to run.
 //
 // What bounds it: the L2 -> LDS stream (8.5 KiB per 128 channels and wave beside 8 MFMAs), as in gemm_mid.hip.  Measured
-// (M = 200, 4096 x 14336, r = 128): 17 us, the tiled kernel with 4 K slices and a second launch 29 us; the rank-r term
+// (M = 200, 4096 x 14336, r = 128): 16 us, the tiled kernel with 4 K slices and a second launch 29 us; the rank-r term
 // costs nothing that shows.
 #include "mid_tile.h"
 
@@ -26,18 +26,18 @@ struct MxMidParams {
 
 constexpr int FR = 2;
 constexpr int STAGE = kMidX + 2 * FR * 1024;         // 8 KiB
+constexpr int NW = 4;                                // waves: two workgroups share a compute unit
 constexpr int NS = 2;
 constexpr int WS_OFF = NS * STAGE;                   // weight scales of a tile: 2 blocks x 64 dwords
 constexpr int XS_OFF = WS_OFF + 512;                 // token scales of a tile: 64 rows x 8 bytes
 constexpr int REGION = XS_OFF + 512;
-constexpr int LDS = kMidWaves * REGION;              // 136 KiB
 static_assert(REGION >= kMidPart, "a partial tile fits the ring it replaces");
 
 struct MxMidOp { u4 w[2][FR], x[2][FR]; };
 
-__global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void serq_mx_mid_kernel(const MxMidParams p) {
-  __shared__ __align__(16) uint8_t lds[LDS];
+  __shared__ __align__(16) uint8_t lds[NW * REGION];      // 17 KiB a wave
   const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tile_m, tile_n;
@@ -52,9 +52,9 @@ void serq_mx_mid_kernel(const MxMidParams p) {
   MidLoads<FR> ld;
   ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
   const int KB = ld.KB, T = (KB + 3) >> 2;             // fragments, scale tiles
-  const int nt = T > w ? (T - w + kMidWaves - 1) / kMidWaves : 0;   // tiles w, w + 8, ... are this wave's
+  const int nt = T > w ? (T - w + NW - 1) / NW : 0;   // tiles w, w + NW, ... are this wave's
   // stages: two per tile, but for a last tile of one or two fragments
-  const bool short_last = nt > 0 && KB - 4 * (w + kMidWaves * (nt - 1)) <= 2;
+  const bool short_last = nt > 0 && KB - 4 * (w + NW * (nt - 1)) <= 2;
   const int nst = 2 * nt - (short_last ? 1 : 0);
   uint8_t* my = lds + w * REGION;
   const uint32_t my_lds = __builtin_amdgcn_readfirstlane(lds_addr(my));
@@ -93,7 +93,7 @@ void serq_mx_mid_kernel(const MxMidParams p) {
   // scales of a tile: lanes 0..15 / 16..31 bring those of weight block 0 / 1, lanes 0..31 those of two token rows each
   const uint32_t wsv = (uint32_t)(((l >> 4) & 1) && nbt > 1 ? T * 256 : 0) + (l & 15) * 16;
   const int rp = 2 * (l & 31) < mrows ? l & 31 : (mrows - 1) >> 1;
-  auto tile = [&](int t) { return w + kMidWaves * (t >> 1); };
+  auto tile = [&](int t) { return w + NW * (t >> 1); };
   auto fill = [&](int t, int k) {
     const int u = tile(t);
     if (k < 8) ld.issue_one(2 * u + (t & 1), my_lds + (t & 1) * STAGE, k);
@@ -166,8 +166,8 @@ void serq_mx_mid_kernel(const MxMidParams p) {
       },
       fill, read, product);
 
-  // ---- compensation fragments w, w + 8, ... ---------------------------------------------------------------------------
-  for (int jf = w; jf < LF; jf += kMidWaves) {
+  // ---- compensation fragments w, w + NW, ... ---------------------------------------------------------------------------
+  for (int jf = w; jf < LF; jf += NW) {
     if (jf != w) lr_fetch(jf);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -177,8 +177,9 @@ void serq_mx_mid_kernel(const MxMidParams p) {
                                                                     (int)rs[i], 0, (int)rxs[j]);
   }
 
-  // ---- the waves meet; wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j ------------------
-  const int ti = w >> 2, tj = (w >> 1) & 1, hq = 2 * (w & 1);
+  // ---- the waves meet; wave w finishes MFMA tile (i, j), w = 2*i + j ------------------------------------------------
+  constexpr int QN = 4, NE = 4 * QN;                   // register quads, registers
+  const int ti = w >> 1, tj = w & 1;
   const int blk = nb0 + (ti < nbt ? ti : 0);
   const int mloc = 32 * tj + lm;
 #pragma unroll
@@ -190,21 +191,21 @@ void serq_mx_mid_kernel(const MxMidParams p) {
         *(v4f*)(my + ((2 * i + j) * 4 + q) * 1024 + l * 16) =
             v4f{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
   __syncthreads();
-  float y[8];
+  float y[NE];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) y[e] = 0.0f;
+  for (int e = 0; e < NE; ++e) y[e] = 0.0f;
 #pragma unroll
-  for (int ww = 0; ww < kMidWaves; ++ww)
+  for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const v4f v = *(const v4f*)(lds + ww * REGION + ((w >> 1) * 4 + hq + q) * 1024 + l * 16);
+    for (int q = 0; q < QN; ++q) {
+      const v4f v = *(const v4f*)(lds + ww * REGION + (w * 4 + q) * 1024 + l * 16);
       y[4 * q] += v.x; y[4 * q + 1] += v.y; y[4 * q + 2] += v.z; y[4 * q + 3] += v.w;
     }
   if (p.y_dtype == SERQ_F32) {
     if (mloc < mrows && ti < nbt) {
-      const int n = 32 * blk + 8 * hq + 4 * g;
+      const int n = 32 * blk + 4 * g;
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
+      for (int q = 0; q < QN; ++q)
         *(float4*)((float*)p.Y + (size_t)(m0 + mloc) * p.ldy + n + 8 * q) =
             make_float4(y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]);
     }
@@ -212,21 +213,20 @@ void serq_mx_mid_kernel(const MxMidParams p) {
   }
   __syncthreads();                                     // every wave has read the partial tiles: the rows take their place
 #pragma unroll
-  for (int q = 0; q < 2; ++q) mid_park16(lds, mloc, 4 * ti + hq + q, g, y + 4 * q, p.y_dtype == SERQ_BF16);
+  for (int q = 0; q < QN; ++q) mid_park16(lds, mloc, 4 * ti + q, g, y + 4 * q, p.y_dtype == SERQ_BF16);
   __syncthreads();
-  mid_store16<kMidThreads>(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
+  mid_store16<64 * NW>(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
 }
 
 }  // namespace
 
-// Up to two tiles per compute unit.  Measured (us, tiled kernel / this one, r = 128):
-//   1 round:  4096 x 14336 M = 200 29.4 / 17.3;  4096 x 11008 M = 256 28.9 / 15.4;  6144 x 4096 M = 100 20.9 / 8.2;
-//             1024 x 1024 M = 1024 10.1 / 5.1
-//   2 rounds: 4096 x 11008 M = 512 36.2 / 27.7;  6144 x 4096 M = 256 21.1 / 15.1;  28672 x 4096 M = 64 28.0 / 21.8
-//   3 rounds: 6144 x 4096 M = 512 21.6 / 21.6;  4096 x 4096 M = 768 21.5 / 21.3;  4096 x 11008 M = 768 47.5 / 41.9;
-//             28672 x 4096 M = 100 (4) 28.1 / 33.6
-// (N x K; "tiled" slices K where its own plan does.)
-bool mx_mid_wanted(const MxLinearArgs& a) { return mid_rounds(a.M, a.N, device_cu_count()) <= 2; }
+// Up to four tiles per compute unit.  Measured (us, tiled kernel / this one, r = 128, N x K):
+//   4096 x 4096 M = 256 21.0 / 8.5, M = 512 (2) 21.2 / 12.4, M = 768 (3) 21.5 / 16.5, M = 1024 (4) 22.1 / 20.4;
+//   4096 x 11008 M = 256 28.8 / 14.8, M = 768 (3) 47.7 / 35.9, M = 1024 (4) 48.6 / 48.3;  11008 x 4096 M = 400 (5) 23.2 / 23.4,
+//   M = 512 (6) 24.0 / 27.2;  28672 x 4096 M = 40 (2) 28.0 / 17.4, M = 100 (4) 27.9 / 26.2, M = 150 (6) 28.5 / 33.6
+// (in brackets: tiles of the busiest compute unit, where more than one; "tiled" slices K where its own plan does).
+// Workgroups of 8 waves, one to a compute unit: 4096 x 4096 M = 256 8.9, M = 512 15.4; 4096 x 11008 M = 256 15.1, M = 768 42.0.
+bool mx_mid_wanted(const MxLinearArgs& a) { return mid_rounds(a.M, a.N, device_cu_count()) <= 4; }
 
 int launch_mx_mid(const MxLinearArgs& a, hipStream_t st) {
   MxMidParams p;
@@ -236,7 +236,8 @@ int launch_mx_mid(const MxLinearArgs& a, hipStream_t st) {
   p.Y = a.Y; p.y_dtype = a.y_dtype; p.ldy = a.ldy;
   p.tiles_m = (a.M + 63) / 64;
   p.tiles_n = (a.N + 63) / 64;
-  hipLaunchKernelGGL(serq_mx_mid_kernel, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(kMidThreads), 0, st, p);
+  const dim3 grid((unsigned)(p.tiles_m * p.tiles_n));
+  hipLaunchKernelGGL(serq_mx_mid_kernel, grid, dim3(64 * NW), 0, st, p);
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;
 }
 

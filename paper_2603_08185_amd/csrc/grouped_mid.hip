@@ -1,5 +1,5 @@
 // The layer with group-128 weight scales for batches between decode and prefill: tiles of 64 tokens x 64 channels, the
-// 8 waves of a workgroup sharing K (mid_tile.h says why; the formulas are those of grouped.hip).
+// 4 or 8 waves of a workgroup sharing K (mid_tile.h says why; the formulas are those of grouped.hip).
 //
 // A wave takes whole groups of 128 channels: one stage of 4-bit tokens, two of 8-bit ones, each with the group's 64
 // scales.  The four products of an MFMA tile start from zero and the INT32 tile is folded into the wave's fp32 tile
@@ -25,20 +25,19 @@ struct GMid {
   static constexpr int NL = 4 + 2 * FR + 1;
   static constexpr int REGION = NS * STAGE;
   static constexpr int SH = ABITS == 8 ? 4 : 8;
-  static constexpr int LDS = kMidWaves * REGION;
   static_assert(REGION >= kMidPart, "a partial tile fits the ring it replaces");
-  static_assert(LDS <= 160 * 1024, "LDS budget");
+  static_assert(8 * REGION <= 160 * 1024, "LDS budget");
 };
 
 template <int FR>
 struct GMidOp { u4 w[2][FR], x[2][2]; float gs[2]; };
 
-template <int ABITS, bool BF>
-__global__ __launch_bounds__(kMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int ABITS, bool BF, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
   using T = GMid<ABITS>;
   constexpr int FR = T::FR, NS = T::NS;
-  __shared__ __align__(16) uint8_t lds[T::LDS];
+  __shared__ __align__(16) uint8_t lds[NW * T::REGION];
   const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tile_m, tile_n;
@@ -51,7 +50,7 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
 
   MidLoads<FR> ld;
   ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
-  const int ng = G > w ? (G - w + kMidWaves - 1) / kMidWaves : 0;   // groups w, w + 8, ... are this wave's
+  const int ng = G > w ? (G - w + NW - 1) / NW : 0;   // groups w, w + NW, ... are this wave's
   constexpr int SPG = ABITS == 8 ? 2 : 1;              // stages per group
   const int nst = ng * SPG;
   uint8_t* my = lds + w * T::REGION;
@@ -63,44 +62,53 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
   // rows per lane, the first chunk requested before anything else (oldest loads: the ring's counting is not disturbed)
   const int JB = p.r >> 4;
   constexpr int NJ = 8;
-  u4 lrr[2], lrx;
-  int lzm = 0;
-  const int lrow = 8 * w + (l >> 3);
-  const int lrm = m0 + (lrow < mrows ? lrow : mrows - 1);
+  constexpr int VH = 8 / NW;                           // (a wave of 4 brings the shares of two of 8)
+  u4 lrr[VH][2], lrx[VH];
+  int lzm[VH];
+  auto lr_row = [&](int v) { return 8 * (VH * w + v) + (l >> 3); };
+  auto lr_m = [&](int v) { return m0 + (lr_row(v) < mrows ? lr_row(v) : mrows - 1); };
   auto lr_fetch = [&](int jb0) {
 #pragma unroll
+    for (int v = 0; v < VH; ++v) {
+#pragma unroll
     for (int q = 0; q < 2; ++q) {
-      const int f = 2 * w + q, b = f >> 3, jb = jb0 + (f & 7);
-      lrr[q] = p.Rp[((size_t)(nb0 + (b < nbt ? b : 0)) * JB + (jb < JB ? jb : JB - 1)) * 64 + l];
+      const int f = 2 * (VH * w + v) + q, b = f >> 3, jb = jb0 + (f & 7);
+      lrr[v][q] = p.Rp[((size_t)(nb0 + (b < nbt ? b : 0)) * JB + (jb < JB ? jb : JB - 1)) * 64 + l];
     }
     const int have = 16 * (JB - jb0);                  // channels of this chunk
     const int c = 16 * (l & 7) < have ? 16 * (l & 7) : 0;
-    const uint8_t* src = p.Xq + (size_t)lrm * rowbytes + (size_t)(p.s_begin + 16 * jb0 + c) * ABITS / 8;
+    const uint8_t* src = p.Xq + (size_t)lr_m(v) * rowbytes + (size_t)(p.s_begin + 16 * jb0 + c) * ABITS / 8;
     if constexpr (ABITS == 8) {
-      lrx = *(const u4*)src;
+      lrx[v] = *(const u4*)src;
     } else {
-      const u2 v = *(const u2*)src;
-      lrx = u4{v.x, v.y, 0u, 0u};
+      const u2 x = *(const u2*)src;
+      lrx[v] = u4{x.x, x.y, 0u, 0u};
+    }
     }
   };
   constexpr int LRX_OFF = 16 * 1024;                   // R fragments at 0, codes (64 rows x 256 B of 16-bit floats) here
   auto lr_park = [&]() {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) *(u4*)(lds + (2 * w + q) * 1024 + l * 16) = lrr[q];
+    for (int v = 0; v < VH; ++v) {
+    const int lrow = lr_row(v);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) *(u4*)(lds + (2 * (VH * w + v) + q) * 1024 + l * 16) = lrr[v][q];
     uint8_t* row = lds + LRX_OFF + lrow * 256;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       int k[8];
-      if constexpr (ABITS == 8) codes_from_a8(h ? lrx.z : lrx.x, h ? lrx.w : lrx.y, k);
-      else codes_from_a4(h ? lrx.y : lrx.x, k);
+      if constexpr (ABITS == 8) codes_from_a8(h ? lrx[v].z : lrx[v].x, h ? lrx[v].w : lrx[v].y, k);
+      else codes_from_a4(h ? lrx[v].y : lrx[v].x, k);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) k[e] -= lzm;         // at most 255 in magnitude: exact in both 16-bit formats
+      for (int e = 0; e < 8; ++e) k[e] -= lzm[v];         // at most 255 in magnitude: exact in both 16-bit formats
       *(u4*)(row + 16 * ((2 * (l & 7) + h) ^ (lrow & 15))) = codes8_to_16bit(k, BF);
+    }
     }
   };
   if (JB > 0) {
     lr_fetch(0);
-    if (p.zero) lzm = p.zero[lrm];
+#pragma unroll
+    for (int v = 0; v < VH; ++v) lzm[v] = p.zero ? p.zero[lr_m(v)] : 0;
   }
 
   // ---- main loop ------------------------------------------------------------------------------------------------
@@ -117,7 +125,7 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
     }
   const int xsw = mid_swz(lm);
   auto slot = [&](int t) { return (t % NS) * T::STAGE; };
-  auto group = [&](int t) { return w + kMidWaves * (SPG == 2 ? t >> 1 : t); };
+  auto group = [&](int t) { return w + NW * (SPG == 2 ? t >> 1 : t); };
   auto fill = [&](int t, int k) {
     const int s = SPG == 2 ? 2 * group(t) + (t & 1) : group(t);
     if (k < T::NL - 1) ld.issue_one(s, my_lds + slot(t), k);
@@ -181,15 +189,18 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
       },
       fill, read, product);
 
-  // ---- the waves meet; wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j ------------------
+  // ---- the waves meet.  8 waves: wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j; 4 waves: all
+  // of tile w = 2*i + j
   constexpr float kInv = 1.0f / (float)(1 << T::SH);
-  const int ti = w >> 2, tj = (w >> 1) & 1, hq = 2 * (w & 1);
+  constexpr int QN = 16 / NW, NE = 4 * QN;             // register quads, registers
+  const int tt = NW == 8 ? w >> 1 : w;
+  const int ti = tt >> 1, tj = tt & 1, hq = NW == 8 ? 2 * (w & 1) : 0;
   const int blk = nb0 + (ti < nbt ? ti : 0);
   const int n = 32 * blk + lm;                         // this lane's channel
   const int mloc = 32 * tj + 8 * hq + 4 * g;           // registers 4*q + e: token mloc + 8*q + e
-  float sm[8], zf[8];
+  float sm[NE], zf[NE];
 #pragma unroll
-  for (int q = 0; q < 2; ++q)
+  for (int q = 0; q < QN; ++q)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = mloc + 8 * q + e, m = m0 + (r < mrows ? r : mrows - 1);
@@ -206,25 +217,22 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
         *(v4f*)(my + ((2 * i + j) * 4 + q) * 1024 + l * 16) =
             v4f{accf[i][j][4 * q], accf[i][j][4 * q + 1], accf[i][j][4 * q + 2], accf[i][j][4 * q + 3]};
   __syncthreads();
-  float y[8];
+  float y[NE];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) y[e] = 0.0f;
+  for (int e = 0; e < NE; ++e) y[e] = 0.0f;
 #pragma unroll
-  for (int ww = 0; ww < kMidWaves; ++ww)
+  for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const v4f v = *(const v4f*)(lds + ww * T::REGION + ((w >> 1) * 4 + hq + q) * 1024 + l * 16);
+    for (int q = 0; q < QN; ++q) {
+      const v4f v = *(const v4f*)(lds + ww * T::REGION + (tt * 4 + hq + q) * 1024 + l * 16);
       y[4 * q] += v.x; y[4 * q + 1] += v.y; y[4 * q + 2] += v.z; y[4 * q + 3] += v.w;
     }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) y[e] = __builtin_fmaf(y[e], kInv, -zf[e] * ws);   // 2^-SH: exact
+  for (int e = 0; e < NE; ++e) y[e] = __builtin_fmaf(y[e], kInv, -zf[e] * ws);   // 2^-SH: exact
   if (JB > 0) {
     v16f af;                                           // the tile the matrix unit adds to
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      af[e] = hq ? 0.0f : y[e];
-      af[8 + e] = hq ? y[e] : 0.0f;
-    }
+    for (int e = 0; e < 16; ++e) af[e] = NW == 4 ? y[e % NE] : (e >> 3) == (hq >> 1) ? y[e & 7] : 0.0f;
     for (int jb0 = 0; jb0 < JB; jb0 += NJ) {
       __syncthreads();                                 // the partial tiles (the chunk before) have been read
       lr_park();
@@ -245,14 +253,14 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
       }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = hq ? af[8 + e] : af[e];
+    for (int e = 0; e < NE; ++e) y[e] = NW == 4 ? af[e] : hq ? af[(8 + e) & 15] : af[e];
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) y[e] *= sm[e];
+  for (int e = 0; e < NE; ++e) y[e] *= sm[e];
 
   if (p.y_dtype == SERQ_F32) {                         // 32 lanes write 128 contiguous bytes
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < NE; ++e) {
       const int r = mloc + 8 * (e >> 2) + (e & 3);
       if (r < mrows && ti < nbt) ((float*)p.Y)[(size_t)(m0 + r) * p.ldy + n] = y[e];
     }
@@ -260,30 +268,40 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
   }
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
+  for (int e = 0; e < NE; ++e) {
     const int r = mloc + 8 * (e >> 2) + (e & 3), c = 32 * ti + lm;
     *(uint16_t*)(lds + r * 128 + 16 * ((c >> 3) ^ (r & 7)) + 2 * (c & 7)) =
         p.y_dtype == SERQ_BF16 ? f32_to_bf16_rne(y[e]) : f32_to_f16_rne(y[e]);
   }
   __syncthreads();
-  mid_store16<kMidThreads>(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
+  mid_store16<64 * NW>(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
 }
 
 }  // namespace
 
-// Up to two tiles per compute unit.  Measured (us, tiled kernel / this one, r = 128, W4A8; W4A4 the same or better):
-//   1 round:  4096 x 11008 M = 256 73.1 / 28.2;  4096 x 4096 M = 256 32.8 / 14.1;  6144 x 4096 M = 100 33.1 / 13.1
-//   2 rounds: 4096 x 11008 M = 512 73.2 / 51.0;  4096 x 4096 M = 512 32.9 / 25.0;  6144 x 4096 M = 256 32.8 / 24.3;
-//             28672 x 4096 M = 64 34.5 / 32.3;  1024 x 1024 M = 2048 14.9 / 13.3
-//   3 rounds: 6144 x 4096 M = 512 33.6 / 36.0;  11008 x 4096 M = 256 33.4 / 35.5;  4096 x 11008 M = 768 74.0 / 73.4
-// (N x K).  From three rounds on the tiled kernel, which moves two thirds of the bytes per product, is as fast or faster.
-bool g128_mid_wanted(const G128Args& a) { return mid_rounds(a.M, a.N, device_cu_count()) <= 2; }
+// Up to three tiles per compute unit.  Measured (us, tiled kernel / this one, r = 128, N x K):
+//   W4A8  4096 x 4096 M = 256 23.1 / 13.7, M = 512 (2) 23.7 / 20.6, M = 768 (3) 34.0 / 29.6, M = 1024 (4) 34.5 / 38.6;
+//         11008 x 4096 M = 256 (3) 33.7 / 29.8;  4096 x 11008 M = 256 47.2 / 26.2, M = 512 (2) 47.6 / 44.6, M = 768 (3) 73.0 / 63.5;
+//         28672 x 4096 M = 40 (2) 36.2 / 25.4, M = 100 (4) 35.3 / 41.6
+//   W4A4  4096 x 4096 M = 512 (2) 24.9 / 18.0, M = 768 (3) 34.0 / 26.0;  4096 x 11008 M = 768 (3) 72.6 / 50.5;  28672 x 4096
+//         M = 100 (4) 35.1 / 36.0
+// (in brackets: tiles of the busiest compute unit, where more than one).
+bool g128_mid_wanted(const G128Args& a) { return mid_rounds(a.M, a.N, device_cu_count()) <= 3; }
 
 int launch_g128_mid(const G128Args& a, int abits, hipStream_t st) {
   const int tm = (a.M + 63) / 64, tn = (a.N + 63) / 64;
-  const dim3 grid((unsigned)(tm * tn)), block(kMidThreads);
+  const dim3 grid((unsigned)(tm * tn));
   const bool bf = a.r_dtype != SERQ_F16;
-#define SERQ_GMID_LAUNCH(AB, BF) hipLaunchKernelGGL((serq_g128_mid_kernel<AB, BF>), grid, block, 0, st, a, tm, tn)
+  // One tile per compute unit at most: 8 waves, which the folds need to keep the vector units busy.  More tiles: workgroups
+  // of 4 waves, two of which share a compute unit, so that one's start and end run beside the other's main loop.
+  // Measured (us, 8 / 4 waves, r = 128, N x K): W4A8 4096 x 11008 M = 100 21.6 / 23.8, M = 333 44.9 / 36.7; 6144 x 4096
+  // M = 100 13.0 / 13.3, M = 256 24.0 / 19.7; W4A4 4096 x 11008 M = 150 19.4 / 21.3, M = 333 35.8 / 32.0.
+  const bool eight = tm * tn <= device_cu_count();
+#define SERQ_GMID_LAUNCH(AB, BF)                                                                                       \
+  do {                                                                                                                 \
+    if (eight) hipLaunchKernelGGL((serq_g128_mid_kernel<AB, BF, 8>), grid, dim3(512), 0, st, a, tm, tn);               \
+    else hipLaunchKernelGGL((serq_g128_mid_kernel<AB, BF, 4>), grid, dim3(256), 0, st, a, tm, tn);                     \
+  } while (0)
   if (abits == 8) {
     if (bf) SERQ_GMID_LAUNCH(8, true); else SERQ_GMID_LAUNCH(8, false);
   } else {

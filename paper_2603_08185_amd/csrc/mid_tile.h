@@ -20,8 +20,6 @@
 namespace serq {
 namespace {
 
-constexpr int kMidWaves = 8;
-constexpr int kMidThreads = 64 * kMidWaves;
 constexpr int kMidX = 64 * 64;                       // token bytes of a stage
 constexpr int kMidPart = 4 * 4 * 64 * 16;            // a wave's partial tile: [tile 2*i + j][register quad][lane][16 B]
 

@@ -53,7 +53,7 @@ def test_salient_block_offset():
 @pytest.mark.parametrize("abits", [4, 8])
 @pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
 @pytest.mark.parametrize("M,K,N,r", [(33, 128, 32, 16), (65, 1152, 96, 0), (100, 4224, 288, 128), (200, 2560, 160, 144),
-                                     (129, 384, 1056, 320), (333, 6144, 64, 64)])
+                                     (129, 384, 1056, 320), (333, 6144, 64, 64), (400, 1152, 5152, 208)])
 def test_g128_layer(abits, in_dtype, out_dtype, M, K, N, r):
     spec = grouped._spec(abits, M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype)
     Y, _, _ = grouped._run(spec, R_mode="residual" if r else "none")
@@ -71,7 +71,8 @@ def test_g128_layer_variants():
 # K: one fragment; a last scale tile of 1, 2 and 3 fragments, alone in its wave and behind others; several compensation fragments
 @pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
 @pytest.mark.parametrize("M,K,N,r", [(33, 64, 32, 32), (65, 128, 96, 0), (100, 448, 64, 96), (200, 4416, 288, 128),
-                                     (129, 2688, 1056, 640), (333, 6144, 64, 64), (64, 4160, 160, 256)])
+                                     (129, 2688, 1056, 640), (333, 6144, 64, 64), (64, 4160, 160, 256),
+                                     (400, 1088, 5152, 352)])
 def test_mx_layer(in_dtype, out_dtype, M, K, N, r):
     spec = mx._spec(M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype)
     Y, Y64, _ = mx._run_mx(spec)
