@@ -59,8 +59,8 @@ extern "C" {
 #define SERQ_I4   3
 
 /* kernel selection for serq_linear / serq_gemm_i32 (low byte of `flags`) */
-#define SERQ_PATH_AUTO   0     /* by size: skinny for M <= 32; a kernel with small tiles while they fill the
-                                * compute units at most twice (no flags); tiled MFMA above */
+#define SERQ_PATH_AUTO   0     /* by size: skinny for M <= 32; a kernel with small tiles while every compute
+                                * unit gets only a few of them (no flags); tiled MFMA above */
 #define SERQ_PATH_SKINNY 1     /* weight-streaming split-K kernel (M <= 32)     */
 #define SERQ_PATH_MFMA   2     /* LDS-tiled int8-MFMA kernel                    */
 /* bits 8..15 of `flags`: number of K slices (0 = the library's choice; 1 = none; n > 1 = exactly n, which
