@@ -51,8 +51,19 @@ extern "C" int serq_linear_noalloc(const void* Xq, const float* scale, int abits
   if (rc != SERQ_OK) return rc;
   // The kernels receive the device address as an argument, exactly as they receive a caller's workspace;
   // they return every word they used to zero before they finish, so nothing has to be cleared per call.
-  // (The array holds the decode path's meeting words only: the tiled path, which could park K slices in a
-  // larger workspace, finds none here and runs unsliced.)
+  // The array holds the decode path's meeting words and nothing else: the tiled path, which parks the tiles of
+  // its K slices behind the words of its own layer and leaves them there, must find no room, or the next decode
+  // call of a wider layer would start from them.  It runs unsliced -- also where the caller asks for slices that
+  // would fit: the INT32 sums are the same integers.
+  size_t bytes = sizeof(unsigned long long) * kScratchWords;
+  const int path = flags & 0xff, slices = (flags >> 8) & 0xff;
+  const bool sizes_ok = N >= 32 && N % 32 == 0 && M > 0 && M <= (1 << 30) && K >= 64 && K <= 131072;
+  if (sizes_ok && (path == SERQ_PATH_MFMA || (path == SERQ_PATH_AUTO && M > 32))) {
+    const size_t words = serq::skinny_workspace_bytes((int)N);
+    if (slices > 1 && words + serq::mfma_split_workspace_bytes((int)M, (int)N, (int)K, abits, slices) <= bytes)
+      flags = (flags & ~SERQ_FLAG_SPLITK(0xff)) | SERQ_FLAG_SPLITK(1);
+    bytes = words;
+  }
   return serq_linear(Xq, scale, abits, Wq, wscale, s_begin, r, Rp, r_dtype, M, N, K, Y, y_dtype, ldy,
-                     ws, sizeof(unsigned long long) * kScratchWords, flags, stream);
+                     ws, bytes, flags, stream);
 }

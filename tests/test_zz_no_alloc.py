@@ -84,3 +84,21 @@ def test_noalloc_under_graph_capture():
     replay_check(step, [Y, Xq, scale], mutate)
     ws = serq.workspace(spec.M, spec.N, spec.K, spec.r, 8, DEV)
     assert torch.equal(Y, serq.linear(Xq, scale, 8, pk.Wq, pk.wscale, spec.M, spec.N, spec.K, Rp=Rp, r=spec.r, ws=ws))
+
+
+def test_noalloc_tiled_call_leaves_nothing_for_the_next_decode_call():
+    # the tiled kernel would cut K here (few tokens, few channels, long K) and park its slices where the decode path of the
+    # wider layer keeps words that must be zero; asked for slices by flag as well, which the built-in array has room for
+    narrow = workloads.LayerSpec("noalloc_narrow", 9, 4, 100, 4096, 32, 32, "bf16", "bf16", 3, 20.0, 60.0)
+    wide = workloads.LayerSpec("noalloc_wide", 9, 8, 8, 4096, 2048, 32, "bf16", "bf16", 3, 20.0, 60.0, seed_index=1)
+    prepared = {spec.name: _prepare(spec) for spec in (narrow, wide)}
+    for fl in (serq.flags(serq.PATH_MFMA), serq.flags(serq.PATH_MFMA, splitk=4), serq.flags(serq.PATH_AUTO, splitk=2)):
+        for spec, f in ((narrow, fl), (wide, serq.flags())):
+            pk, Xq, scale, Rp, Y64 = prepared[spec.name]
+            M, N, K = spec.M, spec.N, spec.K
+            Y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+            kw = dict(Rp=Rp, r=spec.r)
+            serq.linear_noalloc(Xq, scale, spec.abits, pk.Wq, pk.wscale, M, N, K, Y, flags_=f, **kw)
+            Yref = serq.linear(Xq, scale, spec.abits, pk.Wq, pk.wscale, M, N, K, **kw)
+            assert torch.equal(Y, Yref), spec.name             # (sliced or not, the same integers)
+            assert_y_close(Y, Y64, spec.name)
