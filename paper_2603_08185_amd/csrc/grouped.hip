@@ -543,7 +543,13 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void serq_g128_skinny_kernel(con
 // the next group are copied from LDS to registers while this group is multiplied (the registers for that come from
 // the scales and from keeping two INT32 tiles, not four): the products never wait for an LDS read.  The four MFMAs
 // of a group run tile by tile, and the convert-and-FMA pairs that fold the tile before are issued between them, so
-// that the vector unit works in the shadow of the matrix unit.
+// that the vector unit works in the shadow of the matrix unit.  The first group stands outside the loop and does not wait
+// for the second one to land.
+//
+// With a short K the end of the tile counts: everything it takes from LDS is read in one go, before anything is written
+// there, and 16-bit results go through LDS by channel (below).  Measured (us, end as it was with results exchanged between
+// lanes and reads behind tests / this form, W4A8 r = 0, N x K): 2048 x 256 M = 4096 11.1 / 9.8; 11008 x 1024 M = 1024
+// 25.6 / 23.7, fp32 output 31.3 / 28.3; 6144 x 4096 M = 3000 99.5 / 97.9.
 template <int ABITS>
 struct GTile {
   static constexpr int XROW = 128 * ABITS / 8;       // bytes of a token's 128 codes
@@ -571,8 +577,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr float kInv = 1.0f / (float)(1 << SH);
   constexpr int NS = T::NS;
   __shared__ __align__(16) uint8_t lds[T::LDS];
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lm = l & 31, g = l >> 5;
-  const int wn = w & 1, wm = w >> 1;
+  const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
+  const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = wu & 1, wm = wu >> 1;
   const int NB = p.N >> 5, KB = p.K >> 6, G = p.K >> 7;
   // workgroup id -> tile: one contiguous range of tiles per XCD, in bands of 8 token tiles, so that the
   // tiles in flight on one XCD share their weight and token panels in its L2.  HALVES: workgroups from `full` on
@@ -595,7 +602,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // A direct load puts the 16 bytes of lane l at (wave-uniform LDS base) + 16 l, so the swizzle of the
   // token pieces is applied on the source side.  Per group and wave: 2 weight fragments, NLX x 64 token
   // pieces, and (4 lanes) the 64 bytes of scales of block w.
-  const int wu = __builtin_amdgcn_readfirstlane(w);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(lds));
   // (few registers, every one is taken in the main loop: the weight and scale offsets are wave-uniform but for the lane, and
   // the token rows of the NLX loads lie 1024 / XROW * 4 rows apart, with the same swizzle)
@@ -698,10 +704,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // the tiles of a group; the MFMAs of tile u = 2*i + j shadow the fold of the tile before.  The next group's weights
   // are read once the registers of this group's first block are free.
-  auto multiply = [&](const Op& o, int nst, Op& nxt) {
+  auto multiply = [&](auto ahead, const Op& o, int nst, Op& nxt) {
 #pragma unroll
     for (int u = 0; u < 2 * NI; ++u) {
-      if (u == NI) {
+      if (decltype(ahead)::value && u == NI) {
         read_w(nst, nxt);
         fence();
       }
@@ -750,9 +756,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   read_w(0, A);
   read_x(0, A);
   int st = 0;                                         // slot of the current group
-  auto group = [&](int gi, const Op& cur, Op& nxt) {
-    // the next group has landed (its loads but not those of the NS-2 groups behind it), and every wave has read this
-    // one, whose slot may be refilled
+  auto group = [&](auto first_c, int gi, const Op& cur, Op& nxt) {
+    constexpr bool FIRST = decltype(first_c)::value;
+    if (FIRST) multiply(std::false_type{}, cur, 0, nxt);
     const int next = st + 1 == NS ? 0 : st + 1;
     const int last = gi + NS - 1 < GT - 1 ? gi + NS - 1 : GT - 1;
     if (last - gi == NS - 1) wait_dma_barrier<(NS - 2) * T::nl(NI)>();
@@ -760,21 +766,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (gi + NS < GT) issue(gi + NS, st);
     st = next;
     read_x(st, nxt);                                  // (behind the last stage: stale bytes, never used)
+    if (FIRST) read_w(st, nxt);
     fence();
-    multiply(cur, st, nxt);
+    if (!FIRST) multiply(std::true_type{}, cur, st, nxt);
   };
-  int gi = 0;
+  group(std::true_type{}, 0, A, B);
+  int gi = 1;
 #pragma unroll 1
   for (; gi + 1 < G; gi += 2) {
-    group(gi, A, B);
-    group(gi + 1, B, A);
+    group(std::false_type{}, gi, B, A);
+    group(std::false_type{}, gi + 1, A, B);
   }
-  if (gi < G) group(gi, A, B);
+  if (gi < G) group(std::false_type{}, gi, B, A);
 
   // ---- epilogue: zero point, rank-r term on the re-centred codes, token scale, one store ----------------
   // register e of lane (lm, g) in tile (i, j): token 32*(2*wm + j) + 8*(e/4) + 4*g + e%4, channel 32*bi[i] + lm
   // The R fragments come straight from L2, four 16-rank fragments at a time and a batch ahead of their use, the first
   // batch requested here.
+  // (lane indices taken anew: every register that lives through the main loop for the sake of the end is one too many)
+  int te = tid;
+  asm volatile("" : "+v"(te));
+  const int l = te & 63, lm = l & 31, g = l >> 5;
   const int JB = p.r >> 4;
   constexpr int NJ = 4;
   u4 rr[NJ][NI], rn[NJ][NI];
@@ -793,20 +805,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const float* tsc = reinterpret_cast<const float*>(lds + T::TS_OFF);       // (in LDS since the first stage was waited for)
   const int* tzr = reinterpret_cast<const int*>(lds + T::TS_OFF + 512);
   const float* tws = reinterpret_cast<const float*>(lds + T::TS_OFF + 1024);
+  v4i z[2][4];                                          // (read in one go: behind a test each they would be waited for one by one)
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      v4i z = {0, 0, 0, 0};
-      if (p.zero) z = *(const v4i*)(tzr + 32 * (2 * wm + j) + 8 * q4 + 4 * g);
+    for (int q4 = 0; q4 < 4; ++q4) z[j][q4] = v4i{0, 0, 0, 0};
+  if (p.zero) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const float ws = tws[32 * (NI * wn + i) + lm];
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          accf[i][j][4 * q4 + e] = __builtin_fmaf(accf[i][j][4 * q4 + e], kInv, -(float)z[e] * ws);   // 2^-SH: exact
-      }
-    }
+      for (int q4 = 0; q4 < 4; ++q4) z[j][q4] = *(const v4i*)(tzr + 32 * (2 * wm + j) + 8 * q4 + 4 * g);
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const float ws = tws[32 * (NI * wn + i) + lm];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        accf[i][j][e] = __builtin_fmaf(accf[i][j][e], kInv, -(float)z[j][e >> 2][e & 3] * ws);   // 2^-SH: exact
+  }
   if (has_lr) {
     // The token codes of the salient block come back through the ring (they ran ahead of the last main groups,
     // like any stage).
@@ -861,55 +879,80 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
   }
+  v4f sm[2][4];                                         // (all of them before anything is written to LDS, which would hold up the reads)
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) sm[j][q4] = *(const v4f*)(tsc + 32 * (2 * wm + j) + 8 * q4 + 4 * g);
   if (p.y_dtype == SERQ_F32) {
     // fp32 output: 32 lanes write 128 contiguous bytes straight from the accumulators
+    const int mw = 64 * wm;                             // this wave's first row
+    float* yw = (float*)p.Y + (size_t)(m0 + mw) * p.ldy + 32 * nb0;
+    const size_t lane = (size_t)(4 * g) * p.ldy + lm;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < NI; ++i) {
+      const int b = NI * wn + i;
+      if (b >= nbt) break;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int r = 32 * (2 * wm + j) + 8 * (e >> 2) + 4 * g + (e & 3);
-        const float sm = tsc[r];
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int i = 0; i < NI; ++i)
-          if (r < mrows && NI * wn + i < nbt) ((float*)p.Y)[(size_t)(m0 + r) * p.ldy + 32 * bi[i] + lm] = sm * accf[i][j][e];
-      }
+        for (int e = 0; e < 16; ++e) {
+          const int r = 32 * j + 8 * (e >> 2) + (e & 3);
+          if (mw + r + 4 * g < mrows) yw[(size_t)r * p.ldy + 32 * b + lane] = sm[j][e >> 2][e & 3] * accf[i][j][e];
+        }
+    }
     return;
   }
-  // 16-bit output: cast, transpose through LDS (the ring is free now; rows of 256 B, the 16-byte piece pc of
-  // row r at piece pc ^ (r & 15)), then stores of whole row segments: 16 lanes write 256 contiguous bytes.  Two
-  // neighbouring lanes hold two channels of the same tokens: they exchange halves, so that the even lane writes both
-  // channels of one token and the odd lane those of the next.
+  // 16-bit output: cast and transposed through LDS (the ring is free now).  A lane holds four consecutive tokens of one
+  // channel: LDS holds a row of 256 B per channel (128 tokens), the 16-byte piece pt of channel c at piece pt ^ swz_y(c).
+  // A thread reads the same four tokens of eight channels, pairs the channels up and stores 16 bytes per token: 16 lanes
+  // write 256 contiguous bytes.  (Neighbouring lanes exchanging halves before LDS instead: twice the LDS writes and four
+  // times the register moves.)
   __syncthreads();                                      // every wave is done with the ring
   const bool ybf = p.y_dtype == SERQ_BF16;
+  auto swz_y = [](int c) { return (c & 15) ^ ((c >> 3) & 15); };   // distinct over 16 neighbours and over 16 steps of 8
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
-      const int r0 = 32 * (2 * wm + j) + 8 * q4 + 4 * g;
-      const v4f sm = *(const v4f*)(tsc + r0);
+      const int pt = 4 * (2 * wm + j) + q4;             // tokens 8*pt + 4*g + 0..3
 #pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const float y0 = sm[2 * h] * accf[i][j][4 * q4 + 2 * h], y1 = sm[2 * h + 1] * accf[i][j][4 * q4 + 2 * h + 1];
-          const uint32_t own = ybf ? f32x2_to_bf16x2(y0, y1) : f32x2_to_f16x2(y0, y1);
-          const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
-          const uint32_t v = (l & 1) ? __builtin_amdgcn_perm(own, nb, 0x07060302u) : __builtin_amdgcn_perm(nb, own, 0x05040100u);
-          const int r = r0 + 2 * h + (l & 1);
-          const int c = 32 * (NI * wn + i) + (lm & ~1);
-          *(uint32_t*)(lds + r * 256 + 16 * ((c >> 3) ^ (r & 15)) + 2 * (c & 7)) = v;
-        }
+      for (int i = 0; i < NI; ++i) {
+        const v4f f = sm[j][q4];
+        const float y0 = f.x * accf[i][j][4 * q4], y1 = f.y * accf[i][j][4 * q4 + 1];
+        const float y2 = f.z * accf[i][j][4 * q4 + 2], y3 = f.w * accf[i][j][4 * q4 + 3];
+        u2 o;
+        if (ybf) o = u2{f32x2_to_bf16x2(y0, y1), f32x2_to_bf16x2(y2, y3)};
+        else o = u2{f32x2_to_f16x2(y0, y1), f32x2_to_f16x2(y2, y3)};
+        const int c = 32 * (NI * wn + i) + lm;
+        *(u2*)(lds + c * 256 + 16 * (pt ^ swz_y(c)) + 8 * g) = o;
+      }
     }
   __syncthreads();
-  const int npc = 4 * nbt;                              // 16-byte pieces of a row that belong to the layer
-#pragma unroll 2
-  for (int rr = 0; rr < 128 / 16; ++rr) {
-    const int r = rr * 16 + (tid >> 4);
-    const int pc = tid & 15;
-    if (r < mrows && pc < npc) {
-      const u4 v = *(const u4*)(lds + r * 256 + 16 * (pc ^ (r & 15)));
-      *(u4*)((uint16_t*)p.Y + (size_t)(m0 + r) * p.ldy + nb0 * 32 + 8 * pc) = v;
+  const int c8 = te & 15;                              // channels 8*c8 + 0..7
+  if (c8 < 4 * nbt) {
+    u2 v[2][8];
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      const int tq = 16 * it + (te >> 4);               // tokens 4*tq + 0..3
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int c = 8 * c8 + k;
+        v[it][k] = *(const u2*)(lds + c * 256 + 16 * ((tq >> 1) ^ swz_y(c)) + 8 * (tq & 1));
+      }
     }
+    uint16_t* yt = (uint16_t*)p.Y + (size_t)(m0 + 4 * (te >> 4)) * p.ldy + nb0 * 32 + 8 * c8;
+#pragma unroll
+    for (int it = 0; it < 2; ++it)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const uint32_t sel = t & 1 ? 0x07060302u : 0x05040100u;   // the upper / lower halves of two channels
+        auto two = [&](int k) {
+          return __builtin_amdgcn_perm(t < 2 ? v[it][k + 1].x : v[it][k + 1].y, t < 2 ? v[it][k].x : v[it][k].y, sel);
+        };
+        const int r = 64 * it + t;
+        if (4 * (te >> 4) + r < mrows) *(u4*)(yt + (size_t)r * p.ldy) = u4{two(0), two(2), two(4), two(6)};
+      }
   }
   };
   if constexpr (HALVES) {

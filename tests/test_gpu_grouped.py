@@ -239,3 +239,23 @@ def test_g128_tiles_in_halves(abits, M, K, N, r):
     spec = _spec(abits, M, K, N, r, out_dtype="bf16")
     _run(spec, path=serq.PATH_MFMA, R_mode="residual" if r else "none")
     _run(_spec(abits, M, K, N, r, out_dtype="fp32"), path=serq.PATH_MFMA, R_mode="residual" if r else "none")
+
+
+# whole 128 x 128 tiles (more of them than half of the compute units): ragged token and channel edges, one group to five (the
+# first one stands outside the loop, an odd one behind it), the rank-r term over one and two ring stages
+@pytest.mark.parametrize("abits", [4, 8])
+@pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
+@pytest.mark.parametrize("K,r", [(128, 16), (256, 0), (384, 48), (512, 256), (640, 144)])
+def test_g128_whole_tiles(abits, in_dtype, out_dtype, K, r):
+    spec = _spec(abits, 2100, K, 1312, r, in_dtype=in_dtype, out_dtype=out_dtype)     # 17 x 11 tiles
+    _run(spec, path=serq.PATH_MFMA, R_mode="residual" if r else "none")
+
+
+@pytest.mark.parametrize("abits", [4, 8])
+def test_g128_whole_tiles_variants(abits):
+    spec = _spec(abits, 2100, 640, 1312, 144, out_dtype="fp32")
+    _run(spec, path=serq.PATH_MFMA, asym=False)                       # symmetric codes, no zero points
+    _run(spec, path=serq.PATH_MFMA, R_mode="random", s_begin=160)     # salient block elsewhere, over three groups
+    Ya, _, _ = _run(spec, path=serq.PATH_MFMA)
+    Yb, _, _ = _run(spec, path=serq.PATH_MFMA)
+    assert torch.equal(Ya, Yb)                                        # fixed summation order
