@@ -24,7 +24,7 @@ struct MidParams {
   int M, N, K;
   void* Y; int y_dtype; int64_t ldy;
   int32_t* acc_out; int64_t ldacc;
-  int tiles_m, tiles_n;
+  int tiles_m, tiles_n, band;
 };
 
 template <int ABITS, int NW>
@@ -64,7 +64,7 @@ void serq_mid_kernel(const MidParams p) {
   const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tile_m, tile_n;
-  map_block(blockIdx.x, p.tiles_m, p.tiles_n, p.tiles_m, tile_m, tile_n);
+  map_block(blockIdx.x, p.tiles_m, p.tiles_n, p.band, tile_m, tile_n);
   const int m0 = tile_m * 64, nb0 = tile_n * 2;
   const int NB = p.N >> 5;
   const int nbt = NB - nb0 < 2 ? 1 : 2;
@@ -332,6 +332,7 @@ int launch_mid(const LinearArgs& a, hipStream_t st) {
   p.acc_out = a.acc_out; p.ldacc = a.ldacc;
   p.tiles_m = (a.M + 63) / 64;
   p.tiles_n = (a.N + 63) / 64;
+  p.band = mid_band(p.tiles_m, (long long)a.M * a.K * a.abits / 8);
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n));
   const bool has_lr = p.r > 0 && p.acc_out == nullptr;
   const int lrt = !has_lr ? SERQ_BF16 : a.r_dtype;

@@ -21,7 +21,7 @@ struct MxMidParams {
   const u4* Rq; const uint8_t* rsc; int s_begin; int r;
   int M, N, K;
   void* Y; int y_dtype; int64_t ldy;
-  int tiles_m, tiles_n;
+  int tiles_m, tiles_n, band;
 };
 
 constexpr int FR = 2;
@@ -41,7 +41,7 @@ void serq_mx_mid_kernel(const MxMidParams p) {
   const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tile_m, tile_n;
-  map_block(blockIdx.x, p.tiles_m, p.tiles_n, p.tiles_m, tile_m, tile_n);
+  map_block(blockIdx.x, p.tiles_m, p.tiles_n, p.band, tile_m, tile_n);
   const int m0 = tile_m * 64, nb0 = tile_n * 2;
   const int NB = p.N >> 5;
   const int nbt = NB - nb0 < 2 ? 1 : 2;
@@ -236,6 +236,7 @@ int launch_mx_mid(const MxLinearArgs& a, hipStream_t st) {
   p.Y = a.Y; p.y_dtype = a.y_dtype; p.ldy = a.ldy;
   p.tiles_m = (a.M + 63) / 64;
   p.tiles_n = (a.N + 63) / 64;
+  p.band = mid_band(p.tiles_m, (long long)a.M * a.K / 2);
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n));
   hipLaunchKernelGGL(serq_mx_mid_kernel, grid, dim3(64 * NW), 0, st, p);
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;

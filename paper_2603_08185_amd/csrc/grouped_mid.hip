@@ -34,14 +34,14 @@ struct GMidOp { u4 w[2][FR], x[2][2]; float gs[2]; };
 
 template <int ABITS, bool BF, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n) {
+void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) {
   using T = GMid<ABITS>;
   constexpr int FR = T::FR, NS = T::NS;
   __shared__ __align__(16) uint8_t lds[NW * T::REGION];
   const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tile_m, tile_n;
-  map_block(blockIdx.x, tiles_m, tiles_n, tiles_m, tile_m, tile_n);
+  map_block(blockIdx.x, tiles_m, tiles_n, band, tile_m, tile_n);
   const int m0 = tile_m * 64, nb0 = tile_n * 2;
   const int NB = p.N >> 5, G = p.K >> 7;
   const int nbt = NB - nb0 < 2 ? 1 : 2;
@@ -292,6 +292,7 @@ int launch_g128_mid(const G128Args& a, int abits, hipStream_t st) {
   const int tm = (a.M + 63) / 64, tn = (a.N + 63) / 64;
   const dim3 grid((unsigned)(tm * tn));
   const bool bf = a.r_dtype != SERQ_F16;
+  const int band = mid_band(tm, (long long)a.M * a.K * abits / 8);
   // One tile per compute unit at most: 8 waves, which the folds need to keep the vector units busy.  More tiles: workgroups
   // of 4 waves, two of which share a compute unit, so that one's start and end run beside the other's main loop.
   // Measured (us, 8 / 4 waves, r = 128, N x K): W4A8 4096 x 11008 M = 100 21.6 / 23.8, M = 333 44.9 / 36.7; 6144 x 4096
@@ -299,8 +300,8 @@ int launch_g128_mid(const G128Args& a, int abits, hipStream_t st) {
   const bool eight = tm * tn <= device_cu_count();
 #define SERQ_GMID_LAUNCH(AB, BF)                                                                                       \
   do {                                                                                                                 \
-    if (eight) hipLaunchKernelGGL((serq_g128_mid_kernel<AB, BF, 8>), grid, dim3(512), 0, st, a, tm, tn);               \
-    else hipLaunchKernelGGL((serq_g128_mid_kernel<AB, BF, 4>), grid, dim3(256), 0, st, a, tm, tn);                     \
+    if (eight) hipLaunchKernelGGL((serq_g128_mid_kernel<AB, BF, 8>), grid, dim3(512), 0, st, a, tm, tn, band);         \
+    else hipLaunchKernelGGL((serq_g128_mid_kernel<AB, BF, 4>), grid, dim3(256), 0, st, a, tm, tn, band);               \
   } while (0)
   if (abits == 8) {
     if (bf) SERQ_GMID_LAUNCH(8, true); else SERQ_GMID_LAUNCH(8, false);

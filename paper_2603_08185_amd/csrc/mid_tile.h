@@ -27,6 +27,18 @@ constexpr int kMidPart = 4 * 4 * 64 * 16;            // a wave's partial tile: [
 // turn, and the pieces of rows 4 apart are spread by the xor.
 __device__ __forceinline__ int mid_swz(int row) { return (row >> 2) & 3; }
 
+// Token tiles per band of the tile order (map_block).  All of them, while the token codes fit the 4 MiB of an XCD's L2: then
+// every XCD reads its own weight panels and no others.  Beyond that, bands of up to 8: the tiles in flight on an XCD, 32 or
+// 64 of them, read a block of about 8 x 8 panels, not every token panel for one or two weight panels.
+// Measured (us, one band / bands, r = 128, N x K): W4A8 1024 x 14336 M = 2048 68.7 / 47.6, M = 3000 100 / 69.7;
+// 1024 x 4096 M = 3000 31.3 / 22.9; MXFP4 1024 x 4096 M = 4096 26.6 / 20.9; at 4 MiB W4A8 512 x 1024 M = 4096 8.6 / 8.0;
+// below, 1024 x 1536 M = 2048 9.2 / 9.4, 512 x 1024 M = 1500 5.7 / 6.0.  Bands of 4, 6 and 12: within 3 % of 8.
+inline int mid_band(int tiles_m, long long token_bytes) {
+  if (token_bytes < (4LL << 20)) return tiles_m;
+  const int bands = (tiles_m + 7) / 8;
+  return (tiles_m + bands - 1) / bands;
+}
+
 // how many tiles the busiest compute unit gets
 inline long long mid_rounds(int M, int N, int ncu) {
   const long long tiles = ((long long)M + 63) / 64 * (((long long)N + 63) / 64);

@@ -22,6 +22,8 @@ SHAPES = [
     (333, 6144, 64, 64),
     (70, 8256, 4096, 32),        # half of the compute units and a long K: eight waves for 8-bit tokens
     (400, 1024, 5152, 208),      # three tiles for the busiest compute unit
+    (1100, 4096, 96, 32),        # 8-bit token codes beyond 4 MiB: token tiles in bands, 6 + 6 + 6
+    (2100, 4096, 96, 32),        # 4-bit ones too: 7 + 7 + 7 + 7 + 5
 ]
 
 
@@ -53,7 +55,8 @@ def test_salient_block_offset():
 @pytest.mark.parametrize("abits", [4, 8])
 @pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
 @pytest.mark.parametrize("M,K,N,r", [(33, 128, 32, 16), (65, 1152, 96, 0), (100, 4224, 288, 128), (200, 2560, 160, 144),
-                                     (129, 384, 1056, 320), (333, 6144, 64, 64), (400, 1152, 5152, 208)])
+                                     (129, 384, 1056, 320), (333, 6144, 64, 64), (400, 1152, 5152, 208),
+                                     (2100, 4096, 96, 32)])
 def test_g128_layer(abits, in_dtype, out_dtype, M, K, N, r):
     spec = grouped._spec(abits, M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype)
     Y, _, _ = grouped._run(spec, R_mode="residual" if r else "none")
@@ -72,7 +75,7 @@ def test_g128_layer_variants():
 @pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
 @pytest.mark.parametrize("M,K,N,r", [(33, 64, 32, 32), (65, 128, 96, 0), (100, 448, 64, 96), (200, 4416, 288, 128),
                                      (129, 2688, 1056, 640), (333, 6144, 64, 64), (64, 4160, 160, 256),
-                                     (400, 1088, 5152, 352)])
+                                     (400, 1088, 5152, 352), (2100, 4096, 96, 32)])
 def test_mx_layer(in_dtype, out_dtype, M, K, N, r):
     spec = mx._spec(M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype)
     Y, Y64, _ = mx._run_mx(spec)
