@@ -60,7 +60,9 @@ extern "C" {
 
 /* kernel selection for serq_linear / serq_gemm_i32 (low byte of `flags`) */
 #define SERQ_PATH_AUTO   0     /* by size: skinny for M <= 32; a kernel with small tiles while every compute
-                                * unit gets only a few of them (no flags); tiled MFMA above */
+                                * unit gets only a few of them and the tiled kernel, with K slices where the
+                                * workspace has room for them, is not expected to be faster (no other flags);
+                                * tiled MFMA else */
 #define SERQ_PATH_SKINNY 1     /* weight-streaming split-K kernel (M <= 32)     */
 #define SERQ_PATH_MFMA   2     /* LDS-tiled int8-MFMA kernel                    */
 /* bits 8..15 of `flags`: number of K slices (0 = the library's choice; 1 = none; n > 1 = exactly n, which
@@ -86,7 +88,11 @@ size_t serq_workspace_bytes(int64_t M, int64_t N, int64_t K, int r, int abits);
  * that must be zero (the decode path's meeting words, at its start) zeroed again when
  * they finish, so one call after allocation is enough; the rest (where the tiled path
  * parks the INT32 tiles of its K slices for layers with few tokens and a long K) is
- * scratch.  Two calls that share a workspace must not overlap in time. */
+ * scratch.  Two calls that share a workspace must not overlap in time.  Layers of different N may share one under
+ * SERQ_PATH_AUTO, whose slices park beyond every word that a decode call uses without SERQ_FLAG_SPLITK; calls that
+ * force the tiled kernel or slices on a narrower layer leave scratch where a wider one keeps its words.
+ * serq_workspace_bytes does not know the flags: for M > 32 it includes the slices of the tiled kernel also where
+ * SERQ_PATH_AUTO takes the small tiles, which use none of it (with 4-bit tokens: everywhere). */
 int serq_workspace_init(void* workspace, size_t workspace_bytes, void* stream);
 
 /*

@@ -724,9 +724,7 @@ void serq_mfma_kernel(const MfmaParams p) {
 size_t mfma_split_workspace_bytes(int M, int N, int K, int abits, int forced) {
   if (M <= 0) return 0;
   const SplitPlan pl = plan_split(M, N, K, abits, device_cu_count(), forced);
-  if (pl.S <= 1) return 0;
-  const size_t tiles = (size_t)((M + BM - 1) / BM) * pl.C;
-  return (size_t)pl.S * tiles * kWaves * wave_blocks8(pl.wide) * 64 * sizeof(int4);
+  return parked_bytes(pl, (M + BM - 1) / BM);
 }
 
 int launch_mfma(const LinearArgs& a, hipStream_t st) {
@@ -744,8 +742,7 @@ int launch_mfma(const LinearArgs& a, hipStream_t st) {
   const size_t ws_have = (a.workspace && a.workspace_bytes > ws_skip) ? a.workspace_bytes - ws_skip : 0;
   SplitPlan pl = plan_split(a.M, a.N, a.K, a.abits, ncu, a.coltiles > 0 && a.splitk == 0 ? 1 : a.splitk);
   if (pl.S > 1) {
-    const size_t need = (size_t)pl.S * p.tiles_m * pl.C * kWaves * wave_blocks8(pl.wide) * 64 * sizeof(int4);
-    if (need > ws_have) {
+    if (parked_bytes(pl, p.tiles_m) > ws_have) {
       if (a.splitk > 1) return SERQ_EWORKSPACE;         // an explicit request cannot be honoured
       pl = plan_split(a.M, a.N, a.K, a.abits, ncu, 1);
     }

@@ -220,13 +220,20 @@ void serq_mx_mid_kernel(const MxMidParams p) {
 
 }  // namespace
 
-// Up to four tiles per compute unit.  Measured (us, tiled kernel / this one, r = 128, N x K):
-//   4096 x 4096 M = 256 21.0 / 8.5, M = 512 (2) 21.2 / 12.4, M = 768 (3) 21.5 / 16.5, M = 1024 (4) 22.1 / 20.4;
-//   4096 x 11008 M = 256 28.8 / 14.8, M = 768 (3) 47.7 / 35.9, M = 1024 (4) 48.6 / 48.3;  11008 x 4096 M = 400 (5) 23.2 / 23.4,
-//   M = 512 (6) 24.0 / 27.2;  28672 x 4096 M = 40 (2) 28.0 / 17.4, M = 100 (4) 27.9 / 26.2, M = 150 (6) 28.5 / 33.6
-// (in brackets: tiles of the busiest compute unit, where more than one; "tiled" slices K where its own plan does).
-// Workgroups of 8 waves, one to a compute unit: 4096 x 4096 M = 256 8.9, M = 512 15.4; 4096 x 11008 M = 256 15.1, M = 768 42.0.
-bool mx_mid_wanted(const MxLinearArgs& a) { return mid_rounds(a.M, a.N, device_cu_count()) <= 4; }
+// Up to four tiles per compute unit, as far as that is the cheaper kernel (mid_cheaper).  Measured (us, tiled kernel / this
+// one, r = 128, N x K, weights from HBM; in brackets: tiles of the busiest compute unit):
+//   4096 x 4096 M = 256 (1) 20.5 / 8.6, M = 512 (2) 21 / 13.5, M = 768 (3) 23.6 / 19, M = 1024 (4) 24.1 / 24.4;
+//   4096 x 14336 M = 256 (1) 36 / 23, M = 512 (2) 46 / 38.5, M = 768 (3) 67 / 50;  11008 x 14336 M = 100 (2) 46 / 40, M = 256
+//   (3) 52 / 57, weights from the last-level cache 46 / 44;  11008 x 20480 M = 256 (3) 68 / 81 (to the tiled kernel);  4096 x 28672 M = 256 (1) 48.5 / 41.5, M = 512 (2) 59 / 70 (to the tiled kernel)
+// Workgroups of 8 waves, one to a compute unit: 4096 x 4096 M = 256 8.9 against 8.5, M = 512 15.4 against 12.4; 4096 x 11008
+// M = 768 42.0 against 35.9.
+bool mx_mid_wanted(const MxLinearArgs& a) {
+  static constexpr MidPrice small = {{2.45f, 1.17f, 0.22f, 0.52f, 0.39f, 0.06f}};
+  static constexpr TiledPrice tiled = {{6.65f, 3.09f, 0.42f, 0.83f, 9.38f, 0.37f}};
+  const size_t skip = skinny_mx_workspace_bytes(a.N);
+  const size_t have = a.workspace && a.workspace_bytes > skip ? a.workspace_bytes - skip : 0;
+  return mid_cheaper(small, tiled, a.M, a.N, a.K, 0, 4, 0.95f, have);
+}
 
 int launch_mx_mid(const MxLinearArgs& a, hipStream_t st) {
   MxMidParams p;

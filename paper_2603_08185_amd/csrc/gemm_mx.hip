@@ -481,9 +481,7 @@ void serq_mx_kernel(const MxParams p) {
 size_t mx_split_workspace_bytes(int M, int N, int K, int forced) {
   if (M <= 0) return 0;
   const SplitPlan pl = plan_split(M, N, K, 0, device_cu_count(), forced);
-  if (pl.S <= 1) return 0;
-  const size_t tiles = (size_t)((M + BM - 1) / BM) * pl.C;
-  return (size_t)pl.S * tiles * kWaves * wave_blocks8(pl.wide) * 64 * sizeof(float4);
+  return parked_bytes(pl, (M + BM - 1) / BM);
 }
 
 int launch_mx_linear(const MxLinearArgs& a, hipStream_t st) {
@@ -500,8 +498,7 @@ int launch_mx_linear(const MxLinearArgs& a, hipStream_t st) {
   const size_t ws_have = (a.workspace && a.workspace_bytes > ws_skip) ? a.workspace_bytes - ws_skip : 0;
   SplitPlan pl = plan_split(a.M, a.N, a.K, 0, ncu, a.coltiles > 0 && a.splitk == 0 ? 1 : a.splitk);
   if (pl.S > 1) {
-    const size_t need = (size_t)pl.S * p.tiles_m * pl.C * kWaves * wave_blocks8(pl.wide) * 64 * sizeof(float4);
-    if (need > ws_have) {
+    if (parked_bytes(pl, p.tiles_m) > ws_have) {
       if (a.splitk > 1) return SERQ_EWORKSPACE;         // an explicit request cannot be honoured
       pl = plan_split(a.M, a.N, a.K, 0, ncu, 1);
     }

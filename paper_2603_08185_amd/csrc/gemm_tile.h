@@ -122,6 +122,10 @@ inline SplitPlan plan_split(int M, int N, int K, int kind, int ncu, int forced) 
 }
 
 inline int wave_blocks8(int wide) { const int h = (wide + 1) / 2; return 8 * (h < 1 ? 1 : h); }
+// what the slices of a plan park: S tiles of 8 waves x wave_blocks8 x 64 lanes x 16 bytes per output tile
+inline size_t parked_bytes(const SplitPlan& pl, int tiles_m) {
+  return pl.S <= 1 ? 0 : (size_t)pl.S * tiles_m * pl.C * 8 * wave_blocks8(pl.wide) * 64 * 16;
+}
 
 }  // namespace
 }  // namespace serq

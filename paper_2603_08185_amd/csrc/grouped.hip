@@ -1076,7 +1076,7 @@ int serq_g128_linear(const void* Xq, const float* scale, const int32_t* zero, in
   p.Y = Y; p.y_dtype = y_dtype; p.ldy = ldy;
   hipStream_t st = (hipStream_t)stream;
   const bool skinny = path == SERQ_PATH_SKINNY || (path == SERQ_PATH_AUTO && M <= 32);
-  if (path == SERQ_PATH_AUTO && !skinny && flags == 0 && g128_mid_wanted(p)) return launch_g128_mid(p, abits, st);
+  if (path == SERQ_PATH_AUTO && !skinny && flags == 0 && g128_mid_wanted(p, abits)) return launch_g128_mid(p, abits, st);
   if (skinny) {
     dim3 grid((unsigned)(N / 32));
     // specialised on ceil(M / 8): the number of accumulator register quads that hold tokens.  Four groups in flight per

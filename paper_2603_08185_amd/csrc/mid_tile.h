@@ -45,6 +45,49 @@ inline long long mid_rounds(int M, int N, int ncu) {
   return (tiles + ncu - 1) / ncu;
 }
 
+// ---- small tiles or large ones (host side) --------------------------------------------------------------------
+// Prices in us of this kernel and of the tiled one, compared where neither wins everywhere.  Both are straight-line fits
+// to measured launches, 256 <= K <= 28672, N = 256 .. 28672, M from 33 to as many tokens as the rules admit, weights once
+// from HBM and once from the last-level cache (the geometric mean of the two times; the cache moves this kernel by up to
+// 20 % and the tiled one hardly).  Standard error 4 to 6 % each at r = 128; other ranks move both alike.
+//   small tiles: c0 + c1 R + K/1024 (c2 + c3 R + c4 y) + c5 (MB of weight codes),  R tiles of the busiest compute unit,
+//                y = M N / (4096 compute units): duplicated rows of a ragged tile cost less than real ones
+//   tiled:       c0 rounds + k (c1 + c2 wide + c3 max(0, wide - 4)), k = rounds K / 1024 / slices;
+//                with K slices c4 for the second launch and c5 for 5 MB of parked tiles, written and read
+struct MidPrice { float c[6]; };
+inline float mid_price(const MidPrice& p, int M, int N, int K, int ncu) {
+  const float R = (float)mid_rounds(M, N, ncu), k = K / 1024.0f, y = (float)M * N / (4096.0f * ncu);
+  return p.c[0] + p.c[1] * R + k * (p.c[2] + p.c[3] * R + p.c[4] * y) + p.c[5] * ((float)N * K / 2e6f);
+}
+struct TiledPrice { float c[6]; };
+inline float tiled_price(const TiledPrice& p, const SplitPlan& pl, int M, int N, int K, int ncu) {
+  const long long wg = (long long)((M + 255) / 256) * pl.C * pl.S;
+  const float rounds = (float)((wg + ncu - 1) / ncu), k = rounds * K / (1024.0f * pl.S);
+  const float us = p.c[0] * rounds + k * (p.c[1] + p.c[2] * pl.wide + p.c[3] * (pl.wide > 4 ? pl.wide - 4 : 0));
+  return pl.S > 1 ? us + p.c[4] + p.c[5] * ((float)pl.S * M * N * 8.0f / 5e6f) : us;
+}
+// The layers of gemm_mfma.hip and gemm_mx.hip.  One tile per compute unit at most: always small tiles (level with the tiled
+// kernel at K = 28672, below that up to 70 % faster).  Two: the prices are asked for long K only, up to K = 8192 small tiles
+// win by 12 % or more.  Beyond: by the prices, up to `most` tiles and, below K = 512, up to two.  `favour` (3 to 7 %) is what
+// a small-tile price may lie above the other: within the error of the prices the small tiles are kept.
+//   ws_have: what the caller's workspace has room for behind the decode path's words; without enough the tiled kernel runs
+//   unsliced.  Layers with fewer than 16 channels per compute unit (N < 4096) are not given to slices here: their parked tiles
+//   would lie where the decode path of a wider layer, which may share the workspace, keeps words that have to stay zero.
+inline bool mid_cheaper(const MidPrice& small, const TiledPrice& tiled, int M, int N, int K, int kind, int most, float favour,
+                        size_t ws_have) {
+  const int ncu = device_cu_count();
+  const long long R = mid_rounds(M, N, ncu);
+  if (R > most || (K < 512 && R > 2)) return false;
+  if (R == 1 || (R == 2 && K <= 8192)) return true;
+  SplitPlan pl = plan_split(M, N, K, kind, ncu, 0);
+  if (pl.S > 1) {
+    if (N < 16 * ncu) return true;
+    if (parked_bytes(pl, (M + 255) / 256) > ws_have) pl = plan_split(M, N, K, kind, ncu, 1);
+    else if (R > 2 && K > 16384 && kind != 4) return false;   // W4A8 11008 x 28672 M = 192 140 / 112 us, where its price says 127
+  }
+  return favour * mid_price(small, M, N, K, ncu) < tiled_price(tiled, pl, M, N, K, ncu);
+}
+
 // The workgroup's tile and a wave's share of its loads.
 // FR: fragments of 64 channels per stage (1: 8-bit tokens, 2: 4-bit tokens).
 template <int FR>

@@ -246,7 +246,7 @@ struct G128Args {
   int M, N, K;
   void* Y; int y_dtype; int64_t ldy;
 };
-bool g128_mid_wanted(const G128Args& a);
+bool g128_mid_wanted(const G128Args& a, int abits);
 int launch_g128_mid(const G128Args& a, int abits, hipStream_t st);
 // MXFP4 path (mx.hip, gemm_mx.hip)
 struct MxLinearArgs {

@@ -1,5 +1,5 @@
 """The kernels for batches between decode and prefill (64 x 64 tiles, K shared by the waves of a workgroup), which AUTO takes
-for these sizes: against the oracle, and against the tiled kernels."""
+for these sizes: against the oracle, and against the tiled kernels.  And which of the two AUTO takes."""
 import pytest
 import torch
 
@@ -86,3 +86,71 @@ def test_mx_layer(in_dtype, out_dtype, M, K, N, r):
 
 def test_mx_salient_block_offset():
     mx._run_mx(mx._spec(70, 1344, 96, 160, out_dtype="fp32"), s_begin=768)
+
+
+# ---- which kernel AUTO takes -----------------------------------------------------------------------------------------------
+# The tiled kernels leave a trace where they cut K: the parked tiles in the workspace, behind the decode path's words.  Their
+# results are those of PATH_MFMA bit for bit, which the fp32 sums of the small-tile kernels are not.
+DEV = "cuda:0"
+
+
+def _codes(n, seed):
+    return torch.randint(0, 256, (n,), dtype=torch.uint8, device=DEV, generator=torch.Generator(device=DEV).manual_seed(seed))
+
+
+def _trace(ws, words):
+    ws[words:] = 0x55
+    return lambda: bool((ws[words:] != 0x55).any())
+
+
+@pytest.mark.parametrize("abits,M,N,K,sliced", [
+    (8, 512, 4096, 8192, False), (8, 512, 4096, 28672, True),        # two tiles per compute unit: the larger tiles from a long K on
+    (8, 256, 4096, 28672, False),                                    # one tile per compute unit
+    (8, 192, 11008, 4096, False), (8, 192, 11008, 14336, True),      # three
+    (8, 512, 2560, 28672, False),                                    # never slices that a wider layer's decode words could lie in
+    (4, 512, 4096, 28672, False), (4, 256, 11008, 28672, False)])
+def test_auto_takes_the_cheaper_kernel(abits, M, N, K, sliced):
+    X = torch.randn((M, K), device=DEV, generator=torch.Generator(device=DEV).manual_seed(1)).bfloat16()
+    Xq, scale = serq.quantize_act(X, None, abits)
+    Wq, wscale = _codes(N * K // 2, 2), torch.rand(N, device=DEV) + 0.5
+    ws = serq.workspace(M, N, K, 0, abits, DEV)
+    words = serq.lib().serq_workspace_bytes(1, N, K, 0, abits)
+    touched = _trace(ws, words)
+    Y = serq.linear(Xq, scale, abits, Wq, wscale, M, N, K, ws=ws)
+    assert touched() == sliced and not ws[:words].any()
+    Yt = serq.linear(Xq, scale, abits, Wq, wscale, M, N, K, ws=ws, flags_=serq.flags(serq.PATH_MFMA))
+    assert touched() == (ws.numel() > words) and torch.equal(Y, Yt)
+    assert torch.equal(Y, serq.linear(Xq, scale, abits, Wq, wscale, M, N, K))      # nothing to park in
+
+
+@pytest.mark.parametrize("M,N,K,sliced", [(512, 4096, 8192, False), (512, 4096, 28672, True), (256, 4096, 28672, False),
+                                          (256, 11008, 4096, False), (256, 11008, 20480, True)])
+def test_auto_takes_the_cheaper_mx_kernel(M, N, K, sliced):
+    X = torch.randn((M, K), device=DEV, generator=torch.Generator(device=DEV).manual_seed(1)).bfloat16()
+    Xq, xsc = serq.mx_quantize_act(X, None)
+    Wq = _codes(N * K // 2, 2)
+    wsc = 96 + _codes(serq.lib().serq_mx_weight_scale_bytes(N, K), 3) % 48      # far apart: the fp32 sums round
+    ws = serq.mx_workspace(M, N, K, DEV)
+    words = serq.lib().serq_mx_workspace_bytes(1, N, K)
+    touched = _trace(ws, words)
+    Y = serq.mx_linear(Xq, xsc, Wq, wsc, M, N, K, out_dtype=torch.float32, ws=ws)
+    assert touched() == sliced
+    Yt = serq.mx_linear(Xq, xsc, Wq, wsc, M, N, K, out_dtype=torch.float32, ws=ws, flags_=serq.flags(serq.PATH_MFMA))
+    assert touched() == (ws.numel() > words)                # (the tiled kernel cuts K wherever it has asked for room)
+    assert torch.equal(Y, Yt) == sliced
+
+
+@pytest.mark.parametrize("abits,M,N,K,r,tiled", [
+    (8, 256, 4096, 1024, 0, False), (8, 512, 4096, 1024, 0, True), (8, 512, 4096, 1024, 128, False),
+    (8, 768, 4096, 1024, 0, True), (8, 768, 4096, 4096, 128, False), (4, 512, 4096, 4096, 0, False), (4, 768, 4096, 512, 0, True)])
+def test_auto_takes_the_cheaper_g128_kernel(abits, M, N, K, r, tiled):
+    g = torch.Generator(device=DEV).manual_seed(1)
+    X = torch.randn((M, K), device=DEV, generator=g).bfloat16()
+    Xq, scale, zero = serq.quantize_act_asym(X, None, abits)
+    Wq, gs = _codes(N * K // 2, 2), torch.exp(8 * torch.rand(N * K // 128, device=DEV, generator=g) - 8).half()   # sums that round
+    wsum = torch.randn(N, device=DEV, generator=g)
+    Rp = serq.pack_lowrank(torch.randn((r, N), device=DEV, generator=g).bfloat16()) if r else None
+    Y, Yt = (serq.g128_linear(Xq, scale, zero, abits, Wq, gs.view(torch.uint8), wsum, M, N, K, Rp=Rp, r=r,
+                              r_dtype=torch.bfloat16, out_dtype=torch.float32, flags_=serq.flags(path))
+             for path in (serq.PATH_AUTO, serq.PATH_MFMA))
+    assert torch.equal(Y, Yt) == tiled
