@@ -92,7 +92,7 @@ size_t serq_workspace_bytes(int64_t M, int64_t N, int64_t K, int r, int abits);
  * SERQ_PATH_AUTO, whose slices park beyond every word that a decode call uses without SERQ_FLAG_SPLITK; calls that
  * force the tiled kernel or slices on a narrower layer leave scratch where a wider one keeps its words.
  * serq_workspace_bytes does not know the flags: for M > 32 it includes the slices of the tiled kernel also where
- * SERQ_PATH_AUTO takes the small tiles, which use none of it (with 4-bit tokens: everywhere). */
+ * SERQ_PATH_AUTO takes the small tiles, which use none of it (with 4-bit tokens: everywhere up to K = 28672). */
 int serq_workspace_init(void* workspace, size_t workspace_bytes, void* stream);
 
 /*

@@ -159,10 +159,11 @@ __global__ __launch_bounds__(KT) void quantize_act_asym_kernel(const void* __res
 template <int XDT, int ABITS>
 int launch_asym_t(const void* X, const float* s_inv, int64_t M, int K, int64_t ldx, void* Xq, float* scale,
                   int32_t* zero, hipStream_t st) {
-  // as for the symmetric quantiser, but long rows of large batches are better off with 512 threads of 3 or 4 pieces (us,
-  // 256 x 8 / 512 / 1024 threads: K = 11008 M = 100 6.0 / 4.3 / 4.1, M = 4096 37.6 / 32.1 / 37.8)
+  // as for the symmetric quantiser, but long rows of more than 256 tokens are better off with 512 threads of 3 or 4 pieces (us,
+  // 256 / 512 / 1024 threads: K = 11008 M = 128 6.4 / 4.6 / 4.3, M = 512 7.1 / 6.2 / 6.5, M = 4096 28.4 / 26.0 / 30.5; fp32
+  // input, K = 8256 M = 512 5.6 / 5.3 / 5.9)
   const int nchunk = K >> 3;
-  const int threads = nchunk > 1024 && nchunk <= 2048 ? (M <= 512 ? 1024 : 512) : 256;
+  const int threads = nchunk > 1024 && nchunk <= 2048 ? (M <= 256 ? 1024 : 512) : 256;
   const int per = (nchunk + threads - 1) / threads;
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QAA(KT, NC) \

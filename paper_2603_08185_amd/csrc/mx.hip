@@ -280,11 +280,18 @@ __global__ __launch_bounds__(kT) void mx_unpack_act_kernel(const uint32_t* __res
 int launch_mx_quantize_act(const void* X, const void* U, int x_dtype, const float* s_inv, int64_t M, int K, int64_t ldx,
                            int64_t ldu, void* Xq, uint8_t* xsc, hipStream_t st) {
   // A row is walked in rounds of one piece per thread: while the rows do not fill the chip, one round each (two for the
-  // longest), above that the most even of a few.  Measured (us, 256 / 512 / 1024 threads): K = 4096 M = 24 2.8 / 2.5 / -,
-  // K = 11008 M = 24 4.4 / 3.2 / 2.9, M = 256 5.8 / 4.2 / 3.8, M = 4096 27.3 / 27.4 / 29.5 (gated product 46.2 / 42.7 /
-  // 43.0); K = 8192 M = 4096 18.8 / - / 22.2.
+  // longest); above that it depends on how many bytes a thread has in flight.  Measured (us, 256 / 512 / 1024 threads, 16-bit
+  // input; the gated product behind the semicolon): K = 4096 M = 24 2.8 / 2.5 / 2.5; K = 8192 M = 4096 16.0 / 17.1 / 19.3;
+  // K = 11008 M = 24 4.4 / 3.3 / 2.9, M = 256 5.7 / 4.2 / 3.8, M = 1024 7.9 / 6.8 / 7.9; 11.8 / 10.1 / 10.5, M = 4096
+  // 20.7 / 21.4 / 23.8; 46.0 / 42.9 / 43.0; K = 13312 M = 2048 13.2 / 14.3 / 15.3.  fp32 input: K = 14336 M = 513
+  // 7.2 / 7.9 / 7.2, M = 4096 56.9 / 55.1 / 52.6; K = 28672 M = 513 12.1 / 14.0 / 12.9.
   const int nchunk = K >> 3;
-  const int threads = nchunk <= 256 ? 256 : M <= 512 ? (nchunk <= 512 ? 512 : 1024) : nchunk > 1024 ? 512 : 256;
+  const bool f32 = x_dtype == SERQ_F32;
+  const int threads = nchunk <= 256 ? 256
+                      : M <= 512 ? (nchunk <= 512 ? 512 : 1024)
+                      : nchunk <= 1024 ? 256
+                      : f32 && nchunk >= 1792 ? 1024
+                      : !f32 && !U && M > 1024 ? 256 : 512;
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_MXQ_LAUNCH_T(XDT, KT)                                                                                    \
   do {                                                                                                                \

@@ -176,19 +176,26 @@ template <int XDT, int ABITS, bool GLU>
 int launch_t(const void* X, const void* U, const float* s_inv, int64_t M, int K, int64_t ldx, int64_t ldu, void* Xq,
              float* scale, hipStream_t st) {
   const int nchunk = K >> 3;
-  // 256 threads with 1, 2 or 4 pieces each; rows of 1025 .. 2048 pieces would take 8 (most of them past the row) and go to
-  // 1024 threads with 2 instead.  Measured (us, 256 x 8 / 1024 x 2, 8-bit codes; the gated product behind the semicolon):
-  // K = 11008 M = 1 4.4 / 3.1, M = 256 6.3 / 4.6; 7.7 / 5.3, M = 4096 36.6 / 35.3; 51.3 / 45.0; K = 14336 M = 256
-  // 6.9 / 4.9.  Shorter rows gain nothing from more threads (K = 8192 M = 256 4.9 / 4.8, M = 4096 25.0 / 34.6).
-  const int threads = nchunk > 1024 && nchunk <= 2048 ? 1024 : 256;
+  // 256 threads with 1, 2, 4 or 5 pieces each.  Rows of 1025 .. 2048 pieces go to 1024 threads with 2 while the rows do not
+  // fill the chip, to 512 with 3 or 4 below 1024 rows, and beyond that to 1024 again, but for rows of at most 1280 pieces,
+  // where too many of those 2 lie past the row.  Measured (us, 256 / 512 / 1024 threads, 8-bit codes; the gated product behind
+  // the semicolon): K = 8256 M = 256 5.4 / 4.5 / 4.2, M = 2048 12.2 / 13.4 / 14.6; 17.2 / 18.0 / 18.1; K = 11008 M = 1
+  // 4.4 / 3.3 / 3.1, M = 256 6.2 / 4.9 / 4.6; 7.9 / 6.0 / 5.3, M = 513 6.5 / 5.8 / 6.6; 9.4 / 8.0 / 8.9, M = 768
+  // 8.1 / 7.2 / 8.3, M = 1024 9.7 / 9.9 / 9.7, M = 4096 27.5 / 26.9 / 28.8; 48.3 / 46.1 / 44.0; K = 14336 M = 4096
+  // 42.9 / 40.7 / 37.7.  Shorter rows: at K = 8192 256 and 1024 threads are level up to M = 256, beyond that 256 are faster
+  // (M = 4096 20.5 / 29.2).
+  const int threads = nchunk <= 1024 || nchunk > 2048 ? 256 : M <= 512 ? 1024 : M < 1024 ? 512 : nchunk > 1280 ? 1024 : 256;
   const int per = (nchunk + threads - 1) / threads;
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QA_LAUNCH(KT, NC)                                                                                            \
   hipLaunchKernelGGL((quantize_act_kernel<XDT, ABITS, KT, NC, GLU>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, Xq, scale)
   if (threads == 1024) SERQ_QA_LAUNCH(1024, 2);
+  else if (threads == 512 && per <= 3) SERQ_QA_LAUNCH(512, 3);
+  else if (threads == 512) SERQ_QA_LAUNCH(512, 4);
   else if (per <= 1) SERQ_QA_LAUNCH(256, 1);
   else if (per <= 2) SERQ_QA_LAUNCH(256, 2);
   else if (per <= 4) SERQ_QA_LAUNCH(256, 4);
+  else if (per <= 5) SERQ_QA_LAUNCH(256, 5);
   else SERQ_QA_LAUNCH(256, 0);
 #undef SERQ_QA_LAUNCH
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;

@@ -1,5 +1,6 @@
 """The quantisers choose their threads per row by the row length and the number of rows: bit-exact against the oracle on both
-sides of every limit (rows of 1024 / 1032 / 1536 / 1544 / 2048 / 2056 pieces of 16 bytes, batches of 512 and 513 rows)."""
+sides of every limit (rows of 1024 / 1032 / 1280 / 1288 / 1536 / 1544 / 1784 / 1792 / 2048 / 2056 pieces of 8 values, batches
+of 256 / 257, 512 / 513 and 1023 / 1024 / 1025 rows; fp32 input and the gated product have limits of their own)."""
 import numpy as np
 import pytest
 import torch
@@ -11,22 +12,34 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("M", [3, 512, 513])
-@pytest.mark.parametrize("K", [2112, 4096, 4160, 8192, 8256, 12288, 12352, 16384, 16448])
+@pytest.mark.parametrize("M", [3, 256, 257, 512, 513, 1023, 1024, 1025])
+@pytest.mark.parametrize("K", [2112, 4096, 4160, 8192, 8256, 10240, 10304, 12288, 12352, 14272, 14336, 16384, 16448])
 def test_codes_match_the_oracle(M, K):
+    _check(M, K, torch.bfloat16)
+
+
+@pytest.mark.parametrize("M,K", [(3, 14336), (513, 8256), (513, 14272), (513, 14336), (1025, 10240), (600, 16448)])
+def test_codes_match_the_oracle_fp32_input(M, K):
+    _check(M, K, torch.float32)
+
+
+def _check(M, K, dtype):
     g = torch.Generator().manual_seed(M + K)
     X = torch.randn((M, K), generator=g)
     X[:, K - 1] *= 40                                  # the last piece of the row decides the scale
-    X = X.to(torch.bfloat16)
+    X = X.to(dtype)
     s_inv = torch.rand(K, generator=g) + 0.5
     rows = [0, M // 2, M - 1]
     Xo = X[rows].float().numpy()
     Xd, sd = X.to(DEV), s_inv.to(DEV)
+    G = torch.full_like(Xd, 32.0)                      # silu(32) = 32 in fp32: the gated product is 32 X, the same codes
     for abits in (4, 8):
         Xq, sc = serq.quantize_act(Xd, sd, abits)
         c, s = orc.quantize_act(Xo, s_inv.numpy(), abits)
         assert np.array_equal(serq.unpack_act(Xq, abits, M, K).cpu().numpy()[rows], c)
         assert np.array_equal(sc.cpu().numpy()[rows], s)
+        Xg, sg = serq.swiglu_quantize_act(G, Xd, sd, abits)
+        assert torch.equal(Xg, Xq) and torch.equal(sg, 32 * sc)
         Xq, sc, z = serq.quantize_act_asym(Xd, sd, abits)
         c, s, zo = orc.quantize_act_asym(Xo, s_inv.numpy(), abits)
         assert np.array_equal(serq.unpack_act(Xq, abits, M, K).cpu().numpy()[rows], c)
@@ -35,3 +48,6 @@ def test_codes_match_the_oracle(M, K):
     c, e = serq.mx_unpack_act(Xq, xs, M, K)
     co, eo = orc.mx_quantize_act(Xo, s_inv.numpy())
     assert np.array_equal(c.cpu().numpy()[rows], co) and np.array_equal(e.cpu().numpy()[rows], eo)
+    Xg, xg = serq.mx_swiglu_quantize_act(G, Xd, sd)
+    cg, eg = serq.mx_unpack_act(Xg, xg, M, K)
+    assert torch.equal(cg, c) and torch.equal(eg.int(), e.int() + 5)
