@@ -101,10 +101,16 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()          # (ctypes makes the void* from the number)
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
     # torch.cuda.current_stream().cuda_stream without the Stream object built on the way: 0.2 instead of 2.7 us, a
-    # third of what a call costs the host
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    # third of what a call costs the host.  The two names are torch's own; where it has them no longer, the public way.
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _check(fn: str, rc: int):

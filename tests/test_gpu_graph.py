@@ -84,3 +84,9 @@ def test_group128_layer_replays(abits, M):
         X[:, it] += 3.0
 
     _replay_check(step, [Y, Xq, scale, zero], mutate)
+
+
+def test_calls_go_to_the_current_stream():
+    assert serq._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(torch.cuda.Stream()):
+        assert serq._stream() == torch.cuda.current_stream().cuda_stream != torch.cuda.default_stream().cuda_stream

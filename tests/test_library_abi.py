@@ -218,3 +218,14 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(serq, "LIB_PATH", "/nonexistent/libserq.so")
     with pytest.raises(ImportError):
         serq.lib()
+
+
+def test_stream_handle_without_torchs_own_names(monkeypatch):
+    class Stream:
+        cuda_stream = 4711
+
+    monkeypatch.setattr(serq.torch.cuda, "current_stream", lambda: Stream)
+    for name in ("_raw_stream", "_device"):
+        with monkeypatch.context() as m:
+            m.setattr(serq, name, None)
+            assert serq._stream() == 4711
