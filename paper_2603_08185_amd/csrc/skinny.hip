@@ -312,7 +312,8 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu((kG
     for (int ww = 0; ww < kWaves; ++ww) tot_i[q] += *reinterpret_cast<const int*>(lds + (size_t)ww * hregion + 4 * src);
     if (lr_here) {
       // (all waves' words requested before the first is added; a loop over nwl waits for each in turn)
-      int word[kWaves], li = 0;
+      int word[kWaves];
+      uint32_t li = 0;                                    // (unsigned: the sum of 16-bit forms' float bits, unused, may wrap)
       float lf = 0.0f;
 #pragma unroll
       for (int ww = 0; ww < kWaves; ++ww)
@@ -320,10 +321,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu((kG
 #pragma unroll
       for (int ww = 0; ww < kWaves; ++ww) {
         const int v = ww < nwl ? word[ww] : 0;
-        li += v;
+        li += (uint32_t)v;
         lf += __int_as_float(v);
       }
-      tot_l[q] = lr_int ? li : __float_as_int(lf);
+      tot_l[q] = lr_int ? (int)li : __float_as_int(lf);
     }
   }
 
