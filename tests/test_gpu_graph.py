@@ -16,8 +16,10 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("M,which", [(4, "down"), (16, "up"), (300, "up")])
-def test_integer_layer_replays(M, which):
+# (300 tokens: the kernel with small tiles, and the tiled one)
+@pytest.mark.parametrize("M,which,path", [(4, "down", serq.PATH_AUTO), (16, "up", serq.PATH_AUTO), (300, "up", serq.PATH_AUTO),
+                                          (300, "up", serq.PATH_MFMA)])
+def test_integer_layer_replays(M, which, path):
     base = workloads.config3(which, M)
     spec = base.with_(K=1024, N=512 if which == "down" else 1376, r=64)
     L = workloads.make_layer(spec)
@@ -32,7 +34,8 @@ def test_integer_layer_replays(M, which):
 
     def step():
         serq.quantize_act(X, pk.s_inv, spec.abits, Xq=Xq, scale=scale)
-        serq.linear(Xq, scale, spec.abits, pk.Wq, pk.wscale, M, spec.N, spec.K, Rp=Rp, r=spec.r, Y=Y, ws=ws)
+        serq.linear(Xq, scale, spec.abits, pk.Wq, pk.wscale, M, spec.N, spec.K, Rp=Rp, r=spec.r, Y=Y, ws=ws,
+                    flags_=serq.flags(path))
 
     def mutate(it):
         X.copy_(X0 * (1.0 + 0.25 * it))
@@ -41,8 +44,8 @@ def test_integer_layer_replays(M, which):
     _replay_check(step, [Y, Xq, scale], mutate)
 
 
-@pytest.mark.parametrize("M", [8, 300])
-def test_mxfp4_layer_replays(M):
+@pytest.mark.parametrize("M,path", [(8, serq.PATH_AUTO), (300, serq.PATH_AUTO), (300, serq.PATH_MFMA)])
+def test_mxfp4_layer_replays(M, path):
     spec = workloads.config3("up", M).with_(K=1024, N=1376, r=64, abits=4)
     L = workloads.make_layer(spec, want=("X", "s", "W"))
     pk = serq.mx_pack_weights(L["W"].to(DEV), L["s"].to(DEV), spec.r)
@@ -54,7 +57,8 @@ def test_mxfp4_layer_replays(M):
 
     def step():
         serq.mx_quantize_act(X, pk.s_inv, Xq=Xq, xsc=xsc)
-        serq.mx_linear(Xq, xsc, pk.Wq, pk.wsc, M, spec.N, spec.K, Rq=pk.Rq, rsc=pk.rsc, r=spec.r, Y=Y)
+        serq.mx_linear(Xq, xsc, pk.Wq, pk.wsc, M, spec.N, spec.K, Rq=pk.Rq, rsc=pk.rsc, r=spec.r, Y=Y,
+                       flags_=serq.flags(path))
 
     def mutate(it):
         X.copy_(X0 * (1.0 + 0.25 * it))
@@ -63,8 +67,9 @@ def test_mxfp4_layer_replays(M):
     _replay_check(step, [Y, Xq, xsc], mutate)
 
 
-@pytest.mark.parametrize("abits,M", [(4, 8), (8, 16), (8, 300)])
-def test_group128_layer_replays(abits, M):
+@pytest.mark.parametrize("abits,M,path", [(4, 8, serq.PATH_AUTO), (8, 16, serq.PATH_AUTO), (8, 300, serq.PATH_AUTO),
+                                          (8, 300, serq.PATH_MFMA)])
+def test_group128_layer_replays(abits, M, path):
     spec = workloads.config3("up", M).with_(K=1024, N=1376, r=64, abits=abits)
     L = workloads.make_layer(spec, want=("X", "s", "W"))
     pk = serq.g128_pack_weights(L["W"].to(DEV), L["s"].to(DEV), spec.r)
@@ -77,7 +82,8 @@ def test_group128_layer_replays(abits, M):
 
     def step():
         serq.quantize_act_asym(X, pk.s_inv, abits, Xq=Xq, scale=scale, zero=zero)
-        serq.g128_linear(Xq, scale, zero, abits, pk.Wq, pk.gscale, pk.wsum, M, spec.N, spec.K, Rp=pk.Rp, r=spec.r, Y=Y)
+        serq.g128_linear(Xq, scale, zero, abits, pk.Wq, pk.gscale, pk.wsum, M, spec.N, spec.K, Rp=pk.Rp, r=spec.r, Y=Y,
+                         flags_=serq.flags(path))
 
     def mutate(it):
         X.copy_(X0 * (1.0 + 0.25 * it))

@@ -197,10 +197,13 @@ def test_g128_config2_attention_projection():
     _run(workloads.config2(), R_mode="random")
 
 
-@pytest.mark.parametrize("which,M", [("up", 1), ("up", 16), ("down", 1), ("down", 16), ("up", 256), ("down", 256),
-                                     ("up", 4096), ("down", 4096)])
-def test_g128_config3_mlp_pair(which, M):
-    _run(workloads.config3(which, M), R_mode="random")
+@pytest.mark.parametrize("which,M,path", [("up", 1, serq.PATH_AUTO), ("up", 16, serq.PATH_AUTO), ("down", 1, serq.PATH_AUTO),
+                                          ("down", 16, serq.PATH_AUTO), ("up", 256, serq.PATH_AUTO),
+                                          ("down", 256, serq.PATH_AUTO), ("up", 256, serq.PATH_MFMA),
+                                          ("down", 256, serq.PATH_MFMA), ("up", 4096, serq.PATH_AUTO),
+                                          ("down", 4096, serq.PATH_AUTO)])
+def test_g128_config3_mlp_pair(which, M, path):
+    _run(workloads.config3(which, M), R_mode="random", path=path)
 
 
 @pytest.mark.parametrize("M", [1, 4, 32])

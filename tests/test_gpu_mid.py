@@ -11,7 +11,7 @@ from tests import test_gpu_parity as parity
 pytestmark = pytest.mark.gpu
 
 # one token past the decode range, ragged last token tile, one / two / an odd number of channel blocks; K from a single
-# fragment (seven waves idle) over odd fragment counts to rings that wrap
+# fragment (one wave has work) over odd fragment counts to rings that wrap
 SHAPES = [
     (33, 64, 32, 16),
     (64, 192, 64, 0),
@@ -21,6 +21,7 @@ SHAPES = [
     (129, 2560, 1056, 320),
     (333, 6144, 64, 64),
     (70, 8256, 4096, 32),        # half of the compute units and a long K: eight waves for 8-bit tokens
+    (70, 8256, 4096, 208),       # ... and a second chunk of the rank-r term, whose operands replace the first one's
     (400, 1024, 5152, 208),      # three tiles for the busiest compute unit
     (1100, 4096, 96, 32),        # 8-bit token codes beyond 4 MiB: token tiles in bands, 6 + 6 + 6
     (2100, 4096, 96, 32),        # 4-bit ones too: 7 + 7 + 7 + 7 + 5
@@ -51,12 +52,13 @@ def test_salient_block_offset():
         parity._run_layer_q4r(parity._small_spec(abits, 70, 768, 96, 160), s_begin=416)
 
 
-# K: one group (seven waves idle), 9 groups, 33 groups (a ragged last round of the ring)
+# K: one group (one wave has work), 9 groups, 33 groups (a ragged last round of the ring); two tiles per compute unit
+# (workgroups of four waves) with 21 groups, so that their ring comes to its steady state; token tiles in bands
 @pytest.mark.parametrize("abits", [4, 8])
 @pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
 @pytest.mark.parametrize("M,K,N,r", [(33, 128, 32, 16), (65, 1152, 96, 0), (100, 4224, 288, 128), (200, 2560, 160, 144),
                                      (129, 384, 1056, 320), (333, 6144, 64, 64), (400, 1152, 5152, 208),
-                                     (2100, 4096, 96, 32)])
+                                     (300, 2688, 4096, 144), (2100, 4096, 96, 32)])
 def test_g128_layer(abits, in_dtype, out_dtype, M, K, N, r):
     spec = grouped._spec(abits, M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype)
     Y, _, _ = grouped._run(spec, R_mode="residual" if r else "none")

@@ -163,6 +163,7 @@ def _run_mx(spec, rows=None, s_begin=0, with_R=True, coltiles=0, path=serq.PATH_
     return Y, Y64, errs
 
 
+# (the tiled kernel; what AUTO takes for these sizes is tested in test_gpu_mid.py)
 @pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
 @pytest.mark.parametrize("M,K,N,r", [
     (1, 64, 32, 32),        # one fragment, one block
@@ -177,7 +178,7 @@ def _run_mx(spec, rows=None, s_begin=0, with_R=True, coltiles=0, path=serq.PATH_
     (777, 2304, 1056, 96),  # four token tiles (ragged), 33 channel blocks over several column tiles, 9 K tiles
 ])
 def test_mx_layer_small_shapes(in_dtype, out_dtype, M, K, N, r):
-    _run_mx(_spec(M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype))
+    _run_mx(_spec(M, K, N, r, in_dtype=in_dtype, out_dtype=out_dtype), path=serq.PATH_MFMA)
 
 
 @pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32")])
@@ -250,16 +251,18 @@ def test_mx_config4_decode(M):
     _run_mx(workloads.config4(M))
 
 
-def test_mx_layer_compensation_matters_and_can_be_left_out():
+@pytest.mark.parametrize("path", [serq.PATH_AUTO, serq.PATH_MFMA])
+def test_mx_layer_compensation_matters_and_can_be_left_out(path):
     spec = _spec(96, 512, 128, 128, out_dtype="fp32")
-    Y, Y64, _ = _run_mx(spec)
-    Y0, Y064, _ = _run_mx(spec, with_R=False)
+    Y, Y64, _ = _run_mx(spec, path=path)
+    Y0, Y064, _ = _run_mx(spec, with_R=False, path=path)
     assert np.max(np.abs(Y64 - Y064)) > 1e-3 * np.max(np.abs(Y64))
 
 
-def test_mx_layer_salient_block_offset():
-    _run_mx(_spec(70, 1024, 96, 64, out_dtype="fp32"), s_begin=256)
-    _run_mx(_spec(70, 1024, 96, 256, out_dtype="fp32"), s_begin=768)
+@pytest.mark.parametrize("path", [serq.PATH_AUTO, serq.PATH_MFMA])
+def test_mx_layer_salient_block_offset(path):
+    _run_mx(_spec(70, 1024, 96, 64, out_dtype="fp32"), s_begin=256, path=path)
+    _run_mx(_spec(70, 1024, 96, 256, out_dtype="fp32"), s_begin=768, path=path)
 
 
 @pytest.mark.parametrize("coltiles", [1, 3, 5, 9])
@@ -281,13 +284,15 @@ def test_mx_layer_extreme_scales():
     _check_pack(pk, pk_o, N, K, 64)
     Xc_o, Xe_o = orc.mx_quantize_act(X, None)
     Xq, xsc = serq.mx_quantize_act(torch.from_numpy(X).to(DEV), None)
-    Y = serq.mx_linear(Xq, xsc, pk.Wq, pk.wsc, M, N, K, Rq=pk.Rq, rsc=pk.rsc, r=64, out_dtype=torch.float32)
     Y64 = orc.mx_linear(Xc_o, Xe_o, pk_o["Wc"], pk_o["We"], pk_o["Rc"], pk_o["Re"])
-    assert_y_close(Y, Y64, "extreme scales")
-    assert np.all(Y.cpu().numpy()[:, 5] == 0.0)
+    for path in (serq.PATH_AUTO, serq.PATH_MFMA):
+        Y = serq.mx_linear(Xq, xsc, pk.Wq, pk.wsc, M, N, K, Rq=pk.Rq, rsc=pk.rsc, r=64, out_dtype=torch.float32,
+                           flags_=serq.flags(path))
+        assert_y_close(Y, Y64, "extreme scales")
+        assert np.all(Y.cpu().numpy()[:, 5] == 0.0)
 
 
-@pytest.mark.parametrize("M,path", [(8, serq.PATH_SKINNY), (64, serq.PATH_MFMA)])
+@pytest.mark.parametrize("M,path", [(8, serq.PATH_SKINNY), (64, serq.PATH_MFMA), (64, serq.PATH_AUTO)])
 @pytest.mark.parametrize("ex,ew", [(-125, 100), (-110, -16), (100, 20), (-60, 60)])
 def test_mx_layer_ends_of_the_exponent_range(M, path, ex, ew):
     # block exponents at and near both ends of E8M0 (E = 0 .. 2 and E around 225) through the matrix unit
@@ -319,9 +324,10 @@ def test_mx_config3_M4096(which):
     _run_mx(workloads.config3(which, 4096))
 
 
+@pytest.mark.parametrize("path", [serq.PATH_AUTO, serq.PATH_MFMA])
 @pytest.mark.parametrize("which", ["up", "down"])
-def test_mx_config3_M256(which):
-    _run_mx(workloads.config3(which, 256))
+def test_mx_config3_M256(which, path):
+    _run_mx(workloads.config3(which, 256), path=path)
 
 
 def _mx_split_ws(M, N, K, S):
@@ -366,11 +372,12 @@ def test_mx_tiled_kernel_k_slices(out_dtype, M, K, N, r, S):
 
 
 def test_mx_config3_down_M256_sliced_by_the_library():
-    # K = 11008 over 43 tiles of 256 channels, one token tile: the library cuts K when it is given the workspace
+    # K = 11008 over 43 tiles of 256 channels, one token tile: the tiled kernel cuts K when it is given the workspace (the
+    # flags name the kernel, not the slices; which calls AUTO gives to it is tested in test_gpu_mid.py)
     spec = workloads.config3("down", 256)
     assert serq.lib().serq_mx_workspace_bytes(spec.M, spec.N, spec.K) > serq.lib().serq_mx_workspace_bytes(1, spec.N, spec.K)
-    Ya, Y64, _ = _run_mx(spec, ws=True)
-    Yb, _, _ = _run_mx(spec, ws=False)
+    Ya, Y64, _ = _run_mx(spec, ws=True, path=serq.PATH_MFMA)
+    Yb, _, _ = _run_mx(spec, ws=False, path=serq.PATH_MFMA)
     assert np.max(np.abs(f64(Ya) - f64(Yb))) <= 2.0 ** -7 * np.max(np.abs(Y64))
 
 

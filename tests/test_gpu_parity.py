@@ -478,9 +478,10 @@ def test_layer_q4r_salient_block_offset(path):
     _run_layer_q4r(spec, path=path, s_begin=96)
 
 
-@pytest.mark.parametrize("which,M", [("up", 1), ("up", 16), ("down", 1), ("down", 256)])
-def test_config3_q4r(which, M):
-    _run_layer_q4r(workloads.config3(which, M))
+@pytest.mark.parametrize("which,M,path", [("up", 1, serq.PATH_AUTO), ("up", 16, serq.PATH_AUTO), ("down", 1, serq.PATH_AUTO),
+                                          ("down", 256, serq.PATH_AUTO), ("down", 256, serq.PATH_MFMA)])
+def test_config3_q4r(which, M, path):
+    _run_layer_q4r(workloads.config3(which, M), path=path)
 
 
 @pytest.mark.parametrize("which", ["up", "down"])
@@ -507,9 +508,13 @@ def test_config2_attention_projection():
     _run_layer(workloads.config2())
 
 
-@pytest.mark.parametrize("which,M", [("up", 1), ("up", 16), ("down", 1), ("down", 16), ("up", 256), ("down", 256)])
-def test_config3_mlp_pair(which, M):
-    _run_layer(workloads.config3(which, M))
+# (256 tokens: the kernel with small tiles, and the tiled one, which cuts K here by itself)
+@pytest.mark.parametrize("which,M,path", [("up", 1, serq.PATH_AUTO), ("up", 16, serq.PATH_AUTO), ("down", 1, serq.PATH_AUTO),
+                                          ("down", 16, serq.PATH_AUTO), ("up", 256, serq.PATH_AUTO),
+                                          ("down", 256, serq.PATH_AUTO), ("up", 256, serq.PATH_MFMA),
+                                          ("down", 256, serq.PATH_MFMA)])
+def test_config3_mlp_pair(which, M, path):
+    _run_layer(workloads.config3(which, M), path=path)
 
 
 @pytest.mark.parametrize("which", ["up", "down"])
