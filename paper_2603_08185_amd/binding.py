@@ -101,16 +101,22 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()          # (ctypes makes the void* from the number)
 
 
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-_device = getattr(torch._C, "_cuda_getDevice", None)
-
-
-def _stream():
+def _stream_short():
     # torch.cuda.current_stream().cuda_stream without the Stream object built on the way: 0.2 instead of 2.7 us, a
-    # third of what a call costs the host.  The two names are torch's own; where it has them no longer, the public way.
-    if _raw_stream is None or _device is None:
-        return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(_device())
+    # third of what a call costs the host
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _stream_public():
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _pick_stream(names):
+    """The short way stands on two names of torch's own; where it has them no longer, the public way."""
+    return _stream_short if {"_cuda_getCurrentRawStream", "_cuda_getDevice"} <= set(names) else _stream_public
+
+
+_stream = _pick_stream(dir(torch._C))
 
 
 def _check(fn: str, rc: int):

@@ -224,8 +224,8 @@ def test_stream_handle_without_torchs_own_names(monkeypatch):
     class Stream:
         cuda_stream = 4711
 
+    names = ["_cuda_getCurrentRawStream", "_cuda_getDevice"]
+    assert serq._pick_stream(names) is serq._stream_short
     monkeypatch.setattr(serq.torch.cuda, "current_stream", lambda: Stream)
-    for name in ("_raw_stream", "_device"):
-        with monkeypatch.context() as m:
-            m.setattr(serq, name, None)
-            assert serq._stream() == 4711
+    for name in names:
+        assert serq._pick_stream([name])() == 4711
