@@ -13,9 +13,10 @@
  * Conventions for every entry point
  *   - Every data pointer is a DEVICE pointer owned by the caller, 16-byte
  *     aligned.  The library allocates nothing and keeps no state between
- *     calls (the number of compute units is asked of the runtime on every
- *     call); all work is enqueued on `stream` (a hipStream_t passed as
- *     void*, NULL = the default stream) and returns without waiting.
+ *     calls but the built-in scratch of serq_linear_noalloc (the number of
+ *     compute units is asked of the runtime on every call); all work is
+ *     enqueued on `stream` (a hipStream_t passed as void*, NULL = the
+ *     default stream) and returns without waiting.
  *   - Matrices are row-major.  X is [M tokens, K input channels]; W is
  *     [N output channels, K input channels]; R is [r, N]; Y is [M, N].
  *     (The paper writes Y = X.W with W [d_in, d_out]: one of its "weight
@@ -217,7 +218,7 @@ int serq_linear(const void* Xq, const float* scale, int abits,
  * harnesses that forbid hipMalloc.  Same arguments, arithmetic and kernels as serq_linear, minus the
  * workspace: the words in which the K slices of the decode path meet live in a device array inside the
  * library (8 MiB per GPU, held until the process ends), so the call allocates nothing and asks the
- * caller for nothing.  Limit: N <= 32768; beyond it the call returns SERQ_ELIMIT and does nothing.
+ * caller for nothing; the tiled path, which would leave tiles there, runs unsliced.  Limit: N <= 32768; beyond it the call returns SERQ_ELIMIT and does nothing.
  * Results equal serq_linear's with a workspace, bit for bit.
  * Every call on one GPU uses that GPU's one array: calls that overlap in time on the same GPU (two
  * streams, two threads) race; calls on one stream, or otherwise ordered, are fine.  The kernels leave

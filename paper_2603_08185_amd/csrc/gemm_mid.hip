@@ -9,8 +9,8 @@
 // What bounds it: the L2 -> LDS stream.  A step (64 channels of 8-bit tokens) is 6 KiB for 8 MFMAs; with all compute
 // units busy the direct loads bring 70-90 B/ns to each (64 B/clk is the address unit's limit, reached with up to half
 // of the chip).  Fixed costs are about 4.7 us (K = 1024), of which 1.3 us lie between dependent launches.
-// Measured (M = 256, 4096 x 11008, W4A8, r = 128): 20 us, the tiled kernel with 4 K slices and a second launch 30 us;
-// M = 100, 6144 x 4096: 8.7 against 24.0 us.  The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.
+// Measured (M = 256, 4096 x 11008, W4A8, r = 128, graph replay, weights from HBM / the last-level cache): 24 / 22 us, the tiled
+// kernel with 4 K slices and a second launch 32 us; M = 100, 6144 x 4096: 10.4 / 9.3 against 24.4 us.  The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.
 #include "mid_tile.h"
 
 namespace serq {

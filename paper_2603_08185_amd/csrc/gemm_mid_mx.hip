@@ -8,8 +8,8 @@
 // requested before it.  The waves' fp32 tiles are added through LDS in wave order: the same result from run to run.
 //
 // What bounds it: the L2 -> LDS stream (8.5 KiB per 128 channels and wave beside 8 MFMAs), as in gemm_mid.hip.  Measured
-// (M = 200, 4096 x 14336, r = 128): 16 us, the tiled kernel with 4 K slices and a second launch 29 us; the rank-r term
-// costs nothing that shows.
+// (M = 200, 4096 x 14336, r = 128, graph replay): 19.4 us, the tiled kernel with its K slices and second launch 33 us; the rank-r
+// term costs nothing that shows.
 #include "mid_tile.h"
 
 namespace serq {

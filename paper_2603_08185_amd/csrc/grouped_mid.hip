@@ -5,12 +5,12 @@
 // scales.  The four products of an MFMA tile start from zero and the INT32 tile is folded into the wave's fp32 tile
 // while the next tile's products run.  Tokens are the MFMA's row operand and weights its column operand (as in the decode
 // kernel of grouped.hip): a lane holds one channel of each block, so it needs one scale per block and group, not sixteen.
-// The waves' fp32 tiles are added through LDS in wave order (run-to-run identical),
-// each wave finishing half an MFMA tile: zero point, rank-r term on the re-centred codes, token scale.
+// The waves' fp32 tiles are added through LDS in wave order (run-to-run identical), each of 8 waves finishing half an MFMA
+// tile, each of 4 a whole one: zero point, rank-r term on the re-centred codes, token scale.
 //
 // What bounds it: the L2 -> LDS stream, as in gemm_mid.hip, and next to it the vector unit (128 fold operations per wave
-// and group beside 16 products).  Measured (M = 150, 4096 x 11008, W4A4, r = 64): 18 us; the 128 x 128 tiles of the tiled
-// kernel give 64 workgroups there and take 76 us.
+// and group beside 16 products).  Measured (M = 150, 4096 x 11008, W4A4, r = 64, graph replay): 20 us; the 128 x 128 tiles of the
+// tiled kernel give 64 workgroups there, 128 in halves, and take 48 us.
 #include "mid_tile.h"
 
 namespace serq {

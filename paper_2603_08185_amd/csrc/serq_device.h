@@ -199,7 +199,7 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// Number of compute units of the current device, asked on every call (the library keeps no state);
+// Number of compute units of the current device, asked on every call;
 // 256 if the runtime cannot say.
 inline int device_cu_count() {
   int dev = 0, n = 0;
