@@ -6,11 +6,12 @@
 // waves -- integer addition, the same bits as the tiled kernel -- scales it and adds the rank-r term with the matrix unit on
 // top, exactly as the tiled kernel does.
 //
-// What bounds it: the L2 -> LDS stream.  A step (64 channels of 8-bit tokens) is 6 KiB for 8 MFMAs; with all compute
-// units busy the direct loads bring 70-90 B/ns to each (64 B/clk is the address unit's limit, reached with up to half
-// of the chip).  Fixed costs are about 4.7 us (K = 1024), of which 1.3 us lie between dependent launches.
-// Measured (M = 256, 4096 x 11008, W4A8, r = 128, graph replay, weights from HBM / the last-level cache): 24 / 22 us, the tiled
-// kernel with 4 K slices and a second launch 32 us; M = 100, 6144 x 4096: 10.4 / 9.3 against 24.4 us.  The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.
+// What bounds it: with 8-bit tokens at M = 256, N = 4096, K = 11008 the kernel takes 20.2 us (23.2 with 64-byte token rows); the
+// same load stream without products, launch included, 12.6 us (at K = 11264), the matrix unit alone 6.  The rest is the start
+// and the end of a tile and what the two do not overlap.  Fixed costs: 4 us at K = 256, r = 0 in a graph, 1 us more for r = 128.
+// The tiled kernel with 4 K slices and a second launch takes 32 us there; M = 100, 6144 x 4096: 9.3 against 24.4 us.
+// The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.  Rings of twice the depth where a workgroup has
+// a compute unit to itself: 9.3 -> 10.0 us at M = 100, 6144 x 4096 (the first stage lands behind all the others' requests).
 #include "mid_tile.h"
 
 namespace serq {
@@ -29,10 +30,9 @@ struct MidParams {
 
 template <int ABITS, int NW>
 struct Mid {
-  static constexpr int FR = ABITS == 8 ? 1 : 2;
-  static constexpr int STAGE = kMidX + 2 * FR * 1024;   // 6 KiB / 8 KiB
+  static constexpr int STAGE = kMidX + (ABITS == 8 ? 2 : 4) * 1024;   // 6 KiB: half a unit / 8 KiB: a step
   static constexpr int NS = ABITS == 8 ? 3 : 2;
-  static constexpr int NL = 4 + 2 * FR;
+  static constexpr int NL = ABITS == 8 ? 6 : 8;      // direct loads of a stage
   static constexpr int REGION = NS * STAGE;          // LDS of one wave: 18 KiB / 16 KiB
   static constexpr int SH = ABITS == 8 ? 4 : 8;
   // The rank-r term in chunks of 128 ranks.  8 waves: the R fragments that wave w brings lie behind its own partial tile
@@ -52,14 +52,14 @@ struct Mid {
   static_assert(LDS * (8 / NW) <= 160 * 1024, "LDS budget");
 };
 
-template <int FR>
-struct MidOp { u4 w[2][FR], x[2][2]; };              // x: [token block][8-bit: K half, 4-bit: fragment]
+struct MidUnitOp { u4 w[2][2], x[2][4]; };           // w: [channel block][fragment], x: [token block][2 * fragment + K half]
+struct MidStepOp { u4 w[2][2], x[2][2]; };           // x: [token block][fragment]
 
 template <int ABITS, int LRT, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void serq_mid_kernel(const MidParams p) {
   using T = Mid<ABITS, NW>;
-  constexpr int FR = T::FR, NS = T::NS;
+  constexpr int NS = T::NS;
   __shared__ __align__(16) uint8_t lds[T::LDS];
   const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -71,10 +71,11 @@ void serq_mid_kernel(const MidParams p) {
   const int mrows = p.M - m0 < 64 ? p.M - m0 : 64;
   const uint32_t rowbytes = (uint32_t)p.K * ABITS / 8;
 
-  MidLoads<FR> ld;
-  ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
-  const int steps = (ld.KB + FR - 1) / FR;
-  const int nst = steps > w ? (steps - w + NW - 1) / NW : 0;   // steps w, w + NW, ... are this wave's
+  std::conditional_t<ABITS == 8, MidUnits<2, NW>, MidLoads<2>> ld;
+  if constexpr (ABITS == 8) ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, w, l);
+  else ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
+  const int steps = (ld.KB + 1) / 2;
+  const int nst = steps > w ? (steps - w + NW - 1) / NW : 0;   // 4-bit: steps w, w + NW, ... are this wave's
   uint8_t* my = lds + w * T::REGION;
   const uint32_t my_lds = __builtin_amdgcn_readfirstlane(lds_addr(my));
 
@@ -86,43 +87,69 @@ void serq_mid_kernel(const MidParams p) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
 
-  const int xsw = mid_swz(lm);                       // the same for row lm and row 32 + lm
-  auto slot = [&](int t) { return (t % NS) * T::STAGE; };
-  auto read = [&](auto, int t, MidOp<FR>& o) {
-    const uint8_t* s = my + slot(t);
+  if constexpr (ABITS == 8) {
+    const int xsw = mid_swz128(lm);
+    auto slot = [&](int h, int u) { return (2 * u + h) % NS * T::STAGE; };
+    auto read = [&](auto whole_c, auto h_c, int u, MidUnitOp& o) {
+      constexpr int H = decltype(h_c)::value;
+      const uint8_t* s = my + slot(H, u);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+      for (int f = 0; f < 2; ++f) o.w[H][f] = *(const u4*)(s + kMidX + f * 1024 + l * 16);
 #pragma unroll
-      for (int f = 0; f < FR; ++f) o.w[i][f] = *(const u4*)(s + kMidX + (i * FR + f) * 1024 + l * 16);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int c = ABITS == 8 ? 2 * g + h : 2 * h + g;
-        o.x[j][h] = *(const u4*)(s + (32 * j + lm) * 64 + 16 * (c ^ xsw));
+      for (int q = 0; q < 4; ++q) {
+        const int c = 4 * (q >> 1) + 2 * g + (q & 1);
+        o.x[H][q] = *(const u4*)(s + lm * 128 + 16 * (c ^ xsw));
       }
-    if (FR == 2 && ld.KB - (w + NW * t) * FR < FR) {   // no second fragment: zero weights
+      if constexpr (!decltype(whole_c)::value) o.w[H][1] &= 1 < ld.frags(u) ? ~0u : 0u;   // no second fragment: zero weights
+    };
+    // group k of half h: token block k % 2 and channel block k / 2 of fragment h
+    auto product = [&](auto h_c, const MidUnitOp& o, int k) {
+      const int j = k & 1, i = (k >> 1) & 1, f = decltype(h_c)::value;
+      v4i a0, a1, b0, b1;
+      unpack_frag(o.w[i][f], a0, a1);
+      b0 = as_v4i(o.x[j][2 * f]);
+      b1 = as_v4i(o.x[j][2 * f + 1]);
+      acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
+    };
+    mid_unit_loop<NS, T::NL, T::NL, 4, MidUnitOp>(
+        ld.nu, ld.brief(),
+        [&](auto whole_c, auto h_c, int u, int k) {
+          constexpr int H = decltype(h_c)::value;
+          ld.template issue_one<decltype(whole_c)::value>(H, u, my_lds + slot(H, u), k);
+        },
+        read, product, []() {});
+  } else {
+    const int xsw = mid_swz(lm);                       // the same for row lm and row 32 + lm
+    auto slot = [&](int t) { return (t % NS) * T::STAGE; };
+    auto read = [&](auto, int t, MidStepOp& o) {
+      const uint8_t* s = my + slot(t);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) o.w[i][FR - 1] = u4{0u, 0u, 0u, 0u};
-    }
-  };
-  // group k: token block k % 2, channel block k / 2 % 2 of fragment k / 4
-  auto product = [&](auto, const MidOp<FR>& o, int k) {
-    const int j = k & 1, i = (k >> 1) & 1, f = k >> 2;
-    v4i a0, a1, b0, b1;
-    unpack_frag(o.w[i][f], a0, a1);
-    if constexpr (ABITS == 8) {
-      b0 = as_v4i(o.x[j][0]);
-      b1 = as_v4i(o.x[j][1]);
-    } else {
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) o.w[i][f] = *(const u4*)(s + kMidX + (i * 2 + f) * 1024 + l * 16);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) o.x[j][f] = *(const u4*)(s + (32 * j + lm) * 64 + 16 * ((2 * f + g) ^ xsw));
+      if (ld.KB - (w + NW * t) * 2 < 2) {               // no second fragment: zero weights
+#pragma unroll
+        for (int i = 0; i < 2; ++i) o.w[i][1] = u4{0u, 0u, 0u, 0u};
+      }
+    };
+    // group k: token block k % 2, channel block k / 2 % 2 of fragment k / 4
+    auto product = [&](auto, const MidStepOp& o, int k) {
+      const int j = k & 1, i = (k >> 1) & 1, f = k >> 2;
+      v4i a0, a1, b0, b1;
+      unpack_frag(o.w[i][f], a0, a1);
       unpack_frag(o.x[j][f], b0, b1);
-    }
-    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[i][j], 0, 0, 0);
-    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
-  };
-  mid_loop<NS, T::NL, T::NL, 4 * FR, MidOp<FR>>(
-      nst, [&](int t) { ld.issue(w + NW * t, my_lds + slot(t)); },
-      [&](int t, int k) { ld.issue_one(w + NW * t, my_lds + slot(t), k); }, read, product);
+      acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
+    };
+    mid_loop<NS, T::NL, T::NL, 8, MidStepOp>(
+        nst, [&](int t) { ld.issue(w + NW * t, my_lds + slot(t)); },
+        [&](int t, int k) { ld.issue_one(w + NW * t, my_lds + slot(t), k); }, read, product);
+  }
 
   // ---- what the end of the tile needs from memory, requested before the waves meet ------------------------------
   // 8 waves: wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j; 4 waves: all of tile w = 2*i + j
@@ -347,7 +374,7 @@ int launch_mid(const LinearArgs& a, hipStream_t st) {
   // Workgroups of 4 waves, two of which share a compute unit: one's start and end run beside the other's main loop, and
   // fewer partial tiles meet.  Only where there is at most one tile per compute unit (and one for most), K is long
   // and the stages are the small ones of 8-bit tokens, 8 waves keep more loads in flight.  Measured (us, 8 / 4 waves, W4A8
-  // r = 128, N x K): 4096 x 4096 M = 100 9.4 / 8.6, M = 333 17.0 / 14.0; 4096 x 8192 M = 100 12.8 / 11.6, M = 256
+  // r = 128, N x K; 64-byte token rows then): 4096 x 4096 M = 100 9.4 / 8.6, M = 333 17.0 / 14.0; 4096 x 8192 M = 100 12.8 / 11.6, M = 256
   // 14.8 / 14.8; 4096 x 11008 M = 40 15.9 / 14.8, M = 100 16.7 / 17.7, M = 256 19.9 / 21.1, M = 333 36.1 / 30.1; W4A4
   // 4096 x 11008 M = 100 13.8 / 14.0, M = 256 16.2 / 15.3, M = 333 27.7 / 23.2.
   const int ncu = device_cu_count();

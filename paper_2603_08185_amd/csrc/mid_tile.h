@@ -9,8 +9,21 @@
 // waits for its own loads only, and the other wave of its SIMD works meanwhile.
 //
 // A wave's loads run through a ring of stages in its own LDS region, filled by direct global -> LDS loads counted
-// by hand.  A stage holds 64 token rows of 64 bytes and the weight fragments of two channel blocks for the same
-// channels; steps are dealt round-robin, so that the waves read neighbouring pieces of the same rows.
+// by hand.  There are two ways to cut them:
+//   steps (4-bit integer tokens): a stage holds 64 token rows of 64 bytes and the weight fragments of two channel blocks for
+//     the same channels; steps are dealt round-robin, so that the waves read neighbouring pieces of the same rows;
+//   units (8-bit tokens, MXFP4): 128 bytes of the token rows, in two stages.  L2 hands out whole 128-byte lines: measured from
+//     L2, all compute units at once, pieces of 64 bytes come at 17 TB/s, of 128 bytes at 35 TB/s, which is the address
+//     units' 64 B/clk.  Stage h holds the 32 rows of token block h and the fragments of weight block h, so it is no larger
+//     than a step, and the operands of a unit are complete once both have been read to registers.
+// Units need a whole unit in registers before the first product and the next one behind it: 96 operand registers at the peak,
+// and a pipeline that fills later.  Measured (us, steps / units, r = 128, N x K, the layer alone, weights from HBM):
+//   W4A8    4096 x 11008 M = 256 23.2 / 20.2;  4096 x 4096 M = 256 9.5 / 9.3, M = 333 13.4 / 13.2;  6144 x 4096 M = 100
+//           8.9 / 9.3, both launches of the layer (the quantiser in front of it) 12.5 / 12.2
+//   W4A8, group scales  4096 x 11008 M = 256 28.2 / 23.8;  4096 x 4096 M = 150 12.1 / 11.4, M = 400 19.2 / 17.7
+//   MXFP4   4096 x 14336 M = 200 19.5 / 18.4;  4096 x 4096 M = 200 7.7 / 7.4, M = 500 12.1 / 11.5;  4096 x 1024 M = 200 4.5 / 4.7
+//   W4A4    4096 x 14336 M = 333 31.2 / 30.4, but 4096 x 4096 12.6 / 13.3 (few, large units), and with group scales, whose
+//           second accumulators leave too few registers, 4096 x 11008 M = 150 20.1 / 25.2: 4-bit integer tokens keep steps
 #ifndef SERQ_MID_TILE_H_
 #define SERQ_MID_TILE_H_
 #include <type_traits>
@@ -20,12 +33,14 @@
 namespace serq {
 namespace {
 
-constexpr int kMidX = 64 * 64;                       // token bytes of a stage
+constexpr int kMidX = 64 * 64;                       // token bytes of a stage: 64 rows of 64 bytes or 32 of 128
 constexpr int kMidPart = 4 * 4 * 64 * 16;            // a wave's partial tile: [tile 2*i + j][register quad][lane][16 B]
 
 // A 64-byte row is a quarter of the 256 bytes that the 64 banks serve at once: rows r .. r+3 take the quarters in
 // turn, and the pieces of rows 4 apart are spread by the xor.
 __device__ __forceinline__ int mid_swz(int row) { return (row >> 2) & 3; }
+// The same for rows of 128 bytes.
+__device__ __forceinline__ int mid_swz128(int row) { return (row >> 1) & 7; }
 
 // Token tiles per band of the tile order (map_block).  All of them, while the token codes fit the 4 MiB of an XCD's L2: then
 // every XCD reads its own weight panels and no others.  Beyond that, bands of up to 8: the tiles in flight on an XCD, 32 or
@@ -49,7 +64,8 @@ inline long long mid_rounds(int M, int N, int ncu) {
 // Prices in us of this kernel and of the tiled one, compared where neither wins everywhere.  Both are straight-line fits
 // to measured launches, 256 <= K <= 28672, N = 256 .. 28672, M from 33 to as many tokens as the rules admit, weights once
 // from HBM and once from the last-level cache (the geometric mean of the two times; the cache moves this kernel by up to
-// 20 % and the tiled one hardly).  Standard error 4 to 6 % each at r = 128; other ranks move both alike.
+// 20 % and the tiled one hardly).  Standard error 4 to 6 % each at r = 128; other ranks move both alike.  (Measured with 64-byte
+// token rows throughout: where K is long the units are up to 15 % cheaper than their price says.)
 //   small tiles: c0 + c1 R + K/1024 (c2 + c3 R + c4 y) + c5 (MB of weight codes),  R tiles of the busiest compute unit,
 //                y = M N / (4096 compute units): duplicated rows of a ragged tile cost less than real ones
 //   tiled:       c0 rounds + k (c1 + c2 wide + c3 max(0, wide - 4)), k = rounds K / 1024 / slices;
@@ -88,6 +104,7 @@ inline bool mid_cheaper(const MidPrice& small, const TiledPrice& tiled, int M, i
   return favour * mid_price(small, M, N, K, ncu) < tiled_price(tiled, pl, M, N, K, ncu);
 }
 
+// ---- steps ----------------------------------------------------------------------------------------------------
 // The workgroup's tile and a wave's share of its loads.
 // FR: fragments of 64 channels per stage (1: 8-bit tokens, 2: 4-bit tokens).
 template <int FR>
@@ -201,6 +218,192 @@ __device__ __forceinline__ void mid_loop(int nst, const Start& start, const Fill
     half(std::false_type{}, Even{}, A, B);
     if (t < nst) half(std::false_type{}, Odd{}, B, A);
   }
+}
+
+// ---- units ----------------------------------------------------------------------------------------------------
+// The workgroup's tile and a wave's share of its loads.
+// FU: fragments of 64 channels per unit (2: 8-bit tokens, 4: 4-bit tokens).
+// Units w, w + NW, ... are wave w's, as far as they go round; the fragments left over are dealt out in pieces of half a unit
+// if that is enough (SPLIT), else of a unit, one to a wave: its last unit, with nf of FU fragments.
+template <int FU, int NW, bool SPLIT = true>
+struct MidUnits {
+  static constexpr int PPF = 8 / FU;                 // 16-byte pieces of a token row per fragment
+  const uint8_t* xbase; const uint8_t* wbase;        // first token row / first weight fragment of the tile
+  uint32_t xv[2][4];                                 // this lane's token pieces: row offset + piece
+  uint32_t wl;
+  size_t wstep1;                                     // from the fragments of block 0 to those of block 1 (0: there is none)
+  int KB;                                            // fragments per channel block
+  int w, nfull, nu, nf, rest;                        // whole units, units, fragments of a last one and the first of them
+
+  __device__ __forceinline__ void init(const uint8_t* Xq, const u4* Wq, int K, uint32_t rowbytes, int m0, int mrows, int nb0,
+                                       int nbt, int wave, int l) {
+    KB = K >> 6;
+    w = wave;
+    nfull = KB / (FU * NW);
+    const int left = KB - nfull * (FU * NW);
+    const int piece = SPLIT && left <= FU / 2 * NW ? FU / 2 : FU;
+    rest = nfull * (FU * NW) + w * piece;
+    nf = KB - rest < piece ? KB - rest : piece;
+    nf = nf < 0 ? 0 : nf;
+    nu = nfull + (nf > 0 ? 1 : 0);
+    xbase = Xq + (size_t)m0 * rowbytes;
+    wbase = (const uint8_t*)Wq + (size_t)nb0 * KB * 1024;
+    wstep1 = nbt > 1 ? (size_t)KB * 1024 : 0;
+    wl = (uint32_t)l * 16u;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {                  // load k of a half: its rows 8*k .. 8*k + 7
+        int row = 32 * h + 8 * k + (l >> 3);
+        row = row < mrows ? row : mrows - 1;         // rows past M: duplicates, never stored
+        xv[h][k] = (uint32_t)row * rowbytes + 16u * xpiece(l, k);
+      }
+  }
+  static __device__ __forceinline__ int xpiece(int l, int k) { return (l & 7) ^ mid_swz128(8 * k + (l >> 3)); }
+  __device__ __forceinline__ bool brief() const { return nf > 0 && nf <= FU / 2; }
+  __device__ __forceinline__ int frags(int u) const { return u < nfull ? FU : nf; }
+  __device__ __forceinline__ int first(int u) const { return u < nfull ? (w + NW * u) * FU : rest; }
+  // direct load k (of 4 + FU) of half h of unit u into the stage at LDS address `st`; WHOLE: the unit has all its
+  // fragments.  What a unit does not have is replaced by a piece or fragment that it has (in bounds, multiplied by zeros).
+  template <bool WHOLE>
+  __device__ __forceinline__ void issue_one(int h, int u, uint32_t st, int k) const {
+    const int f0 = WHOLE ? (w + NW * u) * FU : first(u);
+    const int have = WHOLE ? FU : frags(u);          // (selected as a number: no control flow around the load)
+    if (k < 4) {
+      uint32_t v = xv[h][k];
+      if constexpr (!WHOLE) {
+        int l = (int)(wl >> 4);
+        asm volatile("" : "+v"(l));                  // computed here, not carried through the main loop
+        const int c = xpiece(l, k);
+        v -= c < have * PPF ? 0u : 16u * c;
+      }
+      dma16(xbase + (size_t)f0 * (16 * PPF), v, st + 1024u * k);
+    } else {
+      const int f = WHOLE ? k - 4 : __builtin_amdgcn_readfirstlane(k - 4 < have ? k - 4 : have - 1);
+      dma16(wbase + (size_t)(f0 + f) * 1024 + (h ? wstep1 : 0), wl, st + 1024u * k);
+    }
+  }
+};
+
+// all but the youngest N vector-memory operations of this wave have completed
+template <int N>
+__device__ __forceinline__ void mid_landed() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+
+// The main loop over a wave's nu units.  Stage t of the ring is half t % 2 of unit t / 2.  The operands of a half
+// are copied to registers one unit ahead, which frees its slot: the slot is refilled, NS stages further, between the
+// products of the current unit.  (A direct load blocks the wave while the address unit is busy with the other waves'
+// loads; between two products that costs nothing.)
+//   fill(whole, h, u, k)  direct load k of half h of unit u into its slot
+//   read(whole, h, u, op) half h of the operands of unit u, from LDS
+//   product(h, op, k)     the k-th of NP groups of products of the h-th half of the fragments
+//   last()                before the products of the last unit: the place to request what the tile's end needs
+// h, whole: compile-time constants; whole: the unit has all its fragments (false: it is the last one and may lack some;
+// `brief`: it has none in its second half).  Half h takes NLh direct loads.
+// Loads requested before the loop are older than its own, so they do not disturb its counting.
+//
+// Everything that depends on how many units are left is decided at compile time: the units behind the steady state are
+// written out one by one.  Control flow between the products lets the compiler sink products and widened codes below it,
+// which keeps the operands of several units alive (up to 50 registers more).
+template <int NS, int NL0, int NL1, int NP, class Op, class Fill, class Read, class Product, class Last>
+__device__ __forceinline__ void mid_unit_loop(int nu, bool brief, const Fill& fill, const Read& read, const Product& product,
+                                         const Last& last) {
+  static_assert(NS == 2 || NS == 3, "waits");
+  using H0 = std::integral_constant<int, 0>;
+  using H1 = std::integral_constant<int, 1>;
+  constexpr int D = (NS + 1) / 2;                    // units between the current one and the one requested, less 1
+  if (nu == 0) {
+    last();
+    return;
+  }
+  // a stage of half H has landed, BEHIND of the ring's stages are under way behind it
+  auto landed = [&](auto h_c, auto behind_c) {
+    constexpr int H = decltype(h_c)::value, BEHIND = decltype(behind_c)::value < NS - 1 ? decltype(behind_c)::value : NS - 1;
+    mid_landed<BEHIND >= 2 ? NL0 + NL1 : BEHIND == 1 ? (H ? NL0 : NL1) : 0>();
+  };
+  auto start = [&](auto h_c, int u) {                // a whole stage
+    constexpr int H = decltype(h_c)::value;
+#pragma unroll
+    for (int k = 0; k < (H ? NL1 : NL0); ++k) fill(std::false_type{}, h_c, u, k);
+  };
+  start(H0{}, 0);
+  start(H1{}, 0);
+  if (NS == 3 && nu > 1) start(H0{}, 1);
+  auto first = [&](Op& op) {
+    using Two = std::integral_constant<int, 2>;
+    if (nu > 1) landed(H0{}, Two{}); else landed(H0{}, H1{});
+    read(std::false_type{}, H0{}, 0, op);
+    mid_reads_done();
+    if (nu > 1) start(std::integral_constant<int, NS & 1>{}, 1);
+    if (nu > 1) landed(H1{}, Two{}); else landed(H1{}, H0{});
+    read(std::false_type{}, H1{}, 0, op);
+    mid_reads_done();
+    if (nu > D) start(std::integral_constant<int, (NS + 1) & 1>{}, D);
+  };
+  int u = 0;
+  // unit u, with LEFT units behind it; LEFT > D + 1 stands for any such number
+  auto unit = [&](auto left_c, Op& cur, Op& nxt) {
+    constexpr int LEFT = decltype(left_c)::value;
+    // two branches that begin with the same products: the compiler would hoist those (and keep their results apart)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (auto& v : cur.w[i]) asm volatile("" : "+v"(v));
+#pragma unroll
+      for (auto& v : cur.x[i]) asm volatile("" : "+v"(v));
+    }
+    auto half = [&](auto h_c) {
+      constexpr int H = decltype(h_c)::value;
+      constexpr int HR = (H + NS) & 1;                // the stage requested here: half HR of unit u + AHEAD
+      constexpr int AHEAD = 1 + (H + NS) / 2;
+      constexpr int NLR = AHEAD > LEFT ? 0 : HR ? NL1 : NL0;
+      using whole_next = std::integral_constant<bool, (LEFT > 1)>;
+      using whole_req = std::integral_constant<bool, (LEFT > AHEAD)>;
+      if constexpr (LEFT > 0) {
+        landed(h_c, std::integral_constant<int, 2 * LEFT - 1 - H>{});
+        read(whole_next{}, h_c, u + 1, nxt);
+      } else if constexpr (H == 0) {
+        last();
+      }
+      fence();
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        product(h_c, cur, k);
+        if (LEFT > 0 && k == 0) mid_reads_done();
+#pragma unroll
+        for (int d = 0; d < NLR; ++d)
+          if (d * (NP - 1) / NLR == k) fill(whole_req{}, std::integral_constant<int, HR>{}, u + AHEAD, d);
+        fence();
+      }
+    };
+    half(H0{});
+    if (LEFT > 0 || !brief) half(H1{});
+    ++u;
+  };
+  using Any = std::integral_constant<int, D + 2>;
+  using L3 = std::integral_constant<int, 3>;
+  using L2 = std::integral_constant<int, 2>;
+  Op A, B;
+  if (nu & 1) {                                      // an even number of units behind the first
+    first(A);
+  } else {
+    first(B);
+    if (nu == 2) unit(H1{}, B, A);
+    else if (NS == 3 && nu == 4) unit(L3{}, B, A);
+    else unit(Any{}, B, A);
+  }
+  while (nu - u > 2 * D + 1) {
+    unit(Any{}, A, B);
+    unit(Any{}, B, A);
+  }
+  if (NS == 3 && nu - u > 3) {
+    unit(Any{}, A, B);
+    unit(L3{}, B, A);
+  }
+  if (nu - u > 1) {
+    unit(L2{}, A, B);
+    unit(H1{}, B, A);
+  }
+  unit(H0{}, A, B);
 }
 
 // Rows of 64 16-bit results in LDS (128 bytes), 16-byte piece pc of row r at piece pc ^ (r & 7): four consecutive channels

@@ -47,6 +47,16 @@ def test_integer_layer_q4r(abits, out_dtype, M, K, N, r):
     parity._run_layer_q4r(parity._small_spec(abits, M, K, N, r, in_dtype="fp16", out_dtype=out_dtype))
 
 
+# 8-bit tokens, four waves, 512 channels a round: 1 to 7 units per wave (both parities, every length of the loop's end), last
+# units of one fragment and of two, waves with and without one
+@pytest.mark.parametrize("K", [320, 512, 1024, 1600, 2048, 2624, 2880, 3072, 3584])
+def test_integer_units(K):
+    spec = parity._small_spec(8, 45, K, 96, 32, in_dtype="fp16", out_dtype="fp32")
+    Y, _, _ = parity._run_layer(spec, R_mode="random")
+    Yt, _, _ = parity._run_layer(spec, R_mode="random", path=serq.PATH_MFMA, check_pack=False)
+    assert torch.equal(Y, Yt)
+
+
 def test_salient_block_offset():
     for abits in (4, 8):
         parity._run_layer_q4r(parity._small_spec(abits, 70, 768, 96, 160), s_begin=416)
