@@ -2,14 +2,16 @@
 // sharing K (mid_tile.h says why).
 //   Y[m,n] = sum_k X^[m,k] W^[n,k] + sum_{j<r} X^[m,s_begin+j] R^[n,j]
 //
-// A wave takes whole 256-channel scale tiles: two stages of 128 channels (two fragments of two channel blocks), the
-// scales of the tile with the first.  A 16-byte piece from LDS is an operand of the block-scaled MFMA as it is.  The
-// compensation fragments (64 ranks each) are dealt to the waves one by one after the main loop; their operands are
-// requested before it.  The waves' fp32 tiles are added through LDS in wave order: the same result from run to run.
+// A wave's units are the 256-channel scale tiles (what is left over is dealt in halves of them), the scales of the tile
+// with the first half.  A 16-byte piece from LDS is an operand of the block-scaled MFMA as it is.  The
+// compensation fragments (64 ranks each) are dealt to the waves one by one after the main loop; the first one's operands
+// are requested in front of the last unit.  The waves' fp32 tiles are added through LDS in wave order: the same result
+// from run to run.
 //
-// What bounds it: the L2 -> LDS stream (8.5 KiB per 128 channels and wave beside 8 MFMAs), as in gemm_mid.hip.  Measured
-// (M = 200, 4096 x 14336, r = 128, graph replay): 19.4 us, the tiled kernel with its K slices and second launch 33 us; the rank-r
-// term costs nothing that shows.
+// What bounds it: the load stream and how far the products overlap it, as in gemm_mid.hip.  Measured (M = 200, 4096 x 14336,
+// r = 128, graph replay): 18.4 us (19.5 with 64-byte token rows; with the quantiser of a gated product in front of it
+// 20.7 -> 18.3 for both launches), the tiled kernel with its K slices and second launch 33 us; M = 500, 4096 x 4096
+// 12.1 -> 11.5 us, M = 200, K = 1024 4.5 -> 4.7 us.  The rank-r term costs nothing that shows.
 #include "mid_tile.h"
 
 namespace serq {
@@ -24,8 +26,8 @@ struct MxMidParams {
   int tiles_m, tiles_n, band;
 };
 
-constexpr int FR = 2;
-constexpr int STAGE = kMidX + 2 * FR * 1024;         // 8 KiB
+constexpr int FU = 4;                                // fragments of a unit: a 256-channel scale tile
+constexpr int STAGE = kMidX + FU * 1024;             // 8 KiB
 constexpr int NW = 4;                                // waves: two workgroups share a compute unit
 constexpr int NS = 2;
 constexpr int WS_OFF = NS * STAGE;                   // weight scales of a tile: 2 blocks x 64 dwords
@@ -33,7 +35,7 @@ constexpr int XS_OFF = WS_OFF + 512;                 // token scales of a tile: 
 constexpr int REGION = XS_OFF + 512;
 static_assert(REGION >= kMidPart, "a partial tile fits the ring it replaces");
 
-struct MxMidOp { u4 w[2][FR], x[2][FR]; };
+struct MxMidOp { u4 w[2][FU], x[2][FU]; uint32_t ws[2], xs[2]; };   // ws, xs: byte c is the scale of fragment c
 
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void serq_mx_mid_kernel(const MxMidParams p) {
@@ -49,18 +51,15 @@ void serq_mx_mid_kernel(const MxMidParams p) {
   const uint32_t rowbytes = (uint32_t)p.K >> 1;
   const size_t Mp = (size_t)((p.M + 1) & ~1);          // rows of a tile of the token-scale array
 
-  MidLoads<FR> ld;
-  ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
-  const int KB = ld.KB, T = (KB + 3) >> 2;             // fragments, scale tiles
-  const int nt = T > w ? (T - w + NW - 1) / NW : 0;   // tiles w, w + NW, ... are this wave's
-  // stages: two per tile, but for a last tile of one or two fragments
-  const bool short_last = nt > 0 && KB - 4 * (w + NW * (nt - 1)) <= 2;
-  const int nst = 2 * nt - (short_last ? 1 : 0);
+  MidUnits<FU, NW> ld;
+  ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, w, l);
+  const int T = (ld.KB + 3) >> 2;                      // scale tiles
   uint8_t* my = lds + w * REGION;
   const uint32_t my_lds = __builtin_amdgcn_readfirstlane(lds_addr(my));
   const uint32_t xsel = g ? 0x07050301u : 0x06040200u;   // bytes g, 2+g, 4+g, 6+g of a token's 8 scales
 
-  // ---- the first compensation fragment of this wave, requested before everything else (oldest loads) ----------------
+  // ---- the first compensation fragment of this wave, requested in front of its last unit (when no load of the ring is
+  // waited for any more)
   const int LF = (p.r + 63) >> 6, LT = (LF + 3) >> 2;   // fragments and scale tiles of the compensation matrix per block
   u4 rq[2], rx[2];
   uint32_t rs[2], rxs[2];
@@ -79,7 +78,6 @@ void serq_mx_mid_kernel(const MxMidParams p) {
       rxs[j] = __builtin_amdgcn_perm(e.y, e.x, xsel) >> (8 * (jf & 3));
     }
   };
-  if (w < LF) lr_fetch(w);
 
   // ---- main loop ------------------------------------------------------------------------------------------------
   v16f acc[2][2];
@@ -89,82 +87,66 @@ void serq_mx_mid_kernel(const MxMidParams p) {
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-  const int xsw = mid_swz(lm);
-  // scales of a tile: lanes 0..15 / 16..31 bring those of weight block 0 / 1, lanes 0..31 those of two token rows each
-  const uint32_t wsv = (uint32_t)(((l >> 4) & 1) && nbt > 1 ? T * 256 : 0) + (l & 15) * 16;
+  const int xsw = mid_swz128(lm);
+  // scales of a tile, in one load: lanes 0..15 / 16..31 bring those of weight block 0 / 1, lanes 32..63 those of two token rows
+  // each
   const int rp = 2 * (l & 31) < mrows ? l & 31 : (mrows - 1) >> 1;
-  auto tile = [&](int t) { return w + NW * (t >> 1); };
-  auto fill = [&](int t, int k) {
-    const int u = tile(t);
-    if (k < 8) ld.issue_one(2 * u + (t & 1), my_lds + (t & 1) * STAGE, k);
-    else if (l < 32) {
-      if (k == 8) dma16(p.wsc + ((size_t)nb0 * T + u) * 256, wsv, my_lds + WS_OFF);
-      else dma16(p.xsc + ((size_t)u * Mp + m0) * 8, (uint32_t)rp * 16u, my_lds + XS_OFF);
+  const uint8_t* scsrc = l < 32 ? p.wsc + ((size_t)nb0 * T + (l >= 16 && nbt > 1 ? T : 0)) * 256 + (l & 15) * 16
+                                : p.xsc + (size_t)m0 * 8 + rp * 16;
+  const uint64_t scstep = l < 32 ? 256 : Mp * 8;       // from one tile's to the next one's
+  auto fill = [&](auto whole_c, auto h_c, int u, int k) {
+    constexpr int H = decltype(h_c)::value;
+    if (k < 8) {
+      ld.template issue_one<decltype(whole_c)::value>(H, u, my_lds + H * STAGE, k);
+    } else {
+      const int tile = (decltype(whole_c)::value ? FU * (w + NW * u) : ld.first(u)) >> 2;
+      dma16_at(scsrc + (uint64_t)tile * scstep, my_lds + WS_OFF);   // WS_OFF + 512 = XS_OFF
     }
   };
-  uint32_t ws[2], xs[2], wsn[2], xsn[2];               // scales of the tile being multiplied / read ahead
-  auto read = [&](auto par, int t, MxMidOp& o) {
-    const uint8_t* s = my + decltype(par)::value * STAGE;
+  auto read = [&](auto whole_c, auto h_c, int u, MxMidOp& o) {
+    constexpr int H = decltype(h_c)::value;
+    const uint8_t* s = my + H * STAGE;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int f = 0; f < FU; ++f) {
+      o.w[H][f] = *(const u4*)(s + kMidX + f * 1024 + l * 16);
+      o.x[H][f] = *(const u4*)(s + lm * 128 + 16 * ((2 * f + g) ^ xsw));
+    }
+    if constexpr (H == 0) {
 #pragma unroll
-      for (int f = 0; f < FR; ++f) o.w[i][f] = *(const u4*)(s + kMidX + (i * FR + f) * 1024 + l * 16);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int f = 0; f < FR; ++f) o.x[j][f] = *(const u4*)(s + (32 * j + lm) * 64 + 16 * ((2 * f + g) ^ xsw));
-    if constexpr (decltype(par)::value == 0) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) wsn[i] = *(const uint32_t*)(my + WS_OFF + 256 * i + 4 * l);
+      for (int i = 0; i < 2; ++i) o.ws[i] = *(const uint32_t*)(my + WS_OFF + 256 * i + 4 * l);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const u2 e = *(const u2*)(my + XS_OFF + (32 * j + lm) * 8);
-        xsn[j] = __builtin_amdgcn_perm(e.y, e.x, xsel);
+        o.xs[j] = __builtin_amdgcn_perm(e.y, e.x, xsel);
       }
-      // a last tile without all its fragments: scales that are not there become 1 (their codes are zero)
-      const int nf = KB - 4 * tile(t);
-      if (nf < 4) {
-        const uint32_t keep = (1u << (8 * nf)) - 1u, one = 0x7f7f7f7fu & ~keep;
+      if constexpr (!decltype(whole_c)::value) {       // the bytes of the fragments it has come first, the others'
+        const int nf = ld.frags(u), sh = u < ld.nfull ? 0 : 8 * (ld.rest & 3);   // scales become 1 (their codes are zero)
+        const uint32_t one = nf < 4 ? 0x7f7f7f7fu << (8 * nf) : 0u, keep = nf < 4 ? ~(~0u << (8 * nf)) : ~0u;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          wsn[i] = (wsn[i] & keep) | one;
-          xsn[i] = (xsn[i] & keep) | one;
+          o.ws[i] = (o.ws[i] >> sh & keep) | one;
+          o.xs[i] = (o.xs[i] >> sh & keep) | one;
         }
       }
     }
-    if (KB - 4 * tile(t) - 2 * decltype(par)::value < 2) {   // no second fragment in this stage
+    if constexpr (!decltype(whole_c)::value) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) o.w[i][1] = u4{0u, 0u, 0u, 0u};
+      for (int f = 1; f < FU; ++f) o.w[H][f] &= f < ld.frags(u) ? ~0u : 0u;
     }
   };
-  auto product = [&](auto par, const MxMidOp& o, int k) {
-    constexpr int PAR = decltype(par)::value;
-    if (PAR == 0 && k == 0) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        ws[i] = wsn[i];
-        xs[i] = xsn[i];
-      }
-    }
+  auto product = [&](auto h_c, const MxMidOp& o, int k) {
+    constexpr int H = decltype(h_c)::value;
     const int j = k & 1, i = (k >> 1) & 1;
     if (k < 4)
-      acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(o.w[i][0]), fp4_operand(o.x[j][0]), acc[i][j], 4, 4,
-                                                                  2 * PAR, (int)ws[i], 2 * PAR, (int)xs[j]);
+      acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(o.w[i][2 * H]), fp4_operand(o.x[j][2 * H]), acc[i][j],
+                                                                  4, 4, 2 * H, (int)o.ws[i], 2 * H, (int)o.xs[j]);
     else
-      acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(o.w[i][1]), fp4_operand(o.x[j][1]), acc[i][j], 4, 4,
-                                                                  2 * PAR + 1, (int)ws[i], 2 * PAR + 1, (int)xs[j]);
+      acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(o.w[i][2 * H + 1]), fp4_operand(o.x[j][2 * H + 1]),
+                                                                  acc[i][j], 4, 4, 2 * H + 1, (int)o.ws[i], 2 * H + 1, (int)o.xs[j]);
   };
-  mid_loop<NS, 10, 8, 8, MxMidOp>(
-      nst,
-      [&](int t) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) fill(t, k);
-        if ((t & 1) == 0) {
-          fill(t, 8);
-          fill(t, 9);
-        }
-      },
-      fill, read, product);
+  mid_unit_loop<NS, 9, 8, 8, MxMidOp>(ld.nu, ld.brief(), fill, read, product, [&]() {
+    if (w < LF) lr_fetch(w);
+  });
 
   // ---- compensation fragments w, w + NW, ... ---------------------------------------------------------------------------
   for (int jf = w; jf < LF; jf += NW) {

@@ -85,7 +85,11 @@ __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :: "s"(lds_base_uniform), "v"(voff), "s"(sbase) : "memory", "m0");
 }
-// The same, 4 bytes per lane.
+// The same from an address of every lane's own.
+__device__ __forceinline__ void dma16_at(const void* src, uint32_t lds_base_uniform) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_base_uniform), "v"(src) : "memory", "m0");
+}
+// dma16 with 4 bytes per lane.
 __device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, uint32_t lds_base_uniform) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                :: "s"(lds_base_uniform), "v"(voff), "s"(sbase) : "memory", "m0");

@@ -96,6 +96,12 @@ def test_mx_layer(in_dtype, out_dtype, M, K, N, r):
     mx._run_mx(spec, path=serq.PATH_MFMA)
 
 
+# four waves, 1024 channels a round: 1 to 7 units per wave, last units of 1 to 4 fragments, some in the second half of a scale tile
+@pytest.mark.parametrize("K", [512, 1024, 1600, 2048, 3072, 3520, 4096, 5120, 6144, 7168])
+def test_mx_units(K):
+    mx._run_mx(mx._spec(45, K, 96, 32, in_dtype="fp16", out_dtype="fp32"))
+
+
 def test_mx_salient_block_offset():
     mx._run_mx(mx._spec(70, 1344, 96, 160, out_dtype="fp32"), s_begin=768)
 
