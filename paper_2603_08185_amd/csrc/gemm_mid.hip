@@ -71,7 +71,7 @@ void serq_mid_kernel(const MidParams p) {
   const int mrows = p.M - m0 < 64 ? p.M - m0 : 64;
   const uint32_t rowbytes = (uint32_t)p.K * ABITS / 8;
 
-  std::conditional_t<ABITS == 8, MidUnits<2, NW>, MidLoads<2>> ld;
+  std::conditional_t<ABITS == 8, MidUnits<2, NW>, MidLoads> ld;
   if constexpr (ABITS == 8) ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, w, l);
   else ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
   const int steps = (ld.KB + 1) / 2;
@@ -122,7 +122,7 @@ void serq_mid_kernel(const MidParams p) {
   } else {
     const int xsw = mid_swz(lm);                       // the same for row lm and row 32 + lm
     auto slot = [&](int t) { return (t % NS) * T::STAGE; };
-    auto read = [&](auto, int t, MidStepOp& o) {
+    auto read = [&](int t, MidStepOp& o) {
       const uint8_t* s = my + slot(t);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -138,7 +138,7 @@ void serq_mid_kernel(const MidParams p) {
       }
     };
     // group k: token block k % 2, channel block k / 2 % 2 of fragment k / 4
-    auto product = [&](auto, const MidStepOp& o, int k) {
+    auto product = [&](const MidStepOp& o, int k) {
       const int j = k & 1, i = (k >> 1) & 1, f = k >> 2;
       v4i a0, a1, b0, b1;
       unpack_frag(o.w[i][f], a0, a1);
@@ -146,7 +146,7 @@ void serq_mid_kernel(const MidParams p) {
       acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, acc[i][j], 0, 0, 0);
       acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
     };
-    mid_loop<NS, T::NL, T::NL, 8, MidStepOp>(
+    mid_loop<T::NL, 8, MidStepOp>(
         nst, [&](int t) { ld.issue(w + NW * t, my_lds + slot(t)); },
         [&](int t, int k) { ld.issue_one(w + NW * t, my_lds + slot(t), k); }, read, product);
   }

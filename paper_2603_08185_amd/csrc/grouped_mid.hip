@@ -1,16 +1,17 @@
 // The layer with group-128 weight scales for batches between decode and prefill: tiles of 64 tokens x 64 channels, the
 // 4 or 8 waves of a workgroup sharing K (mid_tile.h says why; the formulas are those of grouped.hip).
 //
-// A wave takes whole groups of 128 channels: one stage of 4-bit tokens, two of 8-bit ones, each with the group's 64
+// A wave takes whole groups of 128 channels, a step of 4-bit tokens or a unit of 8-bit ones, with the group's 64
 // scales.  The four products of an MFMA tile start from zero and the INT32 tile is folded into the wave's fp32 tile
 // while the next tile's products run.  Tokens are the MFMA's row operand and weights its column operand (as in the decode
 // kernel of grouped.hip): a lane holds one channel of each block, so it needs one scale per block and group, not sixteen.
 // The waves' fp32 tiles are added through LDS in wave order (run-to-run identical), each of 8 waves finishing half an MFMA
 // tile, each of 4 a whole one: zero point, rank-r term on the re-centred codes, token scale.
 //
-// What bounds it: the L2 -> LDS stream, as in gemm_mid.hip, and next to it the vector unit (128 fold operations per wave
+// What bounds it: the load stream, as in gemm_mid.hip, and next to it the vector unit (128 fold operations per wave
 // and group beside 16 products).  Measured (M = 150, 4096 x 11008, W4A4, r = 64, graph replay): 20 us; the 128 x 128 tiles of the
-// tiled kernel give 64 workgroups there, 128 in halves, and take 48 us.
+// tiled kernel give 64 workgroups there, 128 in halves, and take 48 us.  W4A8, r = 128, 64- / 128-byte token rows: 4096 x 11008
+// M = 256 28.2 / 23.8 us, 4096 x 4096 M = 150 12.1 / 11.4, M = 400 19.2 / 17.7.
 #include "mid_tile.h"
 
 namespace serq {
@@ -18,25 +19,24 @@ namespace {
 
 template <int ABITS>
 struct GMid {
-  static constexpr int FR = ABITS == 8 ? 1 : 2;
-  static constexpr int SC_OFF = kMidX + 2 * FR * 1024;   // 2 blocks x 32 fp16 scales
-  static constexpr int STAGE = SC_OFF + 128;
+  static constexpr int SC_OFF = kMidX + (ABITS == 8 ? 2 : 4) * 1024;   // fp16 scales: 32 of a block (4-bit: of two blocks)
+  static constexpr int STAGE = SC_OFF + (ABITS == 8 ? 256 : 128);
   static constexpr int NS = ABITS == 8 ? 3 : 2;
-  static constexpr int NL = 4 + 2 * FR + 1;
+  static constexpr int NL = ABITS == 8 ? 7 : 9;
   static constexpr int REGION = NS * STAGE;
   static constexpr int SH = ABITS == 8 ? 4 : 8;
   static_assert(REGION >= kMidPart, "a partial tile fits the ring it replaces");
   static_assert(8 * REGION <= 160 * 1024, "LDS budget");
 };
 
-template <int FR>
-struct GMidOp { u4 w[2][FR], x[2][2]; float gs[2]; };
+struct GMidUnitOp { u4 w[2][2], x[2][4]; float gs[2]; };
+struct GMidStepOp { u4 w[2][2], x[2][2]; float gs[2]; };
 
 template <int ABITS, bool BF, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) {
   using T = GMid<ABITS>;
-  constexpr int FR = T::FR, NS = T::NS;
+  constexpr int NS = T::NS;
   __shared__ __align__(16) uint8_t lds[NW * T::REGION];
   const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -48,18 +48,18 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) 
   const int mrows = p.M - m0 < 64 ? p.M - m0 : 64;
   const uint32_t rowbytes = (uint32_t)p.K * ABITS / 8;
 
-  MidLoads<FR> ld;
-  ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
-  const int ng = G > w ? (G - w + NW - 1) / NW : 0;   // groups w, w + NW, ... are this wave's
-  constexpr int SPG = ABITS == 8 ? 2 : 1;              // stages per group
-  const int nst = ng * SPG;
+  std::conditional_t<ABITS == 8, MidUnits<2, NW, false>, MidLoads> ld;   // a unit, or a step, is a group: a fold needs all of it
+  if constexpr (ABITS == 8) ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, w, l);
+  else ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, l);
+  const int nst = G > w ? (G - w + NW - 1) / NW : 0;   // 4-bit: groups w, w + NW, ... are this wave's
   uint8_t* my = lds + w * T::REGION;
   const uint32_t my_lds = __builtin_amdgcn_readfirstlane(lds_addr(my));
   const uint8_t* sbase = (const uint8_t*)p.gsc + (size_t)nb0 * G * 64;
   const uint32_t sv = (uint32_t)((l >> 2 & 1) && nbt > 1 ? G * 64 : 0) + (l & 3) * 16;   // lanes 0..3: block 0, 4..7: block 1
 
   // ---- operands of the rank-r term, in chunks of 128 ranks: every wave brings two R fragments and 16 codes of 8 token
-  // rows per lane, the first chunk requested before anything else (oldest loads: the ring's counting is not disturbed)
+  // rows per lane, the first chunk requested before anything else (4-bit: oldest
+  // loads, the ring's counting is not disturbed) or in front of the wave's last unit (8-bit: no load of the ring is waited for any more)
   const int JB = p.r >> 4;
   constexpr int NJ = 8;
   constexpr int VH = 8 / NW;                           // (a wave of 4 brings the shares of two of 8)
@@ -105,7 +105,14 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) 
     }
     }
   };
-  if (JB > 0) {
+  auto lr_first = [&]() {
+    if (JB > 0) {
+      lr_fetch(0);
+#pragma unroll
+      for (int v = 0; v < VH; ++v) lzm[v] = p.zero ? p.zero[lr_m(v)] : 0;
+    }
+  };
+  if (ABITS == 4 && JB > 0) {
     lr_fetch(0);
 #pragma unroll
     for (int v = 0; v < VH; ++v) lzm[v] = p.zero ? p.zero[lr_m(v)] : 0;
@@ -123,71 +130,106 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) 
 #pragma unroll
       for (int e = 0; e < 16; ++e) accf[i][j][e] = 0.0f;
     }
-  const int xsw = mid_swz(lm);
-  auto slot = [&](int t) { return (t % NS) * T::STAGE; };
-  auto group = [&](int t) { return w + NW * (SPG == 2 ? t >> 1 : t); };
-  auto fill = [&](int t, int k) {
-    const int s = SPG == 2 ? 2 * group(t) + (t & 1) : group(t);
-    if (k < T::NL - 1) ld.issue_one(s, my_lds + slot(t), k);
-    else if (l < 8) dma16(sbase + (size_t)group(t) * 64, sv, my_lds + slot(t) + T::SC_OFF);
+  // MFMA tiles one after another, a fragment a step.  In the step after its last product a tile is folded; the last one of a
+  // stage right behind it (the other wave of the SIMD works meanwhile).
+  auto fold = [&](int u, float gs) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      accf[u >> 1][u & 1][e] = __builtin_fmaf(gs, (float)acc[u >> 1][u & 1][e], accf[u >> 1][u & 1][e]);
+    // pinned here: left alone, the compiler puts folds off and keeps every INT32 tile alive (99 registers spilled)
+    asm volatile("" : "+v"(accf[u >> 1][u & 1]));
   };
-  auto read = [&](auto par, int t, GMidOp<FR>& o) {
-    const uint8_t* s = my + slot(t);
+  if constexpr (ABITS == 8) {
+    const int xsw = mid_swz128(lm);
+    auto slot = [&](int h, int u) { return (2 * u + h) % NS * T::STAGE; };
+    auto fill = [&](auto whole_c, auto h_c, int u, int k) {
+      constexpr int H = decltype(h_c)::value;
+      constexpr bool WHOLE = decltype(whole_c)::value;
+      if (k < T::NL - 1) {
+        ld.template issue_one<WHOLE>(H, u, my_lds + slot(H, u), k);
+      } else {
+        const int grp = (WHOLE ? (w + NW * u) * 2 : ld.first(u)) >> 1;
+        dma4(sbase + ((size_t)(H && nbt > 1 ? G : 0) + grp) * 64, 4u * (l & 15), my_lds + slot(H, u) + T::SC_OFF);
+      }
+    };
+    auto read = [&](auto, auto h_c, int u, GMidUnitOp& o) {
+      constexpr int H = decltype(h_c)::value;
+      const uint8_t* s = my + slot(H, u);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+      for (int f = 0; f < 2; ++f) o.w[H][f] = *(const u4*)(s + kMidX + f * 1024 + l * 16);
+      o.gs[H] = (float)*(const _Float16*)(s + T::SC_OFF + 2 * lm);
 #pragma unroll
-      for (int f = 0; f < FR; ++f) o.w[i][f] = *(const u4*)(s + kMidX + (i * FR + f) * 1024 + l * 16);
-      if (SPG == 1 || decltype(par)::value == 1) {       // the scales are used at the end of the group
+      for (int q = 0; q < 4; ++q) {
+        const int c = 4 * (q >> 1) + 2 * g + (q & 1);
+        o.x[H][q] = *(const u4*)(s + lm * 128 + 16 * (c ^ xsw));
+      }
+    };
+    auto product = [&](auto h_c, const GMidUnitOp& o, int k) {   // tile 2*h + k/2, fragment k % 2
+      constexpr int H = decltype(h_c)::value;
+      const int q = 2 * H + k / 2, f = k % 2;
+      const int i = q >> 1, j = q & 1;
+      v4i a0, a1, b0, b1;
+      unpack_frag(o.w[i][f], a0, a1);
+      b0 = as_v4i(o.x[j][2 * f]);
+      b1 = as_v4i(o.x[j][2 * f + 1]);
+      if (f == 0) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0, a0, kZero16, 0, 0, 0);
+      else acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0, a0, acc[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b1, a1, acc[i][j], 0, 0, 0);
+      if (k == 3) {
+        fold(2 * H, o.gs[H]);
+        fence();
+        fold(2 * H + 1, o.gs[H]);
+      }
+    };
+    mid_unit_loop<NS, T::NL, T::NL, 4, GMidUnitOp>(ld.nu, ld.brief(), fill, read, product, lr_first);
+  } else {
+    const int xsw = mid_swz(lm);
+    auto slot = [&](int t) { return (t % NS) * T::STAGE; };
+    auto group = [&](int t) { return w + NW * t; };
+    auto fill = [&](int t, int k) {
+      const int s = group(t);
+      if (k < T::NL - 1) ld.issue_one(s, my_lds + slot(t), k);
+      else if (l < 8) dma16(sbase + (size_t)group(t) * 64, sv, my_lds + slot(t) + T::SC_OFF);
+    };
+    auto read = [&](int t, GMidStepOp& o) {
+      const uint8_t* s = my + slot(t);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f) o.w[i][f] = *(const u4*)(s + kMidX + (i * 2 + f) * 1024 + l * 16);
         o.gs[i] = (float)*(const _Float16*)(s + T::SC_OFF + 64 * i + 2 * lm);
       }
-    }
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int c = ABITS == 8 ? 2 * g + h : 2 * h + g;
-        o.x[j][h] = *(const u4*)(s + (32 * j + lm) * 64 + 16 * (c ^ xsw));
-      }
-  };
-  // MFMA tiles one after another, 2 products a step: tile k / FR (4-bit: fragment k % 2 of it).  In the step after its
-  // last product a tile is folded; the last one right behind it (the other wave of the SIMD works meanwhile).
-  auto product = [&](auto par, const GMidOp<FR>& o, int k) {
-    const int q = k / FR, f = k % FR;
-    const int i = q >> 1, j = q & 1;
-    const bool first = SPG == 2 ? decltype(par)::value == 0 : f == 0;
-    const bool last = SPG == 2 ? decltype(par)::value == 1 : f == FR - 1;
-    v4i a0, a1, b0, b1;
-    unpack_frag(o.w[i][f], a0, a1);
-    if constexpr (ABITS == 8) {
-      b0 = as_v4i(o.x[j][0]);
-      b1 = as_v4i(o.x[j][1]);
-    } else {
-      unpack_frag(o.x[j][f], b0, b1);
-    }
-    if (first) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0, a0, kZero16, 0, 0, 0);
-    else acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0, a0, acc[i][j], 0, 0, 0);
-    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b1, a1, acc[i][j], 0, 0, 0);
-    auto fold = [&](int u) {
-      const float gs = o.gs[u >> 1];
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        accf[u >> 1][u & 1][e] = __builtin_fmaf(gs, (float)acc[u >> 1][u & 1][e], accf[u >> 1][u & 1][e]);
-      // pinned here: left alone, the compiler puts folds off and keeps every INT32 tile alive (99 registers spilled)
-      asm volatile("" : "+v"(accf[u >> 1][u & 1]));
+        for (int h = 0; h < 2; ++h) {
+          const int c = 2 * h + g;
+          o.x[j][h] = *(const u4*)(s + (32 * j + lm) * 64 + 16 * (c ^ xsw));
+        }
     };
-    if (last && q > 0) fold(q - 1);
-    if (last && q == 3) {
-      fence();
-      fold(3);
-    }
-  };
-  mid_loop<NS, T::NL, T::NL, 4 * FR, GMidOp<FR>>(
-      nst,
-      [&](int t) {
+    auto product = [&](const GMidStepOp& o, int k) {   // tile k / 2, fragment k % 2
+      const int q = k / 2, f = k % 2;
+      const int i = q >> 1, j = q & 1;
+      v4i a0, a1, b0, b1;
+      unpack_frag(o.w[i][f], a0, a1);
+      unpack_frag(o.x[j][f], b0, b1);
+      if (f == 0) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0, a0, kZero16, 0, 0, 0);
+      else acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b0, a0, acc[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b1, a1, acc[i][j], 0, 0, 0);
+      if (f == 1 && q > 0) fold(q - 1, o.gs[(q - 1) >> 1]);
+      if (f == 1 && q == 3) {
+        fence();
+        fold(3, o.gs[1]);
+      }
+    };
+    mid_loop<T::NL, 8, GMidStepOp>(
+        nst,
+        [&](int t) {
 #pragma unroll
-        for (int k = 0; k < T::NL; ++k) fill(t, k);
-      },
-      fill, read, product);
+          for (int k = 0; k < T::NL; ++k) fill(t, k);
+        },
+        fill, read, product);
+  }
 
   // ---- the waves meet.  8 waves: wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j; 4 waves: all
   // of tile w = 2*i + j

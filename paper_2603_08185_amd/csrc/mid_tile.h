@@ -106,9 +106,9 @@ inline bool mid_cheaper(const MidPrice& small, const TiledPrice& tiled, int M, i
 
 // ---- steps ----------------------------------------------------------------------------------------------------
 // The workgroup's tile and a wave's share of its loads.
-// FR: fragments of 64 channels per stage (1: 8-bit tokens, 2: 4-bit tokens).
-template <int FR>
+// A step is 128 channels of 4-bit tokens: FR fragments of each weight block.
 struct MidLoads {
+  static constexpr int FR = 2;
   const uint8_t* xbase; const uint8_t* wbase;        // first token row / first weight fragment of the tile
   uint32_t xv[4];                                    // this lane's four token pieces: row offset + piece
   uint32_t back;                                     // what a piece of the second fragment steps back when there is none
@@ -134,9 +134,9 @@ struct MidLoads {
   }
   // direct load k (of 4 + 2*FR) of step s into the stage at LDS address `st`
   __device__ __forceinline__ void issue_one(int s, uint32_t st, int k) const {
-    const bool half = FR == 2 && KB - s * FR < FR;   // the last step of an odd number of fragments
+    const bool half = KB - s * FR < FR;              // the last step of an odd number of fragments
     if (k < 4) {
-      dma16(xbase + (size_t)s * 64, FR == 2 && half ? xv[k] - back : xv[k], st + 1024u * k);
+      dma16(xbase + (size_t)s * 64, half ? xv[k] - back : xv[k], st + 1024u * k);
     } else {
       const int i = (k - 4) / FR, f = (k - 4) % FR;
       dma16(wbase + (size_t)s * FR * 1024 + i * wstep1 + (half ? 0 : f) * 1024, wl, st + 1024u * k);
@@ -148,75 +148,64 @@ struct MidLoads {
   }
 };
 
-// wait until all but the youngest `n * NL` vector-memory operations of this wave have completed (n = 0 .. 2)
-template <int NL>
-__device__ __forceinline__ void mid_wait(int n) {
-  if (n >= 2) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * NL) : "memory");
-  else if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NL) : "memory");
-  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-}
+// all but the youngest N vector-memory operations of this wave have completed
+template <int N>
+__device__ __forceinline__ void mid_landed() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 // this wave's LDS reads have returned: the stage they came from may be refilled
 __device__ __forceinline__ void mid_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// The main loop of a wave: its stages 0 .. nst-1 in order.  The operands of a stage are copied to registers one stage
-// ahead, which frees its slot: the slot is refilled, NS stages further, between the products of the stage before.
+// The main loop of a wave over its stages 0 .. nst-1, in a ring of two.  The operands of a stage are copied to registers one
+// stage ahead, which frees its slot: the slot is refilled, two stages further, between the products of the stage before.
 // (A direct load blocks the wave while the address unit is busy with the other waves' loads; between two products
 // that costs nothing.)
 //   start(t)              the first loads of stage t (prologue)
-//   fill(t, k)            direct load k of stage t into its slot
-//   read(par, t, op)      the operands of stage t, from LDS
-//   product(par, op, k)   the k-th of NP groups of products on the operands `op`
-// par: t % 2 as a compile-time constant.  Even stages take NL0 direct loads, odd ones NL1 (which may differ for NS = 2).
+//   fill(t, k)            direct load k (of NL) of stage t into its slot
+//   read(t, op)           the operands of stage t, from LDS
+//   product(op, k)        the k-th of NP groups of products on the operands `op`
 // Loads requested before the loop are older than its own, so they do not disturb its counting.
-template <int NS, int NL0, int NL1, int NP, class Op, class Start, class Fill, class Read, class Product>
+template <int NL, int NP, class Op, class Start, class Fill, class Read, class Product>
 __device__ __forceinline__ void mid_loop(int nst, const Start& start, const Fill& fill, const Read& read,
                                          const Product& product) {
-  static_assert(NL0 == NL1 || NS == 2, "the youngest NS - 1 stages are one stage of known parity, or all alike");
-  using Even = std::integral_constant<int, 0>;
-  using Odd = std::integral_constant<int, 1>;
+  constexpr int NS = 2;
   if (nst == 0) return;
 #pragma unroll
   for (int t = 0; t < NS; ++t)
     if (t < nst) start(t);
   Op A, B;
-  mid_wait<NL1>(nst - 1 < NS - 1 ? nst - 1 : NS - 1);
-  read(Even{}, 0, A);
+  if (nst > 1) mid_landed<NL>(); else mid_landed<0>();
+  read(0, A);
   mid_reads_done();
   if (NS < nst) start(NS);
   int t = 0;
-  auto half = [&](auto steady_c, auto par_c, const Op& cur, Op& nxt) {
+  auto stage = [&](auto steady_c, const Op& cur, Op& nxt) {
     constexpr bool STEADY = decltype(steady_c)::value;
-    constexpr int PAR = decltype(par_c)::value;
-    constexpr int NLB = PAR ? NL1 : NL0;              // of stage t + 2, which stays in flight (NS = 2)
-    constexpr int NLR = (PAR + 1 + NS) % 2 ? NL1 : NL0;   // of stage t + 1 + NS, which is requested here
     const bool refill = STEADY || t + 1 + NS < nst;
     if (STEADY) {
-      mid_wait<NLB>(NS - 1);
-      read(std::integral_constant<int, 1 - PAR>{}, t + 1, nxt);
+      mid_landed<NL>();
+      read(t + 1, nxt);
     } else if (t + 1 < nst) {
-      const int behind = nst - 2 - t;
-      mid_wait<NLB>(behind < NS - 1 ? behind : NS - 1);
-      read(std::integral_constant<int, 1 - PAR>{}, t + 1, nxt);
+      if (nst - 2 - t >= 1) mid_landed<NL>(); else mid_landed<0>();
+      read(t + 1, nxt);
     }
     fence();
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-      product(par_c, cur, k);
+      product(cur, k);
       if (k == 0) mid_reads_done();
 #pragma unroll
-      for (int d = 0; d < NLR; ++d)
-        if (d * (NP - 1) / NLR == k && refill) fill(t + 1 + NS, d);
+      for (int d = 0; d < NL; ++d)
+        if (d * (NP - 1) / NL == k && refill) fill(t + 1 + NS, d);
       fence();
     }
     ++t;
   };
   while (t + 2 + NS < nst) {
-    half(std::true_type{}, Even{}, A, B);
-    half(std::true_type{}, Odd{}, B, A);
+    stage(std::true_type{}, A, B);
+    stage(std::true_type{}, B, A);
   }
   while (t < nst) {
-    half(std::false_type{}, Even{}, A, B);
-    if (t < nst) half(std::false_type{}, Odd{}, B, A);
+    stage(std::false_type{}, A, B);
+    if (t < nst) stage(std::false_type{}, B, A);
   }
 }
 
@@ -284,10 +273,6 @@ struct MidUnits {
     }
   }
 };
-
-// all but the youngest N vector-memory operations of this wave have completed
-template <int N>
-__device__ __forceinline__ void mid_landed() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
 // The main loop over a wave's nu units.  Stage t of the ring is half t % 2 of unit t / 2.  The operands of a half
 // are copied to registers one unit ahead, which frees its slot: the slot is refilled, NS stages further, between the

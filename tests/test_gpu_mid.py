@@ -76,6 +76,12 @@ def test_g128_layer(abits, in_dtype, out_dtype, M, K, N, r):
     assert torch.equal(Y, Yb)                               # fixed summation order
 
 
+# 8-bit tokens, four groups of 128 channels a round (and eight, with one tile per compute unit at most: here): 1 to 6 units per wave
+@pytest.mark.parametrize("K", [512, 1024, 1152, 2048, 3072, 4096, 5120, 6144])
+def test_g128_units(K):
+    grouped._run(grouped._spec(8, 45, K, 96, 32, in_dtype="fp16", out_dtype="fp32"), R_mode="residual")
+
+
 def test_g128_layer_variants():
     for abits in (4, 8):
         spec = grouped._spec(abits, 70, 768, 96, 160, out_dtype="fp32")
