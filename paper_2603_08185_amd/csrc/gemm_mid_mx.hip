@@ -51,7 +51,7 @@ void serq_mx_mid_kernel(const MxMidParams p) {
   const uint32_t rowbytes = (uint32_t)p.K >> 1;
   const size_t Mp = (size_t)((p.M + 1) & ~1);          // rows of a tile of the token-scale array
 
-  MidUnits<FU, NW> ld;
+  MidUnits<FU, NW, true, true> ld;
   ld.init(p.Xq, p.Wq, p.K, rowbytes, m0, mrows, nb0, nbt, w, l);
   const int T = (ld.KB + 3) >> 2;                      // scale tiles
   uint8_t* my = lds + w * REGION;

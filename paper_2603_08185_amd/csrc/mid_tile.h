@@ -214,11 +214,19 @@ __device__ __forceinline__ void mid_loop(int nst, const Start& start, const Fill
 // FU: fragments of 64 channels per unit (2: 8-bit tokens, 4: 4-bit tokens).
 // Units w, w + NW, ... are wave w's, as far as they go round; the fragments left over are dealt out in pieces of half a unit
 // if that is enough (SPLIT), else of a unit, one to a wave: its last unit, with nf of FU fragments.
-template <int FU, int NW, bool SPLIT = true>
+// LEAN: two registers for the token offsets instead of eight, and two vector and one scalar operation more per load.  For the
+// MXFP4 kernel, whose operands leave no room for eight: with them 4 registers were spilled on the way into the steady loop, and
+// behind their reload the compiler waited for all loads of the ring, every second unit (us, eight / two, r = 128, N x K,
+// weights from HBM: 4096 x 14336 M = 200 17.8 / 17.0, 4096 x 4096 M = 100 7.2 / 6.9).  The integer kernels have the registers and are faster with
+// eight (4096 x 4096 M = 100 8.6 / 9.1, 4096 x 8192 M = 40 11.4 / 12.2).
+template <int FU, int NW, bool SPLIT = true, bool LEAN = false>
 struct MidUnits {
   static constexpr int PPF = 8 / FU;                 // 16-byte pieces of a token row per fragment
   const uint8_t* xbase; const uint8_t* wbase;        // first token row / first weight fragment of the tile
-  uint32_t xv[2][4];                                 // this lane's token pieces: row offset + piece
+  // This lane's token pieces: row offset + piece.  Load k of half h brings the rows of group q = 4*h + k, 8*q .. 8*q + 7.
+  // LEAN: those of groups 0 and 1; the pieces of groups 2 apart are the same, their rows lie 2 * xgroup apart.
+  uint32_t xv[LEAN ? 2 : 8];
+  uint32_t xgroup, xlast;                            // LEAN: bytes of 8 rows; where the last row begins
   uint32_t wl;
   size_t wstep1;                                     // from the fragments of block 0 to those of block 1 (0: there is none)
   int KB;                                            // fragments per channel block
@@ -239,14 +247,14 @@ struct MidUnits {
     wbase = (const uint8_t*)Wq + (size_t)nb0 * KB * 1024;
     wstep1 = nbt > 1 ? (size_t)KB * 1024 : 0;
     wl = (uint32_t)l * 16u;
+    xgroup = 8 * rowbytes;
+    xlast = (uint32_t)(mrows - 1) * rowbytes;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {                  // load k of a half: its rows 8*k .. 8*k + 7
-        int row = 32 * h + 8 * k + (l >> 3);
-        row = row < mrows ? row : mrows - 1;         // rows past M: duplicates, never stored
-        xv[h][k] = (uint32_t)row * rowbytes + 16u * xpiece(l, k);
-      }
+    for (int q = 0; q < (LEAN ? 2 : 8); ++q) {
+      int row = 8 * q + (l >> 3);
+      if (!LEAN && row >= mrows) row = mrows - 1;    // rows past M: duplicates, never stored
+      xv[q] = (uint32_t)row * rowbytes + 16u * xpiece(l, q);
+    }
   }
   static __device__ __forceinline__ int xpiece(int l, int k) { return (l & 7) ^ mid_swz128(8 * k + (l >> 3)); }
   __device__ __forceinline__ bool brief() const { return nf > 0 && nf <= FU / 2; }
@@ -259,12 +267,20 @@ struct MidUnits {
     const int f0 = WHOLE ? (w + NW * u) * FU : first(u);
     const int have = WHOLE ? FU : frags(u);          // (selected as a number: no control flow around the load)
     if (k < 4) {
-      uint32_t v = xv[h][k];
+      uint32_t v = xv[LEAN ? k & 1 : 4 * h + k];
       if constexpr (!WHOLE) {
         int l = (int)(wl >> 4);
         asm volatile("" : "+v"(l));                  // computed here, not carried through the main loop
         const int c = xpiece(l, k);
         v -= c < have * PPF ? 0u : 16u * c;
+      }
+      if constexpr (LEAN) {
+        uint32_t g = xgroup;
+        asm volatile("" : "+s"(g));                  // added here: left alone, the compiler keeps all eight sums
+        v += (4 * h + (k & 2)) * g;
+        // rows past M: the last piece of the last row, never stored (they begin a row's length or more behind that row)
+        const uint32_t lim = xlast + 16u * (have * PPF - 1);
+        v = v < lim ? v : lim;
       }
       dma16(xbase + (size_t)f0 * (16 * PPF), v, st + 1024u * k);
     } else {

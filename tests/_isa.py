@@ -128,6 +128,7 @@ class Wave:
         self.s[0], self.s[2] = KERNARG, workgroup
         self.v[0] = LANES + np.uint64(64 * wave)
         self.loads, self.vm, self.lgkm = [], deque(), deque()
+        self.own_waits = []                                           # when the compiler's own code waited for loads
         self.word = np.full(lds_bytes // 4, -1, np.int64)            # direct load that wrote (or will write) a word of LDS
         self.busy = np.zeros(lds_bytes // 4, np.int32)               # reads of the word that have not returned
         self.seen = np.zeros(lds_bytes // 4, bool)                   # the word has been read since
@@ -299,6 +300,8 @@ class Wave:
     def _scalar(self, i):
         op, a, st = i.op, i.args, self.st
         if op == "s_waitcnt":
+            if "vmcnt" in i.text and not i.asm:
+                self.own_waits.append(self.steps)
             return self._wait(i.text)
         if op in ("s_nop", "s_setprio", "s_sleep"):
             return None

@@ -111,9 +111,12 @@ def _check(asm, name, M, N, K, r=32):
         for w in range(waves):
             where = (name, M, N, K, "workgroup", wg, "wave", w)
             try:
-                loads = _isa.Wave(prog, arg, wg, w, buf, meta[kernel]["group_segment_fixed_size"]).run()
+                wave = _isa.Wave(prog, arg, wg, w, buf, meta[kernel]["group_segment_fixed_size"])
+                loads = wave.run()
             except _isa.Fault as e:
                 raise AssertionError((*where, str(e))) from None
+            # a wait that is not counted by hand empties the ring
+            assert not loads or not any(loads[0].at < t < loads[-1].at for t in wave.own_waits), where
             codes = [ld for ld in loads if ld.buf in ("Xq", "Wq")]
             units = _units(form, waves, FU, KB, w)
             assert len(codes) == len(units) * 2 * (4 + FU), where
@@ -161,6 +164,9 @@ def test_loads(asm, name):
     frags |= {one * u for u in (1, 5, 7, 8, 12, 13)}
     for n in sorted(frags):
         _check(asm, name, 109, 96, 64 * n)
+    for left in (0, step, one - step):                     # a last tile of one row, and of nine
+        _check(asm, name, 65, 64, 64 * (one + left))
+        _check(asm, name, 73, 64, 64 * (one + left))
 
 
 # the kernels that read 4-bit tokens in steps: nothing out of bounds or out of turn, and every fragment is fetched
@@ -183,3 +189,8 @@ def test_step_loads(asm, form, kernel, waves):
                         seen.add(int(ld.off[0]) // 1024)
             nb0 = 0 if wg == 0 else 2                  # (the last tile has one channel block)
             assert seen == set(range(nb0 * KB, min(nb0 + 2, N // 32) * KB)), (kernel, K, wg)
+
+
+def test_registers_suffice(asm):
+    for name, m in asm[1].items():
+        assert m["private_segment_fixed_size"] == 0 and m["vgpr_spill_count"] == 0 and m["sgpr_spill_count"] == 0, (name, m)
