@@ -6,10 +6,10 @@
 // waves -- integer addition, the same bits as the tiled kernel -- scales it and adds the rank-r term with the matrix unit on
 // top, exactly as the tiled kernel does.
 //
-// What bounds it: with 8-bit tokens at M = 256, N = 4096, K = 11008 the kernel takes 20.2 us (23.2 with 64-byte token rows); the
+// What bounds it: with 8-bit tokens at M = 256, N = 4096, K = 11008 the kernel takes 20.1 us (23.1 with 64-byte token rows); the
 // same load stream without products, launch included, 12.6 us (at K = 11264), the matrix unit alone 6.  The rest is the start
 // and the end of a tile and what the two do not overlap.  Fixed costs: 4 us at K = 256, r = 0 in a graph, 1 us more for r = 128.
-// The tiled kernel with 4 K slices and a second launch takes 32 us there; M = 100, 6144 x 4096: 9.3 against 24.4 us.
+// The tiled kernel with 4 K slices and a second launch takes 32 us there; M = 100, 6144 x 4096: 9.0 against 24.4 us.
 // The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.  Rings of twice the depth where a workgroup has
 // a compute unit to itself: 9.3 -> 10.0 us at M = 100, 6144 x 4096 (the first stage lands behind all the others' requests).
 #include "mid_tile.h"
@@ -113,7 +113,7 @@ void serq_mid_kernel(const MidParams p) {
       acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, acc[i][j], 0, 0, 0);
     };
     mid_unit_loop<NS, T::NL, T::NL, 4, MidUnitOp>(
-        ld.nu, ld.brief(),
+        ld.nu, ld.nfull, ld.brief(),
         [&](auto whole_c, auto h_c, int u, int k) {
           constexpr int H = decltype(h_c)::value;
           ld.template issue_one<decltype(whole_c)::value>(H, u, my_lds + slot(H, u), k);

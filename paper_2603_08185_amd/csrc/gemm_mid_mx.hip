@@ -9,9 +9,8 @@
 // from run to run.
 //
 // What bounds it: the load stream and how far the products overlap it, as in gemm_mid.hip.  Measured (M = 200, 4096 x 14336,
-// r = 128, graph replay): 18.4 us (19.5 with 64-byte token rows; with the quantiser of a gated product in front of it
-// 20.7 -> 18.3 for both launches), the tiled kernel with its K slices and second launch 33 us; M = 500, 4096 x 4096
-// 12.1 -> 11.5 us, M = 200, K = 1024 4.5 -> 4.7 us.  The rank-r term costs nothing that shows.
+// r = 128, graph replay): 16.3 us (17.9 with 64-byte token rows), the tiled kernel with its K slices and second launch 33 us; M = 500,
+// 4096 x 4096 11.9 -> 10.5 us, M = 200, K = 1024 4.5 -> 4.6 us.  The rank-r term costs nothing that shows.
 #include "mid_tile.h"
 
 namespace serq {
@@ -144,7 +143,7 @@ void serq_mx_mid_kernel(const MxMidParams p) {
       acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(o.w[i][2 * H + 1]), fp4_operand(o.x[j][2 * H + 1]),
                                                                   acc[i][j], 4, 4, 2 * H + 1, (int)o.ws[i], 2 * H + 1, (int)o.xs[j]);
   };
-  mid_unit_loop<NS, 9, 8, 8, MxMidOp>(ld.nu, ld.brief(), fill, read, product, [&]() {
+  mid_unit_loop<NS, 9, 8, 8, MxMidOp>(ld.nu, ld.nfull, ld.brief(), fill, read, product, [&]() {
     if (w < LF) lr_fetch(w);
   });
 

@@ -11,7 +11,7 @@
 // What bounds it: the load stream, as in gemm_mid.hip, and next to it the vector unit (128 fold operations per wave
 // and group beside 16 products).  Measured (M = 150, 4096 x 11008, W4A4, r = 64, graph replay): 20 us; the 128 x 128 tiles of the
 // tiled kernel give 64 workgroups there, 128 in halves, and take 48 us.  W4A8, r = 128, 64- / 128-byte token rows: 4096 x 11008
-// M = 256 28.2 / 23.8 us, 4096 x 4096 M = 150 12.1 / 11.4, M = 400 19.2 / 17.7.
+// M = 256 28.1 / 23.3 us, 4096 x 4096 M = 150 12.1 / 11.4, M = 400 19.1 / 17.3.
 #include "mid_tile.h"
 
 namespace serq {
@@ -181,7 +181,7 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) 
         fold(2 * H + 1, o.gs[H]);
       }
     };
-    mid_unit_loop<NS, T::NL, T::NL, 4, GMidUnitOp>(ld.nu, ld.brief(), fill, read, product, lr_first);
+    mid_unit_loop<NS, T::NL, T::NL, 4, GMidUnitOp>(ld.nu, ld.nfull, ld.brief(), fill, read, product, lr_first);
   } else {
     const int xsw = mid_swz(lm);
     auto slot = [&](int t) { return (t % NS) * T::STAGE; };

@@ -18,10 +18,12 @@
 //     than a step, and the operands of a unit are complete once both have been read to registers.
 // Units need a whole unit in registers before the first product and the next one behind it: 96 operand registers at the peak,
 // and a pipeline that fills later.  Measured (us, steps / units, r = 128, N x K, the layer alone, weights from HBM):
-//   W4A8    4096 x 11008 M = 256 23.2 / 20.2;  4096 x 4096 M = 256 9.5 / 9.3, M = 333 13.4 / 13.2;  6144 x 4096 M = 100
-//           8.9 / 9.3, both launches of the layer (the quantiser in front of it) 12.5 / 12.2
-//   W4A8, group scales  4096 x 11008 M = 256 28.2 / 23.8;  4096 x 4096 M = 150 12.1 / 11.4, M = 400 19.2 / 17.7
-//   MXFP4   4096 x 14336 M = 200 19.5 / 18.4;  4096 x 4096 M = 200 7.7 / 7.4, M = 500 12.1 / 11.5;  4096 x 1024 M = 200 4.5 / 4.7
+//   W4A8    4096 x 11008 M = 256 23.1 / 20.1;  4096 x 4096 M = 64 9.4 / 8.5, M = 100 8.4 / 8.5, M = 256 9.6 / 9.3, M = 333
+//           13.3 / 13.2;  6144 x 4096 M = 100 8.9 / 9.0;  11008 x 4096 M = 200 20.7 / 20.8;  6144 x 1024 M = 100 6.2 / 5.9
+//   W4A8, group scales  4096 x 11008 M = 256 28.1 / 23.3;  4096 x 4096 M = 150 12.1 / 11.4, M = 400 19.1 / 17.3
+//   MXFP4   4096 x 14336 M = 200 17.9 / 16.3;  4096 x 4096 M = 200 7.7 / 6.9, M = 500 11.9 / 10.5;  4096 x 1024 M = 200 4.5 / 4.6
+// Where units lose a little alone, the layer with its quantiser in front does not (6144 x 4096 M = 100 12.7 / 12.3, 11008 x 4096 M = 200
+// 25.8 / 25.4, MXFP4 4096 x 1024 M = 200 7.2 / 7.1): there is no second form for short K.
 //   W4A4    4096 x 14336 M = 333 31.2 / 30.4, but 4096 x 4096 12.6 / 13.3 (few, large units), and with group scales, whose
 //           second accumulators leave too few registers, 4096 x 11008 M = 150 20.1 / 25.2: 4-bit integer tokens keep steps
 #ifndef SERQ_MID_TILE_H_
@@ -299,14 +301,14 @@ struct MidUnits {
 //   product(h, op, k)     the k-th of NP groups of products of the h-th half of the fragments
 //   last()                before the products of the last unit: the place to request what the tile's end needs
 // h, whole: compile-time constants; whole: the unit has all its fragments (false: it is the last one and may lack some;
-// `brief`: it has none in its second half).  Half h takes NLh direct loads.
+// `brief`: it has none in its second half).  Half h takes NLh direct loads.  The first nfull units are whole.
 // Loads requested before the loop are older than its own, so they do not disturb its counting.
 //
 // Everything that depends on how many units are left is decided at compile time: the units behind the steady state are
 // written out one by one.  Control flow between the products lets the compiler sink products and widened codes below it,
 // which keeps the operands of several units alive (up to 50 registers more).
 template <int NS, int NL0, int NL1, int NP, class Op, class Fill, class Read, class Product, class Last>
-__device__ __forceinline__ void mid_unit_loop(int nu, bool brief, const Fill& fill, const Read& read, const Product& product,
+__device__ __forceinline__ void mid_unit_loop(int nu, int nfull, bool brief, const Fill& fill, const Read& read, const Product& product,
                                          const Last& last) {
   static_assert(NS == 2 || NS == 3, "waits");
   using H0 = std::integral_constant<int, 0>;
@@ -321,10 +323,19 @@ __device__ __forceinline__ void mid_unit_loop(int nu, bool brief, const Fill& fi
     constexpr int H = decltype(h_c)::value, BEHIND = decltype(behind_c)::value < NS - 1 ? decltype(behind_c)::value : NS - 1;
     mid_landed<BEHIND >= 2 ? NL0 + NL1 : BEHIND == 1 ? (H ? NL0 : NL1) : 0>();
   };
-  auto start = [&](auto h_c, int u) {                // a whole stage
-    constexpr int H = decltype(h_c)::value;
+  // All loads of a stage, before the first products.  A unit that is whole is fetched as one here too, which is a choice made at run
+  // time: the other form picks the pieces of every lane and fragment, and the first products wait for it.  Instructions up to a
+  // W4A8 wave's 12th load 324 -> 259, MXFP4 375 -> 307; us, r = 128, N x K, weights from HBM: W4A8 4096 x 4096 M = 100 8.9 -> 8.6,
+  // M = 64 8.8 -> 8.5, 6144 x 4096 M = 100 9.4 -> 9.2 (steps: 8.5, 9.4, 9.0), MXFP4 4096 x 1024 M = 200 4.8 -> 4.6 (4.5).
+  auto start = [&](auto h_c, int u) {
+    constexpr int NLS = decltype(h_c)::value ? NL1 : NL0;
+    if (u < nfull) {
 #pragma unroll
-    for (int k = 0; k < (H ? NL1 : NL0); ++k) fill(std::false_type{}, h_c, u, k);
+      for (int k = 0; k < NLS; ++k) fill(std::true_type{}, h_c, u, k);
+    } else {
+#pragma unroll
+      for (int k = 0; k < NLS; ++k) fill(std::false_type{}, h_c, u, k);
+    }
   };
   start(H0{}, 0);
   start(H1{}, 0);

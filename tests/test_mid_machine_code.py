@@ -94,7 +94,8 @@ def _units(form, waves, FU, KB, w):
     return out + [(first, min(per, KB - first))] if first < KB else out
 
 
-def _check(asm, name, M, N, K, r=32):
+def _check(asm, name, M, N, K, r=32, start=None):
+    """start: instructions that a direct load may take, on average, among a wave's first twelve"""
     form, kernel, waves, FU, NS, stage, region = FORMS[name]
     lines, meta = asm
     kernel = _named(lines, kernel)
@@ -117,6 +118,7 @@ def _check(asm, name, M, N, K, r=32):
                 raise AssertionError((*where, str(e))) from None
             # a wait that is not counted by hand empties the ring
             assert not loads or not any(loads[0].at < t < loads[-1].at for t in wave.own_waits), where
+            assert start is None or loads[11].at - loads[0].at <= 11 * start, where
             codes = [ld for ld in loads if ld.buf in ("Xq", "Wq")]
             units = _units(form, waves, FU, KB, w)
             assert len(codes) == len(units) * 2 * (4 + FU), where
@@ -167,6 +169,14 @@ def test_loads(asm, name):
     for left in (0, step, one - step):                     # a last tile of one row, and of nine
         _check(asm, name, 65, 64, 64 * (one + left))
         _check(asm, name, 73, 64, 64 * (one + left))
+
+
+# whole units are fetched without picking pieces and fragments from the first load on (picking takes 11 to 14 instructions a load)
+@pytest.mark.parametrize("name", FORMS)
+def test_start_of_whole_units(asm, name):
+    waves, FU = FORMS[name][2:4]
+    for u in (1, 2, 3, 4):
+        _check(asm, name, 109, 96, 64 * FU * waves * u, start=10)
 
 
 # the kernels that read 4-bit tokens in steps: nothing out of bounds or out of turn, and every fragment is fetched
