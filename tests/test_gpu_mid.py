@@ -76,10 +76,17 @@ def test_g128_layer(abits, in_dtype, out_dtype, M, K, N, r):
     assert torch.equal(Y, Yb)                               # fixed summation order
 
 
-# 8-bit tokens, four groups of 128 channels a round (and eight, with one tile per compute unit at most: here): 1 to 6 units per wave
+# 8-bit tokens, eight waves (one tile per compute unit at most): eight groups of 128 channels a round, 0 to 6 units per wave
 @pytest.mark.parametrize("K", [512, 1024, 1152, 2048, 3072, 4096, 5120, 6144])
 def test_g128_units(K):
     grouped._run(grouped._spec(8, 45, K, 96, 32, in_dtype="fp16", out_dtype="fp32"), R_mode="residual")
+
+
+# 8-bit tokens, four waves (265 tiles): four groups a round, 1 to 9 units per wave, some waves with one more than the others.
+# (That AUTO takes the small-tile kernel here is shown below, at both ends of the range.)
+@pytest.mark.parametrize("K", [512, 640, 1024, 1920, 2048, 2560, 3072, 3712, 4608])
+def test_g128_units_four_waves(K):
+    grouped._run(grouped._spec(8, 300, K, 3360, 160, in_dtype="fp16", out_dtype="fp32"), R_mode="residual")
 
 
 def test_g128_layer_variants():
@@ -89,7 +96,7 @@ def test_g128_layer_variants():
         grouped._run(spec, R_mode="random", s_begin=416)    # salient block elsewhere, not on a group boundary
 
 
-# K: one fragment; a last scale tile of 1, 2 and 3 fragments, alone in its wave and behind others; several compensation fragments
+# K: one fragment; two; a last scale tile that is dealt in halves, alone in a wave and behind others; several compensation fragments
 @pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "bf16"), ("fp16", "fp32"), ("fp16", "fp16")])
 @pytest.mark.parametrize("M,K,N,r", [(33, 64, 32, 32), (65, 128, 96, 0), (100, 448, 64, 96), (200, 4416, 288, 128),
                                      (129, 2688, 1056, 640), (333, 6144, 64, 64), (64, 4160, 160, 256),
@@ -102,8 +109,9 @@ def test_mx_layer(in_dtype, out_dtype, M, K, N, r):
     mx._run_mx(spec, path=serq.PATH_MFMA)
 
 
-# four waves, 1024 channels a round: 1 to 7 units per wave, last units of 1 to 4 fragments, some in the second half of a scale tile
-@pytest.mark.parametrize("K", [512, 1024, 1600, 2048, 3072, 3520, 4096, 5120, 6144, 7168])
+# four waves, 1024 channels a round: 0 to 7 units per wave, last units of 1 to 4 fragments (of 3, the one that lacks a fragment of its
+# second half: K = 704 alone, 1984 and 4800 behind others), some in the second half of a scale tile
+@pytest.mark.parametrize("K", [512, 704, 1024, 1600, 1984, 2048, 3072, 3520, 4096, 4800, 5120, 6144, 7168])
 def test_mx_units(K):
     mx._run_mx(mx._spec(45, K, 96, 32, in_dtype="fp16", out_dtype="fp32"))
 
@@ -166,7 +174,8 @@ def test_auto_takes_the_cheaper_mx_kernel(M, N, K, sliced):
 
 @pytest.mark.parametrize("abits,M,N,K,r,tiled", [
     (8, 256, 4096, 1024, 0, False), (8, 512, 4096, 1024, 0, True), (8, 512, 4096, 1024, 128, False),
-    (8, 768, 4096, 1024, 0, True), (8, 768, 4096, 4096, 128, False), (4, 512, 4096, 4096, 0, False), (4, 768, 4096, 512, 0, True)])
+    (8, 768, 4096, 1024, 0, True), (8, 768, 4096, 4096, 128, False), (4, 512, 4096, 4096, 0, False), (4, 768, 4096, 512, 0, True),
+    (8, 300, 3360, 512, 160, False), (8, 300, 3360, 4608, 160, False)])
 def test_auto_takes_the_cheaper_g128_kernel(abits, M, N, K, r, tiled):
     g = torch.Generator(device=DEV).manual_seed(1)
     X = torch.randn((M, K), device=DEV, generator=g).bfloat16()
