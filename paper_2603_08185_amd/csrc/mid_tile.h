@@ -383,7 +383,7 @@ __device__ __forceinline__ void mid_unit_loop(int nu, int nfull, bool brief, con
         if (LEFT > 0 && k == 0) mid_reads_done();
 #pragma unroll
         for (int d = 0; d < NLR; ++d)
-          if (d * (NP - 1) / NLR == k) fill(whole_req{}, std::integral_constant<int, HR>{}, u + AHEAD, d);
+          if (d * (NP - 1) / (NLR > 0 ? NLR : 1) == k) fill(whole_req{}, std::integral_constant<int, HR>{}, u + AHEAD, d);
         fence();
       }
     };

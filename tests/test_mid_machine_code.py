@@ -21,21 +21,22 @@ FILES = ("gemm_mid.hip", "gemm_mid_mx.hip", "grouped_mid.hip")
 
 @pytest.fixture(scope="module")
 def asm(tmp_path_factory):
-    """{mangled name: lines} of all small-tile kernels, {mangled name: resource figures}"""
+    """{mangled name: lines} of all small-tile kernels, {mangled name: resource figures}, what the compiler had to say"""
     tmp = tmp_path_factory.mktemp("asm")
 
     def one(f):
         out = str(tmp / (f + ".s"))
-        subprocess.run([HIPCC, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, f), "-o", out], check=True,
-                       capture_output=True)
-        return open(out).read()
+        said = subprocess.run([HIPCC, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, f), "-o", out], check=True,
+                              capture_output=True, text=True).stderr
+        return open(out).read(), said
 
-    lines, meta = {}, {}
+    lines, meta, said = {}, {}, ""
     with ThreadPoolExecutor(len(FILES)) as pool:
-        for text in pool.map(one, FILES):
+        for text, err in pool.map(one, FILES):
             lines.update(_isa.kernels(text))
             meta.update(_isa.metadata(text))
-    return lines, meta
+            said += err
+    return lines, meta, said
 
 
 def _named(table, part):
@@ -97,7 +98,7 @@ def _units(form, waves, FU, KB, w):
 def _check(asm, name, M, N, K, r=32, start=None):
     """start: instructions that a direct load may take, on average, among a wave's first twelve"""
     form, kernel, waves, FU, NS, stage, region = FORMS[name]
-    lines, meta = asm
+    lines, meta, _ = asm
     kernel = _named(lines, kernel)
     prog = _isa.program(lines[kernel])
     arg, buf, tm, tn = _call(form, M, N, K, r)
@@ -183,7 +184,7 @@ def test_start_of_whole_units(asm, name):
 @pytest.mark.parametrize("form,kernel,waves", [("int", "serq_mid_kernelILi4ELi2ELi4E", 4), ("g128", "serq_g128_mid_kernelILi4ELb1ELi4E", 4),
                                                ("g128", "serq_g128_mid_kernelILi4ELb1ELi8E", 8)])
 def test_step_loads(asm, form, kernel, waves):
-    lines, meta = asm
+    lines, meta, _ = asm
     kernel = _named(lines, kernel)
     prog = _isa.program(lines[kernel])
     for KB in (1, 2, 3, 7, 8, 9, 16, 17, 31, 34, 63, 64, 86):
@@ -204,3 +205,7 @@ def test_step_loads(asm, form, kernel, waves):
 def test_registers_suffice(asm):
     for name, m in asm[1].items():
         assert m["private_segment_fixed_size"] == 0 and m["vgpr_spill_count"] == 0 and m["sgpr_spill_count"] == 0, (name, m)
+
+
+def test_no_warnings(asm):
+    assert "warning:" not in asm[2], asm[2]
