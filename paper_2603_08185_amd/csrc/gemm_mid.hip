@@ -90,7 +90,8 @@ void serq_mid_kernel(const MidParams p) {
   if constexpr (ABITS == 8) {
     const int xsw = mid_swz128(lm);
     auto slot = [&](int h, int u) { return (2 * u + h) % NS * T::STAGE; };
-    auto read = [&](auto whole_c, auto h_c, int u, MidUnitOp& o) {
+    // (the second fragment of a unit that has but one is not multiplied: `brief`)
+    auto read = [&](auto, auto h_c, int u, MidUnitOp& o) {
       constexpr int H = decltype(h_c)::value;
       const uint8_t* s = my + slot(H, u);
 #pragma unroll
@@ -100,7 +101,6 @@ void serq_mid_kernel(const MidParams p) {
         const int c = 4 * (q >> 1) + 2 * g + (q & 1);
         o.x[H][q] = *(const u4*)(s + lm * 128 + 16 * (c ^ xsw));
       }
-      if constexpr (!decltype(whole_c)::value) o.w[H][1] &= 1 < ld.frags(u) ? ~0u : 0u;   // no second fragment: zero weights
     };
     // group k of half h: token block k % 2 and channel block k / 2 of fragment h
     auto product = [&](auto h_c, const MidUnitOp& o, int k) {

@@ -112,11 +112,7 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) 
       for (int v = 0; v < VH; ++v) lzm[v] = p.zero ? p.zero[lr_m(v)] : 0;
     }
   };
-  if (ABITS == 4 && JB > 0) {
-    lr_fetch(0);
-#pragma unroll
-    for (int v = 0; v < VH; ++v) lzm[v] = p.zero ? p.zero[lr_m(v)] : 0;
-  }
+  if (ABITS == 4) lr_first();
 
   // ---- main loop ------------------------------------------------------------------------------------------------
   v16i acc[2][2];
