@@ -342,18 +342,19 @@ void serq_mid_kernel(const MidParams p) {
 // Up to three tiles per compute unit, four with 4-bit tokens, as far as that is the cheaper kernel (mid_cheaper): the larger
 // tiles of the tiled kernel move half the bytes per product, and with a long K its slices fill the chip too.  Measured
 // (us, tiled kernel / this one, r = 128, N x K, weights from HBM; in brackets: tiles of the busiest compute unit):
-//   W4A8  4096 x 4096 M = 256 (1) 26.4 / 11.5, M = 512 (2) 27 / 17, M = 768 (3) 26.6 / 24;  4096 x 14336 M = 256 (1) 36 / 29,
-//         M = 512 (2) 49 / 53, M = 768 (3) 73 / 69;  11008 x 14336 M = 100 (2) 80 / 51, M = 192 (3) 58 / 72 (to the tiled kernel);
-//         4096 x 28672 M = 256 (1) 54.5 / 55.7, M = 512 (2) 75 / 101 (to the tiled kernel)
+//   W4A8  4096 x 4096 M = 256 (1) 26.4 / 10.1, M = 512 (2) 25.4 / 16.4, M = 768 (3) 26.9 / 22.7;  4096 x 14336 M = 256 (1) 36.2 / 26.2,
+//         M = 512 (2) 49.6 / 45.8, M = 768 (3) 78.6 / 63.7;  11008 x 14336 M = 100 (2) 78 / 43, M = 192 (3) 59.7 / 58.4, from the
+//         last-level cache 55.9 / 51.2 (to the tiled kernel);  11008 x 11008 M = 192 (3) 49.0 / 46.2;  4096 x 17408 M = 384 (2) 52.7 / 50.1;
+//         4096 x 28672 M = 256 (1) 54.7 / 47.8, M = 512 (2) 74.5 / 82.7 (to the tiled kernel)
 //   W4A4  4096 x 4096 M = 1024 (4) 26 / 24;  4096 x 14336 M = 1024 (4) 67 / 63;  11008 x 28672 M = 256 (3) 92 / 102, weights
 //         from the last-level cache 93 / 87
 // Ranks up to 1024 do not move the line: both kernels pay alike for them.
 bool mid_wanted(const LinearArgs& a) {
-  static constexpr MidPrice small8 = {{2.98f, 1.32f, 0.17f, 0.86f, 0.55f, 0.06f}}, small4 = {{3.02f, 1.66f, 0.17f, 0.53f, 0.40f, 0.07f}};
+  static constexpr MidPrice small8 = {{2.82f, 1.58f, 0.17f, 0.73f, 0.50f, 0.05f}}, small4 = {{3.02f, 1.66f, 0.17f, 0.53f, 0.40f, 0.07f}};
   static constexpr TiledPrice tiled8 = {{8.15f, 2.74f, 0.83f, 3.26f, 8.33f, 0.83f}}, tiled4 = {{8.66f, 2.25f, 0.94f, 0.0f, 6.69f, 0.61f}};
   const size_t skip = skinny_workspace_bytes(a.N);
   const size_t have = a.workspace && a.workspace_bytes > skip ? a.workspace_bytes - skip : 0;
-  return a.abits == 8 ? mid_cheaper(small8, tiled8, a.M, a.N, a.K, 8, 3, 0.97f, have)
+  return a.abits == 8 ? mid_cheaper(small8, tiled8, a.M, a.N, a.K, 8, 3, 1.02f, have)
                       : mid_cheaper(small4, tiled4, a.M, a.N, a.K, 4, 4, 0.93f, have);
 }
 

@@ -203,11 +203,12 @@ void serq_mx_mid_kernel(const MxMidParams p) {
 
 // Up to four tiles per compute unit, as far as that is the cheaper kernel (mid_cheaper).  Measured (us, tiled kernel / this
 // one, r = 128, N x K, weights from HBM; in brackets: tiles of the busiest compute unit):
-//   4096 x 4096 M = 256 (1) 20.5 / 8.6, M = 512 (2) 21 / 13.5, M = 768 (3) 23.6 / 19, M = 1024 (4) 24.1 / 24.4;
-//   4096 x 14336 M = 256 (1) 36 / 23, M = 512 (2) 46 / 38.5, M = 768 (3) 67 / 50;  11008 x 14336 M = 100 (2) 46 / 40, M = 256
-//   (3) 52 / 57, weights from the last-level cache 46 / 44;  11008 x 20480 M = 256 (3) 68 / 81 (to the tiled kernel);  4096 x 28672 M = 256 (1) 48.5 / 41.5, M = 512 (2) 59 / 70 (to the tiled kernel)
-// Workgroups of 8 waves, one to a compute unit: 4096 x 4096 M = 256 8.9 against 8.5, M = 512 15.4 against 12.4; 4096 x 11008
-// M = 768 42.0 against 35.9.
+//   4096 x 4096 M = 256 (1) 20.8 / 7.6, M = 512 (2) 20.7 / 12.0, M = 768 (3) 21.2 / 15.2, M = 1024 (4) 22.1 / 19.1;
+//   4096 x 14336 M = 256 (1) 35.8 / 20.0, M = 512 (2) 46.5 / 32.7, M = 768 (3) 68 / 46;  11008 x 14336 M = 100 (2) 46 / 34, M = 256
+//   (3) 51.5 / 48.6, weights from the last-level cache 46.9 / 36.8;  11008 x 20480 M = 256 (3) 67.4 / 68.8 (to the tiled kernel; from the
+//   last-level cache 60.8 / 51.2);  4096 x 28672 M = 256 (1) 47.9 / 35.4, M = 512 (2) 57.9 / 60.4 (to the tiled kernel; 53.4 / 48.7)
+// Workgroups of 8 waves, one to a compute unit, with 64-byte token rows: 4096 x 4096 M = 256 8.9 against 8.5, M = 512 15.4 against 12.4;
+// 4096 x 11008 M = 768 42.0 against 35.9.
 bool mx_mid_wanted(const MxLinearArgs& a) {
   static constexpr MidPrice small = {{2.45f, 1.17f, 0.22f, 0.52f, 0.39f, 0.06f}};
   static constexpr TiledPrice tiled = {{6.65f, 3.09f, 0.42f, 0.83f, 9.38f, 0.37f}};

@@ -321,22 +321,25 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) 
 // Else by prices as in mid_tile.h, which know the rank here, because the tiled kernel pays more for it:
 //   small tiles  c0 + c1 R + K/1024 (c2 + c3 R + c4 y) + c5 (MB of weight codes) + r/128 (c6 + c7 R)
 //   tiled        d0 + d1 K/1024 (halves of tiles) or d2 K/1024 (whole ones) + d3 (r > 0) + d4 r/128
-// fitted to 800 launches with an error of 4 to 5 % (three tiles per compute unit are at most one round of the tiled kernel).
+// fitted to 800 launches with an error of 4 to 5 % (three tiles per compute unit are at most one round of the tiled kernel); 8-bit tokens'
+// small-tile price to 367 layers of the kernel with whole-line token rows, 7 % (of 288 layers of two and three tiles, 5 would be more than
+// 3 % faster in the other kernel; with the price of 64-byte rows 13, by up to 16 %).
 // Measured (us, tiled kernel / this one, N x K, weights from HBM; in brackets: tiles of the busiest compute unit):
-//   W4A8 r = 128  4096 x 4096 M = 256 (1) 22.6 / 13, M = 512 (2) 23.2 / 21, M = 768 (3) 33.6 / 31.6;  11008 x 14336 M = 128 (2)
-//        61 / 67, from the last-level cache 61 / 52
-//   r = 0  4096 x 1024 M = 512 (2) 8.7 / 9.4, M = 768 (3) 11.3 / 14.2 (both to the tiled kernel);  4096 x 4096 M = 768 (3)
-//        29 / 30
+//   W4A8 r = 128  4096 x 4096 M = 256 (1) 23.1 / 13.4, M = 512 (2) 23.0 / 21.9, M = 768 (3) 33.4 / 28.2;  11008 x 14336 M = 128 (2)
+//        59.5 / 53.3;  15968 x 6144 M = 128 (2) 32.6 / 28.7
+//   r = 0  4096 x 1024 M = 512 (2) 8.5 / 8.8, M = 768 (3) 11.3 / 13.6 (both to the tiled kernel);  4096 x 4096 M = 768 (3)
+//        29.4 / 28.1;  8096 x 5120 M = 192 (2) 23.7 / 21.7
 //   W4A4 r = 128  4096 x 14336 M = 512 (2) 62 / 43, M = 768 (3) 96 / 62;  4096 x 768 M = 768 (3) level
 bool g128_mid_wanted(const G128Args& a, int abits) {
   const int ncu = device_cu_count();
   const long long rounds = mid_rounds(a.M, a.N, ncu);
   if (rounds > 3) return false;
   if (rounds == 1 || (rounds == 2 && abits == 4)) return true;
-  static constexpr MidPrice small8 = {{2.68f, 2.14f, 0.36f, 0.90f, 0.65f, 0.06f}}, small4 = {{2.64f, 2.28f, 0.27f, 0.80f, 0.34f, 0.05f}};
+  static constexpr MidPrice small8 = {{2.28f, 2.24f, 0.11f, 0.81f, 0.60f, 0.07f}}, small4 = {{2.64f, 2.28f, 0.27f, 0.80f, 0.34f, 0.05f}};
   const long long tiles = ((long long)a.M + 127) / 128 * ((a.N + 127) / 128);
   const float k = a.K / 1024.0f, r = a.r / 128.0f;
-  const float small = mid_price(abits == 8 ? small8 : small4, a.M, a.N, a.K, ncu) + r * (0.35f + 0.49f * rounds);
+  const float small = abits == 8 ? mid_price(small8, a.M, a.N, a.K, ncu) + r * (0.69f + 0.31f * rounds)
+                                 : mid_price(small4, a.M, a.N, a.K, ncu) + r * (0.35f + 0.49f * rounds);
   const float tiled = 4.6f + k * (2 * tiles <= ncu ? (abits == 8 ? 3.65f : 3.80f) : (abits == 8 ? 6.1f : 6.4f)) +
                       (a.r > 0 ? 0.31f : 0.0f) + r * 3.45f;
   return 0.97f * small < tiled;

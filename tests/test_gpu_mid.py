@@ -138,7 +138,8 @@ def _trace(ws, words):
 @pytest.mark.parametrize("abits,M,N,K,sliced", [
     (8, 512, 4096, 8192, False), (8, 512, 4096, 28672, True),        # two tiles per compute unit: the larger tiles from a long K on
     (8, 256, 4096, 28672, False),                                    # one tile per compute unit
-    (8, 192, 11008, 4096, False), (8, 192, 11008, 14336, True),      # three
+    (8, 384, 4096, 17408, False), (8, 192, 8192, 15616, False),
+    (8, 192, 11008, 4096, False), (8, 192, 11008, 11008, False), (8, 192, 11008, 14336, True),      # three
     (8, 512, 2560, 28672, False),                                    # never slices that a wider layer's decode words could lie in
     (4, 512, 4096, 28672, False), (4, 256, 11008, 28672, False)])
 def test_auto_takes_the_cheaper_kernel(abits, M, N, K, sliced):
@@ -175,7 +176,8 @@ def test_auto_takes_the_cheaper_mx_kernel(M, N, K, sliced):
 @pytest.mark.parametrize("abits,M,N,K,r,tiled", [
     (8, 256, 4096, 1024, 0, False), (8, 512, 4096, 1024, 0, True), (8, 512, 4096, 1024, 128, False),
     (8, 768, 4096, 1024, 0, True), (8, 768, 4096, 4096, 128, False), (4, 512, 4096, 4096, 0, False), (4, 768, 4096, 512, 0, True),
-    (8, 300, 3360, 512, 160, False), (8, 300, 3360, 4608, 160, False)])
+    (8, 300, 3360, 512, 160, False), (8, 300, 3360, 4608, 160, False),
+    (8, 192, 8096, 5120, 0, False), (8, 128, 14144, 13440, 64, False), (8, 128, 15968, 6144, 128, False)])
 def test_auto_takes_the_cheaper_g128_kernel(abits, M, N, K, r, tiled):
     g = torch.Generator(device=DEV).manual_seed(1)
     X = torch.randn((M, K), device=DEV, generator=g).bfloat16()
