@@ -1,17 +1,23 @@
 // SERQ linear layer for batches between decode and prefill: the integer layer of gemm_mfma.hip in tiles of
-// 64 tokens x 64 channels, the 4 or 8 waves of a workgroup sharing K (mid_tile.h says why).
+// 64 tokens x 64 channels, the 4 waves of a workgroup sharing K (mid_tile.h says why).
 //   Y[m,n] = scale[m] * ( wscale[n] * sum_k Xq[m,k] Wq[n,k] + sum_j Xq[m,S_j] R[j,n] )
 //
-// The waves' INT32 partial tiles meet in LDS once: each wave sums one MFMA tile (4 waves) or half of one (8) over the
-// waves -- integer addition, the same bits as the tiled kernel -- scales it and adds the rank-r term with the matrix unit on
-// top, exactly as the tiled kernel does.
+// The waves' INT32 partial tiles meet in LDS once: each wave sums one MFMA tile over the waves -- integer addition, the same
+// bits as the tiled kernel -- scales it and adds the rank-r term with the matrix unit on top, exactly as the tiled kernel does.
 //
-// What bounds it: with 8-bit tokens at M = 256, N = 4096, K = 11008 the kernel takes 20.1 us (23.1 with 64-byte token rows); the
+// What bounds it: with 8-bit tokens at M = 256, N = 4096, K = 11008 the kernel takes 20.5 us (23.1 with 64-byte token rows); the
 // same load stream without products, launch included, 12.6 us (at K = 11264), the matrix unit alone 6.  The rest is the start
 // and the end of a tile and what the two do not overlap.  Fixed costs: 4 us at K = 256, r = 0 in a graph, 1 us more for r = 128.
 // The tiled kernel with 4 K slices and a second launch takes 32 us there; M = 100, 6144 x 4096: 9.0 against 24.4 us.
 // The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.  Rings of twice the depth where a workgroup has
 // a compute unit to itself: 9.3 -> 10.0 us at M = 100, 6144 x 4096 (the first stage lands behind all the others' requests).
+//
+// Two workgroups share a compute unit: one's start and end run beside the other's main loop.  Workgroups of 8 waves that have one to
+// themselves keep more loads in flight, which pays no more since the loads are whole lines: us, 8 / 4 waves, W4A8, r = 128, N x K, one tile
+// per compute unit at most: 4096 x 11008 M = 100 18.2 / 18.1, M = 256 20.9 / 20.5; 4096 x 9216 M = 150 14.0 / 13.2; 4096 x 14336 M = 256
+// 25.8 / 24.5; 16384 x 11008 M = 64 23.7 / 24.1; 4096 x 4096 M = 100 9.6 / 9.1; the one length where 8 waves are better is K = 2048, whose
+// units come out even: 4096 x 2048 M = 100 6.9 / 7.3 (4096 x 1536 7.2 / 6.9, 4096 x 2560 8.5 / 7.9).  More tiles: 4096 x 4096
+// M = 333 17.7 / 14.3.
 #include "mid_tile.h"
 
 namespace serq {
@@ -28,37 +34,31 @@ struct MidParams {
   int tiles_m, tiles_n, band;
 };
 
-template <int ABITS, int NW>
+constexpr int NW = 4;                                // waves of a workgroup
+
+template <int ABITS>
 struct Mid {
   static constexpr int STAGE = kMidX + (ABITS == 8 ? 2 : 4) * 1024;   // 6 KiB: half a unit / 8 KiB: a step
   static constexpr int NS = ABITS == 8 ? 3 : 2;
   static constexpr int NL = ABITS == 8 ? 6 : 8;      // direct loads of a stage
   static constexpr int REGION = NS * STAGE;          // LDS of one wave: 18 KiB / 16 KiB
   static constexpr int SH = ABITS == 8 ? 4 : 8;
-  // The rank-r term in chunks of 128 ranks.  8 waves: the R fragments that wave w brings lie behind its own partial tile
-  // (the ring leaves 2 KiB there), the token codes behind the rings.  4 waves: both take the place of the partial tiles once
-  // those have been added.
-  static constexpr bool LATE = NW == 4;
-  static constexpr int LRR_STEP = LATE ? 2048 : REGION;
-  static constexpr int LRR_OFF = LATE ? 0 : kMidPart;
-  static __device__ __forceinline__ int lr_frag(bool per_wave_1, int f) {
-    return LRR_OFF + (per_wave_1 ? f * LRR_STEP : (f >> 1) * LRR_STEP + (f & 1) * 1024);
-  }
-  static constexpr int LRX_OFF = LATE ? 16 * 1024 : NW * REGION;
-  static constexpr int LDS = LATE ? NW * REGION : LRX_OFF + 64 * 256;
+  // The rank-r term in chunks of 128 ranks: 16 R fragments (4-bit R: 4) and behind them the token codes take the place of the
+  // partial tiles once those have been added.
+  static constexpr int LRX_OFF = 16 * 1024;
+  static constexpr int LDS = NW * REGION;
   static_assert(REGION >= kMidPart, "a partial tile fits the ring it replaces");
-  static_assert(LATE || REGION - kMidPart >= 2048, "two R fragments fit behind it");
-  static_assert(!LATE || LDS >= LRX_OFF + 64 * 256, "the rank-r operands fit the rings");
-  static_assert(LDS * (8 / NW) <= 160 * 1024, "LDS budget");
+  static_assert(LDS >= LRX_OFF + 64 * 256, "the rank-r operands fit the rings");
+  static_assert(2 * LDS <= 160 * 1024, "LDS budget: two workgroups");
 };
 
 struct MidUnitOp { u4 w[2][2], x[2][4]; };           // w: [channel block][fragment], x: [token block][2 * fragment + K half]
 struct MidStepOp { u4 w[2][2], x[2][2]; };           // x: [token block][fragment]
 
-template <int ABITS, int LRT, int NW>
+template <int ABITS, int LRT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void serq_mid_kernel(const MidParams p) {
-  using T = Mid<ABITS, NW>;
+  using T = Mid<ABITS>;
   constexpr int NS = T::NS;
   __shared__ __align__(16) uint8_t lds[T::LDS];
   const int tid = threadIdx.x, l = tid & 63, lm = l & 31, g = l >> 5;
@@ -152,11 +152,9 @@ void serq_mid_kernel(const MidParams p) {
   }
 
   // ---- what the end of the tile needs from memory, requested before the waves meet ------------------------------
-  // 8 waves: wave w finishes registers 8*(w%2) .. +7 of MFMA tile (i, j), w/2 = 2*i + j; 4 waves: all of tile w = 2*i + j
-  constexpr int QN = 16 / NW;                         // register quads
-  constexpr int NE = 4 * QN;
-  const int tt = NW == 8 ? w >> 1 : w;
-  const int ti = tt >> 1, tj = tt & 1, hq = NW == 8 ? 2 * (w & 1) : 0;
+  // Wave w finishes MFMA tile (i, j), w = 2*i + j.
+  constexpr int QN = 4, NE = 4 * QN;                  // register quads, registers
+  const int ti = w >> 1, tj = w & 1;
   const int blk = nb0 + (ti < nbt ? ti : 0);          // (a block past the layer repeats the first and is not stored)
   const int mloc = 32 * tj + lm;
   const int m = m0 + (mloc < mrows ? mloc : mrows - 1);
@@ -165,10 +163,10 @@ void serq_mid_kernel(const MidParams p) {
   constexpr bool bf = LRT != SERQ_F16;
   const int JB = p.acc_out ? 0 : (lr_int ? (p.r + 63) >> 6 : p.r >> 4);   // fragments of R per channel block
   constexpr int NJ = lr_int ? 2 : 8;                  // of which a chunk holds so many
-  // A chunk of the rank-r term: every wave brings 2 (4-bit R: waves 0..3, one) of its R fragments and 16 codes of 8 token
-  // rows per lane; 16-bit R takes the codes as exact 16-bit floats, converted once here instead of by every wave
-  // that multiplies them.
-  constexpr int VH = 8 / NW;                          // (a wave of 4 brings the shares of two of 8)
+  // A chunk of the rank-r term is dealt out in 8 shares, two to a wave: 2 of its R fragments (4-bit R: one, shares 0..3) and
+  // 16 codes of 8 token rows per lane; 16-bit R takes the codes as exact 16-bit floats, converted once here instead of by
+  // every wave that multiplies them.
+  constexpr int VH = 8 / NW;
   u4 lrr[VH][2], lrx[VH];
   auto lr_fetch = [&](int jb0) {
 #pragma unroll
@@ -199,7 +197,7 @@ void serq_mid_kernel(const MidParams p) {
 #pragma unroll
     for (int q = 0; q < (lr_int ? 1 : 2); ++q) {
       const int f = lr_int ? (vw & 3) : 2 * vw + q;
-      if (!lr_int || vw < 4) *(u4*)(lds + T::lr_frag(lr_int, f) + l * 16) = lrr[v][q];
+      if (!lr_int || vw < 4) *(u4*)(lds + f * 1024 + l * 16) = lrr[v][q];
     }
     uint8_t* row = lds + T::LRX_OFF + lrow * 256;
     const int c = l & 7;                              // 16 channels
@@ -225,7 +223,7 @@ void serq_mid_kernel(const MidParams p) {
     sm = p.scale[m];
 #pragma unroll
     for (int q = 0; q < QN; ++q) {
-      const int n = 32 * blk + 8 * (hq + q) + 4 * g;
+      const int n = 32 * blk + 8 * q + 4 * g;
       const float4 v = *(const float4*)(p.wscale + n);
       wsc[4 * q] = v.x * kInv; wsc[4 * q + 1] = v.y * kInv; wsc[4 * q + 2] = v.z * kInv; wsc[4 * q + 3] = v.w * kInv;
       if (lr_int && JB > 0) {
@@ -244,8 +242,6 @@ void serq_mid_kernel(const MidParams p) {
       for (int q = 0; q < 4; ++q)
         *(v4i*)(my + ((2 * i + j) * 4 + q) * 1024 + l * 16) =
             v4i{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-  // (8-bit: the R fragments land in stages of this and of no other wave, which has read them all)
-  if (JB > 0 && !T::LATE) lr_park();
   __syncthreads();
   int tot[NE];
 #pragma unroll
@@ -254,12 +250,12 @@ void serq_mid_kernel(const MidParams p) {
   for (int ww = 0; ww < NW; ++ww)
 #pragma unroll
     for (int q = 0; q < QN; ++q) {
-      const v4i v = *(const v4i*)(lds + ww * T::REGION + (tt * 4 + hq + q) * 1024 + l * 16);
+      const v4i v = *(const v4i*)(lds + ww * T::REGION + (w * 4 + q) * 1024 + l * 16);
       tot[4 * q] += v.x; tot[4 * q + 1] += v.y; tot[4 * q + 2] += v.z; tot[4 * q + 3] += v.w;
     }
 
   const bool live = mloc < mrows && ti < nbt;
-  const int n = 32 * blk + 8 * hq + 4 * g;             // registers 4*q + e: channel n + 8*q + e
+  const int n = 32 * blk + 4 * g;                      // registers 4*q + e: channel n + 8*q + e
   if (p.acc_out) {
     if (live) {
 #pragma unroll
@@ -274,13 +270,11 @@ void serq_mid_kernel(const MidParams p) {
   for (int e = 0; e < NE; ++e) y[e] = wsc[e] * (float)tot[e];
   v16f af;                                            // 16-bit R: the tile the matrix unit adds to
 #pragma unroll
-  for (int e = 0; e < 16; ++e) af[e] = NW == 4 ? y[e % NE] : (e >> 3) == (hq >> 1) ? y[e & 7] : 0.0f;
+  for (int e = 0; e < 16; ++e) af[e] = y[e];
   for (int jb0 = 0; jb0 < JB; jb0 += NJ) {
-    if (jb0 > 0 || T::LATE) {                          // (the loads of this chunk were requested a chunk ago)
-      __syncthreads();
-      lr_park();
-      __syncthreads();
-    }
+    __syncthreads();                                   // (the loads of this chunk were requested a chunk ago)
+    lr_park();
+    __syncthreads();
     if (jb0 + NJ < JB) lr_fetch(jb0 + NJ);
     const uint8_t* row = lds + T::LRX_OFF + mloc * 256;
     auto piece = [&](int c) { return *(const u4*)(row + 16 * (c ^ (mloc & 15))); };
@@ -288,7 +282,7 @@ void serq_mid_kernel(const MidParams p) {
     for (int q = 0; q < NJ; ++q) {
       if (jb0 + q < JB) {                              // uniform
         const int f = ti * NJ + q;
-        const u4 rr = *(const u4*)(lds + T::lr_frag(lr_int, f) + l * 16);
+        const u4 rr = *(const u4*)(lds + f * 1024 + l * 16);
         if constexpr (lr_int) {
           v4i a0, a1, b0, b1;
           unpack_frag(rr, a0, a1);
@@ -304,7 +298,7 @@ void serq_mid_kernel(const MidParams p) {
           tq = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, tq, 0, 0, 0);
           tq = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, tq, 0, 0, 0);
 #pragma unroll
-          for (int e = 0; e < NE; ++e) y[e] = __builtin_fmaf(rsc[e], (float)(NW == 4 ? tq[e] : hq ? tq[(8 + e) & 15] : tq[e]), y[e]);
+          for (int e = 0; e < NE; ++e) y[e] = __builtin_fmaf(rsc[e], (float)tq[e], y[e]);
         } else {
           const u4 xf = piece(2 * q + g);
           if constexpr (bf)
@@ -317,7 +311,7 @@ void serq_mid_kernel(const MidParams p) {
   }
   if constexpr (!lr_int) {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) y[e] = NW == 4 ? af[e] : hq ? af[(8 + e) & 15] : af[e];
+    for (int e = 0; e < NE; ++e) y[e] = af[e];
   }
 #pragma unroll
   for (int e = 0; e < NE; ++e) y[e] *= sm;
@@ -332,7 +326,7 @@ void serq_mid_kernel(const MidParams p) {
   }
   __syncthreads();                                     // every wave has read the partial tiles: the rows take their place
 #pragma unroll
-  for (int q = 0; q < QN; ++q) mid_park16(lds, mloc, 4 * ti + hq + q, g, y + 4 * q, p.y_dtype == SERQ_BF16);
+  for (int q = 0; q < QN; ++q) mid_park16(lds, mloc, 4 * ti + q, g, y + 4 * q, p.y_dtype == SERQ_BF16);
   __syncthreads();
   mid_store16<64 * NW>(lds, tid, (uint16_t*)p.Y, p.ldy, m0, mrows, 32 * nb0, nbt);
 }
@@ -372,27 +366,15 @@ int launch_mid(const LinearArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n));
   const bool has_lr = p.r > 0 && p.acc_out == nullptr;
   const int lrt = !has_lr ? SERQ_BF16 : a.r_dtype;
-  // Workgroups of 4 waves, two of which share a compute unit: one's start and end run beside the other's main loop, and
-  // fewer partial tiles meet.  Only where there is at most one tile per compute unit (and one for most), K is long
-  // and the stages are the small ones of 8-bit tokens, 8 waves keep more loads in flight.  Measured (us, 8 / 4 waves, W4A8
-  // r = 128, N x K; 64-byte token rows then): 4096 x 4096 M = 100 9.4 / 8.6, M = 333 17.0 / 14.0; 4096 x 8192 M = 100 12.8 / 11.6, M = 256
-  // 14.8 / 14.8; 4096 x 11008 M = 40 15.9 / 14.8, M = 100 16.7 / 17.7, M = 256 19.9 / 21.1, M = 333 36.1 / 30.1; W4A4
-  // 4096 x 11008 M = 100 13.8 / 14.0, M = 256 16.2 / 15.3, M = 333 27.7 / 23.2.
-  const int ncu = device_cu_count();
-  const bool eight = a.abits == 8 && a.K > 8192 && (int)grid.x <= ncu && 2 * (int)grid.x >= ncu;
-#define SERQ_MID_LAUNCH(AB, LRT, NW) hipLaunchKernelGGL((serq_mid_kernel<AB, LRT, NW>), grid, dim3(64 * NW), 0, st, p)
-  if (eight) {
-    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(8, SERQ_I4, 8);
-    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(8, SERQ_F16, 8);
-    else SERQ_MID_LAUNCH(8, SERQ_BF16, 8);
-  } else if (a.abits == 8) {
-    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(8, SERQ_I4, 4);
-    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(8, SERQ_F16, 4);
-    else SERQ_MID_LAUNCH(8, SERQ_BF16, 4);
+#define SERQ_MID_LAUNCH(AB, LRT) hipLaunchKernelGGL((serq_mid_kernel<AB, LRT>), grid, dim3(64 * NW), 0, st, p)
+  if (a.abits == 8) {
+    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(8, SERQ_I4);
+    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(8, SERQ_F16);
+    else SERQ_MID_LAUNCH(8, SERQ_BF16);
   } else {
-    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(4, SERQ_I4, 4);
-    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(4, SERQ_F16, 4);
-    else SERQ_MID_LAUNCH(4, SERQ_BF16, 4);
+    if (lrt == SERQ_I4) SERQ_MID_LAUNCH(4, SERQ_I4);
+    else if (lrt == SERQ_F16) SERQ_MID_LAUNCH(4, SERQ_F16);
+    else SERQ_MID_LAUNCH(4, SERQ_BF16);
   }
 #undef SERQ_MID_LAUNCH
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;

@@ -20,7 +20,7 @@ SHAPES = [
     (200, 4160, 160, 144),       # two chunks of the rank-r term, the second ragged
     (129, 2560, 1056, 320),
     (333, 6144, 64, 64),
-    (70, 8256, 4096, 32),        # half of the compute units and a long K: eight waves for 8-bit tokens
+    (70, 8256, 4096, 32),        # half of the compute units and a long K
     (70, 8256, 4096, 208),       # ... and a second chunk of the rank-r term, whose operands replace the first one's
     (400, 1024, 5152, 208),      # three tiles for the busiest compute unit
     (1100, 4096, 96, 32),        # 8-bit token codes beyond 4 MiB: token tiles in bands, 6 + 6 + 6

@@ -47,8 +47,7 @@ def _named(table, part):
 
 # form, kernel, waves, fragments of a unit, stages of the ring, bytes of a stage and of a wave's region
 FORMS = {
-    "int8, 4 waves": ("int", "serq_mid_kernelILi8ELi2ELi4E", 4, 2, 3, 6144, 18432),
-    "int8, 8 waves": ("int", "serq_mid_kernelILi8ELi2ELi8E", 8, 2, 3, 6144, 18432),
+    "int8": ("int", "serq_mid_kernelILi8ELi2EE", 4, 2, 3, 6144, 18432),
     "mxfp4": ("mx", "serq_mx_mid_kernel", 4, 4, 2, 8192, 17408),
     "g128 int8, 4 waves": ("g128", "serq_g128_mid_kernelILi8ELb1ELi4E", 4, 2, 3, 6400, 19200),
     "g128 int8, 8 waves": ("g128", "serq_g128_mid_kernelILi8ELb1ELi8E", 8, 2, 3, 6400, 19200),
@@ -181,7 +180,7 @@ def test_start_of_whole_units(asm, name):
 
 
 # the kernels that read 4-bit tokens in steps: nothing out of bounds or out of turn, and every fragment is fetched
-@pytest.mark.parametrize("form,kernel,waves", [("int", "serq_mid_kernelILi4ELi2ELi4E", 4), ("g128", "serq_g128_mid_kernelILi4ELb1ELi4E", 4),
+@pytest.mark.parametrize("form,kernel,waves", [("int", "serq_mid_kernelILi4ELi2EE", 4), ("g128", "serq_g128_mid_kernelILi4ELb1ELi4E", 4),
                                                ("g128", "serq_g128_mid_kernelILi4ELb1ELi8E", 8)])
 def test_step_loads(asm, form, kernel, waves):
     lines, meta, _ = asm
