@@ -336,10 +336,10 @@ void serq_mid_kernel(const MidParams p) {
 // Up to three tiles per compute unit, four with 4-bit tokens, as far as that is the cheaper kernel (mid_cheaper): the larger
 // tiles of the tiled kernel move half the bytes per product, and with a long K its slices fill the chip too.  Measured
 // (us, tiled kernel / this one, r = 128, N x K, weights from HBM; in brackets: tiles of the busiest compute unit):
-//   W4A8  4096 x 4096 M = 256 (1) 26.4 / 10.1, M = 512 (2) 25.4 / 16.4, M = 768 (3) 26.9 / 22.7;  4096 x 14336 M = 256 (1) 36.2 / 26.2,
+//   W4A8  4096 x 4096 M = 256 (1) 26.4 / 10.1, M = 512 (2) 25.4 / 16.4, M = 768 (3) 26.9 / 22.7;  4096 x 14336 M = 256 (1) 34.7 / 24.6,
 //         M = 512 (2) 49.6 / 45.8, M = 768 (3) 78.6 / 63.7;  11008 x 14336 M = 100 (2) 78 / 43, M = 192 (3) 59.7 / 58.4, from the
 //         last-level cache 55.9 / 51.2 (to the tiled kernel);  11008 x 11008 M = 192 (3) 49.0 / 46.2;  4096 x 17408 M = 384 (2) 52.7 / 50.1;
-//         4096 x 28672 M = 256 (1) 54.7 / 47.8, M = 512 (2) 74.5 / 82.7 (to the tiled kernel)
+//         4096 x 28672 M = 256 (1) 51.6 / 45.9, M = 512 (2) 74.5 / 82.7 (to the tiled kernel)
 //   W4A4  4096 x 4096 M = 1024 (4) 26 / 24;  4096 x 14336 M = 1024 (4) 67 / 63;  11008 x 28672 M = 256 (3) 92 / 102, weights
 //         from the last-level cache 93 / 87
 // Ranks up to 1024 do not move the line: both kernels pay alike for them.

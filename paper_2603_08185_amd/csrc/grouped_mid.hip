@@ -352,8 +352,8 @@ int launch_g128_mid(const G128Args& a, int abits, hipStream_t st) {
   const int band = mid_band(tm, (long long)a.M * a.K * abits / 8);
   // One tile per compute unit at most: 8 waves, which the folds need to keep the vector units busy.  More tiles: workgroups
   // of 4 waves, two of which share a compute unit, so that one's start and end run beside the other's main loop.
-  // Measured (us, 8 / 4 waves, r = 128, N x K): W4A8 4096 x 11008 M = 100 21.6 / 23.8, M = 333 44.9 / 36.7; 6144 x 4096
-  // M = 100 13.0 / 13.3, M = 256 24.0 / 19.7; W4A4 4096 x 11008 M = 150 19.4 / 21.3, M = 333 35.8 / 32.0.
+  // Measured (us, 8 / 4 waves, r = 128, N x K): W4A8 4096 x 11008 M = 100 21.9 / 23.3, M = 333 41.2 / 35.4; 6144 x 4096
+  // M = 100 12.2 / 13.0, M = 256 22.2 / 18.0; 4096 x 1024 M = 100 7.1 / 8.0, M = 333 12.9 / 9.9; W4A4 4096 x 11008 M = 150 19.4 / 21.3, M = 333 35.8 / 32.0.
   const bool eight = tm * tn <= device_cu_count();
 #define SERQ_GMID_LAUNCH(AB, BF)                                                                                       \
   do {                                                                                                                 \

@@ -1,5 +1,5 @@
 // Pieces shared by the kernels for batches between decode and prefill (gemm_mid.hip, gemm_mid_mx.hip, grouped_mid.hip):
-// 64 tokens x 64 output channels per workgroup, K dealt out to its 4 or 8 waves.
+// 64 tokens x 64 output channels per workgroup, K dealt out to its 4 (group scales: 4 or 8) waves.
 //
 // Why this shape.  With a few hundred tokens the layer is bound by the bytes that go from L2 to the compute
 // units, and by having a workgroup for each of them.  Tiles of 256 tokens leave most of the chip idle (one token
@@ -87,7 +87,7 @@ inline float tiled_price(const TiledPrice& p, const SplitPlan& pl, int M, int N,
   const float us = p.c[0] * rounds + k * (p.c[1] + p.c[2] * pl.wide + p.c[3] * (pl.wide > 4 ? pl.wide - 4 : 0));
   return pl.S > 1 ? us + p.c[4] + p.c[5] * ((float)pl.S * M * N * 8.0f / 5e6f) : us;
 }
-// The layers of gemm_mfma.hip and gemm_mx.hip.  One tile per compute unit at most: always small tiles (13 % faster than the tiled
+// The layers of gemm_mfma.hip and gemm_mx.hip.  One tile per compute unit at most: always small tiles (11 % faster than the tiled
 // kernel at K = 28672, below that up to 70 %).  Two: the prices are asked for long K only, up to K = 8192 small tiles
 // win by 12 % or more.  Beyond: by the prices, up to `most` tiles and, below K = 512, up to two.  `favour` (5 and 7 %) is what
 // a small-tile price may lie above the other: within the error of the prices the small tiles are kept.  W4A8's prices need
@@ -106,7 +106,8 @@ inline bool mid_cheaper(const MidPrice& small, const TiledPrice& tiled, int M, i
   if (pl.S > 1) {
     if (N < 16 * ncu) return true;
     if (parked_bytes(pl, (M + 255) / 256) > ws_have) pl = plan_split(M, N, K, kind, ncu, 1);
-    else if (R > 2 && K > 16384 && kind != 4) return false;   // W4A8 11008 x 28672 M = 192 140 / 112 us, where its price says 127
+    else if (R > 2 && K > 16384 && kind != 4) return false;   // W4A8 11008 M = 192, small / tiled, us: K = 17408 67 / 68, 20480
+                                                              // 80 / 77, 28672 109 / 109, where the prices say 110 / 127
   }
   return favour * mid_price(small, M, N, K, ncu) < tiled_price(tiled, pl, M, N, K, ncu);
 }
