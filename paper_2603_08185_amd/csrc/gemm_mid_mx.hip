@@ -98,7 +98,7 @@ void serq_mx_mid_kernel(const MxMidParams p) {
     if (k < 8) {
       ld.template issue_one<decltype(whole_c)::value>(H, u, my_lds + H * STAGE, k);
     } else {
-      const int tile = (decltype(whole_c)::value ? FU * (w + NW * u) : ld.first(u)) >> 2;
+      const int tile = (decltype(whole_c)::value ? FU * (w + NW * u) : ld.flast) >> 2;
       dma16_at(scsrc + (uint64_t)tile * scstep, my_lds + WS_OFF);   // WS_OFF + 512 = XS_OFF
     }
   };

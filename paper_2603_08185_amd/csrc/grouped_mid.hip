@@ -144,7 +144,7 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) 
       if (k < T::NL - 1) {
         ld.template issue_one<WHOLE>(H, u, my_lds + slot(H, u), k);
       } else {
-        const int grp = (WHOLE ? (w + NW * u) * 2 : ld.first(u)) >> 1;
+        const int grp = (WHOLE ? (w + NW * u) * 2 : ld.flast) >> 1;
         dma4(sbase + ((size_t)(H && nbt > 1 ? G : 0) + grp) * 64, 4u * (l & 15), my_lds + slot(H, u) + T::SC_OFF);
       }
     };

@@ -234,11 +234,12 @@ struct MidUnits {
   // This lane's token pieces: row offset + piece.  Load k of half h brings the rows of group q = 4*h + k, 8*q .. 8*q + 7.
   // LEAN: those of groups 0 and 1; the pieces of groups 2 apart are the same, their rows lie 2 * xgroup apart.
   uint32_t xv[LEAN ? 2 : 8];
-  uint32_t xgroup, xlast;                            // LEAN: bytes of 8 rows; where the last row begins
+  uint32_t xgroup, xlast;                            // LEAN: bytes of 8 rows; where the tile's last row begins
   uint32_t wl;
   size_t wstep1;                                     // from the fragments of block 0 to those of block 1 (0: there is none)
   int KB;                                            // fragments per channel block
   int w, nfull, nu, nf, rest;                        // whole units, units, fragments of a last one and the first of them
+  int flast, hlast;                                  // the last unit, whole or not: its first fragment and how many it has
 
   __device__ __forceinline__ void init(const uint8_t* Xq, const u4* Wq, int K, uint32_t rowbytes, int m0, int mrows, int nb0,
                                        int nbt, int wave, int l) {
@@ -246,11 +247,14 @@ struct MidUnits {
     w = wave;
     nfull = KB / (FU * NW);
     const int left = KB - nfull * (FU * NW);
-    const int piece = SPLIT && left <= FU / 2 * NW ? FU / 2 : FU;
+    constexpr int H = FU / 2 * NW;
+    const int piece = SPLIT ? FU / 2 * ((left + H - 1) / H) : FU;   // (numbers, not conditions: those would go through vector registers)
     rest = nfull * (FU * NW) + w * piece;
     nf = KB - rest < piece ? KB - rest : piece;
     nf = nf < 0 ? 0 : nf;
-    nu = nfull + (nf > 0 ? 1 : 0);
+    nu = nfull + (nf < 1 ? nf : 1);
+    flast = nf > 0 ? rest : (w + NW * (nfull - 1)) * FU;
+    hlast = nf > 0 ? nf : FU;
     xbase = Xq + (size_t)m0 * rowbytes;
     wbase = (const uint8_t*)Wq + (size_t)nb0 * KB * 1024;
     wstep1 = nbt > 1 ? (size_t)KB * 1024 : 0;
@@ -267,32 +271,29 @@ struct MidUnits {
   static __device__ __forceinline__ int xpiece(int l, int k) { return (l & 7) ^ mid_swz128(8 * k + (l >> 3)); }
   __device__ __forceinline__ bool brief() const { return nf > 0 && nf <= FU / 2; }
   __device__ __forceinline__ int frags(int u) const { return u < nfull ? FU : nf; }
-  __device__ __forceinline__ int first(int u) const { return u < nfull ? (w + NW * u) * FU : rest; }
-  // direct load k (of 4 + FU) of half h of unit u into the stage at LDS address `st`; WHOLE: the unit has all its
-  // fragments.  What a unit does not have is replaced by a piece or fragment that it has (in bounds, multiplied by zeros).
+  // direct load k (of 4 + FU) of half h of unit u into the stage at LDS address `st`; WHOLE: the unit is one that has all its
+  // fragments; else it is the last one, which may lack some.  For pieces that it lacks whatever follows in memory is fetched, but nothing
+  // behind its last piece of the tile's last row, and for fragments its last one: both are multiplied by zeros.  The same bound holds for
+  // rows past M (LEAN), which are not stored; they begin a row's length or more behind that row.
   template <bool WHOLE>
   __device__ __forceinline__ void issue_one(int h, int u, uint32_t st, int k) const {
-    const int f0 = WHOLE ? (w + NW * u) * FU : first(u);
-    const int have = WHOLE ? FU : frags(u);          // (selected as a number: no control flow around the load)
+    const int f0 = WHOLE ? (w + NW * u) * FU : flast;
+    const int have = WHOLE || !SPLIT ? FU : hlast;   // (not SPLIT: every unit is whole)
     if (k < 4) {
       uint32_t v = xv[LEAN ? k & 1 : 4 * h + k];
-      if constexpr (!WHOLE) {
-        int l = (int)(wl >> 4);
-        asm volatile("" : "+v"(l));                  // computed here, not carried through the main loop
-        const int c = xpiece(l, k);
-        v -= c < have * PPF ? 0u : 16u * c;
-      }
       if constexpr (LEAN) {
         uint32_t g = xgroup;
         asm volatile("" : "+s"(g));                  // added here: left alone, the compiler keeps all eight sums
         v += (4 * h + (k & 2)) * g;
-        // rows past M: the last piece of the last row, never stored (they begin a row's length or more behind that row)
-        const uint32_t lim = xlast + 16u * (have * PPF - 1);
+      }
+      if constexpr (LEAN || (SPLIT && !WHOLE)) {
+        uint32_t lim = xlast + 16u * (have * PPF - 1);
+        if constexpr (!LEAN) asm volatile("" : "+s"(lim));   // bounded here: the same
         v = v < lim ? v : lim;
       }
       dma16(xbase + (size_t)f0 * (16 * PPF), v, st + 1024u * k);
     } else {
-      const int f = WHOLE ? k - 4 : __builtin_amdgcn_readfirstlane(k - 4 < have ? k - 4 : have - 1);
+      const int f = k - 4 < have ? k - 4 : have - 1;
       dma16(wbase + (size_t)(f0 + f) * 1024 + (h ? wstep1 : 0), wl, st + 1024u * k);
     }
   }
@@ -302,7 +303,7 @@ struct MidUnits {
 // are copied to registers one unit ahead, which frees its slot: the slot is refilled, NS stages further, between the
 // products of the current unit.  (A direct load blocks the wave while the address unit is busy with the other waves'
 // loads; between two products that costs nothing.)
-//   fill(whole, h, u, k)  direct load k of half h of unit u into its slot
+//   fill(whole, h, u, k)  direct load k of half h of unit u into its slot (not whole: of the last unit)
 //   read(whole, h, u, op) half h of the operands of unit u, from LDS
 //   product(h, op, k)     the k-th of NP groups of products of the h-th half of the fragments
 //   last()                before the products of the last unit: the place to request what the tile's end needs

@@ -95,7 +95,7 @@ def _units(form, waves, FU, KB, w):
 
 
 def _check(asm, name, M, N, K, r=32, start=None):
-    """start: instructions that a direct load may take, on average, among a wave's first twelve"""
+    """start: (n, instructions that a direct load may take on average among a wave's first n)"""
     form, kernel, waves, FU, NS, stage, region = FORMS[name]
     lines, meta, _ = asm
     kernel = _named(lines, kernel)
@@ -118,7 +118,7 @@ def _check(asm, name, M, N, K, r=32, start=None):
                 raise AssertionError((*where, str(e))) from None
             # a wait that is not counted by hand empties the ring
             assert not loads or not any(loads[0].at < t < loads[-1].at for t in wave.own_waits), where
-            assert start is None or loads[11].at - loads[0].at <= 11 * start, where
+            assert start is None or loads[start[0] - 1].at - loads[0].at <= (start[0] - 1) * start[1], where
             codes = [ld for ld in loads if ld.buf in ("Xq", "Wq")]
             units = _units(form, waves, FU, KB, w)
             assert len(codes) == len(units) * 2 * (4 + FU), where
@@ -134,8 +134,8 @@ def _check(asm, name, M, N, K, r=32, start=None):
                         if k < 4:
                             r_ = m0 + 32 * h + 8 * k + lane // 8
                             c = (lane % 8) ^ (4 * (k % 2) + lane // 16)
-                            want = r_ * row + 16 * (f0 * per + np.where(c < have * per, c, 0))
-                            real = r_ < M              # (of a row past M any piece will do, as long as it is in bounds)
+                            want = r_ * row + 16 * (f0 * per + c)
+                            real = (r_ < M) & (c < have * per)   # (for any other piece all that is in bounds will do)
                             assert ld.buf == "Xq" and (ld.off[real].astype(np.int64) == want[real]).all(), at
                         else:
                             blk = nb0 + (h if nbt > 1 else 0)
@@ -171,12 +171,16 @@ def test_loads(asm, name):
         _check(asm, name, 73, 64, 64 * (one + left))
 
 
-# whole units are fetched without picking pieces and fragments from the first load on (picking takes 11 to 14 instructions a load)
+# the first loads of a wave, of whole units and of ones that lack fragments, pick no pieces and fragments lane by lane (picking
+# takes 11 to 14 instructions a load)
 @pytest.mark.parametrize("name", FORMS)
-def test_start_of_whole_units(asm, name):
-    waves, FU = FORMS[name][2:4]
+def test_start(asm, name):
+    form, _, waves, FU = FORMS[name][:4]
     for u in (1, 2, 3, 4):
-        _check(asm, name, 109, 96, 64 * FU * waves * u, start=10)
+        _check(asm, name, 109, 96, 64 * FU * waves * u, start=(12, 10))
+    if form != "g128":
+        _check(asm, name, 109, 96, 64 * FU * waves // 2, start=(4 + FU, 10))    # (the first half of a unit)
+        _check(asm, name, 109, 96, 64 * (FU * waves - 1), start=(4 + FU, 10))
 
 
 # the kernels that read 4-bit tokens in steps: nothing out of bounds or out of turn, and every fragment is fetched
