@@ -322,8 +322,8 @@ void serq_g128_mid_kernel(const G128Args p, int tiles_m, int tiles_n, int band) 
 //   small tiles  c0 + c1 R + K/1024 (c2 + c3 R + c4 y) + c5 (MB of weight codes) + r/128 (c6 + c7 R)
 //   tiled        d0 + d1 K/1024 (halves of tiles) or d2 K/1024 (whole ones) + d3 (r > 0) + d4 r/128
 // fitted to 800 launches with an error of 4 to 5 % (three tiles per compute unit are at most one round of the tiled kernel); 8-bit tokens'
-// small-tile price to 367 layers of the kernel with whole-line token rows, 7 % (of 288 layers of two and three tiles, 5 would be more than
-// 3 % faster in the other kernel; with the price of 64-byte rows 13, by up to 16 %).
+// small-tile price to 367 layers of the kernel with whole-line token rows, 7 % (of 500 other layers of two and three tiles 8 would be more
+// than 3 % faster in the other kernel, the worst 6 %; with the price of 64-byte rows 41, the worst 18 %).
 // Measured (us, tiled kernel / this one, N x K, weights from HBM; in brackets: tiles of the busiest compute unit):
 //   W4A8 r = 128  4096 x 4096 M = 256 (1) 23.1 / 13.4, M = 512 (2) 23.0 / 21.9, M = 768 (3) 33.4 / 28.2;  11008 x 14336 M = 128 (2)
 //        59.5 / 53.3;  15968 x 6144 M = 128 (2) 32.6 / 28.7

@@ -68,9 +68,10 @@ inline long long mid_rounds(int M, int N, int ncu) {
 // from HBM and once from the last-level cache (the geometric mean of the two times; the cache moves this kernel by up to
 // 20 % and the tiled one hardly).  Standard error of the tiled prices and of W4A4's 4 to 6 % at r = 128; other ranks move both alike.  W4A8's
 // small-tile price is fitted to its kernel with whole-line token rows (383 layers of one to three tiles, 256 <= K <= 28672, ranks 0 to 256:
-// 10 %).  MXFP4's is that of 64-byte rows: at long K the kernel is up to 15 % cheaper, and the tiled one's price 6 % too low as well.  The
-// rule chooses right with them all the same: of 354 layers of two to four tiles 18 would be more than 3 % faster in the other kernel, and all
-// lose 0.5 % on average; with a small-tile price fitted to whole lines 18 and 0.4 %.
+// 10 %); of 400 other layers of two and three tiles 6 would be more than 3 % faster in the other kernel (the worst 5 %), with the price of
+// 64-byte rows 9 (26 %).  MXFP4's is that of 64-byte rows: at long K the kernel is up to 15 % cheaper, and the tiled one's price 6 % too low
+// as well.  The rule chooses right with them all the same: of 400 layers of two to four tiles 12 would be more than 3 % faster in the other
+// kernel, and all lose 0.3 % on average; with a small-tile price fitted to whole lines 13 and 0.3 %.
 //   small tiles: c0 + c1 R + K/1024 (c2 + c3 R + c4 y) + c5 (MB of weight codes),  R tiles of the busiest compute unit,
 //                y = M N / (4096 compute units): duplicated rows of a ragged tile cost less than real ones
 //   tiled:       c0 rounds + k (c1 + c2 wide + c3 max(0, wide - 4)), k = rounds K / 1024 / slices;
@@ -91,8 +92,8 @@ inline float tiled_price(const TiledPrice& p, const SplitPlan& pl, int M, int N,
 // kernel at K = 28672, below that up to 70 %).  Two: the prices are asked for long K only, up to K = 8192 small tiles
 // win by 12 % or more.  Beyond: by the prices, up to `most` tiles and, below K = 512, up to two.  `favour` (5 and 7 %) is what
 // a small-tile price may lie above the other: within the error of the prices the small tiles are kept.  W4A8's prices need
-// none: with 1.02, 1.00 and 0.97 the layers of two and three tiles lose 0.15, 0.13 and 0.13 % on average (0.25 with its price of
-// 64-byte rows), and 1.02 leaves three tiles of long K, level on fresh weights, to the kernel that reads fewer bytes.
+// none: with 1.02, 1.00 and 0.97 the 293 fitted layers of two and three tiles lose 0.15, 0.13 and 0.13 % on average (0.25 with its price
+// of 64-byte rows), and 1.02 leaves three tiles of long K, level on fresh weights, to the kernel that reads fewer bytes.
 //   ws_have: what the caller's workspace has room for behind the decode path's words; without enough the tiled kernel runs
 //   unsliced.  Layers with fewer than 16 channels per compute unit (N < 4096) are not given to slices here: their parked tiles
 //   would lie where the decode path of a wider layer, which may share the workspace, keeps words that have to stay zero.
