@@ -333,7 +333,7 @@ __device__ __forceinline__ void mid_unit_loop(int nu, int nfull, bool brief, con
   };
   // All loads of a stage, before the first products.  A unit that is whole is fetched as one here too, which is a choice made at run
   // time: the other form picks the pieces of every lane and fragment, and the first products wait for it.  Instructions up to a
-  // W4A8 wave's 12th load 324 -> 259, MXFP4 375 -> 307; us, r = 128, N x K, weights from HBM: W4A8 4096 x 4096 M = 100 8.9 -> 8.6,
+  // W4A8 wave's 12th load 324 -> 264, MXFP4 375 -> 326; us, r = 128, N x K, weights from HBM: W4A8 4096 x 4096 M = 100 8.9 -> 8.6,
   // M = 64 8.8 -> 8.5, 6144 x 4096 M = 100 9.4 -> 9.2 (steps: 8.5, 9.4, 9.0), MXFP4 4096 x 1024 M = 200 4.8 -> 4.6 (4.5).
   auto start = [&](auto h_c, int u) {
     constexpr int NLS = decltype(h_c)::value ? NL1 : NL0;
