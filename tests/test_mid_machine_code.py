@@ -2,7 +2,7 @@
 address lies in its buffer, the direct loads of a wave bring every token piece and weight fragment of its units once, in order
 and to their slots, nothing is read from LDS before it has landed or requested again before it has been read, for waves with
 every number of units and of fragments in the last one.  Tests of results cannot show these: a pointer that a compiler loses on
-one path through the loop (one build did) sends loads to addresses that a GPU answers with a fault."""
+one path through the loop (it has happened) sends loads to addresses that a GPU answers with a fault."""
 import os
 import struct
 import subprocess
