@@ -547,6 +547,16 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void serq_g128_skinny_kernel(con
 // that the vector unit works in the shadow of the matrix unit.  The first group stands outside the loop and does not wait
 // for the second one to land.
 //
+// The loads of a group are spread over the products of the group whose slot they take: requested in one go behind the barrier, as
+// they were, they queue at the address unit and a wave whose load waits there issues nothing else (us, in one go / spread, r = 0,
+// 6144 x 4096 M = 4096 131.6 / 126.6).  R comes through the ring as well, in stages of its own with the token codes it meets, and its
+// type is a compile-time choice: chosen at run time, the two products made the compiler copy a whole tile after each of them, and
+// the fragments had come straight from L2, waited for four at a time (us, with both steps, r = 128 unless stated, N x K: W4A8
+// 6144 x 4096 M = 3000 110.4 / 102.6, 11008 x 4096 M = 4096 254.5 / 240.9, 4096 x 11008 234.1 / 221.9, r = 256 6144 x 4096
+// 159.5 / 145.1; W4A4 11008 x 4096 242.7 / 233.2).
+// What bounds it now (counters, W4A8 6144 x 4096 M = 3000): vector issue slots 71 % taken, matrix unit 40 %, LDS 20 %; 190 vector
+// instructions per wave and group, 128 of them folds.
+//
 // With a short K the end of the tile counts: everything it takes from LDS is read in one go, before anything is written
 // there, and 16-bit results go through LDS by channel (below).  Measured (us, end as it was with results exchanged between
 // lanes and reads behind tests / this form, W4A8 r = 0, N x K): 2048 x 256 M = 4096 11.1 / 9.8; 11008 x 1024 M = 1024
@@ -561,17 +571,25 @@ struct GTile {
   static constexpr int STAGE = SC_OFF + 256;
   static constexpr int NS = ABITS == 8 ? 3 : 4;      // ring depth
   static constexpr int NLX = 128 * P / 256;          // token loads per thread and group: 4 or 2
-  static constexpr int nl(int ni) { return ni + NLX + 1; }   // direct loads per wave and group
+  static constexpr int nl(int ni) { return ni + NLX + 1; }   // direct loads per wave and stage
+  // a stage of the rank-r term: the R fragments of RK ranks where the weights lie, behind them the 128 token rows
+  static constexpr int RK = ABITS == 8 ? 64 : 32;    // 64 / 16 bytes of a token row
+  static constexpr int RF = RK / 16;                 // fragments per channel block
+  static constexpr int RP = RK * ABITS / 128;        // 16-byte pieces per row: 4 or 1
+  static constexpr int RX_OFF = 4 * RF * 1024;
+  static constexpr int NLR = (2 * RP + 3) / 4;       // token loads per wave: 2 or 1
+  static __device__ __forceinline__ int swz_r(int row) { return ABITS == 8 ? (row >> 2) & 3 : 0; }
   static constexpr int TS_OFF = NS * STAGE;          // for the epilogue: 128 token scales, zero points and wsum of the tile
   static constexpr int LDS = TS_OFF + 3 * 128 * 4;
   static __device__ __forceinline__ int swz(int row) { return ABITS == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
   static_assert(2 * LDS <= 160 * 1024, "two workgroups per compute unit");
+  static_assert(RX_OFF + 128 * 16 * RP <= STAGE, "the rank-r operands fit a stage");
 };
 
 template <int ABITS, int NI>
 struct GOp { u4 w[NI][2], x[2][ABITS == 8 ? 4 : 2]; float gs[NI]; };   // raw operands and scales of one group
 
-template <int ABITS, bool HALVES>
+template <int ABITS, bool HALVES, bool BF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void serq_g128_tiled_kernel(const GParams p, int full) {
   using T = GTile<ABITS>;
   constexpr int SH = ABITS == 8 ? 4 : 8;
@@ -615,33 +633,70 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const uint8_t* wbase = (const uint8_t*)p.Wq + (size_t)nb0 * KB * 1024;
   const uint8_t* xbase = p.Xq + (size_t)m0 * rowbytes;
   const uint8_t* sbase = (const uint8_t*)p.gsc + (size_t)nb0 * G * 64;
-  // The sequence of stages: the G groups of the layer, then -- for the rank-r term -- once more the LG groups whose
-  // token codes are the salient block (only their token rows are read then; the loads are the same so that every
-  // stage counts the same number of them).
+  // The sequence of stages: the G groups of the layer, then LG stages of RK ranks each for the rank-r term.
   const bool has_lr = p.r > 0 && p.Rp != nullptr;
-  const int lg0 = p.s_begin >> 7;
-  const int LG = has_lr ? ((p.s_begin + p.r + 127) >> 7) - lg0 : 0;
+  const int JB = has_lr ? p.r >> 4 : 0;
+  const int LG = (JB + T::RF - 1) / T::RF;
   const int GT = G + LG;
   // Everything from here on is specialised on the channel blocks per wave: 2, or 1 in half a tile.
   auto body = [&](auto ni_c) {
   constexpr int NI = decltype(ni_c)::value;
   using Op = GOp<ABITS, NI>;
-  auto issue = [&](int q, int st) {
-    const int gi = q < G ? q : lg0 + (q - G);
+  // direct load d (of nl(NI)) of group gi into slot st
+  auto fill = [&](int gi, int st, int d) {
     const uint32_t sb = lds0 + (uint32_t)st * T::STAGE;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      int b = 2 * i + (wu >> 1);                      // blocks past the tile: duplicates, never stored
+    if (d < NI) {
+      int b = 2 * d + (wu >> 1);                      // blocks past the tile: duplicates, never stored
       b = b < nbt ? b : nbt - 1;
-      dma16(wbase + (size_t)gi * 2048 + (size_t)(b * KB + (wu & 1)) * 1024, (uint32_t)l * 16u, sb + 1024 * wu + 4096 * i);
-    }
-#pragma unroll
-    for (int i = 0; i < T::NLX; ++i) {
-      const uint32_t xv = xv0 + (uint32_t)(i * XSTEP) * (uint32_t)rowbytes;
+      dma16(wbase + (size_t)gi * 2048 + (size_t)(b * KB + (wu & 1)) * 1024, (uint32_t)l * 16u, sb + 1024 * wu + 4096 * d);
+    } else if (d < NI + T::NLX) {
+      const int i = d - NI;
+      uint32_t step = (uint32_t)rowbytes;
+      asm volatile("" : "+s"(step));                  // added here: left alone, the compiler keeps all the sums
+      const uint32_t xv = xv0 + (uint32_t)(i * XSTEP) * step;
       dma16(xbase + (size_t)gi * T::XROW, xv < xlast ? xv : xlast, sb + T::WB + 1024 * wu + 4096 * i);
+    } else {
+      dma64(sbase + (size_t)gi * 64 + (size_t)(wu < nbt ? wu : nbt - 1) * G * 64, (uint32_t)l * 16u, sb + T::SC_OFF + 64 * wu);
     }
-    if (l < 4)
-      dma16(sbase + (size_t)gi * 64 + (size_t)(wu < nbt ? wu : nbt - 1) * G * 64, (uint32_t)l * 16u, sb + T::SC_OFF + 64 * wu);
+  };
+  // The loads of stage lg of the rank-r term: fragment f of block b at (b * RF + f) KiB, then the token rows.  Fragments past r,
+  // rows past M: duplicates, not used.  The count is that of a group, with repetitions: the waits count all stages alike.
+  auto fill_lr = [&](int lg, int st) {
+    const uint32_t sb = lds0 + (uint32_t)st * T::STAGE;
+    constexpr int NR = NI * T::RF / 2;                // fragments per wave
+    constexpr int NT = T::nl(NI) - NR;                // the other loads
+    static_assert(NT >= T::NLR, "a stage of the rank-r term takes no more loads than a group");
+    auto fragment = [&](int i) {
+      const int n = wu + 4 * i, b = n / T::RF, jb = lg * T::RF + n % T::RF;
+      dma16((const uint8_t*)p.Rp + ((size_t)(nb0 + (b < nbt ? b : nbt - 1)) * JB + (jb < JB ? jb : JB - 1)) * 1024,
+            (uint32_t)l * 16u, sb + 1024 * n);
+    };
+#pragma unroll
+    for (int i = 0; i < NR; ++i) fragment(i);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      if (i < T::NLR) {
+        int n = 64 * (wu + 4 * i) + l;                // piece of the stage
+        if (T::RP == 1) n &= 127;                     // 4-bit tokens: waves 2 and 3 repeat the loads of 0 and 1
+        const int row = n / T::RP;
+        int pc = (n % T::RP) ^ T::swz_r(row);
+        const int have = (p.r - lg * T::RK + 15) / 16;   // pieces of 16 channels the rows have (4-bit: one piece holds 32)
+        if (ABITS == 8 && pc >= have) pc = have - 1;
+        dma16(p.Xq + (size_t)m0 * rowbytes + (size_t)(p.s_begin + lg * T::RK) * ABITS / 8,
+              (uint32_t)(row < mrows ? row : mrows - 1) * (uint32_t)rowbytes + 16u * pc,
+              sb + T::RX_OFF + 1024 * (T::RP == 1 ? wu & 1 : wu + 4 * i));
+      } else {
+        fragment(0);
+      }
+    }
+  };
+  auto issue = [&](int q, int st) {
+    if (q < G) {
+#pragma unroll
+      for (int d = 0; d < T::nl(NI); ++d) fill(q, st, d);
+    } else {
+      fill_lr(q - G, st);
+    }
   };
 
   // what the epilogue needs of the tile's tokens and channels, requested before the ring (older loads do not disturb its
@@ -705,7 +760,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // the tiles of a group; the MFMAs of tile u = 2*i + j shadow the fold of the tile before.  The next group's weights
   // are read once the registers of this group's first block are free.
-  auto multiply = [&](auto ahead, const Op& o, int nst, Op& nxt) {
+  // FILL: group `gf` is requested into slot `sf`, its loads spread over the products.  Requested in one go behind the barrier,
+  // the loads of all waves queue at the address unit, and a wave whose load waits there issues nothing else.
+  auto multiply = [&](auto ahead, auto fill_c, const Op& o, int nst, Op& nxt, int gf, int sf) {
+    constexpr int NLF = decltype(fill_c)::value ? T::nl(NI) : 0, NPOS = 8 * NI;
 #pragma unroll
     for (int u = 0; u < 2 * NI; ++u) {
       if (decltype(ahead)::value && u == NI) {
@@ -736,6 +794,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int e = 0; e < 16; ++e)
           if (t > 0 && e * 3 / 16 == t - 1)
             accf[pi][pj][e] = __builtin_fmaf(gs, (float)acc[(u & 1) ^ 1][e], accf[pi][pj][e]);
+#pragma unroll
+        for (int d = 0; d < NLF; ++d)
+          if (d * NPOS / T::nl(NI) == 4 * u + t) fill(gf, sf, d);
         fence();
       }
     }
@@ -757,49 +818,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   read_w(0, A);
   read_x(0, A);
   int st = 0;                                         // slot of the current group
-  auto group = [&](auto first_c, int gi, const Op& cur, Op& nxt) {
-    constexpr bool FIRST = decltype(first_c)::value;
-    if (FIRST) multiply(std::false_type{}, cur, 0, nxt);
+  auto group = [&](auto first_c, auto steady_c, int gi, const Op& cur, Op& nxt) {
+    constexpr bool FIRST = decltype(first_c)::value, STEADY = decltype(steady_c)::value;
+    if (FIRST) multiply(std::false_type{}, std::false_type{}, cur, 0, nxt, 0, 0);
+    const int free = st;
     const int next = st + 1 == NS ? 0 : st + 1;
     const int last = gi + NS - 1 < GT - 1 ? gi + NS - 1 : GT - 1;
-    if (last - gi == NS - 1) wait_dma_barrier<(NS - 2) * T::nl(NI)>();
+    if (STEADY || last - gi == NS - 1) wait_dma_barrier<(NS - 2) * T::nl(NI)>();
     else wait_dma_barrier<0>();
-    if (gi + NS < GT) issue(gi + NS, st);
+    if (!STEADY && gi + NS < GT) issue(gi + NS, free);
     st = next;
-    read_x(st, nxt);                                  // (behind the last stage: stale bytes, never used)
+    read_x(st, nxt);                                  // (behind the last group: bytes that are never used)
     if (FIRST) read_w(st, nxt);
     fence();
-    if (!FIRST) multiply(std::true_type{}, cur, st, nxt);
+    if (!FIRST) multiply(std::true_type{}, steady_c, cur, st, nxt, gi + NS, free);
   };
-  group(std::true_type{}, 0, A, B);
+  using Yes = std::true_type;
+  using No = std::false_type;
+  group(Yes{}, No{}, 0, A, B);
   int gi = 1;
 #pragma unroll 1
-  for (; gi + 1 < G; gi += 2) {
-    group(std::false_type{}, gi, B, A);
-    group(std::false_type{}, gi + 1, A, B);
+  for (; gi + 1 + NS < G; gi += 2) {
+    group(No{}, Yes{}, gi, B, A);
+    group(No{}, Yes{}, gi + 1, A, B);
   }
-  if (gi < G) group(std::false_type{}, gi, B, A);
+#pragma unroll 1
+  for (; gi + 1 < G; gi += 2) {
+    group(No{}, No{}, gi, B, A);
+    group(No{}, No{}, gi + 1, A, B);
+  }
+  if (gi < G) group(No{}, No{}, gi, B, A);
 
   // ---- epilogue: zero point, rank-r term on the re-centred codes, token scale, one store ----------------
   // register e of lane (lm, g) in tile (i, j): token 32*(2*wm + j) + 8*(e/4) + 4*g + e%4, channel 32*bi[i] + lm
-  // The R fragments come straight from L2, four 16-rank fragments at a time and a batch ahead of their use, the first
-  // batch requested here.
   // (lane indices taken anew: every register that lives through the main loop for the sake of the end is one too many)
   int te = tid;
   asm volatile("" : "+v"(te));
   const int l = te & 63, lm = l & 31, g = l >> 5;
-  const int JB = p.r >> 4;
-  constexpr int NJ = 4;
-  u4 rr[NJ][NI], rn[NJ][NI];
-  auto load_r = [&](int jb0) {
-#pragma unroll
-    for (int q4 = 0; q4 < NJ; ++q4) {
-      const int jb = jb0 + q4 < JB ? jb0 + q4 : JB - 1;   // past the end: a duplicate, never used
-#pragma unroll
-      for (int i = 0; i < NI; ++i) rn[q4][i] = p.Rp[((size_t)bi[i] * JB + jb) * 64 + l];
-    }
-  };
-  if (has_lr) load_r(0);
   fence();
 #pragma unroll
   for (int e = 0; e < 16; ++e) accf[NI - 1][1][e] = __builtin_fmaf(gprev, (float)acc[1][e], accf[NI - 1][1][e]);
@@ -827,55 +882,46 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         accf[i][j][e] = __builtin_fmaf(accf[i][j][e], kInv, -(float)z[j][e >> 2][e & 3] * ws);   // 2^-SH: exact
   }
   if (has_lr) {
-    // The token codes of the salient block come back through the ring (they ran ahead of the last main groups,
-    // like any stage).
-    const bool bf = p.r_dtype == SERQ_BF16;
+    // R fragments and token codes come through the ring, RK ranks at a time (they ran ahead of the last main groups, like any
+    // stage), and are read in one go.
     int zm[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) zm[j] = p.zero ? tzr[32 * (2 * wm + j) + lm] : 0;
 #pragma unroll 1
     for (int lg = 0; lg < LG; ++lg) {
       const int q = G + lg;
-      // stage q has landed, and every wave has read the one before, whose slot is refilled (the R fragments in flight are
-      // younger than some of its loads: the wait is then stricter than needed, never looser)
+      // stage q has landed, and every wave has read the one before, whose slot is refilled
       wait_stage(lg == 0 ? behind(q) : (q + NS - 2 < GT - 1 ? q + NS - 2 : GT - 1) - q);
       if (lg > 0) {
         if (q - 1 + NS < GT) issue(q - 1 + NS, st);
         st = st + 1 == NS ? 0 : st + 1;
       }
       const uint8_t* s = lds + st * T::STAGE;
-      const int c0 = 128 * (lg0 + lg);                    // first channel of this group of token codes
-      const int jb_lo = c0 > p.s_begin ? (c0 - p.s_begin) >> 4 : 0;
-      const int jb_end = (c0 + 128 - p.s_begin) >> 4;
-      const int jb_hi = jb_end < JB ? jb_end : JB;
-#pragma unroll 1
-      for (int jb0 = jb_lo; jb0 < jb_hi; jb0 += NJ) {
+      u4 rr[T::RF][NI];
+      u2 xr[T::RF][2];
 #pragma unroll
-        for (int q4 = 0; q4 < NJ; ++q4)
+      for (int f = 0; f < T::RF; ++f) {
 #pragma unroll
-          for (int i = 0; i < NI; ++i) rr[q4][i] = rn[q4][i];
-        load_r(jb0 + NJ < jb_hi ? jb0 + NJ : jb_hi);
+        for (int j = 0; j < 2; ++j) {
+          const int row = 64 * wm + 32 * j + lm;
+          const uint8_t* xs = s + T::RX_OFF + 16 * T::RP * row;
+          if constexpr (ABITS == 8) xr[f][j] = *(const u2*)(xs + 16 * (f ^ T::swz_r(row)) + 8 * g);
+          else xr[f][j] = u2{*(const uint32_t*)(xs + 8 * f + 4 * g), 0u};
+        }
 #pragma unroll
-        for (int q4 = 0; q4 < NJ; ++q4) {
-          if (jb0 + q4 < jb_hi) {                         // uniform
-            const int col = p.s_begin + 16 * (jb0 + q4) + 8 * g - c0;   // this lane's first channel within the group
-            u4 xf[2];
+        for (int i = 0; i < NI; ++i) rr[f][i] = *(const u4*)(s + ((NI * wn + i) * T::RF + f) * 1024 + l * 16);
+      }
+      fence();
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              u2 xr;
-              if constexpr (ABITS == 8) {
-                xr = *(const u2*)(s + xoff + 32 * j * T::XROW + 16 * ((col >> 4) ^ xsw) + (col & 15));
-              } else {
-                const int byte = col >> 1;
-                xr = u2{*(const uint32_t*)(s + xoff + 32 * j * T::XROW + 16 * ((byte >> 4) ^ xsw) + (byte & 15)), 0u};
-              }
-              xf[j] = lr_convert_packed<ABITS>(xr, zm[j], bf);   // rows past M: duplicates, never stored
-            }
+      for (int f = 0; f < T::RF; ++f) {
+        if (lg * T::RF + f < JB) {                        // uniform
+          u4 xf[2];
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
+          for (int j = 0; j < 2; ++j) xf[j] = lr_convert_packed<ABITS>(xr[f][j], zm[j], BF);   // rows past M: duplicates, never stored
 #pragma unroll
-              for (int j = 0; j < 2; ++j) accf[i][j] = mfma_lr16(xf[j], rr[q4][i], accf[i][j], bf);
-          }
+          for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) accf[i][j] = mfma_lr16(xf[j], rr[f][i], accf[i][j], BF);
         }
       }
     }
@@ -1110,15 +1156,23 @@ int serq_g128_linear(const void* Xq, const float* scale, const int32_t* zero, in
     // 14336 x 4096 M = 700 (W4A4) 71.5 / 75.6; 192 left 11008 x 4096 M = 4096 260 / 264.
     const long long ncu = device_cu_count();
     const long long full = tiles / (2 * ncu) * (2 * ncu), left = tiles - full;
-    if (left > 0 && 2 * left <= ncu && full % 8 == 0) {
-      const dim3 grid((unsigned)(full + 16 * ((left + 7) / 8)));
-      if (abits == 8) hipLaunchKernelGGL((serq_g128_tiled_kernel<8, true>), grid, dim3(256), 0, st, p, (int)full);
-      else hipLaunchKernelGGL((serq_g128_tiled_kernel<4, true>), grid, dim3(256), 0, st, p, (int)full);
+    const bool halves = left > 0 && 2 * left <= ncu && full % 8 == 0;
+    const dim3 grid((unsigned)(halves ? full + 16 * ((left + 7) / 8) : tiles));
+    const bool bf = r_dtype != SERQ_F16;
+#define SERQ_G128_TILED(AB, HALVES, BF) \
+  hipLaunchKernelGGL((serq_g128_tiled_kernel<AB, HALVES, BF>), grid, dim3(256), 0, st, p, HALVES ? (int)full : 0)
+    if (abits == 8) {
+      if (halves && bf) SERQ_G128_TILED(8, true, true);
+      else if (halves) SERQ_G128_TILED(8, true, false);
+      else if (bf) SERQ_G128_TILED(8, false, true);
+      else SERQ_G128_TILED(8, false, false);
     } else {
-      const dim3 grid((unsigned)tiles);
-      if (abits == 8) hipLaunchKernelGGL((serq_g128_tiled_kernel<8, false>), grid, dim3(256), 0, st, p, 0);
-      else hipLaunchKernelGGL((serq_g128_tiled_kernel<4, false>), grid, dim3(256), 0, st, p, 0);
+      if (halves && bf) SERQ_G128_TILED(4, true, true);
+      else if (halves) SERQ_G128_TILED(4, true, false);
+      else if (bf) SERQ_G128_TILED(4, false, true);
+      else SERQ_G128_TILED(4, false, false);
     }
+#undef SERQ_G128_TILED
   }
   return hip_ok();
 }

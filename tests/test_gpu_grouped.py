@@ -262,3 +262,14 @@ def test_g128_whole_tiles_variants(abits):
     Ya, _, _ = _run(spec, path=serq.PATH_MFMA)
     Yb, _, _ = _run(spec, path=serq.PATH_MFMA)
     assert torch.equal(Ya, Yb)                                        # fixed summation order
+
+
+# the main loop's steady part (every group requests the one that takes its slot): even and odd numbers of groups, with and
+# without a remainder; the rank-r term in up to 17 stages, the last one in part, refilled within the term
+@pytest.mark.parametrize("abits", [4, 8])
+@pytest.mark.parametrize("in_dtype,out_dtype", [("bf16", "fp32"), ("fp16", "bf16")])
+@pytest.mark.parametrize("G,r", [(6, 0), (7, 16), (8, 176), (9, 528), (10, 64)])
+def test_g128_steady_groups(abits, in_dtype, out_dtype, G, r):
+    for M, N in ((2100, 1312), (140, 224)):                           # whole tiles, halves
+        spec = _spec(abits, M, 128 * G, N, r, in_dtype=in_dtype, out_dtype=out_dtype)
+        _run(spec, path=serq.PATH_MFMA, R_mode="random" if r else "none", s_begin=32 if r else 0)
