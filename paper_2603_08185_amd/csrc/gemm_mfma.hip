@@ -28,7 +28,11 @@
 // loads are issued from inline assembly and counted by hand with vmcnt, because
 // the compiler would wait for every outstanding LDS-bound load before any LDS
 // read it cannot disambiguate.  In the steady state the refill of a stage is
-// spread over the MFMA groups of one 64-channel step.
+// spread over the MFMA groups of two 64-channel steps.  The tile's scales come the same way, ahead of the ring: loaded
+// to registers at the start and behind the last barrier, each cost the tile a trip to memory.  4-bit tokens begin with
+// their first stage landed, not with both.  (us, before / these steps together, r = 128 unless stated, N x K, M = 4096: W4A4
+// 28672 x 4096 348.9 / 339.8, 6144 x 4096 r = 0 76.3 / 74.5, 4096 x 4096 r = 64 M = 2048 32.7 / 31.5; W4A8 4096 x 1024 r = 0
+// 23.2 / 22.7, 11008 x 4096 level: its clock gives way, 2.0 GHz where W4A4 keeps 2.37.)
 //
 // Inside a tile the operand fragments are double-buffered in registers: the LDS
 // reads of the next 64-channel fragment are issued before the MFMAs of the
@@ -71,7 +75,8 @@ struct Tile {
   static constexpr int NL_LR = 4 + LR_NLX;
   static constexpr int WS_OFF = NS * STAGE;           // 256 floats: the tile's weight scales
   static constexpr int RS_OFF = WS_OFF + 256 * 4;     // 256 floats: the scales of a 4-bit compensation matrix
-  static constexpr int LDS_BYTES = RS_OFF + 256 * 4;
+  static constexpr int TS_OFF = RS_OFF + 256 * 4;     // 256 floats: the scales of the tile's tokens
+  static constexpr int LDS_BYTES = TS_OFF + 256 * 4;
   static_assert(LR_R_BYTES + BM * LR_XROW <= STAGE, "a low-rank tile fits a stage");
   static_assert(NS == 2 || NL == NL_LR, "one vmcnt immediate serves both tile kinds");
   static_assert(BM * 512 <= NS * STAGE, "the 16-bit output tile fits the ring");
@@ -162,15 +167,26 @@ void serq_mfma_kernel(const MfmaParams p) {
   constexpr bool lr_int = LRT == SERQ_I4;            // one weight-like fragment per tile and block
   const int TT = KT + LT;
 
-  // the tile's weight scales, times 2^-SH (exact), for the int -> float conversion
-  constexpr float kInv = 1.0f / (float)(1 << T::SH);
-  float* lws = reinterpret_cast<float*>(lds + T::WS_OFF);
-  if (tid < 256 && p.wscale != nullptr) lws[tid] = tid < 32 * nbt ? p.wscale[n0 + tid] * kInv : 0.0f;
-  float* lrs = reinterpret_cast<float*>(lds + T::RS_OFF);
-  if (tid < 256 && lr_int && LT > 0) lrs[tid] = tid < 32 * nbt ? p.rscale[n0 + tid] * kInv : 0.0f;
-
   const int wu = __builtin_amdgcn_readfirstlane(w);
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(lds));
+
+  // The tile's scales, straight into LDS and requested before the ring (older loads do not disturb its counting): waves 0..3
+  // bring those of the channels, waves 4..7 those of the tokens.  Past the tile's edges: duplicates, never used.
+  constexpr float kInv = 1.0f / (float)(1 << T::SH);  // the channels' are used times 2^-SH (exact)
+  const float* lws = reinterpret_cast<const float*>(lds + T::WS_OFF);
+  const float* lrs = reinterpret_cast<const float*>(lds + T::RS_OFF);
+  const float* lts = reinterpret_cast<const float*>(lds + T::TS_OFF);
+  if (p.wscale != nullptr) {
+    const int i = 64 * (wu & 3) + l;
+    const uint32_t to = lds0 + 256 * (wu & 3);
+    if (wu < 4) {
+      const uint32_t ch = 4u * (uint32_t)(i < 32 * nbt ? i : 0);
+      dma4(p.wscale + n0, ch, to + T::WS_OFF);
+      if (lr_int && LT > 0) dma4(p.rscale + n0, ch, to + T::RS_OFF);
+    } else {
+      dma4(p.scale + m0, 4u * (uint32_t)(i < mrows ? i : mrows - 1), to + T::TS_OFF);
+    }
+  }
 
   // ---- per-lane source offsets of the direct loads ------------------------------
   // weights: wave w fetches fragments f = 8*i + w of the stage, f = nbl*CH + ch
@@ -338,12 +354,17 @@ void serq_mfma_kernel(const MfmaParams p) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
 
-    // the 16 (or fewer) MFMAs of one 64-channel fragment; REFILL: spread the NL direct
-    // loads of main tile `rt` into stage `rst` over the 8 groups
-    auto mfma_frag = [&](auto refill_c, const Frag<ABITS>& f, int rt, int rst) {
-      constexpr bool REFILL = decltype(refill_c)::value;
+    // the 16 (or fewer) MFMAs of one 64-channel fragment; PART 1, 2: the first / second half of the NL direct loads of main
+    // tile `rt` into stage `rst`, spread over the 8 groups; DONE: fragments since the last hand-off (-1: leave the priority alone)
+    auto mfma_frag = [&](auto part_c, auto done_c, const Frag<ABITS>& f, int rt, int rst) {
+      constexpr int PART = decltype(part_c)::value, DONE = decltype(done_c)::value;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
+        if constexpr (DONE >= 0) {                      // four levels per tile: by fragment or by half fragment
+          if (CH == 4 && t == 0) set_priority<(3 - DONE) & 3>();
+          if (CH == 2 && t == 0) set_priority<(3 - 2 * DONE) & 3>();
+          if (CH == 2 && t == 1) set_priority<(2 - 2 * DONE) & 3>();
+        }
         v4i xb[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -358,22 +379,29 @@ void serq_mfma_kernel(const MfmaParams p) {
             for (int j = 0; j < 2; ++j)
               acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wa, xb[j], acc[i][j], 0, 0, 0);
           }
-          if constexpr (REFILL) {
+          if constexpr (PART > 0) {
+            constexpr int NH = T::NL / 2;
             const int gi = t * 4 + i;
 #pragma unroll
-            for (int k = 0; k < T::NL; ++k)
-              if (k * 8 / T::NL == gi) issue_main_one(rt, rst, k);
+            for (int k = 0; k < NH; ++k)
+              if (k * 8 / NH == gi) issue_main_one(rt, rst, (PART - 1) * NH + k);
           }
           fence();
         }
       }
     };
+    using Plain = std::integral_constant<int, 0>;
+    using Part1 = std::integral_constant<int, 1>;
+    using Part2 = std::integral_constant<int, 2>;
+    using Same = std::integral_constant<int, -1>;
 
     // ---- prologue: fill the ring ---------------------------------------------------
 #pragma unroll
     for (int s = 0; s < NS; ++s)
       if (s < TT) issue(s, s);
+    // the first tile is enough to begin (the count of a last, 4-bit rank-r tile differs)
     if (NS == 3 && TT >= 3) wait_dma_barrier<2 * T::NL>();
+    else if (NS == 2 && KT >= 2) wait_dma_barrier<T::NL>();
     else wait_dma_barrier<0>();
 
     int t = 0;                                          // tile being computed
@@ -398,23 +426,38 @@ void serq_mfma_kernel(const MfmaParams p) {
 
     load_frags(stage_ptr(0), 0, F[0]);
 
-    // steady state: full main tiles whose refill (tile t+NS) is another full main tile
-    for (; t + NS < KTF; ) {
+    // Steady state: full main tiles whose refill (tile t+NS) is another full main tile.  An iteration begins at a hand-off, with
+    // the last fragment of tile t still to be multiplied, and ends before the next one.  The loads of the refill are spread over
+    // two fragments: eight waves that request a stage within one keep the address unit busy for as long as its products
+    // take (64 loads of 16 cycles, 4-bit tokens), and a wave whose load waits issues nothing else.
+    auto rest_of_tile = [&](auto part_c, int rt, int rst) {   // fragments 0 .. CH-2; the last one to registers
 #pragma unroll
-      for (int ch = 0; ch < CH; ++ch) {
-        if (ch + 1 < CH) {
-          load_frags(stage_ptr(st), ch + 1, F[(ch + 1) & 1]);
-          fence();
-          mfma_frag(std::false_type{}, F[ch & 1], 0, 0);
-        } else {
-          handoff_wait();
-          const int rt = t + NS, rst = st;
-          advance();
-          load_frags(stage_ptr(st), 0, F[0]);
-          fence();
-          mfma_frag(std::true_type{}, F[ch & 1], rt, rst);
-        }
+      for (int ch = 0; ch + 1 < CH; ++ch) {
+        load_frags(stage_ptr(st), ch + 1, F[(ch + 1) & 1]);
+        fence();
+        if (ch == 0) mfma_frag(part_c, std::integral_constant<int, 1>{}, F[0], rt, rst);
+        if (ch == 1) mfma_frag(Plain{}, std::integral_constant<int, 2>{}, F[1], 0, 0);
+        if (ch == 2) mfma_frag(Plain{}, std::integral_constant<int, 3>{}, F[0], 0, 0);
       }
+    };
+    if (KTF > 0) {
+      rest_of_tile(Plain{}, 0, 0);
+      while (t + NS < KTF) {
+        handoff_wait();
+        const int rt = t + NS, rst = st;
+        advance();
+        load_frags(stage_ptr(st), 0, F[0]);
+        fence();
+        mfma_frag(Part1{}, std::integral_constant<int, 0>{}, F[(CH - 1) & 1], rt, rst);
+        rest_of_tile(Part2{}, rt, rst);
+      }
+      set_priority<0>();
+      handoff_wait();
+      if (t + NS < TT) issue(t + NS, st);
+      advance();
+      prefetch_first();
+      fence();
+      mfma_frag(Plain{}, Same{}, F[(CH - 1) & 1], 0, 0);
     }
     // remaining full main tiles
     for (; t < KTF; ) {
@@ -429,7 +472,7 @@ void serq_mfma_kernel(const MfmaParams p) {
           prefetch_first();
         }
         fence();
-        mfma_frag(std::false_type{}, F[ch & 1], 0, 0);
+        mfma_frag(Plain{}, Same{}, F[ch & 1], 0, 0);
       }
     }
     if (KTAIL) {                                        // last main tile with 1 .. CH-1 fragments
@@ -445,7 +488,7 @@ void serq_mfma_kernel(const MfmaParams p) {
             prefetch_first();
           }
           fence();
-          mfma_frag(std::false_type{}, F[ch & 1], 0, 0);
+          mfma_frag(Plain{}, Same{}, F[ch & 1], 0, 0);
         }
       }
     }
@@ -517,7 +560,7 @@ void serq_mfma_kernel(const MfmaParams p) {
       for (int q4 = 0; q4 < 4; ++q4) {
         const int cl = 32 * (blk0 + i) + 8 * q4 + 4 * g;          // channel within the tile
         const float4 ws = *(const float4*)(lws + (cl < 256 ? cl : 0));
-        const float s4[4] = {ws.x, ws.y, ws.z, ws.w};
+        const float s4[4] = {ws.x * kInv, ws.y * kInv, ws.z * kInv, ws.w * kInv};
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -580,7 +623,7 @@ void serq_mfma_kernel(const MfmaParams p) {
         for (int q4 = 0; q4 < 4; ++q4) {
           const int cl = 32 * (blk0 + i) + 8 * q4 + 4 * g;
           const float4 rs = *(const float4*)(lrs_t + (cl < 256 ? cl : 0));
-          const float r4[4] = {rs.x, rs.y, rs.z, rs.w};
+          const float r4[4] = {rs.x * kInv, rs.y * kInv, rs.z * kInv, rs.w * kInv};
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             accf[i][j][4 * q4 + e] = __builtin_fmaf(r4[e], (float)tq[4 * q4 + e], accf[i][j][4 * q4 + e]);
@@ -657,7 +700,7 @@ void serq_mfma_kernel(const MfmaParams p) {
       for (int j = 0; j < 2; ++j) {
         const int m = mbase + 32 * j;
         if (m >= p.M) continue;
-        const float sm = p.scale[m];
+        const float sm = lts[64 * wm + 32 * j + lm];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           if (i >= NBW || blk0 + i >= nbt) continue;
@@ -680,8 +723,7 @@ void serq_mfma_kernel(const MfmaParams p) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int r = 64 * wm + 32 * j + lm;
-      const int m = m0 + r;
-      const float sm = p.scale[m < p.M ? m : p.M - 1];
+      const float sm = lts[r];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (i >= NBW) continue;

@@ -18,7 +18,7 @@
 //   tokens   256 rows x 128 B, the 16-byte piece c of row i at piece c ^ ((i >> 1) & 7),
 //   scales   256 rows x 8 B (tokens), 8 blocks x 64 lanes x 4 B (weights): 4 KiB,
 // two stages of 68 KiB, filled by direct global -> LDS loads (source-side swizzle) that are counted
-// by hand; the refill of a stage is spread over the MFMAs of the tile's last fragment.  The LDS reads
+// by hand; the refill of a stage is spread over the MFMAs of three fragments.  The LDS reads
 // of the next fragment's operands are issued among the MFMAs of the current one.
 #include <type_traits>
 
@@ -257,13 +257,13 @@ void serq_mx_kernel(const MxParams p) {
 
     // The 2*NBW MFMAs of fragment CHI of the current tile, whose token operands are X[PAR].
     // NEXT = 1: fetch fragment CHI+1 of the same stage meanwhile; 2: fragment 0 and the scales of the
-    // tile in stage `nst`; 0: nothing.  REFILL: spread the direct loads of full main tile `rt` into
-    // stage `rst` over the MFMA groups.
-    auto run_frag = [&](auto ch_c, auto par_c, auto next_c, auto refill_c, int nst, int rt, int rst) {
+    // tile in stage `nst`; 0: nothing.  Direct loads LO .. HI-1 of full main tile `rt` into stage `rst` are spread over the
+    // MFMA groups.
+    auto run_frag = [&](auto ch_c, auto par_c, auto next_c, auto lo_c, auto hi_c, int nst, int rt, int rst) {
       constexpr int CHI = decltype(ch_c)::value;
       constexpr int PAR = decltype(par_c)::value;
       constexpr int NEXT = decltype(next_c)::value;
-      constexpr bool REFILL = decltype(refill_c)::value;
+      constexpr int LO = decltype(lo_c)::value, HI = decltype(hi_c)::value;
       constexpr int NCH = NEXT == 1 ? CHI + 1 : 0;
       uint32_t xsn[2] = {0u, 0u};
       if constexpr (NEXT != 0) load_x(nst, NCH, X[PAR ^ 1]);
@@ -283,11 +283,9 @@ void serq_mx_kernel(const MxParams p) {
           if constexpr (NEXT != 0) W[i] = load_w(nst, NCH, i);
           if constexpr (NEXT == 2) ws[i] = load_ws(nst, i);
         }
-        if constexpr (REFILL) {
-          issue_one(std::true_type{}, rt, rst, 2 * i);
-          issue_one(std::true_type{}, rt, rst, 2 * i + 1);
-          if (i == 3) issue_one(std::true_type{}, rt, rst, 8);
-        }
+#pragma unroll
+        for (int k = LO; k < HI; ++k)
+          if ((k - LO) * 4 / (HI - LO > 0 ? HI - LO : 1) == i) issue_one(std::true_type{}, rt, rst, k);
         fence();
       }
       if constexpr (NEXT == 2) {
@@ -304,7 +302,8 @@ void serq_mx_kernel(const MxParams p) {
 #pragma unroll
     for (int s = 0; s < NS; ++s)
       if (s < TT) issue_any(s, s);
-    wait_dma_barrier<0>();
+    if (TT >= 2) wait_dma_barrier<9>();                 // the first tile is enough to begin
+    else wait_dma_barrier<0>();
 
     int t = 0;                                          // tile being computed
     int st = 0;                                         // its stage
@@ -327,15 +326,36 @@ void serq_mx_kernel(const MxParams p) {
     load_x(stage_ptr(0), 0, X[0]);
     load_xs(stage_ptr(0), xs);
 
-    // steady state: full main tiles whose refill (tile t+NS) is another full main tile
-    for (; t + NS < KTF; ) {
-      run_frag(I0{}, I0{}, I1{}, std::false_type{}, stage_ptr(st), 0, 0);
-      run_frag(I1{}, I1{}, I1{}, std::false_type{}, stage_ptr(st), 0, 0);
-      run_frag(I2{}, I0{}, I1{}, std::false_type{}, stage_ptr(st), 0, 0);
-      wait_dma_barrier<0>();                            // hand-off, unconditional here: no control flow in this loop
-      const int rt = t + NS, rst = st;
+    // Steady state: full main tiles whose refill (tile t+NS) is another full main tile.  An iteration begins at a hand-off, with
+    // the last fragment of tile t still to be multiplied, and ends before the next one (no control flow in this loop).
+    // The loads of the refill are spread over three fragments: requested within one, they keep the address unit busy for longer
+    // than its products take (72 loads of 16 cycles against 512); over all four, the last ones land too late.  Measured (us, in
+    // one fragment / two / three / four, r = 128, M = 4096, N x K): 11008 x 4096 113.9 / 110.3 / 107.6 / 110.6, 4096 x 11008 91.7 / 89.0 /
+    // 86.9 / 88.7, 28672 x 4096 278 / 270 / 268 / 273.
+    using L3 = std::integral_constant<int, 3>;
+    using L6 = std::integral_constant<int, 6>;
+    using L9 = std::integral_constant<int, 9>;
+    if (t + NS < KTF) {
+      run_frag(I0{}, I0{}, I1{}, I0{}, I0{}, stage_ptr(st), 0, 0);
+      run_frag(I1{}, I1{}, I1{}, I0{}, I0{}, stage_ptr(st), 0, 0);
+      run_frag(I2{}, I0{}, I1{}, I0{}, I0{}, stage_ptr(st), 0, 0);
+      do {
+        wait_dma_barrier<0>();
+        const int rt = t + NS, rst = st;
+        advance();
+        set_priority<3>();
+        run_frag(I3{}, I1{}, I2{}, I0{}, L3{}, stage_ptr(st), rt, rst);
+        set_priority<2>();
+        run_frag(I0{}, I0{}, I1{}, L3{}, L6{}, stage_ptr(st), rt, rst);
+        set_priority<1>();
+        run_frag(I1{}, I1{}, I1{}, L6{}, L9{}, stage_ptr(st), rt, rst);
+        set_priority<0>();
+        run_frag(I2{}, I0{}, I1{}, I0{}, I0{}, stage_ptr(st), 0, 0);
+      } while (t + NS < KTF);
+      handoff_wait();
+      if (t + NS < TT) issue_any(t + NS, st);
       advance();
-      run_frag(I3{}, I1{}, I2{}, std::true_type{}, stage_ptr(st), rt, rst);
+      run_frag(I3{}, I1{}, I2{}, I0{}, I0{}, stage_ptr(st), 0, 0);
     }
     // Every other tile (the last main tiles, a partial one, the low-rank tiles): nf = 1..4 valid
     // fragments, refilled by whatever comes NS tiles later.  One code path for every fragment: the
