@@ -1,4 +1,5 @@
-"""ctypes binding of libserq.so: argument marshalling only.
+"""Binding of libserq.so: argument marshalling only, through ctypes; the calls of a layer's pass go through the extension
+module `_fastcall` (csrc/fastcall.cpp) where their arguments are plain tensors and ints, and through ctypes otherwise.
 
 Every function has the name of the C entry point it calls (include/serq.h).
 PyTorch supplies device memory and the current stream; no arithmetic of the
@@ -8,6 +9,7 @@ this module's `lib()` raises -- there is no fallback path.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -16,6 +18,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libserq.so")
+FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
 
 F32, F16, BF16, I4 = 0, 1, 2, 3
 PATH_AUTO, PATH_SKINNY, PATH_MFMA = 0, 1, 2
@@ -71,6 +74,11 @@ SIGNATURES = {
 }
 
 _lib = None
+_fast = None            # the extension module, bound to _lib
+
+# the entry points it calls, in the order of its bind()
+_FAST = ["serq_quantize_act", "serq_swiglu_quantize_act", "serq_mx_quantize_act", "serq_mx_swiglu_quantize_act",
+         "serq_quantize_act_asym", "serq_linear", "serq_mx_linear", "serq_g128_linear"]
 
 
 class SerqError(RuntimeError):
@@ -93,8 +101,26 @@ def lib() -> C.CDLL:
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
+        _load_fastcall(L)
         _lib = L
     return _lib
+
+
+def _load_fastcall(L: C.CDLL) -> None:
+    global _fast
+    if not os.path.exists(FASTCALL_PATH):
+        raise ImportError(f"{FASTCALL_PATH} not found: build it with `python -m paper_2603_08185_amd.build`")
+    spec = importlib.util.spec_from_file_location("_fastcall", FASTCALL_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    mod.bind(*(C.cast(getattr(L, name), C.c_void_p).value for name in _FAST))
+    _fast = mod
+
+
+def _native():
+    """The extension module; its functions return None for arguments that need the general way."""
+    lib()
+    return _fast
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -231,6 +257,12 @@ def unpack_act(Xq: torch.Tensor, abits: int, M: int, K: int) -> torch.Tensor:
 def quantize_act(X: torch.Tensor, s_inv: Optional[torch.Tensor], abits: int,
                  Xq: Optional[torch.Tensor] = None, scale: Optional[torch.Tensor] = None):
     """serq_quantize_act: returns (Xq packed uint8 blob, scale fp32 [M])."""
+    if Xq is not None and scale is not None:
+        rc = (_fast or _native()).quantize_act(X, s_inv, abits, Xq, scale)
+        if rc == 0:
+            return Xq, scale
+        if rc is not None:
+            raise SerqError("serq_quantize_act", rc)
     if not X.is_cuda:
         raise ValueError("X must live in device memory")
     if X.dim() != 2 or X.stride(1) != 1:
@@ -257,6 +289,12 @@ def _rows(T: torch.Tensor, what: str):
 def swiglu_quantize_act(G: torch.Tensor, U: torch.Tensor, s_inv: Optional[torch.Tensor], abits: int,
                         Xq: Optional[torch.Tensor] = None, scale: Optional[torch.Tensor] = None):
     """serq_swiglu_quantize_act: quantize_act of silu(G) * U; returns (Xq packed uint8 blob, scale fp32 [M])."""
+    if Xq is not None and scale is not None:
+        rc = (_fast or _native()).swiglu_quantize_act(G, U, s_inv, abits, Xq, scale)
+        if rc == 0:
+            return Xq, scale
+        if rc is not None:
+            raise SerqError("serq_swiglu_quantize_act", rc)
     _rows(G, "G")
     _rows(U, "U")
     if G.shape != U.shape or G.dtype != U.dtype:
@@ -276,6 +314,12 @@ def swiglu_quantize_act(G: torch.Tensor, U: torch.Tensor, s_inv: Optional[torch.
 def mx_swiglu_quantize_act(G: torch.Tensor, U: torch.Tensor, s_inv: Optional[torch.Tensor],
                            Xq: Optional[torch.Tensor] = None, xsc: Optional[torch.Tensor] = None):
     """serq_mx_swiglu_quantize_act: mx_quantize_act of silu(G) * U; returns (codes blob, block-scale blob)."""
+    if Xq is not None and xsc is not None:
+        rc = (_fast or _native()).mx_swiglu_quantize_act(G, U, s_inv, Xq, xsc)
+        if rc == 0:
+            return Xq, xsc
+        if rc is not None:
+            raise SerqError("serq_mx_swiglu_quantize_act", rc)
     _rows(G, "G")
     _rows(U, "U")
     if G.shape != U.shape or G.dtype != U.dtype:
@@ -301,6 +345,11 @@ def linear(Xq: torch.Tensor, scale: torch.Tensor, abits: int, Wq: torch.Tensor, 
     packed R, or the constant I4 when Rp is the blob of pack_lowrank_q4."""
     if Y is None:
         Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device)
+    rc = (_fast or _native()).linear(Xq, scale, abits, Wq, wscale, s_begin, r, Rp, _DT.get(r_dtype, r_dtype), M, N, K, Y, ws, flags_)
+    if rc == 0:
+        return Y
+    if rc is not None:
+        raise SerqError("serq_linear", rc)
     rc = lib().serq_linear(_ptr(Xq), _ptr(scale), abits, _ptr(Wq), _ptr(wscale), s_begin, r, _ptr(Rp),
                            r_dtype if isinstance(r_dtype, int) else _DT[r_dtype], M, N, K, _ptr(Y), _DT[Y.dtype],
                            Y.stride(0),
@@ -385,6 +434,12 @@ def mx_unpack_weights(Wq: torch.Tensor, wsc: torch.Tensor, N: int, K: int):
 def mx_quantize_act(X: torch.Tensor, s_inv: Optional[torch.Tensor],
                     Xq: Optional[torch.Tensor] = None, xsc: Optional[torch.Tensor] = None):
     """serq_mx_quantize_act: returns (E2M1 codes blob, E8M0 block-scale blob)."""
+    if Xq is not None and xsc is not None:
+        rc = (_fast or _native()).mx_quantize_act(X, s_inv, Xq, xsc)
+        if rc == 0:
+            return Xq, xsc
+        if rc is not None:
+            raise SerqError("serq_mx_quantize_act", rc)
     if not X.is_cuda:
         raise ValueError("X must live in device memory")
     if X.dim() != 2 or X.stride(1) != 1:
@@ -424,6 +479,11 @@ def mx_linear(Xq: torch.Tensor, xsc: torch.Tensor, Wq: torch.Tensor, wsc: torch.
     """serq_mx_linear: Y = deq(X) . deq(W)^T + deq(X)[:, S] . deq(R)^T on the block-scaled FP4 units."""
     if Y is None:
         Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device)
+    rc = (_fast or _native()).mx_linear(Xq, xsc, Wq, wsc, s_begin, r, Rq, rsc, M, N, K, Y, ws, flags_)
+    if rc == 0:
+        return Y
+    if rc is not None:
+        raise SerqError("serq_mx_linear", rc)
     rc = lib().serq_mx_linear(_ptr(Xq), _ptr(xsc), _ptr(Wq), _ptr(wsc), s_begin, r, _ptr(Rq), _ptr(rsc), M, N, K,
                               _ptr(Y), _DT[Y.dtype], Y.stride(0) if M > 0 else N,
                               _ptr(ws), 0 if ws is None else ws.numel(), flags_, _stream())
@@ -497,6 +557,12 @@ def g128_unpack_scales(gscale: torch.Tensor, N: int, K: int) -> torch.Tensor:
 def quantize_act_asym(X: torch.Tensor, s_inv: Optional[torch.Tensor], abits: int, Xq: Optional[torch.Tensor] = None,
                       scale: Optional[torch.Tensor] = None, zero: Optional[torch.Tensor] = None):
     """serq_quantize_act_asym: returns (Xq packed uint8 blob, scale fp32 [M], zero int32 [M])."""
+    if Xq is not None and scale is not None and zero is not None:
+        rc = (_fast or _native()).quantize_act_asym(X, s_inv, abits, Xq, scale, zero)
+        if rc == 0:
+            return Xq, scale, zero
+        if rc is not None:
+            raise SerqError("serq_quantize_act_asym", rc)
     _rows(X, "X")
     M, K = X.shape
     L = lib()
@@ -519,6 +585,11 @@ def g128_linear(Xq: torch.Tensor, scale: torch.Tensor, zero: Optional[torch.Tens
     """serq_g128_linear: the layer with group-128 weight scales and (optionally) per-token zero points."""
     if Y is None:
         Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device)
+    rc = (_fast or _native()).g128_linear(Xq, scale, zero, abits, Wq, gscale, wsum, s_begin, r, Rp, _DT.get(r_dtype), M, N, K, Y, flags_)
+    if rc == 0:
+        return Y
+    if rc is not None:
+        raise SerqError("serq_g128_linear", rc)
     rc = lib().serq_g128_linear(_ptr(Xq), _ptr(scale), _ptr(zero), abits, _ptr(Wq), _ptr(gscale), _ptr(wsum), s_begin, r,
                                 _ptr(Rp), _DT[r_dtype], M, N, K, _ptr(Y), _DT[Y.dtype], Y.stride(0), flags_, _stream())
     _check("serq_g128_linear", rc)

@@ -10,6 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libserq.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")
 SOURCES = ["api.hip", "quantize_act.hip", "pack.hip", "skinny.hip", "gemm_mfma.hip", "gemm_mid.hip", "gemm_mx.hip", "gemm_mid_mx.hip", "skinny_mx.hip",
            "mx.hip", "peaks.hip", "noalloc.hip", "grouped.hip", "grouped_mid.hip", "fp6.hip"]
 FLAGS = [
@@ -26,7 +27,8 @@ def build_library(verbose: bool = True, extra=(), jobs: int = 8) -> str:
     """Compile every source to an object file (in parallel) and link them into libserq.so."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     sources = list(SOURCES)
-    with tempfile.TemporaryDirectory(prefix="serq_build_") as tmp:
+    with tempfile.TemporaryDirectory(prefix="serq_build_") as tmp, ThreadPoolExecutor(max_workers=1) as other:
+        fast = other.submit(build_fastcall, verbose)
         def compile_one(src: str) -> str:
             obj = os.path.join(tmp, src + ".o")
             cmd = [hipcc, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
@@ -42,7 +44,26 @@ def build_library(verbose: bool = True, extra=(), jobs: int = 8) -> str:
         if verbose:
             print(" ".join(link), flush=True)
         subprocess.run(link, check=True)
+        fast.result()
     return LIB
+
+
+def build_fastcall(verbose: bool = True) -> str:
+    """Compile the extension module that carries a layer's calls from Python to libserq.so (csrc/fastcall.cpp)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(os.path.abspath(torch.__file__))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(root, "include"),
+           "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"), "-I/opt/rocm/include",
+           os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL, "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu",
+           "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return FASTCALL
 
 
 if __name__ == "__main__":
