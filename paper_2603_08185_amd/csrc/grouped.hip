@@ -36,11 +36,8 @@ __device__ __forceinline__ float f16bits_to_f32(uint16_t u) { return (float)__bu
 // ---------------------------------------------------------------------------------------------------
 template <int KT>
 __device__ __forceinline__ void block_minmax(float& lo, float& hi, float* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    lo = fminf(lo, __shfl_xor(lo, off, 64));
-    hi = fmaxf(hi, __shfl_xor(hi, off, 64));
-  }
+  lo = wave_reduce(lo, [](float a, float b) { return fminf(a, b); });
+  hi = wave_max(hi);
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) { red[2 * w] = lo; red[2 * w + 1] = hi; }
   __syncthreads();
@@ -85,15 +82,6 @@ __device__ __forceinline__ void store_codes8(const int c[8], void* xq_row, int c
   }
 }
 
-__device__ __forceinline__ void flat8(const float* s_inv, int chunk, float v[8]) {
-  if (s_inv) {
-    const float4* p = (const float4*)s_inv + 2 * (size_t)chunk;
-    const float4 a = p[0], b = p[1];
-    v[0] *= a.x; v[1] *= a.y; v[2] *= a.z; v[3] *= a.w;
-    v[4] *= b.x; v[5] *= b.y; v[6] *= b.z; v[7] *= b.w;
-  }
-}
-
 // KT = threads per row, NC = 16-byte pieces a thread keeps in registers (0: any K, the row is read twice)
 template <int XDT, int ABITS, int KT, int NC>
 __global__ __launch_bounds__(KT) void quantize_act_asym_kernel(const void* __restrict__ X, const float* __restrict__ s_inv,
@@ -107,24 +95,24 @@ __global__ __launch_bounds__(KT) void quantize_act_asym_kernel(const void* __res
   char* xq_row = (char*)Xq + (size_t)m * ((size_t)K * ABITS / 8);
   constexpr float top = (float)((1 << ABITS) - 1);
   float lo = 0.0f, hi = 0.0f;                           // the range always contains 0
-  float v[NC > 0 ? NC : 1][8];
+  constexpr int NB = NC > 0 ? NC : 4;                   // pieces under way at a time
+  float v[NB][8];
+  auto fetch = [&](int chunk) { fetch_rows<XDT, KT, NB, false>(row, nullptr, s_inv, chunk, nchunk, v); };
+  auto range = [&](int chunk) {
+    const int nc = pieces_of<KT, NB>(chunk, nchunk);
+#pragma unroll
+    for (int c = 0; c < NB; ++c)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (c < nc) { lo = fminf(lo, v[c][i]); hi = fmaxf(hi, v[c][i]); }
+  };
   if constexpr (NC > 0) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int chunk = threadIdx.x + c * KT;
-      if (chunk < nchunk) {
-        load8<XDT>(row, chunk, v[c]);
-        flat8(s_inv, chunk, v[c]);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { lo = fminf(lo, v[c][i]); hi = fmaxf(hi, v[c][i]); }
-      }
-    }
+    fetch(threadIdx.x);
+    range(threadIdx.x);
   } else {
-    for (int chunk = threadIdx.x; chunk < nchunk; chunk += KT) {
-      load8<XDT>(row, chunk, v[0]);
-      flat8(s_inv, chunk, v[0]);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) { lo = fminf(lo, v[0][i]); hi = fmaxf(hi, v[0][i]); }
+    for (int chunk = threadIdx.x; chunk < nchunk; chunk += NB * KT) {
+      fetch(chunk);
+      range(chunk);
     }
   }
   block_minmax<KT>(lo, hi, red);
@@ -136,22 +124,23 @@ __global__ __launch_bounds__(KT) void quantize_act_asym_kernel(const void* __res
     zero[m] = (int)z - (1 << (ABITS - 1));
   }
   const float rsc = __builtin_amdgcn_rcpf(sc);
-  int c8[8];
-  if constexpr (NC > 0) {
+  auto store = [&](int chunk0) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int chunk = threadIdx.x + c * KT;
+    for (int c = 0; c < NB; ++c) {
+      const int chunk = chunk0 + c * KT;
       if (chunk < nchunk) {
+        int c8[8];
         asym_codes8<ABITS>(v[c], sc, rsc, z, c8);
         store_codes8<ABITS>(c8, xq_row, chunk);
       }
     }
+  };
+  if constexpr (NC > 0) {
+    store(threadIdx.x);
   } else {
-    for (int chunk = threadIdx.x; chunk < nchunk; chunk += KT) {
-      load8<XDT>(row, chunk, v[0]);
-      flat8(s_inv, chunk, v[0]);
-      asym_codes8<ABITS>(v[0], sc, rsc, z, c8);
-      store_codes8<ABITS>(c8, xq_row, chunk);
+    for (int chunk = threadIdx.x; chunk < nchunk; chunk += NB * KT) {
+      fetch(chunk);
+      store(chunk);
     }
   }
 }
@@ -159,22 +148,26 @@ __global__ __launch_bounds__(KT) void quantize_act_asym_kernel(const void* __res
 template <int XDT, int ABITS>
 int launch_asym_t(const void* X, const float* s_inv, int64_t M, int K, int64_t ldx, void* Xq, float* scale,
                   int32_t* zero, hipStream_t st) {
-  // as for the symmetric quantiser, but long rows of more than 256 tokens are better off with 512 threads of 3 or 4 pieces (us,
-  // 256 / 512 / 1024 threads: K = 11008 M = 128 6.4 / 4.6 / 4.3, M = 512 7.1 / 6.2 / 6.5, M = 4096 28.4 / 26.0 / 30.5; fp32
-  // input, K = 8256 M = 512 5.6 / 5.3 / 5.9)
+  // as for the symmetric quantiser
   const int nchunk = K >> 3;
-  const int threads = nchunk > 1024 && nchunk <= 2048 ? (M <= 256 ? 1024 : 512) : 256;
+  const int threads = nchunk <= 128 ? 64 : nchunk <= 384 ? 128 : nchunk <= 512 || nchunk > 2048 ? 256 : 512;
   const int per = (nchunk + threads - 1) / threads;
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QAA(KT, NC) \
   hipLaunchKernelGGL((quantize_act_asym_kernel<XDT, ABITS, KT, NC>), grid, block, 0, st, X, s_inv, K, ldx, Xq, scale, zero)
-  if (threads == 1024) SERQ_QAA(1024, 2);
-  else if (threads == 512 && per <= 3) SERQ_QAA(512, 3);
-  else if (threads == 512) SERQ_QAA(512, 4);
-  else if (per <= 1) SERQ_QAA(256, 1);
-  else if (per <= 2) SERQ_QAA(256, 2);
-  else if (per <= 4) SERQ_QAA(256, 4);
-  else SERQ_QAA(256, 0);
+  if (threads == 512) {
+    if (per <= 2) SERQ_QAA(512, 2);
+    else if (per <= 3) SERQ_QAA(512, 3);
+    else SERQ_QAA(512, 4);
+  } else if (threads == 64) {
+    SERQ_QAA(64, 2);
+  } else if (threads == 128) {
+    if (per <= 2) SERQ_QAA(128, 2);
+    else SERQ_QAA(128, 3);
+  } else {
+    if (per <= 2) SERQ_QAA(256, 2);
+    else SERQ_QAA(256, 0);
+  }
 #undef SERQ_QAA
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;
 }

@@ -83,7 +83,8 @@ __device__ __forceinline__ uint32_t pack8(const uint32_t c[8]) {
 // tile gathered by shuffles into one 8-byte store, measured 10 % slower.)
 // GLU: the row is the gated product silu(X) * U formed in fp32 (the input of the down projection,
 // quantised where it is made; Sec. 3.2, the decoder-layer flow of Fig. 2(b)).
-template <int XDT, int KT, bool GLU>
+// NR: rounds whose loads are under way together (the last one of an odd number repeats the row's last piece)
+template <int XDT, int KT, bool GLU, int NR>
 __global__ __launch_bounds__(KT) void mx_quantize_act_kernel(const void* __restrict__ X, const void* __restrict__ U,
                                                              const float* __restrict__ s_inv, int K, int64_t ldx,
                                                              int64_t ldu, int64_t M, uint32_t* __restrict__ Xq,
@@ -95,37 +96,26 @@ __global__ __launch_bounds__(KT) void mx_quantize_act_kernel(const void* __restr
   const int nchunk = K >> 3;
   const size_t Mp = (size_t)((M + 1) & ~(int64_t)1);
   const int nround = (nchunk + KT - 1) / KT;                          // KT is a multiple of 4: blocks never straddle rounds
-  for (int rd = 0; rd < nround; ++rd) {
-    const int chunk = rd * KT + threadIdx.x;
-    const bool live = chunk < nchunk;
-    float v[8];
+  for (int rd = 0; rd < nround; rd += NR) {
+    float v[NR][8];
+    const int chunk0 = rd * KT + threadIdx.x;
+    if (NR == 1 && __builtin_amdgcn_readfirstlane(chunk0) >= nchunk) break;   // nothing of the row left for this wave
+    fetch_rows<XDT, KT, NR, GLU>(row, urow, s_inv, chunk0, nchunk, v);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = 0.0f;
-    if (live) {
-      load8<XDT>(row, chunk, v);
-      if constexpr (GLU) {
-        float u[8];
-        load8<XDT>(urow, chunk, u);
+    for (int c = 0; c < NR; ++c) {
+      const int chunk = chunk0 + c * KT;
+      float amax = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = silu_mul(v[i], u[i]);
-      }
-      if (s_inv) {
-        const float4* p = (const float4*)s_inv + 2 * (size_t)chunk;
-        const float4 a = p[0], b = p[1];
-        v[0] *= a.x; v[1] *= a.y; v[2] *= a.z; v[3] *= a.w; v[4] *= b.x; v[5] *= b.y; v[6] *= b.z; v[7] *= b.w;
-      }
-    }
-    float amax = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[i]));
-    amax = fmaxf(amax, __shfl_xor(amax, 1, 64));
-    amax = fmaxf(amax, __shfl_xor(amax, 2, 64));
-    const int E = mx_exponent(amax);
-    if (live) {
-      Xq[(size_t)m * nchunk + chunk] = mx_codes8(v, E);
-      if ((chunk & 3) == 0) {
-        const int blk = chunk >> 2;
-        xsc[((size_t)(blk >> 3) * Mp + (size_t)m) * 8 + (blk & 7)] = (uint8_t)E;
+      for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[c][i]));
+      amax = fmaxf(amax, dpp<kDpp1>(amax));                           // (a row is a multiple of 8 pieces: a block's four are all in it or none)
+      amax = fmaxf(amax, dpp<kDpp2>(amax));
+      const int E = mx_exponent(amax);
+      if (chunk < nchunk) {
+        Xq[(size_t)m * nchunk + chunk] = mx_codes8(v[c], E);
+        if ((chunk & 3) == 0) {
+          const int blk = chunk >> 2;
+          xsc[((size_t)(blk >> 3) * Mp + (size_t)m) * 8 + (blk & 7)] = (uint8_t)E;
+        }
       }
     }
   }
@@ -287,30 +277,41 @@ int launch_mx_quantize_act(const void* X, const void* U, int x_dtype, const floa
   // 7.2 / 7.9 / 7.2, M = 4096 56.9 / 55.1 / 52.6; K = 28672 M = 513 12.1 / 14.0 / 12.9.
   const int nchunk = K >> 3;
   const bool f32 = x_dtype == SERQ_F32;
-  const int threads = nchunk <= 256 ? 256
+  const int threads = nchunk <= 256 ? 128
                       : M <= 512 ? (nchunk <= 512 ? 512 : 1024)
                       : nchunk <= 1024 ? 256
                       : f32 && nchunk >= 1792 ? 1024
                       : !f32 && !U && M > 1024 ? 256 : 512;
   dim3 grid((unsigned)M), block((unsigned)threads);
-#define SERQ_MXQ_LAUNCH_T(XDT, KT)                                                                                    \
-  do {                                                                                                                \
-    if (U) hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, KT, true>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu,  \
-                              M, (uint32_t*)Xq, xsc);                                                                 \
-    else hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, KT, false>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu,   \
-                            M, (uint32_t*)Xq, xsc);                                                                   \
+  // Two rounds at a time for many rows of up to 1024 pieces (us, one / two: K = 4096 M = 4096 9.7 / 8.8, K = 8192 15.9 / 15.2; few
+  // rows, whose arithmetic counts: K = 11008 M = 24 2.7 / 3.0, M = 256, gated product 4.7 / 5.1; longer rows: level)
+  const bool two = (M > 1024 || threads == 128) && nchunk > threads && nchunk <= 1024;
+#define SERQ_MXQ_LAUNCH_R(XDT, KT, GLU, NR) \
+  hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, KT, GLU, NR>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, M, (uint32_t*)Xq, xsc)
+#define SERQ_MXQ_LAUNCH_T(XDT, KT, GLU)                   \
+  do {                                                    \
+    if (two) SERQ_MXQ_LAUNCH_R(XDT, KT, GLU, 2);          \
+    else SERQ_MXQ_LAUNCH_R(XDT, KT, GLU, 1);              \
+  } while (0)
+#define SERQ_MXQ_LAUNCH_K(XDT, KT)                 \
+  do {                                             \
+    if (U) SERQ_MXQ_LAUNCH_T(XDT, KT, true);       \
+    else SERQ_MXQ_LAUNCH_T(XDT, KT, false);        \
   } while (0)
 #define SERQ_MXQ_LAUNCH(XDT)                              \
   do {                                                    \
-    if (threads == 1024) SERQ_MXQ_LAUNCH_T(XDT, 1024);    \
-    else if (threads == 512) SERQ_MXQ_LAUNCH_T(XDT, 512); \
-    else SERQ_MXQ_LAUNCH_T(XDT, 256);                     \
+    if (threads == 128) SERQ_MXQ_LAUNCH_K(XDT, 128);      \
+    else if (threads == 1024) SERQ_MXQ_LAUNCH_K(XDT, 1024);    \
+    else if (threads == 512) SERQ_MXQ_LAUNCH_K(XDT, 512); \
+    else SERQ_MXQ_LAUNCH_K(XDT, 256);                     \
   } while (0)
   if (x_dtype == SERQ_F32) SERQ_MXQ_LAUNCH(SERQ_F32);
   else if (x_dtype == SERQ_F16) SERQ_MXQ_LAUNCH(SERQ_F16);
   else SERQ_MXQ_LAUNCH(SERQ_BF16);
 #undef SERQ_MXQ_LAUNCH
+#undef SERQ_MXQ_LAUNCH_K
 #undef SERQ_MXQ_LAUNCH_T
+#undef SERQ_MXQ_LAUNCH_R
   return ok();
 }
 

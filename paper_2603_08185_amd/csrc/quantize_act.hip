@@ -7,7 +7,9 @@
 // quantise pass.  (Variants that walk several tokens per workgroup or per wave,
 // with the next row prefetched and the flattening factors kept in registers,
 // measured slower: thousands of small independent workgroups overlap their
-// phases better than any hand-made pipeline here.)  Every code equals what IEEE
+// phases better than any hand-made pipeline here.)  What bounds a workgroup is the trip to memory: all its loads are under
+// way before the first value is used (fetch_rows; us, before / now: K = 4096 M = 1 2.7 / 2.3, M = 4096 11.3 / 9.2, K = 8192 M = 24
+// 3.9 / 2.7, K = 14336 M = 4096 30.3 / 22.7, gated product 45 / 39.7), and the row's maximum goes through the lanes without LDS.  Every code equals what IEEE
 // fp32 arithmetic gives for one multiply, one division and one
 // round-to-nearest-even (codes8 below avoids most of the divisions without
 // changing any result), so the codes do not depend on how the reduction is
@@ -21,24 +23,6 @@
 
 namespace serq {
 namespace {
-
-// v <- silu(v) * u, elementwise
-template <int XDT>
-__device__ __forceinline__ void glu8(const void* urow, int chunk, float v[8]) {
-  float u[8];
-  load8<XDT>(urow, chunk, u);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = serq::silu_mul(v[i], u[i]);
-}
-
-__device__ __forceinline__ void flatten8(const float* s_inv, int chunk, float v[8]) {
-  if (s_inv) {
-    const float4* p = (const float4*)s_inv + 2 * (size_t)chunk;
-    float4 a = p[0], b = p[1];
-    v[0] *= a.x; v[1] *= a.y; v[2] *= a.z; v[3] *= a.w;
-    v[4] *= b.x; v[5] *= b.y; v[6] *= b.z; v[7] *= b.w;
-  }
-}
 
 __device__ __forceinline__ float absmax8(const float v[8], float m) {
 #pragma unroll
@@ -131,17 +115,12 @@ __global__ __launch_bounds__(KT) void quantize_act_kernel(
 
   if constexpr (NC > 0) {
     float v[NC][8];
+    fetch_rows<XDT, KT, NC, GLU>(row, urow, s_inv, threadIdx.x, nchunk, v);
+    const int nc = pieces_of<KT, NC>(threadIdx.x, nchunk);
     float amax = 0.0f;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int chunk = threadIdx.x + c * KT;
-      if (chunk < nchunk) {
-        load8<XDT>(row, chunk, v[c]);
-        if constexpr (GLU) glu8<XDT>(urow, chunk, v[c]);
-        flatten8(s_inv, chunk, v[c]);
-        amax = absmax8(v[c], amax);
-      }
-    }
+    for (int c = 0; c < NC; ++c)
+      if (c < nc) amax = absmax8(v[c], amax);
     amax = block_max<KT>(amax, red);
     const float sc = amax > 0.0f ? amax / q : 1.0f;
     if (threadIdx.x == 0) scale[m] = sc;
@@ -151,23 +130,24 @@ __global__ __launch_bounds__(KT) void quantize_act_kernel(
       if (chunk < nchunk) quant_store8<ABITS>(v[c], sc, xq_row, chunk);
     }
   } else {
+    constexpr int NB = 4;                               // pieces under way at a time
+    float v[NB][8];
     float amax = 0.0f;
-    for (int chunk = threadIdx.x; chunk < nchunk; chunk += KT) {
-      float v[8];
-      load8<XDT>(row, chunk, v);
-      if constexpr (GLU) glu8<XDT>(urow, chunk, v);
-      flatten8(s_inv, chunk, v);
-      amax = absmax8(v, amax);
+    for (int chunk = threadIdx.x; chunk < nchunk; chunk += NB * KT) {
+      fetch_rows<XDT, KT, NB, GLU>(row, urow, s_inv, chunk, nchunk, v);
+      const int nc = pieces_of<KT, NB>(chunk, nchunk);
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+        if (c < nc) amax = absmax8(v[c], amax);
     }
     amax = block_max<KT>(amax, red);
     const float sc = amax > 0.0f ? amax / q : 1.0f;
     if (threadIdx.x == 0) scale[m] = sc;
-    for (int chunk = threadIdx.x; chunk < nchunk; chunk += KT) {
-      float v[8];
-      load8<XDT>(row, chunk, v);
-      if constexpr (GLU) glu8<XDT>(urow, chunk, v);
-      flatten8(s_inv, chunk, v);
-      quant_store8<ABITS>(v, sc, xq_row, chunk);
+    for (int chunk = threadIdx.x; chunk < nchunk; chunk += NB * KT) {
+      fetch_rows<XDT, KT, NB, GLU>(row, urow, s_inv, chunk, nchunk, v);
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+        if (chunk + c * KT < nchunk) quant_store8<ABITS>(v[c], sc, xq_row, chunk + c * KT);
     }
   }
 }
@@ -176,27 +156,35 @@ template <int XDT, int ABITS, bool GLU>
 int launch_t(const void* X, const void* U, const float* s_inv, int64_t M, int K, int64_t ldx, int64_t ldu, void* Xq,
              float* scale, hipStream_t st) {
   const int nchunk = K >> 3;
-  // 256 threads with 1, 2, 4 or 5 pieces each.  Rows of 1025 .. 2048 pieces go to 1024 threads with 2 while the rows do not
-  // fill the chip, to 512 with 3 or 4 below 1024 rows, and beyond that to 1024 again, but for rows of at most 1280 pieces,
-  // where too many of those 2 lie past the row.  Measured (us, 256 / 512 / 1024 threads, 8-bit codes; the gated product behind
-  // the semicolon): K = 8256 M = 256 5.4 / 4.5 / 4.2, M = 2048 12.2 / 13.4 / 14.6; 17.2 / 18.0 / 18.1; K = 11008 M = 1
-  // 4.4 / 3.3 / 3.1, M = 256 6.2 / 4.9 / 4.6; 7.9 / 6.0 / 5.3, M = 513 6.5 / 5.8 / 6.6; 9.4 / 8.0 / 8.9, M = 768
-  // 8.1 / 7.2 / 8.3, M = 1024 9.7 / 9.9 / 9.7, M = 4096 27.5 / 26.9 / 28.8; 48.3 / 46.1 / 44.0; K = 14336 M = 4096
-  // 42.9 / 40.7 / 37.7.  Shorter rows: at K = 8192 256 and 1024 threads are level up to M = 256, beyond that 256 are faster
-  // (M = 4096 20.5 / 29.2).
-  const int threads = nchunk <= 1024 || nchunk > 2048 ? 256 : M <= 512 ? 1024 : M < 1024 ? 512 : nchunk > 1280 ? 1024 : 256;
+  // 64, 128 or 256 threads with two or three pieces each, 512 with two to four for rows of 513 .. 2048 pieces; the gated product of few
+  // tokens, whose arithmetic counts, takes 1024 with two for the longest of them.  Many short rows are bound by the rate at which
+  // waves are started (us, 64 / 128 / 256 threads, M = 4096: K = 1024 4.3 / 6.0 / 7.1, K = 1536 5.5 / 5.3 / 8.3, K = 2048
+  // 6.3 / 6.1 / 9.6, K = 3072 8.9 / 7.8 / 8.0, K = 4096 11.1 / 9.9 / 9.5; M = 1 K = 1024 2.0 / 2.0 / 2.1, K = 4096 3.4 / 2.6 / 2.3).
+  // Measured (us, 256 / 512 / 1024 threads, 8-bit codes, rows
+  // from the last-level cache; the gated product behind the semicolon): K = 4096 M = 1 2.2 / 2.5 / 2.6, M = 1000
+  // 4.5 / 6.0 / 7.1; K = 6144 M = 16 2.8 / 2.7 / 3.1; K = 8192 M = 24 3.0 / 2.7 / 3.4, M = 1000 6.4 / 5.9 / 9.7, M = 4096
+  // 14.5 / 14.2 / 29; K = 11008 M = 16 3.5 / 3.1 / 3.1, M = 256 4.0 / 3.6 / 3.8; 6.1 / 5.3 / 5.0, M = 1024 12.3 / 10.9 / 11.9, M = 4096
+  // 33.9 / 32.6 / 37.3; K = 14336 M = 16 5.3 / 4.5 / 4.2, M = 600 7.7 / 6.6 / 6.7;, M = 4096 23.7 / 22.7 / 26.0; 42.4 / 39.7 / 41.5.
+  const int threads = nchunk <= 128 ? 64 : nchunk <= 384 ? 128 : nchunk <= 512 || nchunk > 2048 ? 256 : U && nchunk > 1024 && M <= 512 ? 1024 : 512;
   const int per = (nchunk + threads - 1) / threads;
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QA_LAUNCH(KT, NC)                                                                                            \
   hipLaunchKernelGGL((quantize_act_kernel<XDT, ABITS, KT, NC, GLU>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, Xq, scale)
-  if (threads == 1024) SERQ_QA_LAUNCH(1024, 2);
-  else if (threads == 512 && per <= 3) SERQ_QA_LAUNCH(512, 3);
-  else if (threads == 512) SERQ_QA_LAUNCH(512, 4);
-  else if (per <= 1) SERQ_QA_LAUNCH(256, 1);
-  else if (per <= 2) SERQ_QA_LAUNCH(256, 2);
-  else if (per <= 4) SERQ_QA_LAUNCH(256, 4);
-  else if (per <= 5) SERQ_QA_LAUNCH(256, 5);
-  else SERQ_QA_LAUNCH(256, 0);
+  if (threads == 1024) {
+    if constexpr (GLU) SERQ_QA_LAUNCH(1024, 2);
+  } else if (threads == 512) {
+    if (per <= 2) SERQ_QA_LAUNCH(512, 2);
+    else if (per <= 3) SERQ_QA_LAUNCH(512, 3);
+    else SERQ_QA_LAUNCH(512, 4);
+  } else if (threads == 64) {
+    SERQ_QA_LAUNCH(64, 2);
+  } else if (threads == 128) {
+    if (per <= 2) SERQ_QA_LAUNCH(128, 2);
+    else SERQ_QA_LAUNCH(128, 3);
+  } else {
+    if (per <= 2) SERQ_QA_LAUNCH(256, 2);
+    else SERQ_QA_LAUNCH(256, 0);
+  }
 #undef SERQ_QA_LAUNCH
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;
 }

@@ -51,3 +51,11 @@ def _check(M, K, dtype):
     Xg, xg = serq.mx_swiglu_quantize_act(G, Xd, sd)
     cg, eg = serq.mx_unpack_act(Xg, xg, M, K)
     assert torch.equal(cg, c) and torch.equal(eg.int(), e.int() + 5)
+
+
+# short rows, which go to 64 and 128 threads, on both sides of every limit; and rows that are walked several times
+@pytest.mark.parametrize("M,K", [(M, K) for M in (1, 5, 1030) for K in (64, 512, 960, 1024, 1088, 1984, 2048, 2112, 3072, 3136)] +
+                         [(2, 24576), (3, 32832), (5, 65536)])
+def test_codes_match_the_oracle_short_and_walked_rows(M, K):
+    for dtype in (torch.bfloat16, torch.float16, torch.float32):
+        _check(M, K, dtype)
