@@ -9,8 +9,14 @@
 // same load stream without products, launch included, 12.6 us (at K = 11264), the matrix unit alone 6.  The rest is the start
 // and the end of a tile and what the two do not overlap.  Fixed costs: 4 us at K = 256, r = 0 in a graph, 1 us more for r = 128.
 // The tiled kernel with 4 K slices and a second launch takes 32 us there; M = 100, 6144 x 4096: 9.0 against 24.4 us.
-// The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.  Rings of twice the depth where a workgroup has
-// a compute unit to itself: 9.3 -> 10.0 us at M = 100, 6144 x 4096 (the first stage lands behind all the others' requests).
+// The rank-r operands through LDS, converted once: 2.2 -> 1.0 us at r = 128.  They used to wait for the partial tiles to be added and
+// then took their place, two barriers later; beside the partial tiles, of which a wave parks only those it does not finish itself, they
+// are there at the same barrier.  us, before / now, r = 128 unless given, N x K, weights from HBM: W4A8 4096 x 1024 M = 100 5.85 / 5.68,
+// 4096 x 4096 M = 333 15.3 / 14.9, M = 512 17.6 / 17.3, 6144 x 4096 M = 100 10.21 / 10.04, 4096 x 11008 M = 256 20.7 / 20.5; W4A4 4096 x 4096
+// M = 333 r = 64 13.85 / 13.47, M = 900 r = 256 26.6 / 26.1.  Requested before the last products instead of behind them: the same with
+// 8-bit tokens, with 4-bit ones 4096 x 11008 M = 200 16.2 -> 16.8; half a unit earlier still 6144 x 4096 M = 100 10.2 -> 10.45.
+// Rings of twice the depth where a workgroup has a compute unit to itself: 9.3 -> 10.0 us at M = 100, 6144 x 4096 (the first stage
+// lands behind all the others' requests).
 //
 // Two workgroups share a compute unit: one's start and end run beside the other's main loop.  Workgroups of 8 waves that have one to
 // themselves keep more loads in flight, which pays no more since the loads are whole lines: us, 8 / 4 waves, W4A8, r = 128, N x K, one tile
@@ -43,12 +49,13 @@ struct Mid {
   static constexpr int NL = ABITS == 8 ? 6 : 8;      // direct loads of a stage
   static constexpr int REGION = NS * STAGE;          // LDS of one wave: 18 KiB / 16 KiB
   static constexpr int SH = ABITS == 8 ? 4 : 8;
-  // The rank-r term in chunks of 128 ranks: 16 R fragments (4-bit R: 4) and behind them the token codes take the place of the
-  // partial tiles once those have been added.
-  static constexpr int LRX_OFF = 16 * 1024;
-  static constexpr int LDS = NW * REGION;
-  static_assert(REGION >= kMidPart, "a partial tile fits the ring it replaces");
-  static_assert(LDS >= LRX_OFF + 64 * 256, "the rank-r operands fit the rings");
+  // A wave keeps the MFMA tile that it finishes and parks the other three at the start of its region.  Behind them lies its share
+  // of a chunk of the rank-r term, 128 ranks: four R fragments (4-bit R: two, of the first two waves) and the codes of 16 token rows
+  // of 256 bytes, the first XIN of them in its region, the others behind all regions.
+  static constexpr int LRR_OFF = 3 * kMidPart / 4, LRX_OFF = LRR_OFF + 4 * 1024;
+  static constexpr int XIN = REGION - LRX_OFF >= 8 * 256 ? 8 : 0;
+  static constexpr int LDS = NW * (REGION + (16 - XIN) * 256);
+  static_assert(REGION >= LRX_OFF + XIN * 256, "what a wave parks fits the ring it replaces");
   static_assert(2 * LDS <= 160 * 1024, "LDS budget: two workgroups");
 };
 
@@ -175,7 +182,7 @@ void serq_mid_kernel(const MidParams p) {
 #pragma unroll
     for (int q = 0; q < (lr_int ? 1 : 2); ++q) {
       const int f = lr_int ? (vw & 3) : 2 * vw + q;
-      const int b = f / NJ, jb = jb0 + f % NJ;
+      const int b = f >> (lr_int ? 1 : 3), jb = jb0 + (f & (NJ - 1));
       lrr[v][q] = p.Rp[((size_t)(nb0 + (b < nbt ? b : 0)) * JB + (jb < JB ? jb : JB - 1)) * 64 + l];
     }
     const int c0 = p.s_begin + (lr_int ? 64 : 16) * jb0;   // first channel of the chunk
@@ -190,6 +197,13 @@ void serq_mid_kernel(const MidParams p) {
     }
     }
   };
+  // where fragment f of a chunk lies (brought by wave f / 4, 4-bit R: f / 2), and token row `row` of it (by wave row / 16)
+  auto lr_frag = [&](int f) { return lds + (lr_int ? (f >> 1) * T::REGION + (f & 1) * 1024 : (f >> 2) * T::REGION + (f & 3) * 1024) + T::LRR_OFF; };
+  auto lr_row = [&](int row) {
+    const int ww = row >> 4, k = row & 15;
+    return lds + (k < T::XIN ? ww * T::REGION + T::LRX_OFF + k * 256
+                             : NW * T::REGION + (ww * (16 - T::XIN) + k - T::XIN) * 256);
+  };
   auto lr_park = [&]() {
 #pragma unroll
     for (int v = 0; v < VH; ++v) {
@@ -197,9 +211,9 @@ void serq_mid_kernel(const MidParams p) {
 #pragma unroll
     for (int q = 0; q < (lr_int ? 1 : 2); ++q) {
       const int f = lr_int ? (vw & 3) : 2 * vw + q;
-      if (!lr_int || vw < 4) *(u4*)(lds + f * 1024 + l * 16) = lrr[v][q];
+      if (!lr_int || vw < 4) *(u4*)(lr_frag(f) + l * 16) = lrr[v][q];
     }
-    uint8_t* row = lds + T::LRX_OFF + lrow * 256;
+    uint8_t* row = lr_row(lrow);
     const int c = l & 7;                              // 16 channels
     if constexpr (lr_int) {
       if constexpr (ABITS == 8) *(u4*)(row + 16 * (c ^ (lrow & 15))) = lrx[v];
@@ -234,25 +248,30 @@ void serq_mid_kernel(const MidParams p) {
   }
 
   // ---- the waves meet -------------------------------------------------------------------------------------------
+  // Tile t goes to slot (t - w - 1) % 4 of this wave's region; its own stays in registers.
+  v16i tot;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
+  for (int t = 0; t < 4; ++t) {
+    const v16i& a = acc[t >> 1][t & 1];
+    if (t == w) {                                      // uniform
+      tot = a;
+    } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        *(v4i*)(my + ((2 * i + j) * 4 + q) * 1024 + l * 16) =
-            v4i{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        *(v4i*)(my + (((t - w - 1) & 3) * 4 + q) * 1024 + l * 16) = v4i{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+    }
+  }
+  if (JB > 0) lr_park();
   __syncthreads();
-  int tot[NE];
 #pragma unroll
-  for (int e = 0; e < NE; ++e) tot[e] = 0;
-#pragma unroll
-  for (int ww = 0; ww < NW; ++ww)
+  for (int d = 1; d < NW; ++d) {                       // wave w + d has this wave's tile in slot 3 - d
+    const uint8_t* src = lds + ((w + d) & 3) * T::REGION + (3 - d) * 4096 + l * 16;
 #pragma unroll
     for (int q = 0; q < QN; ++q) {
-      const v4i v = *(const v4i*)(lds + ww * T::REGION + (w * 4 + q) * 1024 + l * 16);
+      const v4i v = *(const v4i*)(src + q * 1024);
       tot[4 * q] += v.x; tot[4 * q + 1] += v.y; tot[4 * q + 2] += v.z; tot[4 * q + 3] += v.w;
     }
+  }
 
   const bool live = mloc < mrows && ti < nbt;
   const int n = 32 * blk + 4 * g;                      // registers 4*q + e: channel n + 8*q + e
@@ -272,17 +291,19 @@ void serq_mid_kernel(const MidParams p) {
 #pragma unroll
   for (int e = 0; e < 16; ++e) af[e] = y[e];
   for (int jb0 = 0; jb0 < JB; jb0 += NJ) {
-    __syncthreads();                                   // (the loads of this chunk were requested a chunk ago)
-    lr_park();
-    __syncthreads();
+    if (jb0 > 0) {                                     // (the loads of this chunk were requested a chunk ago)
+      __syncthreads();
+      lr_park();
+      __syncthreads();
+    }
     if (jb0 + NJ < JB) lr_fetch(jb0 + NJ);
-    const uint8_t* row = lds + T::LRX_OFF + mloc * 256;
+    const uint8_t* row = lr_row(mloc);
     auto piece = [&](int c) { return *(const u4*)(row + 16 * (c ^ (mloc & 15))); };
 #pragma unroll
     for (int q = 0; q < NJ; ++q) {
       if (jb0 + q < JB) {                              // uniform
         const int f = ti * NJ + q;
-        const u4 rr = *(const u4*)(lds + f * 1024 + l * 16);
+        const u4 rr = *(const u4*)(lr_frag(f) + l * 16);
         if constexpr (lr_int) {
           v4i a0, a1, b0, b1;
           unpack_frag(rr, a0, a1);
