@@ -78,12 +78,12 @@ __device__ __forceinline__ uint32_t pack8(const uint32_t c[8]) {
 }
 
 // ---- activations ----------------------------------------------------------------------------------
-// One workgroup per token; a thread owns 8 consecutive channels, four neighbouring threads a block.
-// (One 16-byte piece per thread on a two-dimensional grid, with the exponent bytes of a 256-channel
-// tile gathered by shuffles into one 8-byte store, measured 10 % slower.)
+// A thread owns 8 consecutive channels, four neighbouring threads a block.  A block needs nothing from the rest of its row, so a
+// row is cut into workgroups of KT threads (blockIdx.y): what bounds the kernel is how soon all its loads are under way, and below a
+// few hundred rows a workgroup per row leaves the chip idle or walks the row in rounds that wait for one another.
 // GLU: the row is the gated product silu(X) * U formed in fp32 (the input of the down projection,
 // quantised where it is made; Sec. 3.2, the decoder-layer flow of Fig. 2(b)).
-// NR: rounds whose loads are under way together (the last one of an odd number repeats the row's last piece)
+// NR: pieces of a thread, KT apart, whose loads are under way together (one past the row's end repeats its last piece)
 template <int XDT, int KT, bool GLU, int NR>
 __global__ __launch_bounds__(KT) void mx_quantize_act_kernel(const void* __restrict__ X, const void* __restrict__ U,
                                                              const float* __restrict__ s_inv, int K, int64_t ldx,
@@ -95,11 +95,9 @@ __global__ __launch_bounds__(KT) void mx_quantize_act_kernel(const void* __restr
   const char* urow = GLU ? (const char*)U + (size_t)m * (size_t)ldu * esz : nullptr;
   const int nchunk = K >> 3;
   const size_t Mp = (size_t)((M + 1) & ~(int64_t)1);
-  const int nround = (nchunk + KT - 1) / KT;                          // KT is a multiple of 4: blocks never straddle rounds
-  for (int rd = 0; rd < nround; rd += NR) {
+  const int chunk0 = (int)blockIdx.y * (KT * NR) + threadIdx.x;       // KT is a multiple of 4: a block's pieces stay together
+  if (__builtin_amdgcn_readfirstlane(chunk0) < nchunk) {              // else nothing of the row is left for this wave
     float v[NR][8];
-    const int chunk0 = rd * KT + threadIdx.x;
-    if (NR == 1 && __builtin_amdgcn_readfirstlane(chunk0) >= nchunk) break;   // nothing of the row left for this wave
     fetch_rows<XDT, KT, NR, GLU>(row, urow, s_inv, chunk0, nchunk, v);
 #pragma unroll
     for (int c = 0; c < NR; ++c) {
@@ -119,6 +117,7 @@ __global__ __launch_bounds__(KT) void mx_quantize_act_kernel(const void* __restr
       }
     }
   }
+  if (blockIdx.y > 0) return;
   // scale bytes of the blocks that the last 256-channel tile does not have
   const int nblk = K >> 5;
   const int nblk8 = (nblk + 7) & ~7;
@@ -269,48 +268,32 @@ __global__ __launch_bounds__(kT) void mx_unpack_act_kernel(const uint32_t* __res
 
 int launch_mx_quantize_act(const void* X, const void* U, int x_dtype, const float* s_inv, int64_t M, int K, int64_t ldx,
                            int64_t ldu, void* Xq, uint8_t* xsc, hipStream_t st) {
-  // A row is walked in rounds of one piece per thread: while the rows do not fill the chip, one round each (two for the
-  // longest); above that it depends on how many bytes a thread has in flight.  Measured (us, 256 / 512 / 1024 threads, 16-bit
-  // input; the gated product behind the semicolon): K = 4096 M = 24 2.8 / 2.5 / 2.5; K = 8192 M = 4096 16.0 / 17.1 / 19.3;
-  // K = 11008 M = 24 4.4 / 3.3 / 2.9, M = 256 5.7 / 4.2 / 3.8, M = 1024 7.9 / 6.8 / 7.9; 11.8 / 10.1 / 10.5, M = 4096
-  // 20.7 / 21.4 / 23.8; 46.0 / 42.9 / 43.0; K = 13312 M = 2048 13.2 / 14.3 / 15.3.  fp32 input: K = 14336 M = 513
-  // 7.2 / 7.9 / 7.2, M = 4096 56.9 / 55.1 / 52.6; K = 28672 M = 513 12.1 / 14.0 / 12.9.
+  // One piece per thread and 256 threads a workgroup; rows of at most 1024 channels fill 128.  From 700 rows of 16-bit input on, where
+  // the loads in flight count and not how many workgroups there are, two pieces per thread (the gated product has two loads a
+  // piece already, fp32 input two).  Measured (us, a workgroup of up to 1024 threads per row / this rule):
+  //   K = 4096  M = 1500 5.25 / 4.64, M = 2048 6.05 / 5.52, M = 4096 9.88 / 8.35, gated product M = 1000 5.95 / 5.19;  K = 1024 M = 4096
+  //   4.81 / 3.89;  K = 8192 M = 2048 9.2 / 8.6;  K = 11008 M = 700 6.0 / 5.2, M = 4096 20.7 / 19.6;  K = 13312 M = 3000 18.9 / 16.9;
+  //   K = 14336 gated product M = 24 3.85 / 2.49, M = 200 4.34 / 3.99, M = 4096 41.3 / 38.7;  K = 28672 M = 4 3.6 / 2.4;  fp32 K = 11008
+  //   M = 333 6.7 / 5.7.  One round of 256 / two rounds of 128 threads, the second behind the first: K = 11008 M = 700 7.0 / 6.8, K = 14336
+  //   M = 1024 11.0 / 10.6, M = 256 3.94 / 4.09, K = 4096 M = 2048 6.8 / 6.5, M = 400 3.28 / 3.53, gated product M = 1000 6.1 / 6.75.
   const int nchunk = K >> 3;
-  const bool f32 = x_dtype == SERQ_F32;
-  const int threads = nchunk <= 256 ? 128
-                      : M <= 512 ? (nchunk <= 512 ? 512 : 1024)
-                      : nchunk <= 1024 ? 256
-                      : f32 && nchunk >= 1792 ? 1024
-                      : !f32 && !U && M > 1024 ? 256 : 512;
-  dim3 grid((unsigned)M), block((unsigned)threads);
-  // Two rounds at a time for many rows of up to 1024 pieces (us, one / two: K = 4096 M = 4096 9.7 / 8.8, K = 8192 15.9 / 15.2; few
-  // rows, whose arithmetic counts: K = 11008 M = 24 2.7 / 3.0, M = 256, gated product 4.7 / 5.1; longer rows: level)
-  const bool two = (M > 1024 || threads == 128) && nchunk > threads && nchunk <= 1024;
+  const bool two = !U && x_dtype != SERQ_F32 && M >= 700 && nchunk > 128;
+  const int threads = two || nchunk <= 128 ? 128 : 256, per = two ? 256 : threads;
+  dim3 grid((unsigned)M, (unsigned)((nchunk + per - 1) / per)), block((unsigned)threads);
 #define SERQ_MXQ_LAUNCH_R(XDT, KT, GLU, NR) \
   hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, KT, GLU, NR>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, M, (uint32_t*)Xq, xsc)
-#define SERQ_MXQ_LAUNCH_T(XDT, KT, GLU)                   \
-  do {                                                    \
-    if (two) SERQ_MXQ_LAUNCH_R(XDT, KT, GLU, 2);          \
-    else SERQ_MXQ_LAUNCH_R(XDT, KT, GLU, 1);              \
-  } while (0)
-#define SERQ_MXQ_LAUNCH_K(XDT, KT)                 \
-  do {                                             \
-    if (U) SERQ_MXQ_LAUNCH_T(XDT, KT, true);       \
-    else SERQ_MXQ_LAUNCH_T(XDT, KT, false);        \
-  } while (0)
-#define SERQ_MXQ_LAUNCH(XDT)                              \
-  do {                                                    \
-    if (threads == 128) SERQ_MXQ_LAUNCH_K(XDT, 128);      \
-    else if (threads == 1024) SERQ_MXQ_LAUNCH_K(XDT, 1024);    \
-    else if (threads == 512) SERQ_MXQ_LAUNCH_K(XDT, 512); \
-    else SERQ_MXQ_LAUNCH_K(XDT, 256);                     \
+#define SERQ_MXQ_LAUNCH(XDT)                                        \
+  do {                                                              \
+    if (U && threads == 128) SERQ_MXQ_LAUNCH_R(XDT, 128, true, 1);  \
+    else if (U) SERQ_MXQ_LAUNCH_R(XDT, 256, true, 1);               \
+    else if (threads == 256) SERQ_MXQ_LAUNCH_R(XDT, 256, false, 1); \
+    else if (two) SERQ_MXQ_LAUNCH_R(XDT, 128, false, 2);            \
+    else SERQ_MXQ_LAUNCH_R(XDT, 128, false, 1);                     \
   } while (0)
   if (x_dtype == SERQ_F32) SERQ_MXQ_LAUNCH(SERQ_F32);
   else if (x_dtype == SERQ_F16) SERQ_MXQ_LAUNCH(SERQ_F16);
   else SERQ_MXQ_LAUNCH(SERQ_BF16);
 #undef SERQ_MXQ_LAUNCH
-#undef SERQ_MXQ_LAUNCH_K
-#undef SERQ_MXQ_LAUNCH_T
 #undef SERQ_MXQ_LAUNCH_R
   return ok();
 }

@@ -59,3 +59,12 @@ def _check(M, K, dtype):
 def test_codes_match_the_oracle_short_and_walked_rows(M, K):
     for dtype in (torch.bfloat16, torch.float16, torch.float32):
         _check(M, K, dtype)
+
+
+# MXFP4 rows are cut into workgroups: around the row count from which a thread takes two pieces, with a last workgroup that has one
+# piece per thread, two, or less than a wave
+@pytest.mark.parametrize("M", [699, 700, 701])
+@pytest.mark.parametrize("K", [1024, 1088, 2048, 2112, 3200])
+def test_codes_match_the_oracle_two_pieces_per_thread(M, K):
+    for dtype in (torch.bfloat16, torch.float32):
+        _check(M, K, dtype)
