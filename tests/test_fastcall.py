@@ -1,4 +1,8 @@
 """The extension module that carries a layer's calls to the library: the same results, errors and refusals as through ctypes."""
+import ctypes
+import threading
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -139,3 +143,37 @@ def test_current_stream_and_errors(monkeypatch):
             serq.quantize_act(x.double(), None, 8, xq, sc)
         with pytest.raises(KeyError):
             serq.linear(xq, sc, 8, xq, sc, 3, 64, 128, r_dtype=torch.int32, Y=x)
+
+
+# The entry point is a wait of the C library here (for a semaphore in the first operand, until the time in the second): it can only
+# end in time if the thread that posts gets the interpreter lock.
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["linear", "mx_linear", "g128_linear"])
+def test_interpreter_lock_is_free_during_the_call(name):
+    L, f, libc = serq.lib(), serq._fast, ctypes.CDLL(None, use_errno=True)
+    real = [ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in serq._FAST]
+    wait = ctypes.cast(libc.sem_timedwait, ctypes.c_void_p).value
+    sem, until = torch.zeros(16, dtype=torch.int64), torch.zeros(2, dtype=torch.int64)
+    until[0] = int(time.clock_gettime(time.CLOCK_REALTIME)) + 4
+    libc.sem_init(ctypes.c_void_p(sem.data_ptr()), 0, 0)
+    y = torch.zeros((1, 64), dtype=torch.bfloat16)
+    args = {"linear": (sem, until, 8, sem, sem, 0, 0, None, 2, 1, 64, 128, y, None, 0),
+            "mx_linear": (sem, until, sem, sem, 0, 0, None, None, 1, 64, 128, y, None, 0),
+            "g128_linear": (sem, until, None, 8, sem, sem, sem, 0, 0, None, 2, 1, 64, 128, y, 0)}[name]
+    inside = threading.Event()
+
+    def post():
+        inside.wait()
+        time.sleep(0.2)                                                   # the call has begun
+        libc.sem_post(ctypes.c_void_p(sem.data_ptr()))
+
+    t = threading.Thread(target=post)
+    t.start()
+    try:
+        f.bind(*(wait if n == "serq_" + name else r for n, r in zip(serq._FAST, real)))
+        inside.set()
+        assert getattr(f, name)(*args) == 0                               # -1: timed out
+    finally:
+        f.bind(*real)
+        inside.set()
+        t.join()
