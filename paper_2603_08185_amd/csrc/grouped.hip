@@ -148,9 +148,8 @@ __global__ __launch_bounds__(KT) void quantize_act_asym_kernel(const void* __res
 template <int XDT, int ABITS>
 int launch_asym_t(const void* X, const float* s_inv, int64_t M, int K, int64_t ldx, void* Xq, float* scale,
                   int32_t* zero, hipStream_t st) {
-  // as for the symmetric quantiser
   const int nchunk = K >> 3;
-  const int threads = nchunk <= 128 ? 64 : nchunk <= 384 ? 128 : nchunk <= 512 || nchunk > 2048 ? 256 : 512;
+  const int threads = quantizer_threads(nchunk, M, 512, 256);
   const int per = (nchunk + threads - 1) / threads;
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QAA(KT, NC) \
@@ -158,15 +157,22 @@ int launch_asym_t(const void* X, const float* s_inv, int64_t M, int K, int64_t l
   if (threads == 512) {
     if (per <= 2) SERQ_QAA(512, 2);
     else if (per <= 3) SERQ_QAA(512, 3);
-    else SERQ_QAA(512, 4);
+    else if (per <= 4) SERQ_QAA(512, 4);
+    else SERQ_QAA(512, 0);
   } else if (threads == 64) {
     SERQ_QAA(64, 2);
   } else if (threads == 128) {
     if (per <= 2) SERQ_QAA(128, 2);
     else SERQ_QAA(128, 3);
+  } else if (threads == 768) {
+    SERQ_QAA(768, 2);
+  } else if (threads == 1024) {
+    if (per <= 2) SERQ_QAA(1024, 2);
+    else if (per <= 3) SERQ_QAA(1024, 3);
+    else SERQ_QAA(1024, 4);
   } else {
-    if (per <= 2) SERQ_QAA(256, 2);
-    else SERQ_QAA(256, 0);
+    if (per <= 1) SERQ_QAA(256, 1);
+    else SERQ_QAA(256, 2);
   }
 #undef SERQ_QAA
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;

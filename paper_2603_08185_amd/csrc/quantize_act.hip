@@ -2,18 +2,14 @@
 //
 // Sec. 3.2 Eq. 4 (X~ = X diag(1/s)) followed by Sec. 2.1 Eq. 1 per token:
 //   scale[m] = max_k |x~| / qmax,  code = clip(rne(x~ / scale), -qmax, qmax).
-// One workgroup per token; the row is read from HBM once, in
-// 16-byte pieces, and kept in registers between the absmax pass and the
-// quantise pass.  (Variants that walk several tokens per workgroup or per wave,
-// with the next row prefetched and the flattening factors kept in registers,
-// measured slower: thousands of small independent workgroups overlap their
-// phases better than any hand-made pipeline here.)  What bounds a workgroup is the trip to memory: all its loads are under
-// way before the first value is used (fetch_rows; us, before / now: K = 4096 M = 1 2.7 / 2.3, M = 4096 11.3 / 9.2, K = 8192 M = 24
-// 3.9 / 2.7, K = 14336 M = 4096 30.3 / 22.7, gated product 45 / 39.7), and the row's maximum goes through the lanes without LDS.  Every code equals what IEEE
-// fp32 arithmetic gives for one multiply, one division and one
-// round-to-nearest-even (codes8 below avoids most of the divisions without
-// changing any result), so the codes do not depend on how the reduction is
-// scheduled.
+// One workgroup per token; the row is read from HBM once, in 16-byte pieces, and kept in registers between the absmax pass and the
+// quantise pass.  (Variants that walk several tokens per workgroup or per wave, with the next row prefetched and the flattening factors
+// kept in registers, measured slower: thousands of small independent workgroups overlap their phases better than any hand-made pipeline
+// here.)  What bounds a workgroup is the trip to memory: all its loads are under way before the first value is used (fetch_rows; us,
+// before / now: K = 4096 M = 1 2.7 / 2.3, M = 4096 11.3 / 9.2, K = 8192 M = 24 3.9 / 2.7, K = 14336 M = 4096 30.3 / 22.7, gated product
+// 45 / 39.7), and the row's maximum goes through the lanes without LDS.  Every code equals what IEEE fp32 arithmetic gives for one
+// multiply, one division and one round-to-nearest-even (codes8 below avoids most of the divisions without changing any result), so the
+// codes do not depend on how the reduction is scheduled.
 //
 // GLU variants: the token row is the gated product silu(gate) * up of two inputs (the input of the
 // down projection, quantised where it is made instead of being stored in 16 bits and read back;
@@ -156,34 +152,30 @@ template <int XDT, int ABITS, bool GLU>
 int launch_t(const void* X, const void* U, const float* s_inv, int64_t M, int K, int64_t ldx, int64_t ldu, void* Xq,
              float* scale, hipStream_t st) {
   const int nchunk = K >> 3;
-  // 64, 128 or 256 threads with two or three pieces each, 512 with two to four for rows of 513 .. 2048 pieces; the gated product of few
-  // tokens, whose arithmetic counts, takes 1024 with two for the longest of them.  Many short rows are bound by the rate at which
-  // waves are started (us, 64 / 128 / 256 threads, M = 4096: K = 1024 4.3 / 6.0 / 7.1, K = 1536 5.5 / 5.3 / 8.3, K = 2048
-  // 6.3 / 6.1 / 9.6, K = 3072 8.9 / 7.8 / 8.0, K = 4096 11.1 / 9.9 / 9.5; M = 1 K = 1024 2.0 / 2.0 / 2.1, K = 4096 3.4 / 2.6 / 2.3).
-  // Measured (us, 256 / 512 / 1024 threads, 8-bit codes, rows
-  // from the last-level cache; the gated product behind the semicolon): K = 4096 M = 1 2.2 / 2.5 / 2.6, M = 1000
-  // 4.5 / 6.0 / 7.1; K = 6144 M = 16 2.8 / 2.7 / 3.1; K = 8192 M = 24 3.0 / 2.7 / 3.4, M = 1000 6.4 / 5.9 / 9.7, M = 4096
-  // 14.5 / 14.2 / 29; K = 11008 M = 16 3.5 / 3.1 / 3.1, M = 256 4.0 / 3.6 / 3.8; 6.1 / 5.3 / 5.0, M = 1024 12.3 / 10.9 / 11.9, M = 4096
-  // 33.9 / 32.6 / 37.3; K = 14336 M = 16 5.3 / 4.5 / 4.2, M = 600 7.7 / 6.6 / 6.7;, M = 4096 23.7 / 22.7 / 26.0; 42.4 / 39.7 / 41.5.
-  const int threads = nchunk <= 128 ? 64 : nchunk <= 384 ? 128 : nchunk <= 512 || nchunk > 2048 ? 256 : U && nchunk > 1024 && M <= 512 ? 1024 : 512;
+  const int threads = quantizer_threads(nchunk, M, GLU ? 512 : 256, 512);
   const int per = (nchunk + threads - 1) / threads;
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QA_LAUNCH(KT, NC)                                                                                            \
   hipLaunchKernelGGL((quantize_act_kernel<XDT, ABITS, KT, NC, GLU>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, Xq, scale)
-  if (threads == 1024) {
-    if constexpr (GLU) SERQ_QA_LAUNCH(1024, 2);
-  } else if (threads == 512) {
+  if (threads == 512) {
     if (per <= 2) SERQ_QA_LAUNCH(512, 2);
     else if (per <= 3) SERQ_QA_LAUNCH(512, 3);
-    else SERQ_QA_LAUNCH(512, 4);
+    else if (per <= 4) SERQ_QA_LAUNCH(512, 4);
+    else SERQ_QA_LAUNCH(512, 0);
   } else if (threads == 64) {
     SERQ_QA_LAUNCH(64, 2);
   } else if (threads == 128) {
     if (per <= 2) SERQ_QA_LAUNCH(128, 2);
     else SERQ_QA_LAUNCH(128, 3);
+  } else if (threads == 768) {
+    SERQ_QA_LAUNCH(768, 2);
+  } else if (threads == 1024) {
+    if (per <= 2) SERQ_QA_LAUNCH(1024, 2);
+    else if (per <= 3) SERQ_QA_LAUNCH(1024, 3);
+    else SERQ_QA_LAUNCH(1024, 4);
   } else {
-    if (per <= 2) SERQ_QA_LAUNCH(256, 2);
-    else SERQ_QA_LAUNCH(256, 0);
+    if (per <= 1) SERQ_QA_LAUNCH(256, 1);
+    else SERQ_QA_LAUNCH(256, 2);
   }
 #undef SERQ_QA_LAUNCH
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;

@@ -141,13 +141,40 @@ __device__ __forceinline__ void values8(const Raw8<XDT>& r, float v[8]) {
     }
   }
 }
-// The rows of a quantiser: pieces `chunk`, chunk + KT, ... (NC of them) of a row of nchunk, flattened: x * s_inv, or silu(x) * u *
-// s_inv.  All loads -- the row, the second row, the flattening factors -- are requested before the first value is used.  Behind a
-// test of each piece, as they were, every piece waited for its own loads, one after the other, and the factors for the row.  (Pieces
-// past the row: its last one again.)  With 1024 threads, where a good part of the last round lies past the row, and with one piece each, the
-// arithmetic is left out for pieces that no lane of the wave has: a wave has `pieces_of` them, and the values of the others are not set.  (Elsewhere the
-// tests cost more than they spare: gated product, K = 11008 M = 1024, 512 threads 10.9 / 11.4 us without / with them; 1024
-// threads, M = 256 5.3 / 5.0.)
+// Threads per row of a quantiser that needs the whole row before its first code (integer, asymmetric), for M rows of nchunk pieces.
+// Few rows are bound by a row's own latency and want its pieces side by side; many short ones by the rate at which waves start and
+// want fewer threads with two or three pieces each.  `few_short`, `few_long`: how many rows are few; the gated product and the asymmetric
+// quantiser have more to do per piece, so that their short rows are few for longer.  Measured (us, 8-bit codes; threads x pieces):
+//   up to 128 pieces, 64 x 2 / 128 / 256: integer K = 1024 M = 1 2.0 / 2.0 / 2.1, M = 1000 3.05 / 3.28 / 3.68, M = 4096 5.1 / 6.8 / 7.9
+//   129 .. 256 pieces, 128 x 2 / 256 x 1: K = 2048 integer M = 200 2.76 / 2.67, M = 450 3.09 / 3.15, M = 3000 6.0 / 8.6; gated product M
+//   = 450 3.79 / 3.63, M = 600 4.00 / 4.17; asymmetric M = 450 3.36 / 3.07, M = 1500 5.16 / 5.19
+//   257 .. 384, 128 x 3 / 256 x 2: K = 3072 integer M = 1 2.42 / 2.29, M = 1500 5.56 / 5.47, M = 4096 9.6 / 10.1; gated product M = 450
+//   4.76 / 4.12, M = 1500 7.54 / 7.28, M = 4096 14.1 / 14.3; asymmetric M = 300 3.72 / 3.46, M = 3000 8.3 / 8.7
+//   385 .. 512, 128 / 256 x 2 / 512: integer K = 4096 M = 200 3.51 / 3.09 / 3.25, M = 4096 11.8 / 11.2 / 18.9
+//   513 .. 1024, 256 / 512 x 2 / 1024: integer K = 8192 M = 16 3.21 / 2.88 / 3.69, M = 1000 7.1 / 6.8 / 11.0, M = 4096 21.4 / 21.6 / 34.7
+//   1025 .. 1536, 512 x 3 / 768 x 2: integer K = 10240 M = 1 2.82 / 2.70, M = 512 5.91 / 5.70, M = 700 6.71 / 6.85; gated product K =
+//   12288 M = 16 3.94 / 3.86, M = 400 8.1 / 7.7; asymmetric K = 12288 M = 200 4.56 / 4.33, K = 8256 M = 512 5.70 / 5.67
+//   1537 .. 2048, 512 x 4 / 1024 x 2: integer K = 14336 M = 16 3.58 / 3.34, M = 512 6.77 / 6.56, M = 1000 10.8 / 11.2; gated product M =
+//   16 4.55 / 4.20; asymmetric M = 200 4.89 / 4.64, M = 400 7.02 / 7.10
+//   2049 .. 4096, walked twice by 256 / kept by 1024 x 3 or 4: integer K = 20480 M = 1 6.4 / 3.8, M = 1000 20.7 / 14.5, M = 4096 79.7 /
+//   49.9; gated product K = 28672 M = 400 23.7 / 16.5; asymmetric K = 16448 M = 2000 33.2 / 24.3
+//   more, walked by 256 / 512: integer K = 32832 M = 1 8.8 / 6.3, M = 2000 65.2 / 61.4; K = 65536 M = 400 29.0 / 29.4, M = 4096 260 / 246
+inline int quantizer_threads(int nchunk, int64_t M, int64_t few_short, int64_t few_long) {
+  if (nchunk <= 128) return 64;
+  if (nchunk <= 256) return M <= few_short ? 256 : 128;
+  if (nchunk <= 384) return M <= 1536 ? 256 : 128;
+  if (nchunk <= 512) return 256;
+  if (nchunk <= 1024) return 512;
+  if (nchunk <= 2048) return M > few_long ? 512 : nchunk <= 1536 ? 768 : 1024;
+  return nchunk <= 4096 ? 1024 : 512;
+}
+// The rows of a quantiser: pieces `chunk`, chunk + KT, ... (NC of them) of a row of nchunk, flattened: x * s_inv, or silu(x) * u * s_inv.
+// All loads -- the row, the second row, the flattening factors -- are requested before the first value is used.  Behind a test of each
+// piece, as they were, every piece waited for its own loads, one after the other, and the factors for the row.  (Pieces past the row: its
+// last one again.)  With 1024 threads, where a good part of the last round lies past the row, and with one piece each, the arithmetic is
+// left out for pieces that no lane of the wave has: a wave has `pieces_of` them, and the values of the others are not set.  (Elsewhere
+// the tests cost more than they spare: gated product, K = 11008 M = 1024, 512 threads 10.9 / 11.4 us without / with them; 1024 threads,
+// where they pay, M = 256 5.3 / 5.0.)
 template <int KT, int NC>
 __device__ __forceinline__ int pieces_of(int chunk, int nchunk) {
   if (KT < 1024 && NC > 1) return NC;

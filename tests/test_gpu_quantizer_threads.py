@@ -1,6 +1,6 @@
 """The quantisers choose their threads per row by the row length and the number of rows: bit-exact against the oracle on both
-sides of every limit (rows of 1024 / 1032 / 1280 / 1288 / 1536 / 1544 / 1784 / 1792 / 2048 / 2056 pieces of 8 values, batches
-of 256 / 257, 512 / 513 and 1023 / 1024 / 1025 rows; fp32 input and the gated product have limits of their own)."""
+sides of every limit.  Integer and asymmetric: rows of 128, 256, 384, 512, 1024, 1536, 2048 and 4096 pieces of 8 values; 256 and 512
+rows (where the row length and the kind of quantiser have that limit) and 1536.  MXFP4: 128 and 256 pieces, 700 rows."""
 import numpy as np
 import pytest
 import torch
@@ -66,5 +66,14 @@ def test_codes_match_the_oracle_short_and_walked_rows(M, K):
 @pytest.mark.parametrize("M", [699, 700, 701])
 @pytest.mark.parametrize("K", [1024, 1088, 2048, 2112, 3200])
 def test_codes_match_the_oracle_two_pieces_per_thread(M, K):
+    for dtype in (torch.bfloat16, torch.float32):
+        _check(M, K, dtype)
+
+
+# few short rows take more threads than many; rows of up to 4096 pieces stay in registers
+@pytest.mark.parametrize("M,K", [(M, K) for M in (256, 257, 512, 513) for K in (1088, 2048)] +
+                         [(M, K) for M in (1536, 1537) for K in (2112, 3072)] +
+                         [(M, K) for M in (1, 3) for K in (4096, 4160, 8192, 8256, 12288, 12352, 16384, 16448, 24576, 24640, 32768)])
+def test_codes_match_the_oracle_by_rows(M, K):
     for dtype in (torch.bfloat16, torch.float32):
         _check(M, K, dtype)
