@@ -25,6 +25,7 @@ namespace serq {
 namespace {
 
 constexpr int kT = 256;
+constexpr int kMaxGridY = 65535;                      // where a grid's y dimension ends
 inline unsigned blocks_for(size_t n) { return (unsigned)((n + kT - 1) / kT); }
 inline int ok() { return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP; }
 
@@ -79,23 +80,28 @@ __device__ __forceinline__ uint32_t pack8(const uint32_t c[8]) {
 
 // ---- activations ----------------------------------------------------------------------------------
 // A thread owns 8 consecutive channels, four neighbouring threads a block.  A block needs nothing from the rest of its row, so a
-// row is cut into workgroups of KT threads (blockIdx.y): what bounds the kernel is how soon all its loads are under way, and below a
+// row is cut into workgroups of KT threads: what bounds the kernel is how soon all its loads are under way, and below a
 // few hundred rows a workgroup per row leaves the chip idle or walks the row in rounds that wait for one another.
 // GLU: the row is the gated product silu(X) * U formed in fp32 (the input of the down projection,
 // quantised where it is made; Sec. 3.2, the decoder-layer flow of Fig. 2(b)).
 // NR: pieces of a thread, KT apart, whose loads are under way together (one past the row's end repeats its last piece)
-template <int XDT, int KT, bool GLU, int NR>
+// WHOLE: the workgroups of a row follow one another, so that the rows in flight are whole ones; the grid is (workgroups of a row,
+// up to 65535 rows, as often as it takes).  Otherwise one workgroup of each row comes after the other, and the grid is (rows, workgroups
+// of a row).
+template <int XDT, int KT, bool GLU, int NR, bool WHOLE>
 __global__ __launch_bounds__(KT) void mx_quantize_act_kernel(const void* __restrict__ X, const void* __restrict__ U,
                                                              const float* __restrict__ s_inv, int K, int64_t ldx,
                                                              int64_t ldu, int64_t M, uint32_t* __restrict__ Xq,
                                                              uint8_t* __restrict__ xsc) {
-  const int64_t m = blockIdx.x;
+  const int64_t m = WHOLE ? (int64_t)blockIdx.z * kMaxGridY + blockIdx.y : blockIdx.x;
+  const int part = WHOLE ? blockIdx.x : blockIdx.y;
+  if (WHOLE && blockIdx.z > 0 && m >= M) return;      // (M is not loaded for the first rows)
   constexpr size_t esz = (XDT == SERQ_F32) ? 4 : 2;
   const char* row = (const char*)X + (size_t)m * (size_t)ldx * esz;
   const char* urow = GLU ? (const char*)U + (size_t)m * (size_t)ldu * esz : nullptr;
   const int nchunk = K >> 3;
   const size_t Mp = (size_t)((M + 1) & ~(int64_t)1);
-  const int chunk0 = (int)blockIdx.y * (KT * NR) + threadIdx.x;       // KT is a multiple of 4: a block's pieces stay together
+  const int chunk0 = part * (KT * NR) + threadIdx.x;                  // KT is a multiple of 4: a block's pieces stay together
   if (__builtin_amdgcn_readfirstlane(chunk0) < nchunk) {              // else nothing of the row is left for this wave
     float v[NR][8];
     fetch_rows<XDT, KT, NR, GLU>(row, urow, s_inv, chunk0, nchunk, v);
@@ -117,7 +123,7 @@ __global__ __launch_bounds__(KT) void mx_quantize_act_kernel(const void* __restr
       }
     }
   }
-  if (blockIdx.y > 0) return;
+  if (part > 0) return;
   // scale bytes of the blocks that the last 256-channel tile does not have
   const int nblk = K >> 5;
   const int nblk8 = (nblk + 7) & ~7;
@@ -273,22 +279,39 @@ int launch_mx_quantize_act(const void* X, const void* U, int x_dtype, const floa
   // piece already, fp32 input two).  Measured (us, a workgroup of up to 1024 threads per row / this rule):
   //   K = 4096  M = 1500 5.25 / 4.64, M = 2048 6.05 / 5.52, M = 4096 9.88 / 8.35, gated product M = 1000 5.95 / 5.19;  K = 1024 M = 4096
   //   4.81 / 3.89;  K = 8192 M = 2048 9.2 / 8.6;  K = 11008 M = 700 6.0 / 5.2, M = 4096 20.7 / 19.6;  K = 13312 M = 3000 18.9 / 16.9;
-  //   K = 14336 gated product M = 24 3.85 / 2.49, M = 200 4.34 / 3.99, M = 4096 41.3 / 38.7;  K = 28672 M = 4 3.6 / 2.4;  fp32 K = 11008
+  //   K = 14336 gated product M = 24 3.85 / 2.49, M = 200 4.34 / 3.99;  K = 28672 M = 4 3.6 / 2.4;  fp32 K = 11008
   //   M = 333 6.7 / 5.7.  One round of 256 / two rounds of 128 threads, the second behind the first: K = 11008 M = 700 7.0 / 6.8, K = 14336
   //   M = 1024 11.0 / 10.6, M = 256 3.94 / 4.09, K = 4096 M = 2048 6.8 / 6.5, M = 400 3.28 / 3.53, gated product M = 1000 6.1 / 6.75.
+  // One token: 512 threads, which start sooner than twice as many workgroups (K = 8192 2.23 / 2.10, 11008 2.24 / 2.09; two: level).
+  // Input beyond the L2s (32 MB), if there is much per piece: the workgroups of a row follow one another, and memory is read in whole
+  // rows.  In columns of 4 KB out of thousands of rows, some row lengths were slow (us, a workgroup per row / columns / whole rows):
+  // gated product K = 11008 M = 4096 43.9 / 47.2 / 39.9, M = 2500 27.4 / 28.3 / 24.6, K = 5504 M = 4096 25.9 / 26.3 / 22.3, K = 14336
+  // M = 4096 55.7 / 52.4 / 48.4; fp32 input K = 11008 M = 4096 42.8 / 44.0 / 39.6; both M = 700 15.3 / 14.2 / 13.3.  Smaller input: level,
+  // or slower (gated product K = 2752 M = 2500 9.8 / 8.8 / 9.2), as are rows whose second workgroup has little to do (K = 1088
+  // M = 4096 6.9 / 6.8 / 7.8).
   const int nchunk = K >> 3;
   const bool two = !U && x_dtype != SERQ_F32 && M >= 700 && nchunk > 128;
-  const int threads = two || nchunk <= 128 ? 128 : 256, per = two ? 256 : threads;
-  dim3 grid((unsigned)M, (unsigned)((nchunk + per - 1) / per)), block((unsigned)threads);
-#define SERQ_MXQ_LAUNCH_R(XDT, KT, GLU, NR) \
-  hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, KT, GLU, NR>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, M, (uint32_t*)Xq, xsc)
-#define SERQ_MXQ_LAUNCH(XDT)                                        \
-  do {                                                              \
-    if (U && threads == 128) SERQ_MXQ_LAUNCH_R(XDT, 128, true, 1);  \
-    else if (U) SERQ_MXQ_LAUNCH_R(XDT, 256, true, 1);               \
-    else if (threads == 256) SERQ_MXQ_LAUNCH_R(XDT, 256, false, 1); \
-    else if (two) SERQ_MXQ_LAUNCH_R(XDT, 128, false, 2);            \
-    else SERQ_MXQ_LAUNCH_R(XDT, 128, false, 1);                     \
+  const int64_t bytes = M * K * (x_dtype == SERQ_F32 ? 4 : 2) * (U ? 2 : 1);
+  const bool whole = (U || x_dtype == SERQ_F32) && bytes >= (48 << 20) && nchunk > 256;
+  const int threads = whole || two || nchunk <= 128 ? 128 : M == 1 && nchunk > 512 && nchunk <= 1536 ? 512 : 256, per = two ? 256 : threads;
+  const unsigned parts = (unsigned)((nchunk + per - 1) / per);
+  const dim3 grid = whole ? dim3(parts, (unsigned)(M < kMaxGridY ? M : kMaxGridY), (unsigned)((M + kMaxGridY - 1) / kMaxGridY))
+                          : dim3((unsigned)M, parts);
+  const dim3 block((unsigned)threads);
+#define SERQ_MXQ_LAUNCH_R(XDT, KT, GLU, NR, WHOLE)                                                                               \
+  hipLaunchKernelGGL((mx_quantize_act_kernel<XDT, KT, GLU, NR, WHOLE>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, M, (uint32_t*)Xq, \
+                     xsc)
+#define SERQ_MXQ_LAUNCH(XDT)                                               \
+  do {                                                                     \
+    if (U && whole) SERQ_MXQ_LAUNCH_R(XDT, 128, true, 1, true);            \
+    else if (U && threads == 128) SERQ_MXQ_LAUNCH_R(XDT, 128, true, 1, false); \
+    else if (U && threads == 512) SERQ_MXQ_LAUNCH_R(XDT, 512, true, 1, false); \
+    else if (U) SERQ_MXQ_LAUNCH_R(XDT, 256, true, 1, false);               \
+    else if (threads == 512) SERQ_MXQ_LAUNCH_R(XDT, 512, false, 1, false); \
+    else if (whole) SERQ_MXQ_LAUNCH_R(SERQ_F32, 128, false, 1, true); /* fp32 input, then */ \
+    else if (threads == 256) SERQ_MXQ_LAUNCH_R(XDT, 256, false, 1, false); \
+    else if (two) SERQ_MXQ_LAUNCH_R(XDT, 128, false, 2, false);            \
+    else SERQ_MXQ_LAUNCH_R(XDT, 128, false, 1, false);                     \
   } while (0)
   if (x_dtype == SERQ_F32) SERQ_MXQ_LAUNCH(SERQ_F32);
   else if (x_dtype == SERQ_F16) SERQ_MXQ_LAUNCH(SERQ_F16);

@@ -1,6 +1,7 @@
 """The quantisers choose their threads per row by the row length and the number of rows: bit-exact against the oracle on both
 sides of every limit.  Integer and asymmetric: rows of 128, 256, 384, 512, 1024, 1536, 2048 and 4096 pieces of 8 values; 256 and 512
-rows (where the row length and the kind of quantiser have that limit) and 1536.  MXFP4: 128 and 256 pieces, 700 rows."""
+rows (where the row length and the kind of quantiser have that limit) and 1536.  MXFP4: 128, 256, 512 and 1536 pieces, 1 and 700 rows,
+48 MB of input, 65535 rows."""
 import numpy as np
 import pytest
 import torch
@@ -70,10 +71,33 @@ def test_codes_match_the_oracle_two_pieces_per_thread(M, K):
         _check(M, K, dtype)
 
 
-# few short rows take more threads than many; rows of up to 4096 pieces stay in registers
+# few short rows take more threads than many; rows of up to 4096 pieces stay in registers; one MXFP4 token takes 512 threads
 @pytest.mark.parametrize("M,K", [(M, K) for M in (256, 257, 512, 513) for K in (1088, 2048)] +
                          [(M, K) for M in (1536, 1537) for K in (2112, 3072)] +
                          [(M, K) for M in (1, 3) for K in (4096, 4160, 8192, 8256, 12288, 12352, 16384, 16448, 24576, 24640, 32768)])
 def test_codes_match_the_oracle_by_rows(M, K):
     for dtype in (torch.bfloat16, torch.float32):
         _check(M, K, dtype)
+
+
+# MXFP4: from 48 MB of input on (the gated product and fp32 input) the workgroups of a row follow one another: both sides of the
+# limit, last workgroups with little to do, an odd number of rows
+@pytest.mark.parametrize("M,K,dtype", [(5957, 2112, torch.bfloat16), (5958, 2112, torch.float32), (2979, 2112, torch.float32),
+                                       (2287, 5504, torch.bfloat16), (6145, 2048, torch.bfloat16)])
+def test_codes_match_the_oracle_whole_rows(M, K, dtype):
+    _check(M, K, dtype)
+
+
+# more rows than a grid's y dimension takes
+def test_mx_whole_rows_beyond_one_grid():
+    M, K = 65535 + 70, 2112
+    g = torch.Generator(device=DEV).manual_seed(5)
+    X = torch.randn((M, K), generator=g, device=DEV).bfloat16()
+    G = torch.full_like(X, 32.0)
+    s_inv = torch.rand(K, generator=g, device=DEV) + 0.5
+    c, e = serq.mx_unpack_act(*serq.mx_swiglu_quantize_act(G, X, s_inv), M, K)
+    rows = [0, 65533, 65534, 65535, 65536, M - 1]
+    co, eo = orc.mx_quantize_act(X[rows].float().cpu().numpy(), s_inv.cpu().numpy())
+    assert np.array_equal(c[rows].cpu().numpy(), co) and np.array_equal(e[rows].int().cpu().numpy(), eo.astype(int) + 5)
+    c1, e1 = serq.mx_unpack_act(*serq.mx_quantize_act(X, s_inv), M, K)     # (two pieces a thread: the other grid)
+    assert torch.equal(c, c1) and torch.equal(e.int(), e1.int() + 5)
