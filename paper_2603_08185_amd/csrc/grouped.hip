@@ -1044,13 +1044,18 @@ int serq_quantize_act_asym(const void* X, int x_dtype, const float* s_inv, int64
       (reinterpret_cast<uintptr_t>(zero_out) & 3u))
     return SERQ_EALIGN;
   hipStream_t st = (hipStream_t)stream;
+  for (int64_t m0 = 0; m0 < M; m0 += kLaunchRows) {
+    const int64_t mc = M - m0 < kLaunchRows ? M - m0 : kLaunchRows;
+    const void* Xs = (const char*)X + (size_t)m0 * (size_t)ldx * (x_dtype == SERQ_F32 ? 4 : 2);
+    void* Xqs = (char*)Xq_out + (size_t)m0 * ((size_t)K * abits / 8);
 #define SERQ_QAA_DT(DT)                                                                                              \
-  (abits == 4 ? launch_asym_t<DT, 4>(X, s_inv, M, (int)K, ldx, Xq_out, scale_out, zero_out, st)                      \
-              : launch_asym_t<DT, 8>(X, s_inv, M, (int)K, ldx, Xq_out, scale_out, zero_out, st))
-  if (x_dtype == SERQ_F32) return SERQ_QAA_DT(SERQ_F32);
-  if (x_dtype == SERQ_F16) return SERQ_QAA_DT(SERQ_F16);
-  return SERQ_QAA_DT(SERQ_BF16);
+  (abits == 4 ? launch_asym_t<DT, 4>(Xs, s_inv, mc, (int)K, ldx, Xqs, scale_out + m0, zero_out + m0, st)             \
+              : launch_asym_t<DT, 8>(Xs, s_inv, mc, (int)K, ldx, Xqs, scale_out + m0, zero_out + m0, st))
+    const int rc = x_dtype == SERQ_F32 ? SERQ_QAA_DT(SERQ_F32) : x_dtype == SERQ_F16 ? SERQ_QAA_DT(SERQ_F16) : SERQ_QAA_DT(SERQ_BF16);
 #undef SERQ_QAA_DT
+    if (rc != SERQ_OK) return rc;
+  }
+  return SERQ_OK;
 }
 
 int serq_g128_pack_weights(const void* W, int w_dtype, const float* s, const int32_t* perm_in, int64_t N, int64_t K, int r,

@@ -288,12 +288,17 @@ int launch_mx_quantize_act(const void* X, const void* U, int x_dtype, const floa
   // gated product K = 11008 M = 4096 43.9 / 47.2 / 39.9, M = 2500 27.4 / 28.3 / 24.6, K = 5504 M = 4096 25.9 / 26.3 / 22.3, K = 14336
   // M = 4096 55.7 / 52.4 / 48.4; fp32 input K = 11008 M = 4096 42.8 / 44.0 / 39.6; both M = 700 15.3 / 14.2 / 13.3.  Smaller input: level,
   // or slower (gated product K = 2752 M = 2500 9.8 / 8.8 / 9.2), as are rows whose second workgroup has little to do (K = 1088
-  // M = 4096 6.9 / 6.8 / 7.8).
+  // M = 4096 6.9 / 6.8 / 7.8).  And whatever has more rows than there can be threads along a grid (kLaunchRows).
   const int nchunk = K >> 3;
-  const bool two = !U && x_dtype != SERQ_F32 && M >= 700 && nchunk > 128;
   const int64_t bytes = M * K * (x_dtype == SERQ_F32 ? 4 : 2) * (U ? 2 : 1);
-  const bool whole = (U || x_dtype == SERQ_F32) && bytes >= (48 << 20) && nchunk > 256;
-  const int threads = whole || two || nchunk <= 128 ? 128 : M == 1 && nchunk > 512 && nchunk <= 1536 ? 512 : 256, per = two ? 256 : threads;
+  bool two = !U && x_dtype != SERQ_F32 && M >= 700 && nchunk > 128;
+  int threads = two || nchunk <= 128 ? 128 : M == 1 && nchunk > 512 && nchunk <= 1536 ? 512 : 256;
+  const bool whole = ((U || x_dtype == SERQ_F32) && bytes >= (48 << 20) && nchunk > 256) || M * threads >= (1LL << 32);
+  if (whole) {
+    two = false;
+    threads = 128;
+  }
+  const int per = two ? 256 : threads;
   const unsigned parts = (unsigned)((nchunk + per - 1) / per);
   const dim3 grid = whole ? dim3(parts, (unsigned)(M < kMaxGridY ? M : kMaxGridY), (unsigned)((M + kMaxGridY - 1) / kMaxGridY))
                           : dim3((unsigned)M, parts);
@@ -308,7 +313,7 @@ int launch_mx_quantize_act(const void* X, const void* U, int x_dtype, const floa
     else if (U && threads == 512) SERQ_MXQ_LAUNCH_R(XDT, 512, true, 1, false); \
     else if (U) SERQ_MXQ_LAUNCH_R(XDT, 256, true, 1, false);               \
     else if (threads == 512) SERQ_MXQ_LAUNCH_R(XDT, 512, false, 1, false); \
-    else if (whole) SERQ_MXQ_LAUNCH_R(SERQ_F32, 128, false, 1, true); /* fp32 input, then */ \
+    else if (whole) SERQ_MXQ_LAUNCH_R(XDT, 128, false, 1, true);           \
     else if (threads == 256) SERQ_MXQ_LAUNCH_R(XDT, 256, false, 1, false); \
     else if (two) SERQ_MXQ_LAUNCH_R(XDT, 128, false, 2, false);            \
     else SERQ_MXQ_LAUNCH_R(XDT, 128, false, 1, false);                     \

@@ -198,8 +198,8 @@ int launch_b(const void* X, const void* U, const float* s_inv, int64_t M, int K,
 int launch_quantize_act(const void* X, const void* U, int x_dtype, const float* s_inv, int64_t M, int K, int64_t ldx,
                         int64_t ldu, int abits, void* Xq, float* scale, hipStream_t st) {
   // the grid's x dimension carries the token index
-  for (int64_t m0 = 0; m0 < M; m0 += (1 << 30)) {
-    const int64_t mc = (M - m0) < (1 << 30) ? (M - m0) : (1 << 30);
+  for (int64_t m0 = 0; m0 < M; m0 += kLaunchRows) {
+    const int64_t mc = (M - m0) < kLaunchRows ? (M - m0) : kLaunchRows;
     const size_t esz = x_dtype == SERQ_F32 ? 4 : 2;
     const void* Xs = (const char*)X + (size_t)m0 * (size_t)ldx * esz;
     const void* Us = U ? (const char*)U + (size_t)m0 * (size_t)ldu * esz : nullptr;

@@ -168,6 +168,9 @@ inline int quantizer_threads(int nchunk, int64_t M, int64_t few_short, int64_t f
   if (nchunk <= 2048) return M > few_long ? 512 : nchunk <= 1536 ? 768 : 1024;
   return nchunk <= 4096 ? 1024 : 512;
 }
+// Rows of one launch: the threads along a grid are counted in 32 bits, without an error where that wraps round, and a row takes up to
+// 1024.
+constexpr int64_t kLaunchRows = 1 << 21;
 // The rows of a quantiser: pieces `chunk`, chunk + KT, ... (NC of them) of a row of nchunk, flattened: x * s_inv, or silu(x) * u * s_inv.
 // All loads -- the row, the second row, the flattening factors -- are requested before the first value is used.  Behind a test of each
 // piece, as they were, every piece waited for its own loads, one after the other, and the factors for the row.  (Pieces past the row: its

@@ -1,7 +1,7 @@
 """The quantisers choose their threads per row by the row length and the number of rows: bit-exact against the oracle on both
 sides of every limit.  Integer and asymmetric: rows of 128, 256, 384, 512, 1024, 1536, 2048 and 4096 pieces of 8 values; 256 and 512
 rows (where the row length and the kind of quantiser have that limit) and 1536.  MXFP4: 128, 256, 512 and 1536 pieces, 1 and 700 rows,
-48 MB of input, 65535 rows."""
+48 MB of input, 65535 rows.  And more rows than there can be threads along a grid."""
 import numpy as np
 import pytest
 import torch
@@ -101,3 +101,50 @@ def test_mx_whole_rows_beyond_one_grid():
     assert np.array_equal(c[rows].cpu().numpy(), co) and np.array_equal(e[rows].int().cpu().numpy(), eo.astype(int) + 5)
     c1, e1 = serq.mx_unpack_act(*serq.mx_quantize_act(X, s_inv), M, K)     # (two pieces a thread: the other grid)
     assert torch.equal(c, c1) and torch.equal(e.int(), e1.int() + 5)
+
+
+# more rows than one launch takes: 512 threads a row, 2^32 threads and a few more.  (70 GB of input, zero but for the rows looked at.)
+def test_rows_beyond_one_launch():
+    M, K = (1 << 23) + 5, 4160
+    rows = [0, (1 << 21) - 1, 1 << 21, (1 << 22) + 1, (1 << 23) - 1, 1 << 23, M - 1]
+    X = torch.zeros((M, K), dtype=torch.bfloat16, device=DEV)
+    X[rows] = torch.randn((len(rows), K), generator=torch.Generator().manual_seed(3)).bfloat16().to(DEV)
+    s_inv = torch.rand(K, generator=torch.Generator().manual_seed(4)).to(DEV) + 0.5
+    Xq, sc, z = torch.empty(M * K // 2, dtype=torch.uint8, device=DEV), torch.empty(M, device=DEV), torch.empty(M, dtype=torch.int32, device=DEV)
+    codes = lambda: torch.cat([serq.unpack_act(Xq[m * K // 2:(m + 1) * K // 2], 4, 1, K) for m in rows])
+    Xs = X[rows].contiguous()
+    for name in ("quantize_act", "quantize_act_asym"):
+        extra = (z,) if name.endswith("asym") else ()
+        Xq.fill_(255)
+        getattr(serq, name)(X, s_inv, 4, Xq, sc, *extra)
+        Sq, ss, *sz = getattr(serq, name)(Xs, s_inv, 4)
+        assert torch.equal(codes(), serq.unpack_act(Sq, 4, len(rows), K)) and torch.equal(sc[rows], ss)
+        assert int((sc != 1.0).sum()) == len(rows)                        # a zero row's scale is 1, and every row was written
+        for zz in sz:
+            assert torch.equal(z[rows], zz)
+    del X, Xq
+    torch.cuda.empty_cache()
+
+
+# the same for MXFP4, whose short rows take 128 threads; and the integer quantisers with 64
+def test_short_rows_beyond_one_launch():
+    M, K = (1 << 26) + 5, 64
+    rows = [0, (1 << 21) + 1, (1 << 25) - 1, 1 << 25, (1 << 26) - 1, 1 << 26, M - 1]
+    X = torch.zeros((M, K), dtype=torch.bfloat16, device=DEV)
+    X[rows] = torch.randn((len(rows), K), generator=torch.Generator().manual_seed(3)).bfloat16().to(DEV)
+    Xs = X[rows].contiguous()
+    Xq, xs = torch.full((M * K // 2,), 255, dtype=torch.uint8, device=DEV), torch.full((4 * (M + 2) * 2,), 9, dtype=torch.uint8, device=DEV)
+    serq.mx_quantize_act(X, None, Xq, xs)
+    c, e = serq.mx_unpack_act(*serq.mx_quantize_act(Xs, None), len(rows), K)
+    codes = lambda: torch.cat([serq.unpack_act(Xq[m * K // 2:(m + 1) * K // 2], 4, 1, K) for m in rows])
+    assert torch.equal(codes() & 15, c.to(torch.int8))                    # (nibbles, read as two's complement numbers)
+    E = xs[:8 * (M + 1)].view(M + 1, 8)
+    assert torch.equal(E[rows, :2].int(), e.int())
+    assert bool((E[:M, 2:] == 127).all()) and int((E[:M, :2] != 127).any(1).sum()) <= len(rows)   # zero blocks: 127, all written
+    sc = torch.empty(M, device=DEV)
+    serq.quantize_act(X, None, 4, Xq, sc)
+    Sq, ss = serq.quantize_act(Xs, None, 4)
+    assert torch.equal(codes(), serq.unpack_act(Sq, 4, len(rows), K)) and torch.equal(sc[rows], ss)
+    assert int((sc != 1.0).sum()) == len(rows)
+    del X, Xq, xs
+    torch.cuda.empty_cache()
