@@ -75,6 +75,7 @@ SIGNATURES = {
 
 _lib = None
 _fast = None            # the extension module, bound to _lib
+_fast_error = None      # why there is none
 
 # the entry points it calls, in the order of its bind()
 _FAST = ["serq_quantize_act", "serq_swiglu_quantize_act", "serq_mx_quantize_act", "serq_mx_swiglu_quantize_act",
@@ -107,12 +108,15 @@ def lib() -> C.CDLL:
 
 
 def _load_fastcall(L: C.CDLL) -> None:
-    global _fast
-    if not os.path.exists(FASTCALL_PATH):
-        raise ImportError(f"{FASTCALL_PATH} not found: build it with `python -m paper_2603_08185_amd.build`")
-    spec = importlib.util.spec_from_file_location("_fastcall", FASTCALL_PATH)
-    mod = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(mod)
+    # (packing and sizes do without it: that it is missing, or built for another torch, is an error where it is used)
+    global _fast, _fast_error
+    try:
+        spec = importlib.util.spec_from_file_location("_fastcall", FASTCALL_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+    except ImportError as e:
+        _fast_error = e
+        return
     mod.bind(*(C.cast(getattr(L, name), C.c_void_p).value for name in _FAST))
     _fast = mod
 
@@ -120,6 +124,8 @@ def _load_fastcall(L: C.CDLL) -> None:
 def _native():
     """The extension module; its functions return None for arguments that need the general way."""
     lib()
+    if _fast is None:
+        raise ImportError(f"{FASTCALL_PATH} cannot be loaded: build it with `python -m paper_2603_08185_amd.build`") from _fast_error
     return _fast
 
 

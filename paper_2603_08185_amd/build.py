@@ -54,10 +54,10 @@ def build_fastcall(verbose: bool = True) -> str:
 
     import torch
     root = os.path.dirname(os.path.abspath(torch.__file__))
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(root, "include"),
-           "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"), "-I/opt/rocm/include",
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
            os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL, "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu",
            "-ltorch_python"]
     if verbose:

@@ -62,6 +62,19 @@ def test_refuses_what_is_not_plain():
         f.bind(*([0] * len(NAMES)))
 
 
+def test_packing_and_sizes_do_without_the_module(monkeypatch, tmp_path):
+    (tmp_path / "broken.so").write_bytes(b"not a library")
+    for path in (tmp_path / "missing.so", tmp_path / "broken.so"):
+        for name in ("_lib", "_fast", "_fast_error"):
+            monkeypatch.setattr(serq, name, None)
+        monkeypatch.setattr(serq, "FASTCALL_PATH", str(path))
+        assert serq.lib().serq_packed_weight_bytes(64, 128) == 64 * 128 // 2
+        x, u, s = torch.zeros((1, 128), dtype=torch.bfloat16), torch.zeros(128, dtype=torch.uint8), torch.zeros(1)
+        for call in (lambda: serq.quantize_act(x, None, 8, u, s), lambda: serq.linear(u, s, 8, u, s, 1, 64, 128, Y=x)):
+            with pytest.raises(ImportError, match="build it with"):       # and no silent other way for a layer's calls
+                call()
+
+
 def _calls(dt, M, K=384, N=96, r=32):
     g = torch.Generator().manual_seed(M)
     wide = torch.randn((M + 1, K + 64), generator=g).to(dt).to(DEV)
