@@ -94,10 +94,11 @@ __device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, uint32_t 
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                :: "s"(lds_base_uniform), "v"(voff), "s"(sbase) : "memory", "m0");
 }
-// dma16 by the first four lanes only, in code that all lanes execute (a test of the lane would be a branch).
+// dma16 by the active ones of the first four lanes (a test of the lane would be a branch).
 __device__ __forceinline__ void dma64(const void* sbase, uint32_t voff, uint32_t lds_base_uniform) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, 15\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
-               :: "s"(lds_base_uniform), "v"(voff), "s"(sbase) : "memory", "m0");
+  uint64_t lanes;
+  asm volatile("s_mov_b32 m0, %1\n\ts_and_saveexec_b64 %0, 15\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
+               : "=&s"(lanes) : "s"(lds_base_uniform), "v"(voff), "s"(sbase) : "memory", "m0", "scc");
 }
 // 16 bytes of E2M1 codes as an operand of the block-scaled MFMA (its FP4 forms read the first 16 bytes only)
 __device__ __forceinline__ v8i fp4_operand(const u4& v) {
