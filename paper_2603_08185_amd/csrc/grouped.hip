@@ -719,12 +719,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // stage offsets leave those bits free
   const int xbase_off = xoff + 16 * ((ABITS == 8 ? 2 * g : g) ^ xsw);
   static_assert(T::STAGE % 128 == 0 && T::WB % 128 == 0, "stage offsets keep the low address bits free for the xor");
-  int bi[NI];                                         // block index in the layer, clamped for the loads of the epilogue
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int b = NI * wn + i;
-    bi[i] = nb0 + (b < nbt ? b : nbt - 1);
-  }
   auto read_w = [&](int st, Op& o) {
     const uint8_t* s = lds + st * T::STAGE;
 #pragma unroll
@@ -849,7 +843,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (gi < G) group(No{}, No{}, gi, B, A);
 
   // ---- epilogue: zero point, rank-r term on the re-centred codes, token scale, one store ----------------
-  // register e of lane (lm, g) in tile (i, j): token 32*(2*wm + j) + 8*(e/4) + 4*g + e%4, channel 32*bi[i] + lm
+  // register e of lane (lm, g) in tile (i, j): token 32*(2*wm + j) + 8*(e/4) + 4*g + e%4, channel
+  // 32*(nb0 + NI*wn + i) + lm; blocks from nbt on are not stored
   // (lane indices taken anew: every register that lives through the main loop for the sake of the end is one too many)
   int te = tid;
   asm volatile("" : "+v"(te));
