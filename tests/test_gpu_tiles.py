@@ -1,5 +1,5 @@
-"""Tiled kernels: every count of main tiles around the ring's depth with every remainder, and more tiles than compute units, so
-that a workgroup takes several tiles of different widths one after the other."""
+"""Tiled kernels: every count of main tiles around the ring's depth with every remainder, and more tiles, of different widths, than
+compute units.  (A workgroup takes one tile.)"""
 import numpy as np
 import pytest
 import torch
@@ -73,11 +73,11 @@ def test_tile_counts(n):
 
 
 # 9 token tiles x 30, 41, 13 column tiles (30: of two blocks and of one; 41: one each; 13: four and three) on 256 compute units,
-# and 17 x 41: three rounds
+# and 17 x 41: workgroups in up to three rounds, the first tiles of a round beside the last ones of the round before
 @pytest.mark.parametrize("out_dtype", ["bf16", "fp16", "fp32"])
 @pytest.mark.parametrize("M,coltiles", [(2100, 30), (2049, 41), (2100, 13), (4200, 41)])
 @pytest.mark.parametrize("K,r", [(64, 32), (320, 0), (576, 64), (1344, 128)])
-def test_several_tiles_per_workgroup(M, coltiles, K, r, out_dtype):
+def test_more_tiles_than_compute_units(M, coltiles, K, r, out_dtype):
     dt = "fp16" if out_dtype == "fp16" else "bf16"
     for abits, rform in ((8, dt), (4, "i4" if M == 2049 else dt)):
         rr = r if rform != "i4" or 64 * ((r + 63) // 64) <= K else 0
