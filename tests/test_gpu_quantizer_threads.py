@@ -148,3 +148,39 @@ def test_short_rows_beyond_one_launch():
     assert int((sc != 1.0).sum()) == len(rows)
     del X, Xq, xs
     torch.cuda.empty_cache()
+
+
+# NaN never decides a row's maximum or range, and an infinity makes the scale infinite and every finite code that of zero; other rows,
+# and for MXFP4 other blocks of 32, do not notice.  (The codes of the NaN and the infinity themselves are not defined.)
+@pytest.mark.parametrize("M,K", [(8, K) for K in (64, 1024, 2048, 3072, 4096, 8192, 12288, 14336, 20480, 32832)] +
+                         [(600, 2048), (2000, 3072), (700, 14336), (4096, 11008)])
+def test_rows_that_are_not_finite(M, K):
+    nan, inf = float("nan"), float("inf")
+    g = torch.Generator().manual_seed(K)
+    for dtype in (torch.bfloat16, torch.float32):
+        X = torch.randn((M, K), generator=g).to(dtype)
+        X[0, 5], X[1, K - 1], X[2, [3, K - 9]] = nan, nan, nan            # rows 0, 1, 2: NaN; 3: nothing else; 4, 5: an infinity; others finite
+        X[3], X[4, 7], X[5, K - 2] = nan, inf, inf
+        clean = X.clone().nan_to_num(0.0, 0.0, 0.0)
+        X, clean = X.to(DEV), clean.to(DEV)
+        G, s_inv = torch.full_like(X, 32.0), torch.rand(K, generator=g).to(DEV) + 0.5
+        odd = ~torch.isfinite(X)
+        rest = torch.ones(M, dtype=torch.bool, device=DEV)
+        rest[4:6] = False
+        want = lambda a, b: bool(((a == b) | odd)[rest].all())
+        for abits in (4, 8):
+            for call in (lambda x: serq.quantize_act(x, s_inv, abits), lambda x: serq.swiglu_quantize_act(G, x, s_inv, abits),
+                         lambda x: serq.quantize_act_asym(x, s_inv, abits)):
+                (q, sc, *z), (qc, scc, *zc) = call(X), call(clean)
+                c = serq.unpack_act(q, abits, M, K)
+                assert torch.equal(sc[rest], scc[rest]) and want(c, serq.unpack_act(qc, abits, M, K))
+                assert bool(torch.isinf(sc[4:6]).all())
+                zero = -(1 << (abits - 1)) if z else 0                    # (asymmetric: the lowest code, and the zero point too)
+                assert bool((c[4:6] == zero)[~odd[4:6]].all()) and all(bool((t[4:6] == zero).all()) and torch.equal(t[rest], u[rest])
+                                                                       for t, u in zip(z, zc))
+        for call in (lambda x: serq.mx_quantize_act(x, s_inv), lambda x: serq.mx_swiglu_quantize_act(G, x, s_inv)):
+            (c, e), (cc, ec) = (serq.mx_unpack_act(*call(x), M, K) for x in (X, clean))
+            hit = torch.isinf(X).view(M, K // 32, 32).any(2)              # blocks with an infinity
+            assert torch.equal(e[~hit], ec[~hit]) and bool((e[hit] == 253).all())
+            block = hit.repeat_interleave(32, 1)
+            assert bool(((c == cc) | odd | block).all()) and bool(((c == 0) | odd | ~block).all())
