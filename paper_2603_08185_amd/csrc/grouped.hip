@@ -588,7 +588,11 @@ struct GTile {
 template <int ABITS, int NI>
 struct GOp { u4 w[NI][2], x[2][ABITS == 8 ? 4 : 2]; float gs[NI]; };   // raw operands and scales of one group
 
-template <int ABITS, bool HALVES, bool BF>
+// LR: the type of R, or kNoRank for a layer without the rank-r term, whose code is in the way of short layers (us, with it / without,
+// r = 0, N x K: W4A8 1856 x 512 M = 931 6.65 / 6.38, 6144 x 640 M = 2048 19.0 / 18.75, 1856 x 1024 8.28 / 8.02; W4A4 8800 x 1024 M = 1384
+// 23.8 / 23.1).
+constexpr int kNoRank = -1;
+template <int ABITS, bool HALVES, int LR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void serq_g128_tiled_kernel(const GParams p, int full) {
   using T = GTile<ABITS>;
   constexpr int SH = ABITS == 8 ? 4 : 8;
@@ -633,7 +637,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const uint8_t* xbase = p.Xq + (size_t)m0 * rowbytes;
   const uint8_t* sbase = (const uint8_t*)p.gsc + (size_t)nb0 * G * 64;
   // The sequence of stages: the G groups of the layer, then LG stages of RK ranks each for the rank-r term.
-  const bool has_lr = p.r > 0 && p.Rp != nullptr;
+  constexpr bool has_lr = LR != kNoRank, BF = LR != SERQ_F16;
   const int JB = has_lr ? p.r >> 4 : 0;
   const int LG = (JB + T::RF - 1) / T::RF;
   const int GT = G + LG;
@@ -690,7 +694,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   };
   auto issue = [&](int q, int st) {
-    if (q < G) {
+    if (!has_lr || q < G) {
 #pragma unroll
       for (int d = 0; d < T::nl(NI); ++d) fill(q, st, d);
     } else {
@@ -875,7 +879,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int e = 0; e < 16; ++e)
         accf[i][j][e] = __builtin_fmaf(accf[i][j][e], kInv, -(float)z[j][e >> 2][e & 3] * ws);   // 2^-SH: exact
   }
-  if (has_lr) {
+  if constexpr (has_lr) {
     // R fragments and token codes come through the ring, RK ranks at a time (they ran ahead of the last main groups, like any
     // stage), and are read in one go.
     int zm[2];
@@ -1157,20 +1161,23 @@ int serq_g128_linear(const void* Xq, const float* scale, const int32_t* zero, in
     const long long full = tiles / (2 * ncu) * (2 * ncu), left = tiles - full;
     const bool halves = left > 0 && 2 * left <= ncu && full % 8 == 0;
     const dim3 grid((unsigned)(halves ? full + 16 * ((left + 7) / 8) : tiles));
-    const bool bf = r_dtype != SERQ_F16;
-#define SERQ_G128_TILED(AB, HALVES, BF) \
-  hipLaunchKernelGGL((serq_g128_tiled_kernel<AB, HALVES, BF>), grid, dim3(256), 0, st, p, HALVES ? (int)full : 0)
+    const int lr = r > 0 && Rp != nullptr ? r_dtype : kNoRank;
+#define SERQ_G128_TILED(AB, HALVES, LR) \
+  hipLaunchKernelGGL((serq_g128_tiled_kernel<AB, HALVES, LR>), grid, dim3(256), 0, st, p, HALVES ? (int)full : 0)
+#define SERQ_G128_TILED_R(AB, HALVES)                                \
+  do {                                                               \
+    if (lr == kNoRank) SERQ_G128_TILED(AB, HALVES, kNoRank);         \
+    else if (lr == SERQ_F16) SERQ_G128_TILED(AB, HALVES, SERQ_F16);  \
+    else SERQ_G128_TILED(AB, HALVES, SERQ_BF16);                     \
+  } while (0)
     if (abits == 8) {
-      if (halves && bf) SERQ_G128_TILED(8, true, true);
-      else if (halves) SERQ_G128_TILED(8, true, false);
-      else if (bf) SERQ_G128_TILED(8, false, true);
-      else SERQ_G128_TILED(8, false, false);
+      if (halves) SERQ_G128_TILED_R(8, true);
+      else SERQ_G128_TILED_R(8, false);
     } else {
-      if (halves && bf) SERQ_G128_TILED(4, true, true);
-      else if (halves) SERQ_G128_TILED(4, true, false);
-      else if (bf) SERQ_G128_TILED(4, false, true);
-      else SERQ_G128_TILED(4, false, false);
+      if (halves) SERQ_G128_TILED_R(4, true);
+      else SERQ_G128_TILED_R(4, false);
     }
+#undef SERQ_G128_TILED_R
 #undef SERQ_G128_TILED
   }
   return hip_ok();
