@@ -30,9 +30,14 @@
 // read it cannot disambiguate.  In the steady state the refill of a stage is
 // spread over the MFMA groups of two 64-channel steps.  The tile's scales come the same way, ahead of the ring: loaded
 // to registers at the start and behind the last barrier, each cost the tile a trip to memory.  4-bit tokens begin with
-// their first stage landed, not with both.  (us, before / these steps together, r = 128 unless stated, N x K, M = 4096: W4A4
-// 28672 x 4096 348.9 / 339.8, 6144 x 4096 r = 0 76.3 / 74.5, 4096 x 4096 r = 64 M = 2048 32.7 / 31.5; W4A8 4096 x 1024 r = 0
-// 23.2 / 22.7, 11008 x 4096 level: its clock gives way, 2.0 GHz where W4A4 keeps 2.37.)
+// their first stage landed, not with both.  us, the kernel without the step / as it is, r = 128 unless stated, N x K, M = 4096 unless
+// stated:
+//   refill over two steps: W4A4 11008 x 4096 M = 1500 (4-bit R) 72.3 / 68.9, 4096 x 4096 r = 64 M = 2048 33.6 / 32.7, 6144 x 4096 r = 0
+//     72.9 / 72.2, 28672 x 4096 318.3 / 319.3; W4A8 4096 x 11008 127.7 / 126.9, 11008 x 4096 M = 1000 45.8 / 45.3
+//   scales by direct loads: W4A4 4096 x 1024 r = 0 23.2 / 22.9, 6144 x 4096 r = 0 72.8 / 72.2, 28672 x 4096 321.2 / 319.3; W4A8 11008 x 4096
+//     M = 1000 45.8 / 45.3, 11008 x 4096 153.5 / 153.0
+//   early start: W4A4 4096 x 1024 r = 0 23.1 / 22.9, 4096 x 4096 M = 2048 32.9 / 32.7, 28672 x 4096 320.5 / 319.3
+// (W4A8 gains little: its clock gives way, 2.0 GHz where W4A4 keeps 2.37.)
 //
 // Inside a tile the operand fragments are double-buffered in registers: the LDS
 // reads of the next 64-channel fragment are issued before the MFMAs of the
@@ -174,7 +179,7 @@ void serq_mfma_kernel(const MfmaParams p) {
   // bring those of the channels, waves 4..7 those of the tokens.  Past the tile's edges: duplicates, never used.
   constexpr float kInv = 1.0f / (float)(1 << T::SH);  // the channels' are used times 2^-SH (exact)
   const float* lws = reinterpret_cast<const float*>(lds + T::WS_OFF);
-  const float* lrs = reinterpret_cast<const float*>(lds + T::RS_OFF);
+  float* lrs = reinterpret_cast<float*>(lds + T::RS_OFF);
   const float* lts = reinterpret_cast<const float*>(lds + T::TS_OFF);
   if (p.wscale != nullptr) {
     const int i = 64 * (wu & 3) + l;
@@ -425,6 +430,13 @@ void serq_mfma_kernel(const MfmaParams p) {
     };
 
     load_frags(stage_ptr(0), 0, F[0]);
+    // The scales of a 4-bit R, which every rank-r tile uses, times 2^-SH in place, by the wave that brought them; behind the main tiles'
+    // last hand-off, or this barrier, all waves see it.  (At each use instead, us: W4A8 r = 256 2912 x 512 M = 2103 16.0 / 15.5, 4096 x 448
+    // M = 4096 25.6 / 25.0.)
+    if constexpr (lr_int) {
+      if (wu < 4 && LT > 0) lrs[64 * wu + l] *= kInv;
+      if (KT == 0) __syncthreads();
+    }
 
     // Steady state: full main tiles whose refill (tile t+NS) is another full main tile.  An iteration begins at a hand-off, with
     // the last fragment of tile t still to be multiplied, and ends before the next one.  The loads of the refill are spread over
@@ -623,7 +635,7 @@ void serq_mfma_kernel(const MfmaParams p) {
         for (int q4 = 0; q4 < 4; ++q4) {
           const int cl = 32 * (blk0 + i) + 8 * q4 + 4 * g;
           const float4 rs = *(const float4*)(lrs_t + (cl < 256 ? cl : 0));
-          const float r4[4] = {rs.x * kInv, rs.y * kInv, rs.z * kInv, rs.w * kInv};
+          const float r4[4] = {rs.x, rs.y, rs.z, rs.w};
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             accf[i][j][4 * q4 + e] = __builtin_fmaf(r4[e], (float)tq[4 * q4 + e], accf[i][j][4 * q4 + e]);
