@@ -154,26 +154,7 @@ int launch_asym_t(const void* X, const float* s_inv, int64_t M, int K, int64_t l
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QAA(KT, NC) \
   hipLaunchKernelGGL((quantize_act_asym_kernel<XDT, ABITS, KT, NC>), grid, block, 0, st, X, s_inv, K, ldx, Xq, scale, zero)
-  if (threads == 512) {
-    if (per <= 2) SERQ_QAA(512, 2);
-    else if (per <= 3) SERQ_QAA(512, 3);
-    else if (per <= 4) SERQ_QAA(512, 4);
-    else SERQ_QAA(512, 0);
-  } else if (threads == 64) {
-    SERQ_QAA(64, 2);
-  } else if (threads == 128) {
-    if (per <= 2) SERQ_QAA(128, 2);
-    else SERQ_QAA(128, 3);
-  } else if (threads == 768) {
-    SERQ_QAA(768, 2);
-  } else if (threads == 1024) {
-    if (per <= 2) SERQ_QAA(1024, 2);
-    else if (per <= 3) SERQ_QAA(1024, 3);
-    else SERQ_QAA(1024, 4);
-  } else {
-    if (per <= 1) SERQ_QAA(256, 1);
-    else SERQ_QAA(256, 2);
-  }
+  SERQ_QUANTIZER_LAUNCH(threads, per, SERQ_QAA);
 #undef SERQ_QAA
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;
 }

@@ -157,26 +157,7 @@ int launch_t(const void* X, const void* U, const float* s_inv, int64_t M, int K,
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QA_LAUNCH(KT, NC)                                                                                            \
   hipLaunchKernelGGL((quantize_act_kernel<XDT, ABITS, KT, NC, GLU>), grid, block, 0, st, X, U, s_inv, K, ldx, ldu, Xq, scale)
-  if (threads == 512) {
-    if (per <= 2) SERQ_QA_LAUNCH(512, 2);
-    else if (per <= 3) SERQ_QA_LAUNCH(512, 3);
-    else if (per <= 4) SERQ_QA_LAUNCH(512, 4);
-    else SERQ_QA_LAUNCH(512, 0);
-  } else if (threads == 64) {
-    SERQ_QA_LAUNCH(64, 2);
-  } else if (threads == 128) {
-    if (per <= 2) SERQ_QA_LAUNCH(128, 2);
-    else SERQ_QA_LAUNCH(128, 3);
-  } else if (threads == 768) {
-    SERQ_QA_LAUNCH(768, 2);
-  } else if (threads == 1024) {
-    if (per <= 2) SERQ_QA_LAUNCH(1024, 2);
-    else if (per <= 3) SERQ_QA_LAUNCH(1024, 3);
-    else SERQ_QA_LAUNCH(1024, 4);
-  } else {
-    if (per <= 1) SERQ_QA_LAUNCH(256, 1);
-    else SERQ_QA_LAUNCH(256, 2);
-  }
+  SERQ_QUANTIZER_LAUNCH(threads, per, SERQ_QA_LAUNCH);
 #undef SERQ_QA_LAUNCH
   return hipGetLastError() == hipSuccess ? SERQ_OK : SERQ_EHIP;
 }

@@ -1,7 +1,7 @@
 """The quantisers choose their threads per row by the row length and the number of rows: bit-exact against the oracle on both
-sides of every limit.  Integer and asymmetric: rows of 128, 256, 384, 512, 1024, 1536, 2048 and 4096 pieces of 8 values; 256 and 512
-rows (where the row length and the kind of quantiser have that limit) and 1536.  MXFP4: 128, 256, 512 and 1536 pieces, 1 and 700 rows,
-48 MB of input, 65535 rows.  And more rows than there can be threads along a grid."""
+sides of every limit.  Integer and asymmetric: rows of 128, 256, 384, 512, 640, 768, 896, 1024, 1152, 1536, 2048 and 4096 pieces of 8
+values; 256 and 512 rows (where the row length and the kind of quantiser have that limit) and 1024.  MXFP4: 128, 256, 512 and 1536
+pieces, 1 and 700 rows, 48 MB of input, 65535 rows.  And more rows than there can be threads along a grid."""
 import numpy as np
 import pytest
 import torch
@@ -76,6 +76,14 @@ def test_codes_match_the_oracle_two_pieces_per_thread(M, K):
                          [(M, K) for M in (1536, 1537) for K in (2112, 3072)] +
                          [(M, K) for M in (1, 3) for K in (4096, 4160, 8192, 8256, 12288, 12352, 16384, 16448, 24576, 24640, 32768)])
 def test_codes_match_the_oracle_by_rows(M, K):
+    for dtype in (torch.bfloat16, torch.float32):
+        _check(M, K, dtype)
+
+
+# workgroups that are little larger than the row needs: their shortest and longest rows
+@pytest.mark.parametrize("M,K", [(M, K) for M in (1, 300, 515) for K in (4160, 5120, 5184, 7168, 7232, 9216, 9280)] +
+                         [(M, K) for M in (1, 1024, 1025) for K in (5184, 6144, 6208)])
+def test_codes_match_the_oracle_close_workgroups(M, K):
     for dtype in (torch.bfloat16, torch.float32):
         _check(M, K, dtype)
 
