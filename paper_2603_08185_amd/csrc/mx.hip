@@ -282,7 +282,8 @@ int launch_mx_quantize_act(const void* X, const void* U, int x_dtype, const floa
   //   K = 14336 gated product M = 24 3.85 / 2.49, M = 200 4.34 / 3.99;  K = 28672 M = 4 3.6 / 2.4;  fp32 K = 11008
   //   M = 333 6.7 / 5.7.  One round of 256 / two rounds of 128 threads, the second behind the first: K = 11008 M = 700 7.0 / 6.8, K = 14336
   //   M = 1024 11.0 / 10.6, M = 256 3.94 / 4.09, K = 4096 M = 2048 6.8 / 6.5, M = 400 3.28 / 3.53, gated product M = 1000 6.1 / 6.75.
-  // One token: 512 threads, which start sooner than twice as many workgroups (K = 8192 2.23 / 2.10, 11008 2.24 / 2.09; two: level).
+  // One token: 512 threads, which start sooner than twice as many workgroups (K = 3200 1.96 / 1.82, 8192 2.23 / 2.10, 11008 2.24 / 2.09; two
+  // tokens: level).
   // Input beyond the L2s (32 MB), if there is much per piece: the workgroups of a row follow one another, and memory is read in whole
   // rows.  In columns of 4 KB out of thousands of rows, some row lengths were slow (us, a workgroup per row / columns / whole rows):
   // gated product K = 11008 M = 4096 43.9 / 47.2 / 39.9, M = 2500 27.4 / 28.3 / 24.6, K = 5504 M = 4096 25.9 / 26.3 / 22.3, K = 14336
@@ -292,7 +293,7 @@ int launch_mx_quantize_act(const void* X, const void* U, int x_dtype, const floa
   const int nchunk = K >> 3;
   const int64_t bytes = M * K * (x_dtype == SERQ_F32 ? 4 : 2) * (U ? 2 : 1);
   bool two = !U && x_dtype != SERQ_F32 && M >= 700 && nchunk > 128;
-  int threads = two || nchunk <= 128 ? 128 : M == 1 && nchunk > 512 && nchunk <= 1536 ? 512 : 256;
+  int threads = two || nchunk <= 128 ? 128 : M == 1 && nchunk > 256 && nchunk <= 1536 ? 512 : 256;
   const bool whole = ((U || x_dtype == SERQ_F32) && bytes >= (48 << 20) && nchunk > 256) || M * threads >= (1LL << 32);
   if (whole) {
     two = false;
