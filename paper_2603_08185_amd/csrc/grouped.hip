@@ -149,7 +149,7 @@ template <int XDT, int ABITS>
 int launch_asym_t(const void* X, const float* s_inv, int64_t M, int K, int64_t ldx, void* Xq, float* scale,
                   int32_t* zero, hipStream_t st) {
   const int nchunk = K >> 3;
-  const int threads = quantizer_threads(nchunk, M, 512, 256);
+  const int threads = quantizer_threads(Quantizer::kAsym, nchunk, M);
   const int per = (nchunk + threads - 1) / threads;
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QAA(KT, NC) \

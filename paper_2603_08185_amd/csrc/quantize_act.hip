@@ -152,7 +152,7 @@ template <int XDT, int ABITS, bool GLU>
 int launch_t(const void* X, const void* U, const float* s_inv, int64_t M, int K, int64_t ldx, int64_t ldu, void* Xq,
              float* scale, hipStream_t st) {
   const int nchunk = K >> 3;
-  const int threads = quantizer_threads(nchunk, M, GLU ? 512 : 256, 512);
+  const int threads = quantizer_threads(GLU ? Quantizer::kGated : Quantizer::kPlain, nchunk, M);
   const int per = (nchunk + threads - 1) / threads;
   dim3 grid((unsigned)M), block((unsigned)threads);
 #define SERQ_QA_LAUNCH(KT, NC)                                                                                            \

@@ -145,22 +145,26 @@ __device__ __forceinline__ void values8(const Raw8<XDT>& r, float v[8]) {
 // Threads per row of a quantiser that needs the whole row before its first code (integer, asymmetric), for M rows of nchunk pieces.
 // Few rows are bound by a row's own latency and want its pieces side by side; many short ones by the rate at which waves start and
 // want fewer threads with two or three pieces each.  In between the arithmetic counts, most of all the gated product's, and a thread
-// whose last piece lies past the row does it for nothing: up to 1152 pieces the workgroup is little larger than the row needs.
-// `few_short`, `few_long`: how many rows are few; the gated product and the asymmetric quantiser have more to do per piece, so that
-// their short rows are few for longer.  Measured (us, 8-bit codes; threads x pieces; int: integer, glu: its gated product, asym):
+// whose last piece lies past the row does it for nothing: up to 896 pieces the workgroup is little larger than the row needs.
+// The gated product and the asymmetric quantiser have more to do per piece, so that their short rows are few for longer.  Without
+// flattening factors more codes of 16-bit input take the long way (an exact division), and waves that share a SIMD evenly count for few
+// rows.  Measured (us, 8-bit codes, with the factors unless stated; threads x pieces; int: integer, glu: its gated product, asym):
 //   up to 128 pieces, 64 x 2 / 128 / 256: int K = 1024 M = 1 2.0 / 2.0 / 2.1, M = 1000 3.05 / 3.28 / 3.68, M = 4096 5.1 / 6.8 / 7.9
 //   129 .. 256, 128 x 2 / 256 x 1: K = 2048 int M = 200 2.44 / 2.39, M = 549 2.67 / 3.04, M = 4096 6.3 / 9.5; glu M = 400 3.10 / 2.94,
 //   M = 549 3.20 / 3.44; asym M = 400 2.87 / 2.59, M = 1000 3.15 / 3.31
 //   257 .. 384, 128 x 3 / 192 x 2 / 256 x 2: K = 3072 int M = 1 2.13 / 1.94 / 1.99, M = 1000 3.47 / 3.37 / 3.55, M = 4096 8.16 / 7.76 /
 //   8.14; glu M = 549 3.89 / 3.72 / 3.75, M = 1000 4.12 / 4.11 / 4.53; asym M = 1000 3.82 / 3.72 / 3.98
 //   385 .. 512, 128 / 192 x 3 / 256 x 2: K = 4096 int M = 300 3.21 / 3.08 / 2.74, M = 4096 9.9 / 9.7 / 9.4; glu M = 549 4.60 / 4.63 / 3.93
-//   513 .. 640, 256 x 3 / 320 x 2 / 512 x 2: K = 4352 int M = 1 2.31 / 2.00 / 2.22, M = 549 3.53 / 3.32 / 3.62, M = 4096 10.3 / 10.4 / 12.0;
-//   glu M = 549 4.61 / 4.20 / 4.97, M = 1649 8.5 / 8.0 / 9.6, M = 4096 15.8 / 15.1 / 18.3; asym M = 1000 5.20 / 4.97 / 5.54
-//   641 .. 768, 256 x 3 / 384 x 2 / 512 x 2: K = 6144 int M = 549 3.85 / 3.80 / 3.89, M = 4096 13.0 / 13.4 / 13.8; glu M = 1000 6.65 / 6.48 /
-//   6.94, M = 1649 9.4 / 9.8 / 10.4; asym M = 1000 6.04 / 6.02 / 6.18, M = 4096 13.9 / 15.4 / 16.0
+//   513 .. 640, 256 x 3 / 320 x 2 / 512 x 2: K = 4352 int M = 300 3.06 / 2.88 / 3.15, M = 549 3.53 / 3.32 / 3.62, M = 4096 10.3 / 10.4 /
+//   12.0; glu M = 549 4.61 / 4.20 / 4.97, M = 1649 8.5 / 8.0 / 9.6, M = 4096 15.8 / 15.1 / 18.3; asym M = 1000 5.20 / 4.97 / 5.54; without
+//   factors, 320 x 2 / 512 x 2: K = 5120 asym M = 24 3.57 / 2.85, M = 200 3.45 / 3.02, int M = 200 3.16 / 2.91
+//   641 .. 768, 256 x 3 / 384 x 2 / 512 x 2: K = 6144 int M = 64 2.75 / 2.62 / 2.62, M = 549 3.85 / 3.80 / 3.89, M = 4096 13.0 / 13.4 / 13.8; glu
+//   M = 400 4.16 / 4.34 / 4.29, M = 549 4.99 / 5.00 / 5.24, M = 1649 9.4 / 9.8 / 10.4; asym M = 400 3.68 / 3.84 / 3.75, M = 4096 13.9 / 15.4 / 16.0;
+//   without factors, 384 x 2 / 512 x 2: asym M = 200 3.47 / 3.08, int M = 24 3.11 / 2.76
 //   769 .. 896, 448 x 2 / 512 x 2: K = 6656 glu M = 1000 7.04 / 7.39, M = 4096 20.1 / 20.6
 //   897 .. 1024, 256 / 512 x 2 / 768: K = 8192 int M = 64 3.01 / 2.67 / 2.77, M = 1000 6.9 / 6.5 / 7.4; glu M = 1000 8.3 / 7.9 / 9.3
-//   1025 .. 1152, 384 x 3 / 512 x 3 / 768 x 2: K = 9216 glu M = 400 5.53 / 5.41 / 5.37, M = 549 6.83 / 7.15 / 7.06, M = 4096 30.2 / 30.9 / 33.3
+//   1025 .. 1152, 384 x 3 / 512 x 3 / 768 x 2: K = 9216 glu M = 400 5.53 / 5.41 / 5.37, M = 549 6.83 / 7.15 / 7.06, M = 4096 30.2 / 30.9 / 33.3;
+//   without factors, 384 x 3 / 512 x 3: int M = 700 7.61 / 7.14, asym 8.80 / 7.96
 //   1153 .. 1536, 512 x 3 / 768 x 2: int K = 10240 M = 1 2.82 / 2.70, M = 512 5.91 / 5.70, M = 700 6.71 / 6.85; glu K = 12288 M = 400 6.10 /
 //   6.05, M = 4096 38.2 / 39.6; asym K = 12288 M = 200 4.56 / 4.33
 //   1537 .. 2048, 512 x 4 / 1024 x 2: int K = 14336 M = 16 3.58 / 3.34, M = 512 6.77 / 6.56, M = 1000 10.8 / 11.2; glu M = 16 4.55 / 4.20;
@@ -168,16 +172,19 @@ __device__ __forceinline__ void values8(const Raw8<XDT>& r, float v[8]) {
 //   2049 .. 4096, walked twice by 256 / kept by 1024 x 3 or 4: int K = 20480 M = 1 6.4 / 3.8, M = 1000 20.7 / 14.5, M = 4096 79.7 /
 //   49.9; glu K = 28672 M = 400 23.7 / 16.5; asym K = 16448 M = 2000 33.2 / 24.3
 //   more, walked by 256 / 512: int K = 32832 M = 1 8.8 / 6.3, M = 2000 65.2 / 61.4; K = 65536 M = 400 29.0 / 29.4, M = 4096 260 / 246
-inline int quantizer_threads(int nchunk, int64_t M, int64_t few_short, int64_t few_long) {
+enum class Quantizer { kPlain, kGated, kAsym };
+inline int quantizer_threads(Quantizer q, int nchunk, int64_t M) {
   if (nchunk <= 128) return 64;
-  if (nchunk <= 256) return M <= few_short ? 256 : 128;
+  if (nchunk <= 256) return M <= (q == Quantizer::kPlain ? 256 : 512) ? 256 : 128;
   if (nchunk <= 384) return 192;
   if (nchunk <= 512) return 256;
-  if (nchunk <= 640) return 320;
-  if (nchunk <= 768) return M <= 1024 ? 384 : 256;
+  if (nchunk <= 768) return M <= 384 ? 512 : nchunk <= 640 ? 320 : 256;
   if (nchunk <= 896) return 448;
   if (nchunk <= 1024) return 512;
-  if (nchunk <= 2048) return M > few_long ? (nchunk <= 1152 ? 384 : 512) : nchunk <= 1536 ? 768 : 1024;
+  if (nchunk <= 2048) {
+    if (M <= (q == Quantizer::kAsym ? 256 : 512)) return nchunk <= 1536 ? 768 : 1024;
+    return q == Quantizer::kGated && nchunk <= 1152 ? 384 : 512;
+  }
   return nchunk <= 4096 ? 1024 : 512;
 }
 // Its launch: LAUNCH(threads, pieces), 0 pieces for a row that is walked twice.
@@ -190,7 +197,6 @@ inline int quantizer_threads(int nchunk, int64_t M, int64_t few_short, int64_t f
     else if ((threads) == 256 && (per) == 2) LAUNCH(256, 2); \
     else if ((threads) == 256) LAUNCH(256, 3);             \
     else if ((threads) == 320) LAUNCH(320, 2);             \
-    else if ((threads) == 384 && (per) == 2) LAUNCH(384, 2); \
     else if ((threads) == 384) LAUNCH(384, 3);             \
     else if ((threads) == 448) LAUNCH(448, 2);             \
     else if ((threads) == 768) LAUNCH(768, 2);             \
@@ -209,10 +215,10 @@ constexpr int64_t kLaunchRows = 1 << 21;
 // All loads -- the row, the second row, the flattening factors -- are requested before the first value is used, piece by piece: the first
 // one's arithmetic runs while the others are on their way (gated product K = 4096 M = 4096, all of the row first 14.0, piece by piece 13.8;
 // K = 12288 M = 1000 10.99 / 10.50; K = 14336 M = 1000 12.9 / 12.4).  Behind a test of each piece, as they were, every piece waited for
-// its own loads, one after the other, and the factors for the row.  (Pieces past the row: its last one again.)  With 1024 threads, where a good part of the last round lies past the row, and with one piece each, the arithmetic is
-// left out for pieces that no lane of the wave has: a wave has `pieces_of` them, and the values of the others are not set.  (Elsewhere
-// the tests cost more than they spare: gated product, K = 11008 M = 1024, 512 threads 10.9 / 11.4 us without / with them; 1024 threads,
-// where they pay, M = 256 5.3 / 5.0.)
+// its own loads, one after the other, and the factors for the row.  (Pieces past the row: its last one again.)  With 1024 threads, where a
+// good part of the last round lies past the row, and with one piece each, the arithmetic is left out for pieces that no lane of the wave
+// has: a wave has `pieces_of` them, and the values of the others are not set.  (Elsewhere the tests cost more than they spare: gated
+// product, K = 11008 M = 1024, 512 threads 10.9 / 11.4 us without / with them; 1024 threads, where they pay, M = 256 5.3 / 5.0.)
 template <int KT, int NC>
 __device__ __forceinline__ int pieces_of(int chunk, int nchunk) {
   if (KT < 1024 && NC > 1) return NC;
@@ -238,6 +244,7 @@ __device__ __forceinline__ void fetch_rows_form(const void* row, const void* uro
       sb[c] = ((const v4f*)s_inv)[2 * (size_t)at[c] + 1];
     }
   }
+  __builtin_amdgcn_sched_barrier(0);                    // (else the compiler requests some of them behind the arithmetic of others)
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     if (c >= nc) continue;                              // uniform

@@ -14,19 +14,18 @@ SOURCE = """
 #include <cstdio>
 int main() {
   for (int nchunk = 8; nchunk <= 131072 / 8; nchunk += 8)
-    for (long long M : {1, 256, 257, 512, 513, 1024, 1025, 4096})
-      for (int few_short : {256, 512})
-        for (int few_long : {256, 512}) {
-          const int threads = serq::quantizer_threads(nchunk, M, few_short, few_long);
-          const int per = (nchunk + threads - 1) / threads;
-          int kt = 0, nc = -1;
+    for (long long M : {1, 256, 257, 384, 385, 512, 513, 4096})
+      for (auto kind : {serq::Quantizer::kPlain, serq::Quantizer::kGated, serq::Quantizer::kAsym}) {
+        const int threads = serq::quantizer_threads(kind, nchunk, M);
+        const int per = (nchunk + threads - 1) / threads;
+        int kt = 0, nc = -1;
 #define LAUNCH(KT, NC) (kt = KT, nc = NC)
-          SERQ_QUANTIZER_LAUNCH(threads, per, LAUNCH);
-          if (kt != threads || (nc > 0 ? nc < per : nc < 0 || nchunk <= 4096) || kt %% 64 || kt > 1024) {
-            printf("nchunk %%d M %%lld: threads %%d per %%d, kernel of %%d x %%d\\n", nchunk, M, threads, per, kt, nc);
-            return 1;
-          }
+        SERQ_QUANTIZER_LAUNCH(threads, per, LAUNCH);
+        if (kt != threads || (nc > 0 ? nc < per : nc < 0 || nchunk <= 4096) || kt %% 64 || kt > 1024) {
+          printf("nchunk %%d, M %%lld: %%d threads, %%d pieces, kernel of %%d x %%d", nchunk, M, threads, per, kt, nc);
+          return 1;
         }
+      }
   return 0;
 }
 """
