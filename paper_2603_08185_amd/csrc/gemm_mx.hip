@@ -302,7 +302,9 @@ void serq_mx_kernel(const MxParams p) {
 #pragma unroll
     for (int s = 0; s < NS; ++s)
       if (s < TT) issue_any(s, s);
-    if (TT >= 2) wait_dma_barrier<9>();                 // the first tile is enough to begin
+    // the first tile is enough to begin (us, both / the first, r = 0, N x K: 4096 x 1024 M = 4096 18.1 / 17.8, 6144 x 1984 M = 2381 24.7 / 24.3;
+    // r = 128 28672 x 4096 M = 4096 276.1 / 273.1, 4096 x 11008 level)
+    if (TT >= 2) wait_dma_barrier<9>();
     else wait_dma_barrier<0>();
 
     int t = 0;                                          // tile being computed

@@ -533,7 +533,9 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void serq_g128_skinny_kernel(con
 // type is a compile-time choice: chosen at run time, the two products made the compiler copy a whole tile after each of them, and
 // the fragments had come straight from L2, waited for four at a time (us, with both steps, r = 128 unless stated, N x K: W4A8
 // 6144 x 4096 M = 3000 110.4 / 102.6, 11008 x 4096 M = 4096 254.5 / 240.9, 4096 x 11008 234.1 / 221.9, r = 256 6144 x 4096
-// 159.5 / 145.1; W4A4 11008 x 4096 242.7 / 233.2).
+// 159.5 / 145.1; W4A4 11008 x 4096 242.7 / 233.2;
+// the type alone, at run time / compile time: W4A8 6144 x 4096 M = 3000 107.0 / 104.2, r = 256 M = 4096 146.8 / 142.9, 2912 x 1024 M = 1649
+// r = 64 17.6 / 17.3, W4A4 11008 x 4096 235.7 / 232.3, W4A8 11008 x 4096 and 4096 x 11008 level).
 // What bounds it now (counters, W4A8 6144 x 4096 M = 3000): vector issue slots 71 % taken, matrix unit 40 %, LDS 20 %; 190 vector
 // instructions per wave and group, 128 of them folds.
 //
